@@ -185,7 +185,8 @@ size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* layout, int32_t n_q_head
  * blocks above the upper end are not supported there.  The scaled query q * softmax_scale * log2(e) must
  * stay between 2^-100 and 2^100 in magnitude wherever it matters to the scores.  Wider groups, and exponent
  * planes that are not 16-byte aligned, take the general pass (fp32 multiply-adds), which has no such limits
- * beyond those of fp32 itself.
+ * beyond those of fp32 itself; with 16-bit I/O and 16-byte aligned planes wider groups run on the matrix cores as
+ * well, with the exponent bytes at the ends of the range handled apart.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP. */
 int kvbfp_decode_attention(const kvbfp_layout* layout, const kvbfp_cache* cache, int32_t n_q_heads,
                            const void* q, kvbfp_dtype dtype, const int32_t* seq_len_dev,
@@ -244,9 +245,9 @@ int kvbfp_append_decode_attention(const kvbfp_layout* layout, const kvbfp_cache*
  *   q, out      : DEVICE [batch][n_q_tokens][n_q_heads][head_dim] of `dtype`, contiguous.
  *   workspace   : at least kvbfp_decode_workspace_bytes(layout, n_q_heads * n_q_tokens, max_len) bytes.
  *   n_q_tokens  : 1..64.  With n_q_tokens * (n_q_heads / n_kv_heads) <= 8 the spare rows of the
- *                 matrix-core passes hold the extra tokens and the cost is that of one token; up to
- *                 32 the cache is read once per 16 (4-bit mantissas in blocks of 16/32 with 16-bit
- *                 I/O) or once per 8 (otherwise); more go through the general pass.
+ *                 matrix-core passes hold the extra tokens and the cost is that of one token; more take a
+ *                 pass that serves up to 128 per workgroup and reads the cache once (16-bit I/O).  With
+ *                 fp32 I/O the cache is read once per 8 up to 32, and more go through the general pass.
  * Everything else as kvbfp_decode_attention_qbfp.  n_q_tokens = 1 is that call. */
 int kvbfp_decode_attention_multi(const kvbfp_layout* layout, const kvbfp_cache* cache,
                                  int32_t n_q_heads, int32_t n_q_tokens, const void* q,

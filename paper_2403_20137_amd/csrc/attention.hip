@@ -56,7 +56,7 @@ __device__ __forceinline__ float code_value(uint32_t c) {
 
 // Generic split pass: fp32 FMAs everywhere, any block size, any group size (query heads are processed
 // four per workgroup; larger groups re-read the cache).  The fallback for what the matrix-core passes
-// do not take: more than 32 (virtual) heads per kv-head, planes that are not 16-byte aligned.
+// do not take: more than 32 (virtual) heads per kv-head with fp32 I/O, planes that are not 16-byte aligned.
 // grid = (n_splits, H_kv * ceil(G/4), B), block = 256.
 //
 // ROPE: the keys were cached before the rotary embedding and are rotated here, at token index m = their
@@ -565,11 +565,19 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     if ((int64_t)a.H_kv * gg > 65535)
         return fail(KVBFP_ERR_UNSUPPORTED, "decode_attention: too many heads for the grid");
     auto aligned16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-    // Matrix-core passes (not with the rotation at read): up to 8 (virtual) heads of a kv-head per launch; larger groups take
-    // several launches over head subsets (the cache is then read once per subset), up to 4 of them.
+    // Matrix-core passes (not with the rotation at read): up to 8 (virtual) heads of a kv-head per launch; larger groups with
+    // fp32 I/O take several launches over head subsets (the cache is then read once per subset), up to 4 of them.
     // (mantissa planes are 16-byte aligned, checked above; exponent planes that are not go to the general
     // pass, which reads them byte by byte)
     const bool fast = !rope && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
+    // More heads than one launch of those takes (16 for 4-bit mantissas in blocks of 16 and 32, else 8), 16-bit I/O: all of
+    // them in one pass that decodes a row once.  12000 tokens, 8 sequences x 8 kv-heads, 4 bits, blocks of 32, call time
+    // before -> now: 32 heads 90.4 -> 60.3 us, 64 heads (general pass) 1135 -> 78 us; 8 bits, 16 heads in blocks of 16
+    // 95.3 -> 68.8 us; at 16 heads in blocks of 32 the LDS pipeline is ahead, 48 against 58 us.
+    const int one_launch = L->mant_bits == 4 && L->block <= 32 ? 16 : 8;
+    const bool wide = !rope && a.G > one_launch && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
+    const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
+    if (wide) sp.n_splits = wp.n_splits;
     // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
     const bool rope_fast = rope && !paging && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 &&
                            aligned16(a.k_exp) && aligned16(a.v_exp);
@@ -593,7 +601,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
             return fail(KVBFP_ERR_INVALID_ARG, "append_decode_attention: negative stride");
         // Inside the LDS split pass the cast is done by the one wavefront that reads the new row, off
         // the path of everybody else; elsewhere the cache-write kernel goes first, as in the two calls.
-        const bool in_kernel = fast && dtype != KVBFP_F32;      // the LDS pipeline: every block size, both mantissa widths
+        // (the pass for many heads: where one workgroup serves all heads of a kv-head)
+        const bool in_kernel = wide ? wp.row_tiles == 1 : (fast && dtype != KVBFP_F32);
         if (in_kernel) {
             a.k_new = k_new; a.v_new = v_new; a.new_stride_b = new_stride_b; a.new_stride_h = new_stride_h;
         } else {
@@ -616,9 +625,11 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     }
     hipError_t err = hipSuccess;
     auto launch_split = [&]() {
-        if (fast) {
-            // heads per launch: 8, or 16 where the LDS pipeline applies and more than 8 are left (its
-            // sixteen-head variant keeps two workgroups per CU resident instead of three)
+        if (wide) {
+            err = launch_decode_split_wide(a, L->mant_bits, (int)dtype, L->block, L->batch, wp, s);
+        } else if (fast) {
+            // heads per launch: 8, or up to 16 where the LDS pipeline applies (its sixteen-head variant keeps two
+            // workgroups per CU resident instead of three)
             const bool lds_path = dtype != KVBFP_F32 && L->mant_bits == 4 && L->block <= 32;
             for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += a.g_cnt) {
                 const int left = a.G - g0;

@@ -103,5 +103,12 @@ hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, i
 hipError_t launch_decode_split_mfma_p8(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s);
 // Rotation at read on the matrix cores (decode_rope.hip): 4-bit mantissas, 16-bit I/O, a.g_cnt <= 4.
 hipError_t launch_decode_split_rope(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s);
+// Many (virtual) heads per kv-head, 16-bit I/O (decode_wide.hip): all of them in one launch.
+struct WidePlan {
+    int32_t row_tiles, groups;   // workgroups per (split, kv-head), groups of 32 heads in each
+    int32_t n_splits;            // <= max_splits, what the workspace is sized for
+};
+WidePlan plan_wide(int G, int64_t units, int64_t max_len, int max_splits);
+hipError_t launch_decode_split_wide(const DecodeArgs& a, int mant_bits, int dtype, int block, int batch, const WidePlan& w, hipStream_t s);
 
 }  // namespace kvbfp

@@ -1,0 +1,140 @@
+"""Many (virtual) query heads per kv-head: the pass that decodes cached rows once to bf16 and multiplies whole
+matrix-core tiles with them (decode_wide.hip), against the oracle at the edges of its tiles of 32 heads and of 64 and
+128 tokens, over regions and pages, with queries as given and cast to BFP."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kvbfp_oracle as O
+from paper_2403_20137_amd import kvbfp, synth
+from test_gpu_paged import fill_both
+from util import assert_attention_close, assert_planes_equal, dev_i32, gpu_cache, oracle_cache
+
+pytestmark = pytest.mark.gpu
+D = 128
+DT = {"f16": torch.float16, "bf16": torch.bfloat16}
+LENS = [517, 1, 64, 129, 255]          # below, at and above the 64- and 128-token tiles, and a single token
+
+
+def _inputs(dt, Hkv, S, B, seed, heads):
+    kg, vg = synth.outlier_gains(seed, 0, Hkv, D), synth.outlier_gains(seed, 1, Hkv, D)
+    k = synth.kv_rows(B, S, Hkv, D, dt, kg, seed, 2)
+    v = synth.kv_rows(B, S, Hkv, D, dt, vg, seed, 3)
+    q = synth.queries(B, heads, D, dt, seed, 4)
+    pk = O.calibrate_perm(synth.to_f32_numpy(synth.kv_rows(1, 32, Hkv, D, dt, kg, seed, 5)[0]))
+    pv = O.calibrate_perm(synth.to_f32_numpy(synth.kv_rows(1, 32, Hkv, D, dt, vg, seed, 6)[0]))
+    return k, v, q, pk, pv
+
+
+@pytest.mark.parametrize("dt,p,n,G,Tq,qbits,page", [
+    ("bf16", 4, 32, 9, 1, 0, 0),
+    ("f16", 8, 16, 16, 1, 0, 0),
+    ("bf16", 4, 32, 17, 1, 0, 0),       # one group of 32 heads, mostly unused
+    ("bf16", 4, 16, 4, 8, 0, 16),       # exactly 32
+    ("f16", 4, 32, 11, 3, 0, 0),        # 33: two groups
+    ("bf16", 4, 64, 8, 8, 8, 64),       # exactly 64
+    ("f16", 8, 16, 13, 5, 0, 16),       # 65: three of four groups
+    ("bf16", 8, 32, 32, 4, 8, 0),       # exactly 128
+    ("bf16", 4, 128, 43, 3, 4, 0),      # 129: two workgroups
+    ("f16", 4, 16, 20, 13, 8, 32),      # 260: three workgroups, fp16 query cast to BFP
+    ("f16", 8, 64, 33, 4, 0, 256),
+])
+def test_against_the_oracle(dt, p, n, G, Tq, qbits, page):
+    B, Hkv, S = len(LENS), 2, max(LENS)
+    k, v, q, pk, pv = _inputs(dt, Hkv, S, B, 40 + G + p, Hkv * G * Tq)
+    q = q.view(B, Tq, Hkv * G, D).contiguous()
+    scale = float(np.float32(-0.07 if qbits == 4 else 0.09))          # the sign of the scale travels with the query
+    lens = dev_i32(np.asarray(LENS))
+    kw = dict(seq_len_dev=lens, perm_k=dev_i32(pk), perm_v=dev_i32(pv), q_mant_bits=qbits)
+    if page:
+        pages = -(-S // page)
+        pool, table, planes = fill_both(k, v, n, p, page, pages, LENS, pk, pv, 7)
+        got = kvbfp.decode_attention_multi_paged(pool, table, q.cuda(), S, scale, **kw)
+    else:
+        planes = oracle_cache(k, v, n, p, S, 0, pk, pv)
+        cache = gpu_cache(k.cuda(), v.cuda(), n, p, S, perm_k=pk, perm_v=pv)
+        got = kvbfp.decode_attention_multi(cache, q.cuda(), S, scale, **kw)
+    torch.cuda.synchronize()
+    for i in range(Tq):
+        seen = [max(l - (Tq - 1 - i), 0) for l in LENS]
+        want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q[:, i]), seen, scale, pk, pv, q_mant_bits=qbits)
+        assert_attention_close(got[:, i], want, DT[dt], "G=%d Tq=%d p=%d n=%d page=%d, token %d" % (G, Tq, p, n, page, i))
+
+
+@pytest.mark.parametrize("G", [12, 40, 150])       # cast inside the pass (one workgroup has all heads) and ahead of it
+@pytest.mark.parametrize("lens", [[300, 1, 65], [128, 0, 129]])
+def test_append_equals_two_calls(G, lens):
+    B, Hkv, S, n, p = len(lens), 2, 320, 32, 4
+    k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 90 + G, Hkv * G)
+    kn, vn = (synth.kv_rows(B, 1, Hkv, D, "bf16", synth.outlier_gains(5, 0, Hkv, D), 5, t).cuda() for t in (7, 8))
+    kw = dict(seq_len_dev=dev_i32(np.asarray(lens)), perm_k=dev_i32(pk), perm_v=dev_i32(pv))
+    one, two = (gpu_cache(k.cuda(), v.cuda(), n, p, S, perm_k=pk, perm_v=pv) for _ in range(2))
+    kvbfp.quantize_append(two, kn, vn, pos_dev=kw["seq_len_dev"] - 1, perm_k=kw["perm_k"], perm_v=kw["perm_v"])
+    b = kvbfp.decode_attention(two, q.cuda(), S, 0.1, **kw)
+    a = kvbfp.append_decode_attention(one, kn, vn, q.cuda(), S, 0.1, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b) and all(torch.equal(x, y) for x, y in zip(one.planes(), two.planes()))
+
+
+@pytest.mark.parametrize("k_shift,q_shift", [(-100, 0), (100, 0), (0, -90), (0, 90)])
+@pytest.mark.parametrize("p", [4, 8])
+def test_ends_of_the_range(p, k_shift, q_shift):
+    B, Hkv, G, S, n = 2, 1, 33, 300, 32
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    k, q = (k.float() * 2.0 ** k_shift).bfloat16(), (q.float() * 2.0 ** q_shift).bfloat16()
+    planes = oracle_cache(k, v, n, p, S, 0)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    assert_planes_equal(cache, planes)
+    scale = float(np.float32(0.09) * np.float32(2.0 ** -(k_shift + q_shift)))
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S, S], scale), torch.bfloat16)
+
+
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("n", [16, 32])
+@pytest.mark.parametrize("which,byte", [("k", 255), ("v", 254), ("k", 1), ("v", 1), ("v", 2)])
+def test_every_exponent_byte(p, n, which, byte):
+    """Blocks with the first and last exponent bytes next to ordinary ones, written into the planes as they are."""
+    B, Hkv, G, S = 1, 1, 33, 200
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    scale = float(np.float32(0.09))
+    mant, exps = (planes[0], planes[1]) if which == "k" else (planes[2], planes[3])
+    if byte > 200:      # block 0 of some tokens; as keys against a query that is tiny there
+        exps[0, 0, [150] if which == "v" else slice(None, None, 3), 0] = byte
+        if which == "k":
+            q = q.float()
+            q[..., :n] *= 2.0 ** -126
+            q = q.bfloat16()
+    elif which == "k":  # all blocks of all keys at the lowest bytes, the scale to match
+        exps[:] = byte + (np.arange(exps.size).reshape(exps.shape) % 2)
+        q, scale = (q.float() * 2.0 ** 60).bfloat16(), float(np.float32(2.0 ** 60))
+    else:               # values: the output is as small as they are, compared after scaling up
+        exps[:] = byte
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale)
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(got).all()) and np.isfinite(want).all()
+    if which == "v" and byte < 200:
+        # bf16 outputs below 2^-126 have an absolute step of 2^-133
+        diff = np.abs(got.cpu().double().numpy() - want)
+        assert (diff <= 2.0 ** -134 + 2.0 ** -8 * np.abs(want)).all(), diff.max()
+    else:
+        assert_attention_close(got, want, torch.bfloat16, "%s %d" % (which, byte))
+
+
+def test_query_and_output_at_any_address():
+    B, Hkv, G, S = 1, 1, 40, 200
+    k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
+    cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
+    want = kvbfp.decode_attention(cache, q.cuda(), S, 0.1, perm_v=dev_i32(pv))
+    shifted = torch.zeros(q.numel() + 1, dtype=q.dtype, device="cuda")
+    shifted[1:] = q.cuda().flatten()
+    out = torch.zeros(q.numel() + 1, dtype=q.dtype, device="cuda")
+    got = kvbfp.decode_attention(cache, shifted[1:].view(q.shape), S, 0.1, perm_v=dev_i32(pv), out=out[1:].view(q.shape))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and float(out[0]) == 0.0
