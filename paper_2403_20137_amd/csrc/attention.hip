@@ -636,12 +636,11 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // (mantissa planes are 16-byte aligned, checked above; exponent planes that are not go to the general
     // pass, which reads them byte by byte)
     const bool fast = !rope && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
-    // More heads than one launch of those takes (16 for 4-bit mantissas in blocks of 16 and 32, else 8), 16-bit I/O: all of
-    // them in one pass that decodes a row once.  12000 tokens, 8 sequences x 8 kv-heads, 4 bits, blocks of 32, call time
-    // before -> now: 32 heads 90.4 -> 60.3 us, 64 heads (general pass) 1135 -> 78 us; 8 bits, 16 heads in blocks of 16
-    // 95.3 -> 68.8 us; at 16 heads in blocks of 32 the LDS pipeline is ahead, 48 against 58 us.
-    const int one_launch = L->mant_bits == 4 && L->block <= 32 ? 16 : 8;
-    const bool wide = !rope && a.G > one_launch && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
+    // More heads than one launch of those takes, 16-bit I/O: all of them in one pass that decodes a row once.  8 sequences x
+    // 12000 tokens x 8 kv-heads, call time before (16 heads per launch of an LDS pipeline for 4 bits and blocks of 16 / 32,
+    // 8 heads otherwise, from 33 heads the general pass) -> now: 16 heads, blocks of 32 48 -> 46 us, of 16 62 -> 47 us, of 64
+    // 67 -> 45 us, 8 bits 95 -> 65 us; 32 heads 90 -> 50 us, 8 bits 168 -> 68 us; 64 heads 1135 -> 73 us.
+    const bool wide = !rope && a.G > 8 && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
     if (wide) sp.n_splits = wp.n_splits;
     // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
@@ -694,13 +693,9 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         if (wide) {
             err = launch_decode_split_wide(a, L->mant_bits, (int)dtype, L->block, L->batch, wp, s);
         } else if (fast) {
-            // heads per launch: 8, or up to 16 where the LDS pipeline applies (its sixteen-head variant keeps two
-            // workgroups per CU resident instead of three)
-            const bool lds_path = dtype != KVBFP_F32 && L->mant_bits == 4 && L->block <= 32;
-            for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += a.g_cnt) {
-                const int left = a.G - g0;
+            for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += a.g_cnt) {      // 8 heads per launch
                 a.g_base = g0;
-                a.g_cnt = (lds_path && left > 8) ? (left < 16 ? left : 16) : (left < 8 ? left : 8);
+                a.g_cnt = a.G - g0 < 8 ? a.G - g0 : 8;
                 err = L->mant_bits == 4 ? launch_decode_split_mfma(a, (int)dtype, L->block, L->batch, s)
                                         : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, s);
                 a.k_new = a.v_new = nullptr;       // the current token is cast by the first launch only

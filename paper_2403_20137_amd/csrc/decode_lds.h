@@ -160,8 +160,7 @@ __device__ __forceinline__ void lds_wait(u32x4& a, uint32_t (&e)[4]) {
 template <int HG>
 __device__ __forceinline__ void lds_wait(uint64_t& w01, uint64_t& w23, uint64_t (&pp)[HG]) {
     if constexpr (HG == 1) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w01), "+v"(w23), "+v"(pp[0]) : : "memory");
-    else if constexpr (HG == 2) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w01), "+v"(w23), "+v"(pp[0]), "+v"(pp[1]) : : "memory");
-    else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w01), "+v"(w23), "+v"(pp[0]), "+v"(pp[1]), "+v"(pp[2]), "+v"(pp[3]) : : "memory");
+    else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(w01), "+v"(w23), "+v"(pp[0]), "+v"(pp[1]) : : "memory");
 }
 __device__ __forceinline__ void lds_wait(u32x4 (&e)[4]) {
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(e[0]), "+v"(e[1]), "+v"(e[2]), "+v"(e[3]) : : "memory");
@@ -199,7 +198,7 @@ template <int P, int N, int HG, bool PAGED, bool QI8 = false>
 __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const int dt) {
     static_assert(P == 4 || P == 8, "mantissa widths of the format");
     static_assert(!QI8 || (P == 8 && N >= 32), "integer score product: 8-bit codes, one key exponent per 32 channels");
-    static_assert(P == 4 || HG <= 2, "8-bit mantissas: one or two groups of four heads");
+    static_assert(HG <= 2, "one or two groups of four heads");
     // value conversions produce value * 2^-kShift (the stored exponent byte is their scale operand); the
     // probabilities carry the inverse
     constexpr int kShift = P == 4 ? 7 : 3;
@@ -207,7 +206,6 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     constexpr int kStageB = 16 * kRowB;            // bytes of a 16-token stage: 1 KB / 2 KB
     constexpr int kM = kStageB / 1024;             // DMA instructions per stage (64 lanes x 16 bytes each)
     static_assert(N == 16 || N == 32 || N == 64 || N == 128, "block sizes of the format");
-    static_assert(HG < 4 || N <= 32, "the sixteen-head variant is built for blocks of 16 and 32");
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
     constexpr int kTileTok = 64;
@@ -241,9 +239,10 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // its FP8 limbs [NH*4 rows][128] in the second (the permutation and the block maxima of the BFP cast
     // pass through there before the limbs are written); the limbs' scale bytes [NH*4][4] sit beside.
     static_assert(sizeof(p_lds) == NH * kD * 4 + NH * 4 * kD, "query staging fills the probability buffer exactly");
-    // sixteen heads: the query operand (4 x 8 registers) does not stay in registers between tiles; it lives in LDS,
-    // [NH * 4 limb rows][128], and every tile reads it back for its score phase
-    constexpr bool kQueryInLds = HG == 4 || (HG == 2 && PAGED && ((P == 4 && N == 32) || (P == 8 && N == 16)));   // (and where paging would push a three-wavefront variant over its registers)
+    // where paging would push a three-wavefront variant with two head groups over its registers, the query operand does
+    // not stay in registers between tiles; it lives in LDS, [NH * 4 limb rows][128], and every tile reads it back for its
+    // score phase
+    constexpr bool kQueryInLds = HG == 2 && PAGED && ((P == 4 && N == 32) || (P == 8 && N == 16));
     // One small LDS object either way: the limbs' scale bytes [NH * 4][4] of the set-up, or -- where the query
     // operand lives in LDS -- that operand; the scale bytes then sit at the end of the query staging area, whose
     // second half the limbs do not need in that case.
@@ -736,8 +735,8 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         // and a stage is re-filled for the wavefront's next tile as soon as its reads have returned.  The
         // exponent bytes of a whole tile are read with its first stage (and re-filled right after).
         const int kStep = a.n_splits * kWaves * kTileTok;      // this workgroup's next 256-token tile
-        // (Where registers are short -- four head groups, or two with blocks of 32, which keep three wavefronts per
-        // SIMD -- every stage issues its own reads and waits for them; the probabilities look ahead with one group only.)
+        // (Where registers are short -- two head groups with blocks of 32, which keep three wavefronts per SIMD --
+        // every stage issues its own reads and waits for them; the probabilities look ahead with one group only.)
         constexpr bool kPipe = HG == 1 || (HG == 2 && N != 32), kPipeP = HG == 1;
         u32x4 rawk[kPipe ? 2 : 1];
         u32x4 rawk8[kPipe ? 2 : 1][2], vw8a[kPipe ? 2 : 1], vw8b[kPipe ? 2 : 1];     // 8-bit mantissas
@@ -745,9 +744,9 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         uint64_t vw01[kPipe ? 2 : 1], vw23[kPipe ? 2 : 1], ppv[kPipeP ? 2 : 1][HG];
         u32x4 vexp32[4];          // blocks of 32: per stage the exponent dwords of tokens 4kg..4kg+3
         uint32_t vexp16[16];      // blocks of 16: per (stage, token) this lane's exponent byte
-        // sixteen heads: the sixteen exponent bytes this lane needs of a tile, packed into four registers right after
+        // the same variant: the sixteen exponent bytes this lane needs of a tile, packed into four registers right after
         // they arrive (blocks of 32: register i = token 4kg + i, byte u = stage; blocks of 16: register u, byte i)
-        constexpr bool kPackVexp = HG == 4 || (HG == 2 && N == 32 && PAGED && P == 4);   // (and where paging would push a three-wavefront variant over its registers)
+        constexpr bool kPackVexp = HG == 2 && N == 32 && PAGED && P == 4;
         uint32_t vexp_pk[4];
         const uint32_t pk_sel01 = (uint32_t)(j >> 2) | ((4u + (uint32_t)(j >> 2)) << 8) | 0x0c0c0000u;
         const uint32_t pk_sel23 = ((uint32_t)(j >> 2) << 16) | ((4u + (uint32_t)(j >> 2)) << 24) | 0x00000c0cu;
@@ -841,10 +840,6 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
 
             // ---------------- scores
             f32x4 s_acc[HG][4];
-            // sixteen heads: the four limb rows of a stage are added up while the next stage's products run, so that
-            // one stage of accumulators is live at a time instead of four (64 registers less at the peak)
-            constexpr bool kEarlySum = HG == 4;
-            float s_sum[kEarlySum ? HG : 1][4];
             static_for<4>([&](auto U) {
                 constexpr int u = decltype(U)::value;
                 constexpr int cur = kPipe ? (u & 1) : 0;
@@ -952,16 +947,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
                     for (int hg = 0; hg < HG; ++hg)
                         s_acc[hg][u] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aq8[hg], hi2, s_acc[hg][u], 0, 4, 0, sa8[hg], 0, sb1);
                 }
-                if constexpr (kEarlySum && u > 0) {
-#pragma unroll
-                    for (int hg = 0; hg < HG; ++hg)
-                        s_sum[hg][u - 1] = (s_acc[hg][u - 1][0] + s_acc[hg][u - 1][1]) + (s_acc[hg][u - 1][2] + s_acc[hg][u - 1][3]);
-                }
             });
-            if constexpr (kEarlySum) {
-#pragma unroll
-                for (int hg = 0; hg < HG; ++hg) s_sum[hg][3] = (s_acc[hg][3][0] + s_acc[hg][3][1]) + (s_acc[hg][3][2] + s_acc[hg][3][3]);
-            }
 
             // ---------------- online softmax; lane (j, kg) owns head kg of each group, tokens 16u + j
 #pragma unroll
@@ -969,7 +955,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
                 float s[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)      // the limb rows
-                    s[u] = kEarlySum ? s_sum[kEarlySum ? hg : 0][u] : (s_acc[hg][u][0] + s_acc[hg][u][1]) + (s_acc[hg][u][2] + s_acc[hg][u][3]);
+                    s[u] = (s_acc[hg][u][0] + s_acc[hg][u][1]) + (s_acc[hg][u][2] + s_acc[hg][u][3]);
                 if (masked) {
                     const int vis = min(left, lim[hg] - T0);
 #pragma unroll

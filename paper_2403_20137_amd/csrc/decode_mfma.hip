@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
 
 // The LDS-DMA pipeline (decode_lds.h) for 4-bit mantissas.
 template <int N, int HG, bool PAGED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 4 ? 2 : ((N != 32 && HG == 2) ? 2 : 3), 4)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((N != 32 && HG == 2) ? 2 : 3, 4)))
 void decode_split_lds_p4(DecodeArgs a, int dt) {
     kvbfp::lds::decode_split_lds_body<4, N, HG, PAGED>(a, dt);
 }
@@ -425,17 +425,6 @@ namespace kvbfp {
 
 hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s) {
     const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
-    if (a.g_cnt > 8) {      // sixteen heads per workgroup: LDS pipeline only (the host asks for it nowhere else)
-        if (dtype == KVBFP_F32 || block > 32) return hipErrorInvalidValue;
-        if (a.block_table) {
-            if (block == 16) decode_split_lds_p4<16, 4, true><<<grid, 256, 0, s>>>(a, dtype);
-            else decode_split_lds_p4<32, 4, true><<<grid, 256, 0, s>>>(a, dtype);
-        } else {
-            if (block == 16) decode_split_lds_p4<16, 4, false><<<grid, 256, 0, s>>>(a, dtype);
-            else decode_split_lds_p4<32, 4, false><<<grid, 256, 0, s>>>(a, dtype);
-        }
-        return hipGetLastError();
-    }
     if (a.block_table) return a.g_cnt <= 4 ? launch_n<1, true>(a, dtype, block, grid, s) : launch_n<2, true>(a, dtype, block, grid, s);
     return a.g_cnt <= 4 ? launch_n<1, false>(a, dtype, block, grid, s) : launch_n<2, false>(a, dtype, block, grid, s);
 }

@@ -5,18 +5,19 @@
 // With G rows a cached element takes 2 G multiply-adds, so from some G on the pass is bound by arithmetic, not by
 // memory, and the arithmetic has to go into full matrix-core tiles:
 //   * A workgroup decodes a tile of cached rows once, to bf16 in LDS (a code times its block's power of two is
-//     exact there), and its four wavefronts, 32 virtual heads each, multiply with it.  With 64 heads or fewer two
-//     or all four wavefronts take the same heads and share the tokens of the tile out instead.
+//     exact there), and its four wavefronts, 32 virtual heads each, multiply with it (decode_split_wide).  With 64 heads or
+//     fewer two wavefronts take the same heads and share the tokens of the tile out, and with 32 or fewer every
+//     wavefront decodes and multiplies its own tokens (decode_split_few).
 //   * Both products are formed transposed, v_mfma_f32_32x32x16_bf16 with S^T = K Q^T and O^T = V^T P^T: a lane then
 //     holds scores, running maximum, sum and outputs of ONE head, the softmax needs one exchange with the other half
 //     of the wavefront, and the registers that hold S^T are, converted, the second operand of the value product -- the
 //     order of the tokens in its reduction is free, and V^T is laid out in LDS in the order S^T leaves them in.
 //   * The query is not rounded: a bf16 query (or one cast to BFP) is one bf16 operand, an fp16 query is two (8 + 3
 //     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities are two bf16 limbs (16 bits), as in the other passes for 16-bit I/O.
-// Bound by: 64 and more heads, the vector ALUs and the matrix cores about alike (per wavefront, 64 tokens and 32 heads:
-// 48 MFMAs of 32 cycles, some 320 vector instructions of softmax and 110 of decoding, 4 cycles each).  256 virtual heads (64
-// query tokens, groups of 4) over 4 x 8192 tokens x 8 kv-heads: 67 us against 1470 us in the general pass.  32 heads and
-// fewer: waiting for the rows of the next tile (two workgroups per compute unit, one tile ahead).
+// Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 48 MFMAs of 32 cycles,
+// some 320 vector instructions of softmax and 110 of decoding, 4 cycles each).  256 virtual heads (64 query tokens, groups of
+// 4) over 4 x 8192 tokens x 8 kv-heads: 63 us against 1470 us in the general pass.  Up to 32 heads: vector ALUs 70 % busy (490
+// instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us, 2.6 TB/s, against 65 us in two launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -58,19 +59,14 @@ __device__ __forceinline__ void unpack8_p4(uint32_t w, float scale, uint32_t (&p
 // Four 8-bit codes -> fp32, scaled by 2^(E - 136) per unit (value * 2^-3).  The byte s mmmm lll is the sum of the FP8
 // numbers s000mmmm (at eight times the scale) and s0000lll; the sum has at most 7 significant bits, so its upper
 // half is the bf16 number.
-__device__ __forceinline__ void unpack4_p8(uint32_t w, uint32_t E, float (&x)[4]) {
-    const float s_lo = __uint_as_float(E << 23), s_hi = __uint_as_float((E + 3u) << 23);
+// `field`: the exponent byte at bit 23 (nothing else of the scale operand counts).
+__device__ __forceinline__ void unpack4_p8(uint32_t w, uint32_t field, float (&x)[4]) {
+    const float s_lo = __uint_as_float(field), s_hi = __uint_as_float(field + (3u << 23));
     const uint32_t hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u), lo = w & 0x87878787u;
     const f32x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, s_hi, false), h23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, s_hi, true);
     const f32x2 l01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, s_lo, false), l23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, s_lo, true);
     x[0] = h01[0] + l01[0]; x[1] = h01[1] + l01[1];
     x[2] = h23[0] + l23[0]; x[3] = h23[1] + l23[1];
-}
-
-// channel of k-slot x of the 8-channel group `grp` of a key row in LDS
-template <int P>
-__device__ __forceinline__ int slot_channel(int grp, int x) {
-    return 8 * grp + (P == 8 ? x : (x < 4 ? 2 * x : 2 * (x - 4) + 1));
 }
 
 // Exponent bytes at the ends of their range.  The conversions take the byte as their scale operand, which fits all but the
@@ -96,8 +92,176 @@ __device__ __forceinline__ int exp_mode(bool above_top, bool above_low, bool tin
 
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32); }
 
+// The query operand: lane (head l32, half), MFMA m: the 8 channels of group `group(m, half)`, in key slot order, QL bf16
+// limbs.  ROWS heads of the workgroup (`used` of them there) are requested ahead of everything else (loads return in
+// order), pass through LDS in cache channel order, and every wavefront takes the 32 from `row0` on.
+template <int ROWS>
+struct QueryRows {
+    static constexpr int kPieces = ROWS * 16 / kThreads;               // 16 pieces of 16 bytes per head
+    u32x4 w[kPieces];
+    int perm;
+    __device__ __forceinline__ void request(const DecodeArgs& a, int b, int kvh, int s_first, int used) {
+        const int tid = threadIdx.x;
+        perm = a.perm_k ? (a.perm_k[kvh * kD + (tid & (kD - 1))] & (kD - 1)) : (tid & (kD - 1));   // masked: device data the host cannot check
+        const bool vec = ((uintptr_t)a.q & 15u) == 0;
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int row = (tid >> 4) + i * (kThreads / 16);
+            const uint16_t* src = (const uint16_t*)a.q + kvbfp::query_row(a, b, kvh, s_first + min(row, used - 1)) * kD + (tid & 15) * 8;
+            if (vec) {
+                w[i] = *(const u32x4*)src;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[i][k] = (uint32_t)src[2 * k] | ((uint32_t)src[2 * k + 1] << 16);
+            }
+        }
+    }
+    // smem: ROWS * 256 bytes, inv_s: kD ints.  Called by the whole workgroup; ends with a barrier.
+    template <int P, int QL, class Group>
+    __device__ __forceinline__ void build(const DecodeArgs& a, int dt, int used, int row0, uint8_t* smem, int* inv_s, float query_mul,
+                                          Group&& group, bf16x8 (&q_op)[QL][8]) {
+        const int tid = threadIdx.x, l32 = tid & 31, half = (tid >> 5) & 1;
+        // cache position of every channel; position c goes to slot order inside its group of 8
+        if (tid < kD) inv_s[perm] = P == 8 ? tid : ((tid & ~7) | ((tid & 1) ? 4 + ((tid & 7) >> 1) : ((tid & 7) >> 1)));
+        lds_only_barrier();
+        int at[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) at[k] = inv_s[(tid & 15) * 8 + k] & (kD - 1);
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int row = (tid >> 4) + i * (kThreads / 16);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t h = row < used ? (w[i][k >> 1] >> (16 * (k & 1))) & 0xFFFFu : 0u;
+                *(uint16_t*)(smem + row * 256 + (((at[k] >> 3) ^ (row & 15)) * 16) + (at[k] & 7) * 2) = (uint16_t)h;
+            }
+        }
+        lds_only_barrier();
+        const int row = row0 + l32;
+        u32x4 raw[8];
+#pragma unroll
+        for (int m = 0; m < 8; ++m) raw[m] = *(const u32x4*)(smem + row * 256 + ((group(m, half) ^ (row & 15)) * 16));
+        lds_only_barrier();                             // the queries give way to the cached rows
+        if (QL == 1 && dt == KVBFP_BF16 && a.q_mant_bits == 0 && query_mul == 1.0f) {      // the operand as it is
+#pragma unroll
+            for (int m = 0; m < 8; ++m) q_op[0][m] = __builtin_bit_cast(bf16x8, raw[m]);
+            return;
+        }
+        auto value = [&](int m, int k) {
+            const uint32_t h = (raw[m][k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
+            return dt == KVBFP_F16 ? (float)__builtin_bit_cast(_Float16, (unsigned short)h) : __uint_as_float(h << 16);
+        };
+        int cast_e[8];                                  // power of two of a mantissa step, if the query is cast to BFP
+        if (a.q_mant_bits) {                            // like a cached row
+            // a group of 8 channels lies in one block; the maximum of a block is that of its groups, here or in the other half
+            float top[8], other[8];
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                top[m] = 0.f;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) top[m] = fmaxf(top[m], fabsf(value(m, k)));
+                other[m] = other_half(top[m]);
+            }
+            const int sh = a.log2_block - 3;            // groups per block, log2
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                float t = 0.f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    t = (group(j, half) >> sh) == (group(m, half) >> sh) ? fmaxf(t, top[j]) : t;
+                    t = (group(j, half ^ 1) >> sh) == (group(m, half) >> sh) ? fmaxf(t, other[j]) : t;
+                }
+                const uint32_t amax = __float_as_uint(t);
+                const uint32_t bumped = (amax + (1u << (24 - a.q_mant_bits))) >> 23;
+                cast_e[m] = (amax == 0 ? 0 : (int)max(bumped, 1u)) - 127 - (a.q_mant_bits - 2);
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                float v = value(m, k);
+                if (a.q_mant_bits) v = ldexpf(rintf(ldexpf(v, -cast_e[m])), cast_e[m]);
+                v *= query_mul;                         // a power of two and the sign of the scale: exact
+                const uint32_t top_bits = __float_as_uint(v) & 0xFFFF0000u;
+                q_op[0][m][k] = __builtin_bit_cast(__bf16, (unsigned short)(top_bits >> 16));
+                if (QL == 2) q_op[QL - 1][m][k] = (__bf16)(v - __uint_as_float(top_bits));
+            }
+            __builtin_amdgcn_sched_barrier(0);          // one group of 8 at a time: the rows in flight hold the registers
+        }
+    }
+};
+
+// kvbfp_append_decode_attention: the current token's rows (position pos), cast and stored by one wavefront before it requests
+// its first tile; returns when they are stored.  Lanes 0-7 take the key row, lanes 8-15 the value row; the others run along
+// with zeros (the block maximum is a cross-lane reduction).
+template <int P>
+__device__ __forceinline__ void append_row(const DecodeArgs& a, int dt, int b, int kvh, int lane, int64_t pos) {
+    const int sub = lane & 7, which = (lane >> 3) & 1;
+    const bool live = lane < 16;
+    const int32_t* pr = which ? a.perm_v : a.perm_k;
+    const uint16_t* src = (const uint16_t*)(which ? a.v_new : a.k_new) + (int64_t)b * a.new_stride_b + (int64_t)kvh * a.new_stride_h;
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int c = (pr && live) ? (pr[kvh * kD + sub * 16 + i] & (kD - 1)) : sub * 16 + i;
+        x[i] = live ? load_as_float(src, dt, c) : 0.f;
+    }
+    uint8_t* const mant = const_cast<uint8_t*>(which ? a.v_mant : a.k_mant);
+    uint8_t* const exps = const_cast<uint8_t*>(which ? a.v_exp : a.k_exp);
+    const int64_t row = kvbfp::cache_row(a, b, kvh, pos);
+    if (a.log2_block == 4) kvbfp::cast::encode_store<P, 16>(x, sub, live, mant, exps, row);
+    else if (a.log2_block == 5) kvbfp::cast::encode_store<P, 32>(x, sub, live, mant, exps, row);
+    else if (a.log2_block == 6) kvbfp::cast::encode_store<P, 64>(x, sub, live, mant, exps, row);
+    else kvbfp::cast::encode_store<P, 128>(x, sub, live, mant, exps, row);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+// Merges the 4 / RG wavefronts that hold the same heads over different tokens (wavefront w: heads 32 (w % RG) ..) and
+// writes this split's partial result for `count` heads from row `h` on.  o_s: LDS, [4][32][kD + 4] floats and [4][32][2].
+template <int RG>
+__device__ __forceinline__ void merge_waves(const DecodeArgs& a, int64_t h, int count, int split, float* o_s, int wave, int lane,
+                                            const f32x16 (&o)[4], float m_run, float l_run) {
+    constexpr int kOStride = kD + 4;
+    const int half = lane >> 5, l32 = lane & 31;
+    float* const ml_s = o_s + 4 * kRows * kOStride;
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(f32x4*)(o_s + (wave * kRows + l32) * kOStride + 32 * ct + 8 * i + 4 * half) = f32x4{o[ct][4 * i], o[ct][4 * i + 1], o[ct][4 * i + 2], o[ct][4 * i + 3]};
+    if (half == 0) {
+        ml_s[(wave * kRows + l32) * 2] = m_run;
+        ml_s[(wave * kRows + l32) * 2 + 1] = l_run;
+    }
+    lds_only_barrier();
+    for (int i = threadIdx.x; i < count * kD; i += kThreads) {
+        const int g = i / kD, c = i % kD;
+        const int w0 = g / kRows, r = g % kRows;
+        float M = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < 4 / RG; ++t) M = fmaxf(M, ml_s[((w0 + t * RG) * kRows + r) * 2]);
+        float acc = 0.f, lsum = 0.f;
+#pragma unroll
+        for (int t = 0; t < 4 / RG; ++t) {
+            const float mw = ml_s[((w0 + t * RG) * kRows + r) * 2];
+            if (mw > -INFINITY) {
+                const float f = exp2f(mw - M);
+                acc = fmaf(f, o_s[((w0 + t * RG) * kRows + r) * kOStride + c], acc);
+                lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 2 + 1], lsum);
+            }
+        }
+        a.part_o[((h + g) * a.n_splits + split) * kD + c] = acc;
+        if (c == 0) {
+            float* ml = a.part_ml + ((h + g) * a.n_splits + split) * 2;
+            ml[0] = M;
+            ml[1] = lsum;
+        }
+    }
+}
+
 // P = mantissa bits; N16: blocks of 16 (a 16-byte chunk of 4-bit codes then spans two blocks).
-// RG = groups of 32 heads per workgroup, 4 / RG wavefronts share the tokens of a tile; QL = bf16 limbs of the query.
+// RG = groups of 32 heads per workgroup (2 or 4), 4 / RG wavefronts share the tokens of a tile; QL = bf16 limbs of the query.
 // grid = (n_splits, H_kv * row_tiles, B), block = 256; a workgroup takes the heads of `groups` (<= RG) groups of 32,
 // and every n_splits-th tile of TT tokens.
 template <int P, bool N16, int RG, int QL>
@@ -105,15 +269,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float score_mul, float query_mul) {
     constexpr int kShift = P == 4 ? 7 : 3;             // decoded values are value * 2^-kShift
     constexpr int TG = 4 / RG;                         // wavefronts that share the tokens of a tile
-    constexpr int TT = RG == 1 ? 128 : 64;             // tokens per tile
+    constexpr int TT = 64;                             // tokens per tile
     constexpr int CB = TT / 32 / TG;                   // blocks of 32 tokens per wavefront
     constexpr int SP = TT / 64;                        // decode passes: a wavefront decodes 16 tokens of every 64
     constexpr int kRowB = kD * P / 8;
     constexpr int kKeyChunks = P == 4 ? 1 : 2;         // 16-byte chunks of a key row per thread and pass
     constexpr int kValWords = P == 4 ? 1 : 2;          // dwords (8 channels) of a value row per thread
     // keys: [TT tokens][16 groups of 8 channels], 16 bytes each, the group's place exchanged with token % 16 so that
-    // the reads of 16 neighbouring tokens hit different banks; values: [128 channels][TT / 8 groups of 8 tokens], the
-    // place exchanged with the channel's bits for both the writes (same bits 0-2, different bits 3-5) and the reads.
+    // the reads of 16 neighbouring tokens hit different banks; values: [128 channels][TT / 8 groups of 8 tokens], row and
+    // place exchanged with the channel's bits so that neither the writes (equal bits 0-2) nor the reads (16 neighbouring
+    // channels) meet in a bank
+    auto value_at = [](int ch, int place) { return (ch ^ ((ch >> 6) & 1)) * (TT * 2) + ((place ^ ((ch ^ (ch >> 3)) & 7)) * 16); };
     constexpr int kKeyBytes = TT * 256, kValBytes = kD * TT * 2;
     constexpr int kOStride = kD + 4;
     constexpr int kMerge = TG > 1 ? 4 * kRows * kOStride * 4 + 4 * kRows * 2 * 4 : 0;
@@ -151,6 +317,9 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         }
         return;
     }
+
+    QueryRows<RG * kRows> query;
+    query.request(a, b, kvh, s_first, s_count);
 
     // ---- packed rows of one tile, as loaded: this wavefront's 16 tokens of every 64
     const int log2_nb = 7 - a.log2_block;              // exponent bytes per row
@@ -243,8 +412,8 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 #pragma unroll
                     for (int d = 0; d < 2; ++d) {
                         float x[4], y[4];
-                        unpack4_p8(r.k[p][i][2 * d], r.ke[p][i], x);
-                        unpack4_p8(r.k[p][i][2 * d + 1], r.ke[p][i], y);
+                        unpack4_p8(r.k[p][i][2 * d], r.ke[p][i] << 23, x);
+                        unpack4_p8(r.k[p][i][2 * d + 1], r.ke[p][i] << 23, y);
                         const u32x4 w = {pack_hi(__float_as_uint(x[0]), __float_as_uint(x[1])), pack_hi(__float_as_uint(x[2]), __float_as_uint(x[3])),
                                          pack_hi(__float_as_uint(y[0]), __float_as_uint(y[1])), pack_hi(__float_as_uint(y[2]), __float_as_uint(y[3]))};
                         *(u32x4*)(krow + (((8 * i + 2 * k_chunk + d) ^ (tok & 15)) * 16)) = w;
@@ -256,8 +425,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             const int place = 2 * (4 * p + wave) + (v_quad & 1);
             auto put = [&](const int c, const uint32_t t01, const uint32_t t23) {      // c = channel % 8
                 const int ch = 8 * v_word + c;
-                const int at = ch * (TT * 2) + ((place ^ ((v_word ^ c) & 7)) * 16) + (v_quad >> 1) * 8;
-                *(u32x2*)(v_lds + at) = u32x2{t01, t23};
+                *(u32x2*)(v_lds + value_at(ch, place) + (v_quad >> 1) * 8) = u32x2{t01, t23};
             };
             if constexpr (P == 4) {
                 uint32_t q[4][4];
@@ -274,7 +442,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
                 for (int w = 0; w < kValWords; ++w) {
                     float x[4][4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack4_p8(r.v[p][i][w], r.ve[p][i], x[i]);
+                    for (int i = 0; i < 4; ++i) unpack4_p8(r.v[p][i][w], r.ve[p][i] << 23, x[i]);
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         put(4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
@@ -283,121 +451,15 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         }
     };
 
-    // ---- kvbfp_append_decode_attention (one row tile only): the current token, position L - 1, is cast and stored by
-    // the one wavefront that decodes that row, before it requests the row's tile.  Lanes 0-7 take the key row, lanes
-    // 8-15 the value row; the others run along with zeros (the block maximum is a cross-lane reduction).
-    const bool appends = a.k_new != nullptr && (int)(((L - 1) / TT) % a.n_splits) == split && (int)(((L - 1) >> 4) & 3) == wave;
-    const int64_t T_new = (L - 1) / TT * TT;             // the tile that holds it
-    const int nr_sub = lane & 7, nr_which = (lane >> 3) & 1;
-    int nr_c[16];
-    float nr_x[16];
-    auto new_row_perm = [&] {
-        const int32_t* pr = nr_which ? a.perm_v : a.perm_k;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) nr_c[i] = (pr && lane < 16) ? (pr[kvh * kD + nr_sub * 16 + i] & (kD - 1)) : nr_sub * 16 + i;
-    };
-    auto new_row_load = [&] {
-        const uint16_t* src = (const uint16_t*)(nr_which ? a.v_new : a.k_new) + (int64_t)b * a.new_stride_b + (int64_t)kvh * a.new_stride_h;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) nr_x[i] = lane < 16 ? load_as_float(src, dt, nr_c[i]) : 0.f;
-    };
-    auto new_row_store = [&] {
-        uint8_t* const mant = const_cast<uint8_t*>(nr_which ? a.v_mant : a.k_mant);
-        uint8_t* const exps = const_cast<uint8_t*>(nr_which ? a.v_exp : a.k_exp);
-        const int64_t row = kvbfp::cache_row(a, b, kvh, L - 1);
-        const bool live = lane < 16;
-        if (a.log2_block == 4) kvbfp::cast::encode_store<P, 16>(nr_x, nr_sub, live, mant, exps, row);
-        else if (a.log2_block == 5) kvbfp::cast::encode_store<P, 32>(nr_x, nr_sub, live, mant, exps, row);
-        else if (a.log2_block == 6) kvbfp::cast::encode_store<P, 64>(nr_x, nr_sub, live, mant, exps, row);
-        else kvbfp::cast::encode_store<P, 128>(nr_x, nr_sub, live, mant, exps, row);
-    };
-    auto stores_done = [&] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-    if (appends) {
-        new_row_perm();
-        if (T_new == t_first) {
-            new_row_load();
-            new_row_store();
-            stores_done();
-        }
-    }
+    // the current token (one row tile only): by the wavefront that decodes its row
+    if (a.k_new != nullptr && (int)(((L - 1) / TT) % a.n_splits) == split && (int)(((L - 1) >> 4) & 3) == wave)
+        append_row<P>(a, dt, b, kvh, lane, L - 1);
 
     Raw raw;
     fetch(t_first, raw);
-    if (appends && T_new != t_first) new_row_load();     // waited for after the set-up
 
-    // ---- query operand: lane (head l32, half), MFMA m: channels of the groups 2m + half, in key slot order
     bf16x8 q_op[QL][8];
-    {
-        if (tid < kD) perm_s[tid] = a.perm_k ? (a.perm_k[kvh * kD + tid] & (kD - 1)) : tid;     // masked: device data the host cannot check
-        const bool vec = ((uintptr_t)a.q & 15u) == 0;
-        for (int i = tid; i < RG * kRows * 16; i += kThreads) {        // 16 pieces of 16 bytes per head
-            const int row = i >> 4;
-            u32x4 w = {0u, 0u, 0u, 0u};
-            if (row < s_count) {
-                const uint16_t* src = (const uint16_t*)a.q + kvbfp::query_row(a, b, kvh, s_first + row) * kD + (i & 15) * 8;
-                if (vec) {
-                    w = *(const u32x4*)src;
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)src[2 * k] | ((uint32_t)src[2 * k + 1] << 16);
-                }
-            }
-            *(u32x4*)(smem + row * 256 + (((i & 15) ^ (row & 15)) * 16)) = w;
-        }
-        lds_only_barrier();
-        const int row = rg * kRows + l32;
-        float x[8][8];
-        float top[8];                                   // largest magnitude of channels 16m .. 16m + 15
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            top[m] = 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int c = perm_s[slot_channel<P>(2 * m + half, k)];
-                const uint32_t h = *(const uint16_t*)(smem + row * 256 + (((c >> 3) ^ (row & 15)) * 16) + (c & 7) * 2);
-                x[m][k] = dt == KVBFP_F16 ? (float)__builtin_bit_cast(_Float16, (unsigned short)h) : __uint_as_float(h << 16);
-                top[m] = fmaxf(top[m], fabsf(x[m][k]));
-            }
-        }
-        if (a.q_mant_bits) {                            // cast to BFP first, in cache channel order, like a cached row
-#pragma unroll
-            for (int m = 0; m < 8; ++m) top[m] = fmaxf(top[m], other_half(top[m]));
-            if (a.log2_block >= 5) {
-#pragma unroll
-                for (int m = 0; m < 8; m += 2) top[m] = top[m + 1] = fmaxf(top[m], top[m + 1]);
-            }
-            if (a.log2_block >= 6) {
-#pragma unroll
-                for (int m = 0; m < 8; m += 4) top[m] = top[m + 1] = top[m + 2] = top[m + 3] = fmaxf(top[m], top[m + 2]);
-            }
-            if (a.log2_block >= 7) {
-                const float t = fmaxf(top[0], top[4]);
-#pragma unroll
-                for (int m = 0; m < 8; ++m) top[m] = t;
-            }
-#pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const uint32_t amax = __float_as_uint(top[m]);
-                const uint32_t bumped = (amax + (1u << (24 - a.q_mant_bits))) >> 23;
-                const int E = amax == 0 ? 0 : (int)max(bumped, 1u);
-                const int e = E - 127 - (a.q_mant_bits - 2);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) x[m][k] = ldexpf(rintf(ldexpf(x[m][k], -e)), e);
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float v = x[m][k] * query_mul;    // a power of two and the sign of the scale: exact
-                const uint32_t top_bits = __float_as_uint(v) & 0xFFFF0000u;
-                q_op[0][m][k] = __builtin_bit_cast(__bf16, (unsigned short)(top_bits >> 16));
-                if (QL == 2) q_op[QL - 1][m][k] = (__bf16)(v - __uint_as_float(top_bits));
-            }
-        }
-        lds_only_barrier();                             // the queries give way to the first tile
-    }
-    if (appends && T_new != t_first) new_row_store();
+    query.template build<P, QL>(a, dt, s_count, rg * kRows, smem, perm_s, query_mul, [](int m, int h) { return 2 * m + h; }, q_op);
 
     const int64_t lim = L - kvbfp::hidden_tokens(a, my_s);         // this head sees tokens below
     const int64_t all_see = L - (a.n_q_tokens - 1);                // every head does
@@ -412,7 +474,6 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     const int my_tok0 = tg * CB * 32;                              // first token of this wavefront inside a tile
     for (int64_t T0 = t_first; T0 < L; T0 += step) {
         decode(raw);
-        if (appends && T0 + step == T_new) stores_done();
         if (T0 + step < L) fetch(T0 + step, raw);
         lds_only_barrier();
         if (active) {
@@ -514,7 +575,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 #pragma unroll
                     for (int ct = 0; ct < 4; ++ct) {
                         const int ch = 32 * ct + l32;
-                        const bf16x8 va = *(const bf16x8*)(v_lds + ch * (TT * 2) + ((place ^ ((ch ^ (ch >> 3)) & 7)) * 16));
+                        const bf16x8 va = *(const bf16x8*)(v_lds + value_at(ch, place));
                         o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, ph, o[ct], 0, 0, 0);
                         o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl, o[ct], 0, 0, 0);
                     }
@@ -539,42 +600,281 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             ml[1] = l_run;
         }
     } else {       // merge the wavefronts that shared the tokens
-        float* const o_s = (float*)smem;                           // [wave][head][kOStride]
-        float* const ml_s = (float*)(smem + 4 * kRows * kOStride * 4);
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *(f32x4*)(o_s + (wave * kRows + l32) * kOStride + 32 * ct + 8 * i + 4 * half) = f32x4{o[ct][4 * i], o[ct][4 * i + 1], o[ct][4 * i + 2], o[ct][4 * i + 3]};
-        if (half == 0) {
-            ml_s[(wave * kRows + l32) * 2] = m_run;
-            ml_s[(wave * kRows + l32) * 2 + 1] = l_run;
+        merge_waves<RG>(a, h0 + s_first, s_count, split, (float*)smem, wave, lane, o, m_run, l_run);
+    }
+}
+
+// Up to 32 heads: the cache is read once, so the pass is bound by memory, and what counts is how much of it is on its way.
+// The four wavefronts take 32 tokens each of a tile of 128 and share nothing until the merge: keys go from memory to
+// registers, where they are the first operand of S^T = K Q^T as they are decoded (a lane holds half of a token's row);
+// values are transposed through 8 KB of LDS of the wavefront's own.  No barrier in the loop, and kDepth tiles per wavefront
+// in flight (one for 8-bit mantissas, whose rows take twice the registers: with two the variants spill, 76 -> 68 us).
+template <int P, int N, int QL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
+    constexpr int kShift = P == 4 ? 7 : 3;
+    constexpr int kDepth = P == 8 ? 1 : 2;
+    constexpr int NB = kD / N;
+    constexpr int kRowB = kD * P / 8;
+    constexpr int kKeyChunks = kRowB / 32;             // 16-byte chunks of a key row per lane (every other one)
+    constexpr int kValWords = P / 4;                   // dwords (8 channels) of a value row per lane
+    constexpr int TT = 32;                             // tokens per wavefront and tile
+    constexpr int kOStride = kD + 4;
+    constexpr int kMerge = 4 * kRows * kOStride * 4 + 4 * kRows * 2 * 4;
+    __shared__ __align__(16) uint8_t smem[kMerge];     // queries, then the transposed values (8 KB per wavefront), then the merge
+    __shared__ int perm_s[kD];
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int half = lane >> 5, l32 = lane & 31;
+    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int64_t h0 = (int64_t)b * a.H_q + (int64_t)kvh * a.G;
+
+    int64_t L = a.seq_len ? (int64_t)a.seq_len[b] : a.max_len;
+    L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
+    if ((int64_t)split * 128 >= L) {       // nothing cached in this split
+        for (int i = tid; i < a.G * kD; i += kThreads) a.part_o[((h0 + i / kD) * a.n_splits + split) * kD + i % kD] = 0.f;
+        if (tid < a.G) {
+            float* ml = a.part_ml + ((h0 + tid) * a.n_splits + split) * 2;
+            ml[0] = -INFINITY;
+            ml[1] = 0.f;
         }
-        lds_only_barrier();
-        for (int i = tid; i < s_count * kD; i += kThreads) {
-            const int g = i / kD, c = i % kD;
-            const int w0 = g / kRows, r = g % kRows;
-            float M = -INFINITY;
+        return;
+    }
+    const int64_t t_first = (int64_t)split * 128 + wave * TT;
+    const int64_t step = (int64_t)a.n_splits * 128;
+    QueryRows<kRows> query;
+    query.request(a, b, kvh, 0, a.G);
+
+    // Plane rows of the two 16-token stages of the tile at T (wave-uniform).  Paged: the page numbers are requested a tile
+    // ahead by the lanes (an ordinary load, so that it queues with the rows and is not waited for by itself).
+    const int64_t unit = ((int64_t)b * a.H_kv + kvh) * a.max_seq;
+    int page_next = 0;
+    auto request_pages = [&](const int64_t T) {
+        if (a.block_table && T < L) {
+            int64_t t = T + 16 * ((lane >> 4) & 1);
+            if (t >= L) t = L - 1;
+            page_next = a.block_table[(int64_t)b * a.table_stride + (t >> a.log2_page)];
+        }
+    };
+    auto stage_row = [&](const int64_t T, const int st) -> int64_t {
+        const int64_t t = T + 16 * st;
+        if (!a.block_table) return unit + t;
+        int page = __builtin_amdgcn_readlane(page_next, 16 * st);
+        page = page < 0 ? 0 : (page >= a.n_pages ? a.n_pages - 1 : page);
+        return (((int64_t)page * a.H_kv + kvh) << a.log2_page) + (t & (((int64_t)1 << a.log2_page) - 1));
+    };
+    // (exponents as loaded: keys, all bytes of the lane's row; values, the byte of this lane's channels per token)
+    struct Raw {
+        u32x4 k[kKeyChunks];
+        uint32_t ke[N == 16 ? 2 : 1];
+        uint32_t v[2][4][kValWords];
+        uint32_t ve[2][4];
+    };
+    const int v_quad = lane >> 4, v_word = lane & 15;
+    auto load_keys = [&](Raw& r, const uint8_t* km, const uint8_t* kx) {       // a lane's row
 #pragma unroll
-            for (int t = 0; t < TG; ++t) M = fmaxf(M, ml_s[((w0 + t * RG) * kRows + r) * 2]);
-            float acc = 0.f, lsum = 0.f;
+        for (int i = 0; i < kKeyChunks; ++i) r.k[i] = __builtin_nontemporal_load((const u32x4*)(km + 32 * i));
+        if constexpr (N == 16) {
+            const u32x2 e = *(const u32x2*)kx;
+            r.ke[0] = e[0];
+            r.ke[N == 16 ? 1 : 0] = e[1];
+        } else if constexpr (N == 32) {
+            r.ke[0] = *(const uint32_t*)kx;
+        } else if constexpr (N == 64) {
+            r.ke[0] = *(const uint16_t*)kx;
+        } else {
+            r.ke[0] = *kx;
+        }
+    };
+    auto load_value = [&](Raw& r, const int st, const int i, const uint8_t* vm, const uint8_t* vx, const uint32_t vr) {
+        if constexpr (P == 4) {
+            r.v[st][i][0] = __builtin_nontemporal_load((const uint32_t*)(vm + (vr * kRowB + v_word * 4)));
+        } else {
+            const u32x2 w = __builtin_nontemporal_load((const u32x2*)(vm + (vr * kRowB + v_word * 8)));
+            r.v[st][i][0] = w[0];
+            r.v[st][i][kValWords - 1] = w[1];
+        }
+        r.ve[st][i] = vx[vr * NB + (8 * v_word) / N];
+    };
+    auto fetch = [&](const int64_t T, Raw& r) {        // T < L; requests the pages of the tile after it
+        const int64_t row0 = stage_row(T, 0);
+        const bool two = T + 16 < L;                   // wave-uniform
+        const int64_t row1 = two ? stage_row(T, 1) : row0;
+        request_pages(T + step);
+        const int last0 = (int)min((int64_t)15, L - 1 - T), last1 = two ? (int)min((int64_t)15, L - 1 - (T + 16)) : last0;
+        const int64_t kr = (l32 >= 16 ? row1 : row0) + min(l32 & 15, l32 >= 16 ? last1 : last0);
+        load_keys(r, a.k_mant + kr * kRowB + half * 16, a.k_exp + kr * NB);
 #pragma unroll
-            for (int t = 0; t < TG; ++t) {
-                const float mw = ml_s[((w0 + t * RG) * kRows + r) * 2];
-                if (mw > -INFINITY) {
-                    const float f = exp2f(mw - M);
-                    acc = fmaf(f, o_s[((w0 + t * RG) * kRows + r) * kOStride + c], acc);
-                    lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 2 + 1], lsum);
+        for (int st = 0; st < 2; ++st) {
+            const uint8_t* __restrict__ vm = a.v_mant + (st ? row1 : row0) * kRowB;
+            const uint8_t* __restrict__ vx = a.v_exp + (st ? row1 : row0) * NB;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) load_value(r, st, i, vm, vx, (uint32_t)min(4 * v_quad + i, st ? last1 : last0));
+        }
+    };
+    // scale operands (only the exponent field counts) of the 16-byte key chunk i, of its blocks of 16, of a value row
+    auto key_exp = [&](const Raw& r, const int i, const int sub) -> uint32_t {      // byte in the exponent field
+        const int ch = (P == 4 ? 32 : 16) * 2 * i + 16 * sub;                      // first channel for half 0
+        constexpr int kHalf = P == 4 ? 32 : 16;                                    // half 1: that many channels on
+        if constexpr (N == 128) return r.ke[0] << 23;
+        const int at0 = ch / N, at1 = (ch + kHalf) / N;                            // constants once unrolled
+        const uint32_t w = r.ke[N == 16 ? at0 / 4 : 0];                            // (at1 never crosses the dword)
+        const int sh = half ? 8 * (at1 & 3) : 8 * (at0 & 3);
+        return __builtin_amdgcn_alignbit(w, w, (uint32_t)((sh + 32 - 23) & 31));
+    };
+
+    // the current token: by the wavefront whose tile holds it
+    if (a.k_new != nullptr && (int)(((L - 1) >> 7) % a.n_splits) == split && (int)(((L - 1) >> 5) & 3) == wave)
+        append_row<P>(a, dt, b, kvh, lane, L - 1);
+
+    Raw raw[kDepth];
+    request_pages(t_first);
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d)
+        if (t_first + d * step < L) fetch(t_first + d * step, raw[d]);
+
+    // MFMA m multiplies the 8 channels of key group group_of(m, half)
+    auto group_of = [](int m, int h) { return P == 4 ? 8 * (m >> 2) + 4 * h + (m & 3) : 4 * (m >> 1) + 2 * h + (m & 1); };
+    bf16x8 q_op[QL][8];
+    query.template build<P, QL>(a, dt, a.G, 0, smem, perm_s, query_mul, group_of, q_op);
+
+    // [128 channels][4 groups of 8 tokens], row and place exchanged with the channel's bits so that neither the writes (equal
+    // bits 0-2) nor the reads (16 neighbouring channels) meet in a bank
+    uint8_t* const v_lds = smem + wave * (kD * TT * 2);
+    auto value_at = [](int ch, int place) { return (ch ^ ((ch >> 3) & 3)) * (TT * 2) + ((place ^ (((ch >> 2) ^ (ch >> 5)) & 3)) * 16); };
+    const int64_t lim = L - kvbfp::hidden_tokens(a, l32);
+    const int64_t all_see = L - (a.n_q_tokens - 1);
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x16 o[4];
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
+
+    auto tile = [&](const int64_t T0, Raw& r) {
+        // ---- values to LDS, the four tokens of a quad side by side per channel; quads 0 and 2 of a stage make its first 16
+        // bytes, 1 and 3 the second (the order in which S^T leaves the tokens)
+#pragma unroll
+        for (int st = 0; st < 2; ++st) {
+            const int place = 2 * st + (v_quad & 1);
+            auto put = [&](const int c, const uint32_t t01, const uint32_t t23) {
+                const int ch = 8 * v_word + c;
+                *(u32x2*)(v_lds + value_at(ch, place) + (v_quad >> 1) * 8) = u32x2{t01, t23};
+            };
+            if constexpr (P == 4) {
+                uint32_t q[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) unpack8_p4(r.v[st][i][0], __uint_as_float(r.ve[st][i] << 23), q[i]);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {          // pair x: channels (0,2), (4,6), (1,3), (5,7)
+                    const int c = x < 2 ? 4 * x : 4 * (x - 2) + 1;
+                    put(c, pack_lo(q[0][x], q[1][x]), pack_lo(q[2][x], q[3][x]));
+                    put(c + 2, pack_hi(q[0][x], q[1][x]), pack_hi(q[2][x], q[3][x]));
+                }
+            } else {
+#pragma unroll
+                for (int w = 0; w < kValWords; ++w) {
+                    float x[4][4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) unpack4_p8(r.v[st][i][w], r.ve[st][i] << 23, x[i]);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        put(4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
                 }
             }
-            a.part_o[((h0 + s_first + g) * a.n_splits + split) * kD + c] = acc;
-            if (c == 0) {
-                float* ml = a.part_ml + ((h0 + s_first + g) * a.n_splits + split) * 2;
-                ml[0] = M;
-                ml[1] = lsum;
+        }
+        // ---- S^T
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            u32x4 kw;
+            if constexpr (P == 4) {
+                uint32_t q[4];
+                unpack8_p4(r.k[m >> 2][m & 3], __uint_as_float(key_exp(r, m >> 2, N == 16 ? (m & 3) >> 1 : 0)), q);
+                kw = u32x4{q[0], q[1], q[2], q[3]};
+            } else {
+                float x[4], y[4];
+                unpack4_p8(r.k[m >> 1][2 * (m & 1)], key_exp(r, m >> 1, 0), x);
+                unpack4_p8(r.k[m >> 1][2 * (m & 1) + 1], key_exp(r, m >> 1, 0), y);
+                kw = u32x4{pack_hi(__float_as_uint(x[0]), __float_as_uint(x[1])), pack_hi(__float_as_uint(x[2]), __float_as_uint(x[3])),
+                           pack_hi(__float_as_uint(y[0]), __float_as_uint(y[1])), pack_hi(__float_as_uint(y[2]), __float_as_uint(y[3]))};
+            }
+            const bf16x8 ka = __builtin_bit_cast(bf16x8, kw);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, q_op[0][m], s, 0, 0, 0);
+            if (QL == 2) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, q_op[QL - 1][m], s, 0, 0, 0);
+        }
+        // the rows are used up: the tile kDepth ahead is requested into the same registers
+        if (T0 + kDepth * step < L) {
+            fetch(T0 + kDepth * step, r);
+        }
+        if (T0 + TT > all_see) {                       // register i: token 8 (i / 4) + 4 half + i % 4
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = T0 + 8 * (i >> 2) + 4 * half + (i & 3) < lim ? s[i] : -INFINITY;
+        }
+        // ---- online softmax, base 2
+        float tmax = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
+        tmax = fmaxf(tmax, other_half(tmax)) * score_mul;          // -inf only if this head sees none of the tile
+        const float m_new = fmaxf(m_run, tmax);
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = exp2_raw(m_run - m_ref);
+        const float m_p = m_ref - (float)kShift;                   // probabilities carry 2^kShift
+        uint32_t p_hi[8], p_lo[8];
+        float psum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+            const float p0 = exp2_raw(fmaf(s[i], score_mul, -m_p));
+            const float p1 = exp2_raw(fmaf(s[i + 1], score_mul, -m_p));
+            psum += p0;
+            psum += p1;
+            p_hi[i / 2] = pack_hi(__float_as_uint(p0), __float_as_uint(p1));
+            bf16x2 lo;
+            lo[0] = (__bf16)(p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u));
+            lo[1] = (__bf16)(p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
+            p_lo[i / 2] = bits(lo);
+        }
+        l_run = l_run * alpha + psum;
+        m_run = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the values were written by other lanes of this wavefront
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // ---- O^T += V^T P^T
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{p_hi[4 * kk], p_hi[4 * kk + 1], p_hi[4 * kk + 2], p_hi[4 * kk + 3]});
+            const bf16x8 pl = __builtin_bit_cast(bf16x8, u32x4{p_lo[4 * kk], p_lo[4 * kk + 1], p_lo[4 * kk + 2], p_lo[4 * kk + 3]});
+#pragma unroll
+            for (int ct = 0; ct < 4; ct += 2) {        // (two blocks in turn: no product waits for the one before it)
+                const bf16x8 v0 = *(const bf16x8*)(v_lds + value_at(32 * ct + l32, 2 * kk + half));
+                const bf16x8 v1 = *(const bf16x8*)(v_lds + value_at(32 * ct + 32 + l32, 2 * kk + half));
+                o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0, ph, o[ct], 0, 0, 0);
+                o[ct + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1, ph, o[ct + 1], 0, 0, 0);
+                o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0, pl, o[ct], 0, 0, 0);
+                o[ct + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1, pl, o[ct + 1], 0, 0, 0);
             }
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the next tile overwrites them
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int64_t T0 = t_first; T0 < L; T0 += kDepth * step) {
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d)
+            if (T0 + d * step < L) tile(T0 + d * step, raw[d]);
     }
+    l_run = (l_run + other_half(l_run)) * (1.0f / (float)(1 << kShift));
+
+    // ---- merge the four wavefronts
+    lds_only_barrier();
+    merge_waves<1>(a, h0, a.G, split, (float*)smem, wave, lane, o, m_run, l_run);
 }
 
 template <int P, bool N16, int RG>
@@ -584,10 +884,21 @@ void launch_ql(const DecodeArgs& a, int dt, dim3 grid, int row_tiles, int groups
     else
         decode_split_wide<P, N16, RG, 1><<<grid, kThreads, 0, s>>>(a, dt, row_tiles, groups, score_mul, query_mul);
 }
+template <int P, int N>
+void launch_few_n(const DecodeArgs& a, int dt, dim3 grid, float score_mul, float query_mul, hipStream_t s) {
+    if (dt == KVBFP_F16 && a.q_mant_bits == 0) decode_split_few<P, N, 2><<<grid, kThreads, 0, s>>>(a, dt, score_mul, query_mul);
+    else decode_split_few<P, N, 1><<<grid, kThreads, 0, s>>>(a, dt, score_mul, query_mul);
+}
+template <int P>
+void launch_few(const DecodeArgs& a, int dt, int block, dim3 grid, float score_mul, float query_mul, hipStream_t s) {
+    if (block == 16) launch_few_n<P, 16>(a, dt, grid, score_mul, query_mul, s);
+    else if (block == 32) launch_few_n<P, 32>(a, dt, grid, score_mul, query_mul, s);
+    else if (block == 64) launch_few_n<P, 64>(a, dt, grid, score_mul, query_mul, s);
+    else launch_few_n<P, 128>(a, dt, grid, score_mul, query_mul, s);
+}
 template <int P, bool N16>
 void launch_rg(const DecodeArgs& a, int dt, dim3 grid, int row_tiles, int groups, float score_mul, float query_mul, hipStream_t s) {
-    if (groups == 1) launch_ql<P, N16, 1>(a, dt, grid, row_tiles, groups, score_mul, query_mul, s);
-    else if (groups == 2) launch_ql<P, N16, 2>(a, dt, grid, row_tiles, groups, score_mul, query_mul, s);
+    if (groups == 2) launch_ql<P, N16, 2>(a, dt, grid, row_tiles, groups, score_mul, query_mul, s);
     else launch_ql<P, N16, 4>(a, dt, grid, row_tiles, groups, score_mul, query_mul, s);
 }
 
@@ -623,7 +934,10 @@ hipError_t launch_decode_split_wide(const DecodeArgs& a, int mant_bits, int dtyp
     const int shift = mant_bits == 4 ? 7 : 3;
     const float score_mul = a.scale_log2e != 0.f ? std::ldexp(2.f * f, e - 1 - at + shift) : 1.f;
     const float query_mul = a.scale_log2e != 0.f ? std::copysign(std::ldexp(1.0f, at), a.scale_log2e) : 0.f;
-    if (mant_bits == 4 && block == 16) launch_rg<4, true>(a, dtype, grid, w.row_tiles, w.groups, score_mul, query_mul, s);
+    if (w.row_tiles == 1 && w.groups == 1) {
+        if (mant_bits == 4) launch_few<4>(a, dtype, block, grid, score_mul, query_mul, s);
+        else launch_few<8>(a, dtype, block, grid, score_mul, query_mul, s);
+    } else if (mant_bits == 4 && block == 16) launch_rg<4, true>(a, dtype, grid, w.row_tiles, w.groups, score_mul, query_mul, s);
     else if (mant_bits == 4) launch_rg<4, false>(a, dtype, grid, w.row_tiles, w.groups, score_mul, query_mul, s);
     else launch_rg<8, false>(a, dtype, grid, w.row_tiles, w.groups, score_mul, query_mul, s);
     return hipGetLastError();

@@ -74,9 +74,9 @@ int check_paging(const kvbfp_layout* pool, const Paging& pg, kvbfp_layout* logic
 
 SplitPlan plan_splits(const kvbfp_layout* L, int32_t n_q_heads, int64_t max_len) {
     // Enough workgroups to fill 256 compute units with as many as are resident per unit - three, or two
-    // of the sixteen-head variant of the LDS pipeline (4-bit mantissas, blocks of 16/32, more than 8 heads
-    // per kv-head) and of the passes for 8-bit mantissas - but no more splits than there are 256-token
-    // tiles: the tiles are dealt out round-robin over the splits.
+    // with 8-bit mantissas (the passes for more than 8 heads also keep two; the workspace of callers counts on
+    // these figures, a pass takes fewer splits where it wants them) - but no more splits than there are
+    // 256-token tiles: the tiles are dealt out round-robin over the splits.
     const int64_t units = (int64_t)L->batch * L->n_kv_heads;
     const int64_t tiles = (max_len + kTokenTile - 1) / kTokenTile;
     const bool sixteen = L->mant_bits == 4 && L->block <= 32 && n_q_heads / L->n_kv_heads > 8;
