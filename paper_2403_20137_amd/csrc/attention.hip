@@ -18,6 +18,7 @@
 
 #include "decode_args.h"
 #include "decode_dev.h"
+#include "decode_spans.h"
 #include "kvbfp_internal.h"
 
 using kvbfp::DecodeArgs;
@@ -356,7 +357,7 @@ __device__ __forceinline__ uint16_t narrow_bf16(float v) {
 // times the workgroups, a quarter of the bytes through each compute unit.
 constexpr int kCombineThreads = 512;
 template <int kCombineBatch, int kChan>
-__global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, int dt) {
+__global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, int dt, int log2_tile) {
     constexpr int kSlices = kCombineThreads / kChan;
     constexpr int kMaxLds = 1024;
     __shared__ float m_s[kMaxLds];
@@ -366,32 +367,40 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
     const int jl = threadIdx.x % kChan, sl = threadIdx.x / kChan;
     const int j = blockIdx.z * kChan + jl;      // channel (cache order)
     const int h = blockIdx.x, b = blockIdx.y;
-    const int64_t bh = (int64_t)b * a.H_q + h;
-    const float* ml = a.part_ml + bh * a.n_splits * 2;
-    const float* po = a.part_o + bh * a.n_splits * kD;
-    const int n = a.n_splits;
-    const bool staged = n <= kMaxLds;           // otherwise (m, l) are read from global memory each time
+    kvbfp::spans::Parts parts = kvbfp::spans::parts_of(a, b, h);
 
     // where this channel goes in the output row: requested with the partial outputs, not after the sums (a load here
     // costs nothing, at the end it is one more round trip to memory)
     const int kvh = h / a.G;
     const int c_raw = a.perm_v ? a.perm_v[kvh * kD + j] : j;
     float v[kCombineBatch];                     // first batch of this thread's partial outputs: splits sl + kSlices k
+    auto first_batch = [&] {
 #pragma unroll
-    for (int k = 0; k < kCombineBatch; ++k) {
-        const int i = sl + k * kSlices;
-        v[k] = i < n ? po[(int64_t)i * kD + j] : 0.f;
+        for (int k = 0; k < kCombineBatch; ++k) {
+            const int i = sl + k * kSlices;
+            v[k] = i < parts.n ? a.part_o[(parts.first + i * parts.step) * kD + j] : 0.f;
+        }
+    };
+    first_batch();
+    // (requested where they are if the lengths are equal; the mark of the first row tells whether they are)
+    if (a.spread && signbit(a.part_ml[parts.first * 2 + 1])) {
+        parts = kvbfp::spans::listed_parts(a, gridDim.y, b, h, log2_tile);
+        first_batch();
     }
+    const float* const ml = a.part_ml + parts.first * 2;
+    const float* const po = a.part_o + parts.first * kD;
+    const int n = parts.n;
+    const bool staged = n <= kMaxLds;           // otherwise (m, l) are read from global memory each time
     if (staged) {
         for (int i = threadIdx.x; i < n; i += kCombineThreads) {
-            const float2 t = *(const float2*)(ml + 2 * i);
+            const float2 t = *(const float2*)(ml + 2 * i * parts.step);
             m_s[i] = t.x;
-            l_s[i] = t.y;
+            l_s[i] = fabsf(t.y);
         }
         __syncthreads();
     }
-    auto m_of = [&](int i) { return staged ? m_s[i] : ml[2 * i]; };
-    auto l_of = [&](int i) { return staged ? l_s[i] : ml[2 * i + 1]; };
+    auto m_of = [&](int i) { return staged ? m_s[i] : ml[2 * i * parts.step]; };
+    auto l_of = [&](int i) { return staged ? l_s[i] : fabsf(ml[2 * i * parts.step + 1]); };
     // Each slice works relative to the maximum of its own splits (a short, unrolled scan instead of
     // one long serial loop over all of them); the slices are brought to the common maximum at the end.
     float mk[kCombineBatch];
@@ -416,7 +425,7 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
         }
         for (int i = sl + kCombineBatch * kSlices; i < n; i += kSlices) {
             const float w = exp2f(m_of(i) - Ms);
-            num = fmaf(w, po[(int64_t)i * kD + j], num);
+            num = fmaf(w, po[i * parts.step * kD + j], num);
             den = fmaf(w, l_of(i), den);
         }
     }
@@ -451,14 +460,15 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
 // partial outputs are tens of megabytes and this is a streaming pass: bound by memory there (8192 heads, 8 splits, 34 MB:
 // 20.6 us with a 512-thread workgroup per head, 8.2 us with this one), by the launch and one round trip otherwise (4.6 us).
 constexpr int kRowSplits = 32;
-__global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt, int n_rows) {
+template <bool SPREAD>
+__global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt, int batch, int log2_tile) {
     __shared__ float out_s[4][kD];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int bh = blockIdx.x * 4 + wave;       // b * H_q + h
-    if (bh >= n_rows) return;
+    if (bh >= batch * a.H_q) return;
     const int b = bh / a.H_q, h = bh % a.H_q;
     const int kvh = h / a.G;
-    const int n = a.n_splits;
+    const int n = a.n_splits;                   // <= kRowSplits
     const float2 ml = lane < n ? ((const float2*)a.part_ml)[(int64_t)bh * n + lane] : make_float2(-INFINITY, 0.f);
     const float2* const po = (const float2*)(a.part_o + (int64_t)bh * n * kD) + lane;
     float2 v[kRowSplits];
@@ -474,20 +484,47 @@ __global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt,
         c0 = a.perm_v[kvh * kD + c0] & (kD - 1);         // masked: the store stays inside the row
         c1 = a.perm_v[kvh * kD + c1] & (kD - 1);
     }
-    const float M = wave_max(ml.x);
-    const float w = M > -INFINITY ? exp2f(ml.x - M) : 0.f;     // 0 for a split without cached tokens
-    const float den = wave_sum(w * ml.y);
-    float n0 = 0.f, n1 = 0.f;
+    // adds 32 or fewer partial results, (m, l) of one per lane and two channels of each in v, to what is merged so far
+    float M = -INFINITY, den = 0.f, n0 = 0.f, n1 = 0.f;
+    auto merge = [&](const float2 t, const int count) {
+        const float M_new = fmaxf(M, wave_max(t.x));
+        const float ref = M_new > -INFINITY ? M_new : 0.f;
+        const float w = exp2f(t.x - ref);                // 0 for a split without cached tokens
+        const float was = exp2f(M - ref);
+        den = den * was + wave_sum(w * fabsf(t.y));
+        n0 *= was;
+        n1 *= was;
+        M = M_new;
 #pragma unroll
-    for (int i = 0; i < kRowSplits; i += 4) {
-        if (i < n) {
+        for (int i = 0; i < kRowSplits; i += 4) {
+            if (i < count) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float wi = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i + k));   // 0 beyond the last split
-                n0 = fmaf(wi, v[i + k].x, n0);
-                n1 = fmaf(wi, v[i + k].y, n1);
+                for (int k = 0; k < 4; ++k) {
+                    const float wi = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i + k));   // 0 beyond the last one
+                    n0 = fmaf(wi, v[i + k].x, n0);
+                    n1 = fmaf(wi, v[i + k].y, n1);
+                }
             }
         }
+    };
+    if (SPREAD && __builtin_amdgcn_ballot_w64(signbit(ml.y)) != 0) {
+        // the lengths differ: other rows, and more than 32 of them for a long sequence among short ones
+        const kvbfp::spans::Parts p = kvbfp::spans::listed_parts(a, batch, b, h, log2_tile);
+        for (int i0 = 0; i0 < p.n; i0 += kRowSplits) {
+            const int count = min(p.n - i0, kRowSplits);
+            const int64_t r0 = p.first + i0 * p.step;
+            const float2 t = lane < count ? ((const float2*)a.part_ml)[r0 + lane * p.step] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+            for (int i = 0; i < kRowSplits; i += 4) {
+                if (i < count) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[i + k] = ((const float2*)(a.part_o + (r0 + min(i + k, count - 1) * p.step) * kD))[lane];
+                }
+            }
+            merge(t, count);
+        }
+    } else {
+        merge(ml, n);
     }
     out_s[wave][c0] = den > 0.f ? n0 / den : 0.f;
     out_s[wave][c1] = den > 0.f ? n1 / den : 0.f;
@@ -643,6 +680,9 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     const bool wide = !rope && a.G > 8 && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
     if (wide) sp.n_splits = wp.n_splits;
+    // tokens of a tile, and whether the splits are shared out by the lengths (decode_spans.h): where there are lengths and
+    // a sequence can have more tiles than splits (otherwise no split has more than one).  The general pass does not.
+    const int log2_tile = wide ? wp.log2_tile : 8;
     // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
     const bool rope_fast = rope && !paging && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 &&
                            aligned16(a.k_exp) && aligned16(a.v_exp);
@@ -653,6 +693,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         if (sp.n_splits > two_per_cu) sp.n_splits = (int32_t)two_per_cu;
     }
     a.n_splits = sp.n_splits;
+    a.spread = (fast || wide || rope_fast) && seq_len_dev && L->batch > 1 && sp.n_splits > 1 &&
+               ((max_len + (1 << log2_tile) - 1) >> log2_tile) > sp.n_splits;
     a.part_ml = a.part_o + (size_t)L->batch * n_q_heads * sp.n_splits * kD;
     const dim3 grid1((unsigned)sp.n_splits, (unsigned)(a.H_kv * gg), (unsigned)L->batch);
     a.g_base = 0;
@@ -730,13 +772,14 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         // few (batch, head) pairs with many splits: 32 channels per workgroup (16 slices x 8 loads cover 128 splits)
         if (sp.n_splits > 32 && (int64_t)n_q_heads * L->batch < 256) {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, kD / 32);
-            decode_combine<8, 32><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
+            decode_combine<8, 32><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype, log2_tile);
         } else if (sp.n_splits <= kRowSplits) {
-            const int n_rows = n_q_heads * L->batch;
-            decode_combine_rows<<<dim3((unsigned)((n_rows + 3) / 4)), 256, 0, s>>>(a, (int)dtype, n_rows);
+            const dim3 grid2((unsigned)((n_q_heads * L->batch + 3) / 4));
+            if (a.spread) decode_combine_rows<true><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch, log2_tile);
+            else decode_combine_rows<false><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch, log2_tile);
         } else {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, 1);
-            decode_combine<32, kD><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
+            decode_combine<32, kD><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype, log2_tile);
         }
         err = hipGetLastError();
     }

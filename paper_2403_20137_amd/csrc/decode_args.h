@@ -17,8 +17,8 @@ struct DecodeArgs {
     const int32_t* seq_len;   // [B] or nullptr
     const int32_t* perm_k;    // [H_kv][D] or nullptr
     const int32_t* perm_v;
-    float* part_ml;           // [B][H_q][n_splits][2]  (m in base-2 units, l)
-    float* part_o;            // [B][H_q][n_splits][D]
+    float* part_ml;           // [rows][2]  (m in base-2 units, l), rows of the partial results: [B][H_q][n_splits], or as
+    float* part_o;            // [rows][D]   decode_spans.h has them where the lengths differ
     int64_t max_seq, max_len;
     // Work division: the sequence is cut into 256-token tiles and split s (blockIdx.x) takes tiles
     // s, s + n_splits, s + 2 n_splits, ...; each split leaves one partial result for the combine pass.
@@ -27,6 +27,7 @@ struct DecodeArgs {
     // s of a kv-head is query token s / real_G, real head kvh * real_G + s % real_G, and may attend
     // to n_q_tokens - 1 - s / real_G tokens fewer than the sequence holds (causal order of the new tokens).
     int32_t H_kv, H_q, G, n_splits, log2_block;
+    int32_t spread;           // 1: where the lengths differ, the n_splits * B workgroups of a kv-head are shared out by them
     int32_t n_q_tokens, real_Hq, real_G;
     int32_t g_base, g_cnt;    // matrix-core passes: this launch serves virtual heads [g_base, g_base + g_cnt) of every kv-head;
                               // g_cnt <= 8
@@ -106,6 +107,7 @@ hipError_t launch_decode_split_rope(const DecodeArgs& a, int dtype, int block, i
 struct WidePlan {
     int32_t row_tiles, groups;   // workgroups per (split, kv-head), groups of 32 heads in each
     int32_t n_splits;            // <= max_splits, what the workspace is sized for
+    int32_t log2_tile;           // tokens of a tile
 };
 WidePlan plan_wide(int G, int64_t units, int64_t max_len, int max_splits);
 hipError_t launch_decode_split_wide(const DecodeArgs& a, int mant_bits, int dtype, int block, int batch, const WidePlan& w, hipStream_t s);

@@ -10,6 +10,7 @@
 
 #include "decode_args.h"
 #include "decode_dev.h"
+#include "decode_spans.h"
 #include "kvbfp_internal.h"
 #include "quantize_dev.h"
 
@@ -254,12 +255,42 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS bases stay in scalar registers
     const int lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int kvh = blockIdx.y;
+    const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
+    // ---- the query and its permutation are requested ahead of everything, before the sequence lengths have arrived, the
+    // first tile of this wavefront right after them, and only then does anybody wait: issued later, these small loads
+    // would queue behind the first tiles of every workgroup of the grid (tens of megabytes).
+    // (Loaded as raw bits and widened later: a conversion right here would make the compiler wait for
+    // each load in turn.  For the same reason the set-up below synchronises with LDS-only barriers:
+    // __syncthreads() also waits for every vector-memory operation, i.e. for the whole first tile.)
+    constexpr int kQPerThread = NH * kD / 256;
+    uint32_t q_bits[kQPerThread];
+    auto request_queries = [&](const int seq) {
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) {
+            const int i = tid + 256 * k, g = i / kD, c = i % kD;
+            const int64_t idx = kvbfp::query_row(a, seq, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + c;   // clamped: rows beyond the count are zeroed below
+            q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
+        }
+    };
+    request_queries(blockIdx.z);
+    // This thread builds the operand bytes at position `qpos` of the heads tid / 128 + 2k.  FP8 operand layout
+    // (measured): byte i of lane-group g is channel 64*(i/16) + 16*g + i%16, and the E8M0 scale of channel block kb
+    // (32 consecutive channels) is taken from lane-group kb.
+    const int qpos = tid & (kD - 1);
+    const int qchan = (qpos & 16) ? 64 + 16 * (qpos >> 5) + (qpos & 15) : 16 * (qpos >> 5) + (qpos & 15);
+    int perm_c = qchan;                 // source channel of cache channel qchan
+    if (a.perm_k) perm_c = a.perm_k[kvh * kD + qchan];
+    __builtin_amdgcn_sched_barrier(0);
+
+    kvbfp::spans::Span span;
+    if (!kvbfp::spans::take(a, len0, 8, kvh * a.G + a.g_base, a.g_cnt, span)) return;
+    if (span.b != (int)blockIdx.z) request_queries(span.b);
+    const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
-    int64_t L = a.seq_len ? (int64_t)a.seq_len[b] : a.max_len;
-    L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
-    // Tiles are dealt out round-robin: split s takes the 256-token tiles s, s + n_splits, s + 2 n_splits, ...
+    const int64_t L = span.L;
+    // Tiles are dealt out round-robin: split s takes the 256-token tiles s, s + n, s + 2 n, ...
     // The workgroups of one (batch, kv-head) then sweep the sequence side by side instead of each
     // streaming a distant region of its own, which the memory system serves a few percent faster, and no
     // split is more than one tile longer than another.  "Split-relative" tokens below count from t_begin.
@@ -268,9 +299,9 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256)
-            a.part_o[(((int64_t)b * a.H_q + h0 + i / kD) * a.n_splits + split) * kD + (i % kD)] = 0.f;
+            a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         if (tid < a.g_cnt) {
-            float* ml = a.part_ml + (((int64_t)b * a.H_q + h0 + tid) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
@@ -286,7 +317,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // room for the list: it looks its pages up tile by tile.)
     constexpr int kPreTiles = !PAGED || (P == 8 && HG == 2 && N == 16) ? 0 : 64;      // 4 KB of LDS per workgroup
     __shared__ __align__(16) int32_t pt_lds[kPreTiles > 0 ? kWaves * kPreTiles * 4 : 4];
-    const int64_t tile_step = (int64_t)a.n_splits * kWaves * kTileTok;
+    const int64_t tile_step = (int64_t)span.n * kWaves * kTileTok;
     auto fetch_pages = [&](auto n_tag, const int first_tile) {    // tiles first_tile .. first_tile + n - 1, n = 32 or 64
         constexpr int n = decltype(n_tag)::value;
         int32_t got[n / 16];
@@ -320,7 +351,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     //     stores (new_row_stored below).
     // If that tile is the wavefront's first, all of this happens right here instead, before the first
     // request.
-    const bool appends = a.k_new != nullptr && (int)(((L - 1) >> 8) % a.n_splits) == split &&
+    const bool appends = a.k_new != nullptr && (int)(((L - 1) >> 8) % span.n) == split &&
                          (int)(((L - 1) & 255) >> 6) == wave;                       // wave-uniform
     const bool appends_first = appends && (L - 1) < t_begin + 256;
     const int nr_sub = lane & 7, nr_which = (lane >> 3) & 1;
@@ -518,27 +549,6 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         }
     };
 
-    // ---- the query and its permutation are requested first, the first tile of this wavefront right
-    // after them, and only then does anybody wait: issued later, these small loads would queue
-    // behind the first tiles of every workgroup of the grid (tens of megabytes).
-    // (Loaded as raw bits and widened later: a conversion right here would make the compiler wait for
-    // each load in turn.  For the same reason the set-up below synchronises with LDS-only barriers:
-    // __syncthreads() also waits for every vector-memory operation, i.e. for the whole first tile.)
-    constexpr int kQPerThread = NH * kD / 256;
-    uint32_t q_bits[kQPerThread];
-#pragma unroll
-    for (int k = 0; k < kQPerThread; ++k) {
-        const int i = tid + 256 * k, g = i / kD, c = i % kD;
-        const int64_t idx = kvbfp::query_row(a, b, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + c;   // clamped: rows beyond the count are zeroed below
-        q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
-    }
-    // This thread builds the operand bytes at position `qpos` of the heads tid / 128 + 2k.  FP8 operand layout
-    // (measured): byte i of lane-group g is channel 64*(i/16) + 16*g + i%16, and the E8M0 scale of channel block kb
-    // (32 consecutive channels) is taken from lane-group kb.
-    const int qpos = tid & (kD - 1);
-    const int qchan = (qpos & 16) ? 64 + 16 * (qpos >> 5) + (qpos & 15) : 16 * (qpos >> 5) + (qpos & 15);
-    int perm_c = qchan;                 // source channel of cache channel qchan
-    if (a.perm_k) perm_c = a.perm_k[kvh * kD + qchan];
     auto lds_barrier = [] { lds_only_barrier(); };
     // The permuted (and, on request, BFP-cast) queries wait in the probability buffer, which is free
     // until the main loop; the operand builders below read them from there.  The raw values go to LDS
@@ -734,7 +744,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         // one stage ahead of its arithmetic, so their latency is covered by the arithmetic of the stage before,
         // and a stage is re-filled for the wavefront's next tile as soon as its reads have returned.  The
         // exponent bytes of a whole tile are read with its first stage (and re-filled right after).
-        const int kStep = a.n_splits * kWaves * kTileTok;      // this workgroup's next 256-token tile
+        const int kStep = span.n * kWaves * kTileTok;      // this workgroup's next 256-token tile
         // (Where registers are short -- two head groups with blocks of 32, which keep three wavefronts per SIMD --
         // every stage issues its own reads and waits for them; the probabilities look ahead with one group only.)
         constexpr bool kPipe = HG == 1 || (HG == 2 && N != 32), kPipeP = HG == 1;
@@ -1145,7 +1155,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[(w * NH + g) * kD + c], acc);
         }
-        a.part_o[(((int64_t)b * a.H_q + h0 + g) * a.n_splits + split) * kD + c] = acc;
+        a.part_o[span.row(h0 + g) * kD + c] = acc;
     }
     if (tid < a.g_cnt) {
         const int g = tid;
@@ -1158,9 +1168,9 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) lsum = fmaf(exp2f(mw - M), ml_s[(w * NH + g) * 2 + 1], lsum);
         }
-        float* ml = a.part_ml + (((int64_t)b * a.H_q + h0 + g) * a.n_splits + split) * 2;
+        float* ml = a.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
-        ml[1] = lsum;
+        ml[1] = span.mark(lsum);
     }
 }
 

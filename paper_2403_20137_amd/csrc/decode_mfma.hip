@@ -33,6 +33,7 @@
 
 #include "decode_args.h"
 #include "decode_dev.h"
+#include "decode_spans.h"
 #include "kvbfp_internal.h"
 #include "quantize_dev.h"
 #include "decode_lds.h"
@@ -84,21 +85,22 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    kvbfp::spans::Span span;
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, blockIdx.y * a.G + a.g_base, a.g_cnt, span)) return;
+    const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
-    int64_t L = a.seq_len ? (int64_t)a.seq_len[b] : a.max_len;
-    L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
-    // 256-token tiles are dealt out round-robin: split s takes tiles s, s + n_splits, s + 2 n_splits, ...;
+    const int64_t L = span.L;
+    // 256-token tiles are dealt out round-robin: split s takes tiles s, s + n, s + 2 n, ...;
     // "split-relative" tokens below count from t_begin
     const int64_t t_begin = (int64_t)split * 256;
     const int64_t t_end = L;
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256)
-            a.part_o[(((int64_t)b * a.H_q + h0 + i / kD) * a.n_splits + split) * kD + (i % kD)] = 0.f;
+            a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         if (tid < a.g_cnt) {
-            float* ml = a.part_ml + (((int64_t)b * a.H_q + h0 + tid) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
 
     {
         int T0 = wave * kSuper;
-        const int step = a.n_splits * kWaves * kSuper;      // this workgroup's next 256-token tile
+        const int step = span.n * kWaves * kSuper;      // this workgroup's next 256-token tile
         for (; T0 + kSuper <= n_full; T0 += step) tile(T0, std::true_type{});
         if (T0 < n_tok) tile(T0, std::false_type{});     // at most one ragged tile per wavefront
     }
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        a.part_o[(((int64_t)b * a.H_q + h0 + g) * a.n_splits + split) * kD + c] = acc;
+        a.part_o[span.row(h0 + g) * kD + c] = acc;
     }
     if (tid < a.g_cnt) {
         const int g = tid;
@@ -381,9 +383,9 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) lsum = fmaf(exp2f(mw - M), ml_s[w][g][1], lsum);
         }
-        float* ml = a.part_ml + (((int64_t)b * a.H_q + h0 + g) * a.n_splits + split) * 2;
+        float* ml = a.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
-        ml[1] = lsum;
+        ml[1] = span.mark(lsum);
     }
 }
 

@@ -26,6 +26,7 @@
 
 #include "decode_args.h"
 #include "decode_dev.h"
+#include "decode_spans.h"
 #include "kvbfp_internal.h"
 #include "quantize_dev.h"
 
@@ -218,9 +219,9 @@ __device__ __forceinline__ void append_row(const DecodeArgs& a, int dt, int b, i
 }
 
 // Merges the 4 / RG wavefronts that hold the same heads over different tokens (wavefront w: heads 32 (w % RG) ..) and
-// writes this split's partial result for `count` heads from row `h` on.  o_s: LDS, [4][32][kD + 4] floats and [4][32][2].
+// writes this split's partial result for `count` heads from head `h` on.  o_s: LDS, [4][32][kD + 4] floats and [4][32][2].
 template <int RG>
-__device__ __forceinline__ void merge_waves(const DecodeArgs& a, int64_t h, int count, int split, float* o_s, int wave, int lane,
+__device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::spans::Span& span, int h, int count, float* o_s, int wave, int lane,
                                             const f32x16 (&o)[4], float m_run, float l_run) {
     constexpr int kOStride = kD + 4;
     const int half = lane >> 5, l32 = lane & 31;
@@ -251,11 +252,11 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, int64_t h, int 
                 lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 2 + 1], lsum);
             }
         }
-        a.part_o[((h + g) * a.n_splits + split) * kD + c] = acc;
+        a.part_o[span.row(h + g) * kD + c] = acc;
         if (c == 0) {
-            float* ml = a.part_ml + ((h + g) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h + g) * 2;
             ml[0] = M;
-            ml[1] = lsum;
+            ml[1] = span.mark(lsum);
         }
     }
 }
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float score_mul, float query_mul) {
     constexpr int kShift = P == 4 ? 7 : 3;             // decoded values are value * 2^-kShift
     constexpr int TG = 4 / RG;                         // wavefronts that share the tokens of a tile
-    constexpr int TT = 64;                             // tokens per tile
+    constexpr int kLog2Tile = 6, TT = 1 << kLog2Tile;  // tokens per tile
     constexpr int CB = TT / 32 / TG;                   // blocks of 32 tokens per wavefront
     constexpr int SP = TT / 64;                        // decode passes: a wavefront decodes 16 tokens of every 64
     constexpr int kRowB = kD * P / 8;
@@ -295,23 +296,23 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int half = lane >> 5, l32 = lane & 31;
-    const int split = blockIdx.x, kvh = blockIdx.y / row_tiles, rt = blockIdx.y % row_tiles, b = blockIdx.z;
-    const int rg = wave % RG, tg = wave / RG;
+    kvbfp::spans::Span span;
+    const int kvh = blockIdx.y / row_tiles, rt = blockIdx.y % row_tiles;
     const int s_first = rt * groups * kRows;                     // first virtual head of the workgroup
     const int s_count = min(groups * kRows, a.G - s_first);      // its heads
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), kLog2Tile, kvh * a.G + s_first, s_count, span)) return;
+    const int split = span.split, b = span.b;
+    const int rg = wave % RG, tg = wave / RG;
     const int my_s = s_first + rg * kRows + l32;                 // this lane's head
     const bool active = rg * kRows < s_count;                    // wave-uniform
-    const int64_t h0 = (int64_t)b * a.H_q + (int64_t)kvh * a.G;
-
-    int64_t L64 = a.seq_len ? (int64_t)a.seq_len[b] : a.max_len;
-    L64 = L64 < 0 ? 0 : (L64 > a.max_len ? a.max_len : L64);
-    const int64_t L = L64;
+    const int h0 = kvh * a.G;
+    const int64_t L = span.L;
     const int64_t t_first = (int64_t)split * TT;
     if (t_first >= L) {       // nothing cached in this split
         for (int i = tid; i < s_count * kD; i += kThreads)
-            a.part_o[((h0 + s_first + i / kD) * a.n_splits + split) * kD + i % kD] = 0.f;
+            a.part_o[span.row(h0 + s_first + i / kD) * kD + i % kD] = 0.f;
         for (int i = tid; i < s_count; i += kThreads) {
-            float* ml = a.part_ml + ((h0 + s_first + i) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h0 + s_first + i) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
@@ -452,7 +453,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     };
 
     // the current token (one row tile only): by the wavefront that decodes its row
-    if (a.k_new != nullptr && (int)(((L - 1) / TT) % a.n_splits) == split && (int)(((L - 1) >> 4) & 3) == wave)
+    if (a.k_new != nullptr && (int)(((L - 1) / TT) % span.n) == split && (int)(((L - 1) >> 4) & 3) == wave)
         append_row<P>(a, dt, b, kvh, lane, L - 1);
 
     Raw raw;
@@ -470,7 +471,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
 
-    const int64_t step = (int64_t)a.n_splits * TT;
+    const int64_t step = (int64_t)span.n * TT;
     const int my_tok0 = tg * CB * 32;                              // first token of this wavefront inside a tile
     for (int64_t T0 = t_first; T0 < L; T0 += step) {
         decode(raw);
@@ -588,19 +589,19 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     // ---- partial result of this split: registers 4i .. 4i+3 of block ct are channels 32 ct + 8 i + 4 half ..
     if constexpr (TG == 1) {
         if (!active || my_s - s_first >= s_count) return;
-        float* const po = a.part_o + ((h0 + my_s) * a.n_splits + split) * kD;
+        float* const po = a.part_o + span.row(h0 + my_s) * kD;
 #pragma unroll
         for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 *(f32x4*)(po + 32 * ct + 8 * i + 4 * half) = f32x4{o[ct][4 * i], o[ct][4 * i + 1], o[ct][4 * i + 2], o[ct][4 * i + 3]};
         if (half == 0) {
-            float* ml = a.part_ml + ((h0 + my_s) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h0 + my_s) * 2;
             ml[0] = m_run;
-            ml[1] = l_run;
+            ml[1] = span.mark(l_run);
         }
     } else {       // merge the wavefronts that shared the tokens
-        merge_waves<RG>(a, h0 + s_first, s_count, split, (float*)smem, wave, lane, o, m_run, l_run);
+        merge_waves<RG>(a, span, h0 + s_first, s_count, (float*)smem, wave, lane, o, m_run, l_run);
     }
 }
 
@@ -627,22 +628,22 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int half = lane >> 5, l32 = lane & 31;
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int64_t h0 = (int64_t)b * a.H_q + (int64_t)kvh * a.G;
-
-    int64_t L = a.seq_len ? (int64_t)a.seq_len[b] : a.max_len;
-    L = L < 0 ? 0 : (L > a.max_len ? a.max_len : L);
+    kvbfp::spans::Span span;
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 7, blockIdx.y * a.G, a.G, span)) return;
+    const int split = span.split, kvh = blockIdx.y, b = span.b;
+    const int h0 = kvh * a.G;
+    const int64_t L = span.L;
     if ((int64_t)split * 128 >= L) {       // nothing cached in this split
-        for (int i = tid; i < a.G * kD; i += kThreads) a.part_o[((h0 + i / kD) * a.n_splits + split) * kD + i % kD] = 0.f;
+        for (int i = tid; i < a.G * kD; i += kThreads) a.part_o[span.row(h0 + i / kD) * kD + i % kD] = 0.f;
         if (tid < a.G) {
-            float* ml = a.part_ml + ((h0 + tid) * a.n_splits + split) * 2;
+            float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
         return;
     }
     const int64_t t_first = (int64_t)split * 128 + wave * TT;
-    const int64_t step = (int64_t)a.n_splits * 128;
+    const int64_t step = (int64_t)span.n * 128;
     QueryRows<kRows> query;
     query.request(a, b, kvh, 0, a.G);
 
@@ -725,7 +726,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     };
 
     // the current token: by the wavefront whose tile holds it
-    if (a.k_new != nullptr && (int)(((L - 1) >> 7) % a.n_splits) == split && (int)(((L - 1) >> 5) & 3) == wave)
+    if (a.k_new != nullptr && (int)(((L - 1) >> 7) % span.n) == split && (int)(((L - 1) >> 5) & 3) == wave)
         append_row<P>(a, dt, b, kvh, lane, L - 1);
 
     Raw raw[kDepth];
@@ -874,7 +875,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
 
     // ---- merge the four wavefronts
     lds_only_barrier();
-    merge_waves<1>(a, h0, a.G, split, (float*)smem, wave, lane, o, m_run, l_run);
+    merge_waves<1>(a, span, h0, a.G, (float*)smem, wave, lane, o, m_run, l_run);
 }
 
 template <int P, bool N16, int RG>
@@ -919,6 +920,7 @@ WidePlan plan_wide(int G, int64_t units, int64_t max_len, int max_splits) {
     if (n > tiles) n = tiles;
     if (n > max_splits) n = max_splits;
     w.n_splits = n < 1 ? 1 : (int32_t)n;
+    w.log2_tile = w.groups > 1 ? 6 : 7;
     return w;
 }
 
