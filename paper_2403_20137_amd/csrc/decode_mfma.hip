@@ -74,7 +74,8 @@ __device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
 template <int N, int HG, int PL, bool PAGED>
-__global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 1 ? 3 : 2, 4)))
+void decode_split_mfma_p4(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
     __shared__ float q_s[NH][kD];                               // scaled, permuted queries
@@ -107,6 +108,74 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
         return;
     }
 
+    // Plane bases of this (batch, kv-head) are wave-uniform (scalar registers); everything inside
+    // the split is addressed with 32-bit offsets from them.
+    // (Paged cache: the bases are those of the pool and every 16-token stage of a tile looks up its page.)
+    const int64_t base = PAGED ? 0 : ((int64_t)b * a.H_kv + kvh) * a.max_seq + t_begin;
+    const uint8_t* __restrict__ k_mant = a.k_mant + base * 64;
+    const uint8_t* __restrict__ v_mant = a.v_mant + base * 64;
+    const uint8_t* __restrict__ k_exp = a.k_exp + base * NB;
+    const uint8_t* __restrict__ v_exp = a.v_exp + base * NB;
+    const int n_tok = (int)(t_end - t_begin);       // tokens from this split's first tile to the end of the sequence
+    // several query tokens: head slot s sees tokens below lim[.] only (split-relative), and a tile counts
+    // as full only if every head sees all of it
+    const int n_vis = (int)(L - t_begin);
+    const int n_full = min(n_tok, n_vis - (a.n_q_tokens - 1));
+    int lim[HG];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) lim[hg] = n_vis - kvbfp::hidden_tokens(a, a.g_base + hg * 4 + kg);
+
+    // exponent byte(s) of key chunk kg of a row
+    const uint32_t ke_col = N == 16 ? 2u * kg : (N == 32 ? (uint32_t)kg : (N == 64 ? (uint32_t)(kg >> 1) : 0u));
+    // The packed rows of one 64-token tile as this lane uses them: key chunk kg of rows 16u + j, value dword j of rows
+    // 16u + 4kg + i, each with its exponent bytes.  The rows of the wavefront's next tile are requested as soon as these are
+    // used up, keys before the softmax and values at the end of a tile, and those of the first tile before the set-up
+    // (which waits for LDS only): a round trip to memory takes longer than the arithmetic of a tile.  4 x 8192 tokens, 8
+    // kv-heads, blocks of 16, fp32 I/O: a call takes 22.2 us, with every tile's rows requested when they are needed 32.6;
+    // 10 x 8000 tokens, blocks of 32 35.3 against 55.1 (2.5 TB/s).  168 registers keep three workgroups per compute unit.
+    struct Rows {
+        u32x4 k[4];
+        uint32_t ke[4], v[4][4], ve[4][4];
+    };
+    auto fetch_keys = [&](const int T0, Rows& r) {
+        kvbfp::StageBases sb{};
+        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
+        const int left = n_tok - T0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t base_u = PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0;
+            const uint8_t* __restrict__ kp = k_mant + base_u * 64;
+            const uint8_t* __restrict__ kep = k_exp + base_u * NB;
+            const uint32_t row = (uint32_t)min(16 * u + j, left - 1);        // rows past the last cached token re-read it
+            r.k[u] = __builtin_nontemporal_load((const u32x4*)(kp + (row * 64u + (uint32_t)kg * 16u)));   // streamed once: keep it out of the caches' way
+            if (N == 16) r.ke[u] = *(const uint16_t*)(kep + (row * NB + ke_col));
+            else r.ke[u] = kep[row * NB + ke_col];
+        }
+    };
+    auto fetch_values = [&](const int T0, Rows& r) {
+        kvbfp::StageBases sb{};
+        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
+        const int left = n_tok - T0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t base_u = PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0;
+            const uint8_t* __restrict__ vp = v_mant + base_u * 64;
+            const uint8_t* __restrict__ vep = v_exp + base_u * NB;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t row = (uint32_t)min(16 * u + 4 * kg + i, left - 1);
+                r.v[u][i] = __builtin_nontemporal_load((const uint32_t*)(vp + (row * 64u + 4u * (uint32_t)j)));
+                r.ve[u][i] = vep[row * NB + (uint32_t)((8 * j) / N)];
+            }
+        }
+    };
+    const int T_first = wave * kSuper, T_step = span.n * kWaves * kSuper;     // this wavefront's tiles
+    Rows rows;
+    if (T_first < n_tok) {
+        fetch_keys(T_first, rows);
+        fetch_values(T_first, rows);
+    }
+
     // q' = permuted query (optionally cast to BFP) * softmax_scale*log2(e) * 2^kShift; head slots beyond G are zero
     {
         const float two_k = (float)(1 << kShift);
@@ -119,11 +188,11 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
             }
             q_s[g][c] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
         }
-        __syncthreads();
+        lds_only_barrier();
         if (a.q_mant_bits) {
             bfp_round_queries(&q_s[0][0], (uint32_t*)&o_s[0][0][0], NH, a.log2_block, a.q_mant_bits);
             for (int i = tid; i < NH * kD; i += 256) (&q_s[0][0])[i] = ((&q_s[0][0])[i] * a.scale_log2e) * two_k;
-            __syncthreads();
+            lds_only_barrier();
         }
     }
 
@@ -154,23 +223,6 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
     const uint32_t sel_even = a_par ? 0x01000c0cu : 0x0c0c0100u;   // halfword 0 of the source
     const uint32_t sel_odd = a_par ? 0x03020c0cu : 0x0c0c0302u;    // halfword 1 of the source
 
-    // Plane bases of this (batch, kv-head) are wave-uniform (scalar registers); everything inside
-    // the split is addressed with 32-bit offsets from them.
-    // (Paged cache: the bases are those of the pool and every 16-token stage of a tile looks up its page.)
-    const int64_t base = PAGED ? 0 : ((int64_t)b * a.H_kv + kvh) * a.max_seq + t_begin;
-    const uint8_t* __restrict__ k_mant = a.k_mant + base * 64;
-    const uint8_t* __restrict__ v_mant = a.v_mant + base * 64;
-    const uint8_t* __restrict__ k_exp = a.k_exp + base * NB;
-    const uint8_t* __restrict__ v_exp = a.v_exp + base * NB;
-    const int n_tok = (int)(t_end - t_begin);       // tokens from this split's first tile to the end of the sequence
-    // several query tokens: head slot s sees tokens below lim[.] only (split-relative), and a tile counts
-    // as full only if every head sees all of it
-    const int n_vis = (int)(L - t_begin);
-    const int n_full = min(n_tok, n_vis - (a.n_q_tokens - 1));
-    int lim[HG];
-#pragma unroll
-    for (int hg = 0; hg < HG; ++hg) lim[hg] = n_vis - kvbfp::hidden_tokens(a, a.g_base + hg * 4 + kg);
-
     float m_run[HG], l_run[HG];
     f32x4 o_acc[HG][4];
 #pragma unroll
@@ -181,47 +233,19 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
         for (int m = 0; m < 4; ++m) o_acc[hg][m] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // Per-lane byte offsets inside a 64-token tile; the tile's base pointers are wave-uniform, so a
-    // load is (scalar base) + (this lane offset) + (compile-time constant).
-    const uint32_t koff = (uint32_t)j * 64u + (uint32_t)kg * 16u;                       // key row j, chunk kg
-    const uint32_t keoff = (uint32_t)j * NB + (N == 16 ? 2u * kg : (N == 32 ? (uint32_t)kg : (N == 64 ? (uint32_t)(kg >> 1) : 0u)));
-    const uint32_t voff = (uint32_t)(4 * kg) * 64u + 4u * (uint32_t)j;                  // value rows 4kg.., dword j
-    const uint32_t veoff = (uint32_t)(4 * kg) * NB + (uint32_t)((8 * j) / N);
-
     // One 64-token tile starting at token T0 of the split.  FULL: all 64 tokens are cached, no
     // clamping or masking; otherwise rows are clamped to the last cached token and masked.
     auto tile = [&](const int T0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        // first row of the tile, wave-uniform; a pool of pages has one base per 16-token stage (a page may hold 16 tokens)
-        kvbfp::StageBases sb{};
-        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
-        auto tile_base = [&](const int u) -> size_t { return PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0; };
         const int left = n_tok - T0;                 // cached tokens from T0 on (>= 1)
 
         // ---------------- scores of 64 tokens
         f32x4 s_acc[HG][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint8_t* __restrict__ kp = k_mant + tile_base(u) * 64;
-            const uint8_t* __restrict__ kep = k_exp + tile_base(u) * NB;
-            uint32_t mo, eo;
-            if (FULL) {
-                mo = koff + 1024u * u;
-                eo = keoff + 16u * NB * u;
-            } else {
-                const uint32_t r = (uint32_t)min(16 * u + j, left - 1);
-                mo = r * 64u + (uint32_t)kg * 16u;
-                eo = r * NB + (keoff - (uint32_t)j * NB);
-            }
-            const u32x4 raw = __builtin_nontemporal_load((const u32x4*)(kp + mo));   // streamed once: keep it out of the caches' way
-            float sc0, sc1;
-            if (N == 16) {
-                const uint32_t e2 = *(const uint16_t*)(kep + eo);
-                sc0 = scale_operand(e2 & 0xFFu);
-                sc1 = scale_operand(e2 >> 8);
-            } else {
-                sc0 = sc1 = scale_operand(kep[eo]);
-            }
+            const u32x4 raw = rows.k[u];
+            const float sc0 = scale_operand(N == 16 ? (rows.ke[u] & 0xFFu) : rows.ke[u]);
+            const float sc1 = N == 16 ? scale_operand(rows.ke[u] >> 8) : sc0;
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) s_acc[hg][u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -233,6 +257,8 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
                     s_acc[hg][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[hg][d], bk, s_acc[hg][u], 0, 0, 0);
             }
         }
+        const bool more = T0 + T_step < n_tok;       // wave-uniform
+        if (more) fetch_keys(T0 + T_step, rows);
 
         // ---------------- online softmax; lane (j, kg) owns head kg of each group, tokens 16u + j
 #pragma unroll
@@ -286,23 +312,9 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
         // ---------------- values of the same 64 tokens
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint8_t* __restrict__ vp = v_mant + tile_base(u) * 64;
-            const uint8_t* __restrict__ vep = v_exp + tile_base(u) * NB;
             Unpacked vv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                uint32_t mo, eo;
-                if (FULL) {
-                    mo = voff + 64u * (16 * u + i);
-                    eo = veoff + NB * (16 * u + i);
-                } else {
-                    const uint32_t r = (uint32_t)min(16 * u + 4 * kg + i, left - 1);
-                    mo = r * 64u + 4u * (uint32_t)j;
-                    eo = r * NB + (uint32_t)((8 * j) / N);
-                }
-                const uint32_t w = __builtin_nontemporal_load((const uint32_t*)(vp + mo));
-                vv[i] = unpack8(w, scale_operand(vep[eo]));
-            }
+            for (int i = 0; i < 4; ++i) vv[i] = unpack8(rows.v[u][i], scale_operand(rows.ve[u][i]));
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) {
                 // probabilities of tokens 16u + 4kg .. +3 for this lane's row (head, parity, limb); a third
@@ -325,6 +337,7 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
                 }
             }
         }
+        if (more) fetch_values(T0 + T_step, rows);
         // the next tile overwrites the probability buffer
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -332,9 +345,8 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p4(DecodeArgs a, int dt
     };
 
     {
-        int T0 = wave * kSuper;
-        const int step = span.n * kWaves * kSuper;      // this workgroup's next 256-token tile
-        for (; T0 + kSuper <= n_full; T0 += step) tile(T0, std::true_type{});
+        int T0 = T_first;
+        for (; T0 + kSuper <= n_full; T0 += T_step) tile(T0, std::true_type{});
         if (T0 < n_tok) tile(T0, std::false_type{});     // at most one ragged tile per wavefront
     }
 
