@@ -687,15 +687,16 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
     const bool rope_fast = rope && !paging && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 &&
                            aligned16(a.k_exp) && aligned16(a.v_exp);
-    // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas
-    // and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
+    // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas,
+    // for more than four heads with fp32 I/O and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
     // others.  8 kv-heads, 8000 tokens, one call with the splits rounded up -> down: 10 sequences 26.5 -> 23.0 us, 13 29.4 ->
     // 26.5, 30 51.3 -> 49.8; 8 bits, 7 sequences 33.8 -> 28.5; rotation, 7 sequences 50.4 -> 39.0.  Not down to one split: lengths
     // that differ need two to be shared out (50 ragged sequences 32.6 us with two, 45.1 with one), and 65 equal ones took
     // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).
     if (rope_fast || (fast && !wide)) {
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
-        const int64_t round = 256 * (rope_fast || L->mant_bits == 8 ? 2 : 3) / units;
+        const bool two = rope_fast || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
+        const int64_t round = 256 * (two ? 2 : 3) / units;
         if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
         else if (rope_fast && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }

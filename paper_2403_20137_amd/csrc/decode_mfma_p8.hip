@@ -76,7 +76,8 @@ __device__ __forceinline__ Pieces unpack4(uint32_t w, float s_hi, float s_lo) {
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
 template <int N, int HG, int PL, bool PAGED>
-__global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
+void decode_split_mfma_p8(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
     __shared__ float q_s[NH][kD];                               // scaled, permuted queries
@@ -109,6 +110,81 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
         return;
     }
 
+    // Plane bases of this (batch, kv-head) are wave-uniform; everything inside the split is
+    // addressed with 32-bit offsets from them.
+    // (Paged cache: the bases are those of the pool and every 16-token stage of a tile looks up its page.)
+    const int64_t base = PAGED ? 0 : ((int64_t)b * a.H_kv + kvh) * a.max_seq + t_begin;
+    const uint8_t* __restrict__ k_mant = a.k_mant + base * 128;
+    const uint8_t* __restrict__ v_mant = a.v_mant + base * 128;
+    const uint8_t* __restrict__ k_exp = a.k_exp + base * NB;
+    const uint8_t* __restrict__ v_exp = a.v_exp + base * NB;
+    const int n_tok = (int)(t_end - t_begin);       // tokens from this split's first tile to the end of the sequence
+    // several query tokens: head slot s sees tokens below lim[.] only (split-relative), and a tile counts
+    // as full only if every head sees all of it
+    const int n_vis = (int)(L - t_begin);
+    const int n_full = min(n_tok, n_vis - (a.n_q_tokens - 1));
+    int lim[HG];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) lim[hg] = n_vis - kvbfp::hidden_tokens(a, a.g_base + hg * 4 + kg);
+
+    const uint32_t kchunk = (uint32_t)kg * 16u;                 // first chunk; the second is 64 bytes on
+    const uint32_t keb0 = (uint32_t)((16 * kg) / N);            // exponent byte of the first chunk
+    const uint32_t keb1 = (uint32_t)((64 + 16 * kg) / N);       // and of the second
+    const uint32_t veb = (uint32_t)((8 * j) / N);               // exponent byte of value channels 8j..8j+7
+
+    // The packed rows of one 64-token tile as this lane uses them, requested a tile ahead (keys before the softmax, values at
+    // the end of a tile, those of the first tile before the set-up, which waits for LDS only): a round trip to memory takes
+    // longer than the arithmetic of a tile.  fp32 I/O, blocks of 16, 8 query heads per kv-head, 4 x 8192 tokens: a call takes 31.4 us
+    // against 52.5 with every row requested where it is needed; over 16-token pages with 4 heads 28.5 against 44.0.
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    struct Rows {
+        u32x4 k[4][2];
+        uint32_t ke[4][2];
+        u32x2 v[4][4];
+        uint32_t ve[4][4];
+    };
+    auto fetch_keys = [&](const int T0, Rows& r) {
+        kvbfp::StageBases sb{};
+        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
+        const int left = n_tok - T0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t base_u = PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0;
+            const uint8_t* __restrict__ kp = k_mant + base_u * 128;
+            const uint8_t* __restrict__ kep = k_exp + base_u * NB;
+            const uint32_t row = (uint32_t)min(16 * u + j, left - 1);        // rows past the last cached token re-read it
+            r.k[u][0] = __builtin_nontemporal_load((const u32x4*)(kp + row * 128u + kchunk));   // streamed once
+            r.k[u][1] = __builtin_nontemporal_load((const u32x4*)(kp + row * 128u + kchunk + 64u));
+            r.ke[u][0] = kep[row * NB + keb0];
+            r.ke[u][1] = (N == 128) ? 0u : (uint32_t)kep[row * NB + keb1];
+        }
+    };
+    auto fetch_values = [&](const int T0, Rows& r) {
+        kvbfp::StageBases sb{};
+        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
+        const int left = n_tok - T0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t base_u = PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0;
+            const uint8_t* __restrict__ vp = v_mant + base_u * 128;
+            const uint8_t* __restrict__ vep = v_exp + base_u * NB;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t row = (uint32_t)min(16 * u + 4 * kg + i, left - 1);
+                r.v[u][i] = __builtin_nontemporal_load((const u32x2*)(vp + row * 128u + 8u * (uint32_t)j));   // streamed once
+                r.ve[u][i] = vep[row * NB + veb];
+            }
+        }
+    };
+    const int T_first = wave * kSuper, T_step = span.n * kWaves * kSuper;     // this wavefront's tiles
+    Rows rows;
+    // (two head groups leave no registers for that: there keys are requested at the top of a tile and values before the softmax)
+    constexpr bool kAhead = HG == 1;
+    if (kAhead && T_first < n_tok) {
+        fetch_keys(T_first, rows);
+        fetch_values(T_first, rows);
+    }
+
     // q' = permuted query (optionally cast to BFP) * softmax_scale*log2(e) * 2^kShift; head slots beyond G are zero
     {
         const float two_k = (float)(1 << kShift);
@@ -121,11 +197,11 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
             }
             q_s[g][c] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
         }
-        __syncthreads();
+        lds_only_barrier();
         if (a.q_mant_bits) {
             bfp_round_queries(&q_s[0][0], (uint32_t*)&o_s[0][0][0], NH, a.log2_block, a.q_mant_bits);
             for (int i = tid; i < NH * kD; i += 256) (&q_s[0][0])[i] = ((&q_s[0][0])[i] * a.scale_log2e) * two_k;
-            __syncthreads();
+            lds_only_barrier();
         }
     }
 
@@ -159,23 +235,6 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
     const uint32_t sel_even = a_par ? 0x01000c0cu : 0x0c0c0100u;   // halfword 0 of the source
     const uint32_t sel_odd = a_par ? 0x03020c0cu : 0x0c0c0302u;    // halfword 1 of the source
 
-    // Plane bases of this (batch, kv-head) are wave-uniform; everything inside the split is
-    // addressed with 32-bit offsets from them.
-    // (Paged cache: the bases are those of the pool and every 16-token stage of a tile looks up its page.)
-    const int64_t base = PAGED ? 0 : ((int64_t)b * a.H_kv + kvh) * a.max_seq + t_begin;
-    const uint8_t* __restrict__ k_mant = a.k_mant + base * 128;
-    const uint8_t* __restrict__ v_mant = a.v_mant + base * 128;
-    const uint8_t* __restrict__ k_exp = a.k_exp + base * NB;
-    const uint8_t* __restrict__ v_exp = a.v_exp + base * NB;
-    const int n_tok = (int)(t_end - t_begin);       // tokens from this split's first tile to the end of the sequence
-    // several query tokens: head slot s sees tokens below lim[.] only (split-relative), and a tile counts
-    // as full only if every head sees all of it
-    const int n_vis = (int)(L - t_begin);
-    const int n_full = min(n_tok, n_vis - (a.n_q_tokens - 1));
-    int lim[HG];
-#pragma unroll
-    for (int hg = 0; hg < HG; ++hg) lim[hg] = n_vis - kvbfp::hidden_tokens(a, a.g_base + hg * 4 + kg);
-
     float m_run[HG], l_run[HG];
     f32x4 o_acc[HG][4];
 #pragma unroll
@@ -186,32 +245,19 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
         for (int m = 0; m < 4; ++m) o_acc[hg][m] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    const uint32_t kchunk = (uint32_t)kg * 16u;                 // first chunk; the second is 64 bytes on
-    const uint32_t keb0 = (uint32_t)((16 * kg) / N);            // exponent byte of the first chunk
-    const uint32_t keb1 = (uint32_t)((64 + 16 * kg) / N);       // and of the second
-    const uint32_t veb = (uint32_t)((8 * j) / N);               // exponent byte of value channels 8j..8j+7
-
     // One 64-token tile starting at token T0 of the split.  FULL: all 64 tokens are cached;
     // otherwise rows are clamped to the last cached token and masked.
     auto tile = [&](const int T0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
-        // first row of the tile, wave-uniform; a pool of pages has one base per 16-token stage (a page may hold 16 tokens)
-        kvbfp::StageBases sb{};
-        if constexpr (PAGED) sb = kvbfp::stage_bases(a, b, kvh, t_begin + T0, t_end);
-        auto tile_base = [&](const int u) -> size_t { return PAGED ? (size_t)(sb.v[u] + t_begin + T0) : (size_t)T0; };
         const int left = n_tok - T0;                 // cached tokens from T0 on (>= 1)
 
+        if (!kAhead) fetch_keys(T0, rows);
         // ---------------- scores of 64 tokens
         f32x4 s_acc[HG][4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint8_t* __restrict__ kp = k_mant + tile_base(u) * 128;
-            const uint8_t* __restrict__ kep = k_exp + tile_base(u) * NB;
-            const uint32_t r = FULL ? (uint32_t)(16 * u + j) : (uint32_t)min(16 * u + j, left - 1);
-            const u32x4 raw0 = __builtin_nontemporal_load((const u32x4*)(kp + r * 128u + kchunk));   // streamed once
-            const u32x4 raw1 = __builtin_nontemporal_load((const u32x4*)(kp + r * 128u + kchunk + 64u));
-            const uint32_t E0 = kep[r * NB + keb0];
-            const uint32_t E1 = (N == 128) ? E0 : (uint32_t)kep[r * NB + keb1];
+            const u32x4 raw0 = rows.k[u][0], raw1 = rows.k[u][1];
+            const uint32_t E0 = rows.ke[u][0], E1 = (N == 128) ? E0 : rows.ke[u][1];
             const float sh0 = scale_hi(E0), sl0 = scale_lo(E0);
             const float sh1 = scale_hi(E1), sl1 = scale_lo(E1);
 #pragma unroll
@@ -225,6 +271,10 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
                     s_acc[hg][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[hg][d], bk, s_acc[hg][u], 0, 0, 0);
             }
         }
+
+        const bool more = kAhead && T0 + T_step < n_tok;       // wave-uniform
+        if (more) fetch_keys(T0 + T_step, rows);
+        if (!kAhead) fetch_values(T0, rows);
 
         // ---------------- online softmax; lane (j, kg) owns head kg of each group, tokens 16u + j
 #pragma unroll
@@ -276,19 +326,14 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
         // ---------------- values of the same 64 tokens
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint8_t* __restrict__ vp = v_mant + tile_base(u) * 128;
-            const uint8_t* __restrict__ vep = v_exp + tile_base(u) * NB;
             Pieces va[4], vb[4];   // channels 8j..8j+3 and 8j+4..8j+7 of tokens 16u + 4kg + i
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t r = FULL ? (uint32_t)(16 * u + 4 * kg + i) : (uint32_t)min(16 * u + 4 * kg + i, left - 1);
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                const u32x2 wv = __builtin_nontemporal_load((const u32x2*)(vp + r * 128u + 8u * (uint32_t)j));   // streamed once
-                const uint2 w = make_uint2(wv[0], wv[1]);
-                const uint32_t E = vep[r * NB + veb];
+                const u32x2 w = rows.v[u][i];
+                const uint32_t E = rows.ve[u][i];
                 const float sh = scale_hi(E), sl = scale_lo(E);
-                va[i] = unpack4(w.x, sh, sl);
-                vb[i] = unpack4(w.y, sh, sl);
+                va[i] = unpack4(w[0], sh, sl);
+                vb[i] = unpack4(w[1], sh, sl);
             }
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) {
@@ -316,6 +361,7 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
                 }
             }
         }
+        if (more) fetch_values(T0 + T_step, rows);
         // the next tile overwrites the probability buffer
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -323,9 +369,8 @@ __global__ __launch_bounds__(256) void decode_split_mfma_p8(DecodeArgs a, int dt
     };
 
     {
-        int T0 = wave * kSuper;
-        const int step = span.n * kWaves * kSuper;      // this workgroup's next 256-token tile
-        for (; T0 + kSuper <= n_full; T0 += step) tile(T0, std::true_type{});
+        int T0 = T_first;
+        for (; T0 + kSuper <= n_full; T0 += T_step) tile(T0, std::true_type{});
         if (T0 < n_tok) tile(T0, std::false_type{});     // at most one ragged tile per wavefront
     }
 
