@@ -163,8 +163,9 @@ class Cache:
 
     @property
     def ptrs(self) -> CachePtrs:
-        return CachePtrs(*[t.data_ptr() if t is not None else None
-                           for t in (self.k_mant, self.k_exp, self.v_mant, self.v_exp)])
+        k, ke, v, ve = self.k_mant, self.k_exp, self.v_mant, self.v_exp
+        return CachePtrs(k.data_ptr() if k is not None else None, ke.data_ptr() if ke is not None else None,
+                         v.data_ptr() if v is not None else None, ve.data_ptr() if ve is not None else None)
 
     def planes(self):
         return self.k_mant, self.k_exp, self.v_mant, self.v_exp
@@ -187,10 +188,18 @@ def alloc_cache(layout: Layout, device="cuda", fill=None) -> Cache:
     return Cache(layout, *planes)
 
 
+# Marshalling is most of the host time of a small call (an appended decode step: 16.2 us when the stream was looked up
+# through a torch Stream object, every pointer wrapped in a ctypes object and the new rows taken as views; 11.2 us now):
+# addresses go through the argument types as plain integers and the current stream as the raw handle torch keeps.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _dev_ptr(t, dtype=None):
@@ -200,7 +209,7 @@ def _dev_ptr(t, dtype=None):
         raise ValueError("expected a device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError("expected dtype %s, got %s" % (dtype, t.dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _host_array(x):
@@ -466,6 +475,24 @@ def decode_attention_paged(pool: Cache, block_table, q, max_len, softmax_scale, 
     return (out, float(ms[0]), float(ms[1])) if profile else out
 
 
+def _new_row_strides(k_new, v_new, dtype, shape):
+    """Checks the current token's rows, [batch][1][n_kv_heads][head_dim] or without the 1; (batch, head) strides."""
+    ks, vs, kt, vt = tuple(k_new.shape), tuple(v_new.shape), k_new.stride(), v_new.stride()
+    if len(ks) == 4:                 # the first row of every sequence (no view: making one costs as much as the checks)
+        if ks[1] == 0:
+            raise IndexError("k_new holds no row")
+        ks, kt = (ks[0], ks[2], ks[3]), (kt[0], kt[2], kt[3])
+        if len(vs) == 4 and vs[1] > 0:
+            vs, vt = (vs[0], vs[2], vs[3]), (vt[0], vt[2], vt[3])
+        else:
+            vs = ()
+    if len(ks) != 3 or kt[2] != 1 or ks != vs or kt != vt or k_new.dtype != dtype or v_new.dtype != dtype:
+        raise ValueError("k_new/v_new must be [batch][n_kv_heads][head_dim], channel-contiguous, same strides, q's dtype")
+    if ks != shape:
+        raise ValueError("k_new/v_new shape does not match the layout")
+    return kt[0], kt[1]
+
+
 def append_decode_attention_paged(pool: Cache, block_table, k_new, v_new, q, max_len, softmax_scale, seq_len_dev=None,
                                   perm_k=None, perm_v=None, q_mant_bits=0, out=None, workspace=None, stream=None):
     """DEVICE, async.  append_decode_attention over a pool of pages."""
@@ -473,13 +500,7 @@ def append_decode_attention_paged(pool: Cache, block_table, k_new, v_new, q, max
     if q.dim() != 3 or not q.is_contiguous():
         raise ValueError("q must be a contiguous [batch][n_q_heads][head_dim] tensor")
     _check_table(block_table, q.shape[0])
-    if k_new.dim() == 4:
-        k_new, v_new = k_new[:, 0], v_new[:, 0]
-    if k_new.dim() != 3 or k_new.stride(2) != 1 or k_new.shape != v_new.shape or k_new.stride() != v_new.stride() \
-            or k_new.dtype != q.dtype or v_new.dtype != q.dtype:
-        raise ValueError("k_new/v_new must be [batch][n_kv_heads][head_dim], channel-contiguous, same strides, q's dtype")
-    if k_new.shape != (q.shape[0], L.n_kv_heads, L.head_dim):
-        raise ValueError("k_new/v_new shape does not match the layout")
+    stride_b, stride_h = _new_row_strides(k_new, v_new, q.dtype, (q.shape[0], L.n_kv_heads, L.head_dim))
     n_q_heads = q.shape[1]
     if out is None:
         out = torch.empty_like(q)
@@ -491,7 +512,7 @@ def append_decode_attention_paged(pool: Cache, block_table, k_new, v_new, q, max
     ptrs = pool.ptrs
     _check(lib().kvbfp_append_decode_attention_paged(
         C.byref(L), C.byref(ptrs), _dev_ptr(block_table, torch.int32), block_table.shape[1], q.shape[0], n_q_heads,
-        _dev_ptr(k_new), _dev_ptr(v_new), k_new.stride(0), k_new.stride(1), _dev_ptr(q), _TORCH_DT[q.dtype],
+        _dev_ptr(k_new), _dev_ptr(v_new), stride_b, stride_h, _dev_ptr(q), _TORCH_DT[q.dtype],
         _dev_ptr(seq_len_dev, torch.int32), int(max_len), float(softmax_scale), _dev_ptr(perm_k, torch.int32),
         _dev_ptr(perm_v, torch.int32), int(q_mant_bits), _dev_ptr(out), _dev_ptr(workspace), workspace.numel(),
         _stream_ptr(stream)))
@@ -542,16 +563,10 @@ def append_decode_attention(cache: Cache, k_new, v_new, q, max_len, softmax_scal
     """DEVICE, async.  k_new / v_new: [batch][1][n_kv_heads][head_dim] (or [batch][n_kv_heads][head_dim]), the
     current token; stored at position seq_len - 1 (max_len - 1 without seq_len_dev), then attention."""
     L, n_q_heads, out, workspace = _decode_common(cache, q, max_len, out, workspace)
-    if k_new.dim() == 4:
-        k_new, v_new = k_new[:, 0], v_new[:, 0]
-    if k_new.dim() != 3 or k_new.stride(2) != 1 or k_new.shape != v_new.shape or k_new.stride() != v_new.stride() \
-            or k_new.dtype != q.dtype or v_new.dtype != q.dtype:
-        raise ValueError("k_new/v_new must be [batch][n_kv_heads][head_dim], channel-contiguous, same strides, q's dtype")
-    if k_new.shape != (L.batch, L.n_kv_heads, L.head_dim):
-        raise ValueError("k_new/v_new shape does not match the layout")
+    stride_b, stride_h = _new_row_strides(k_new, v_new, q.dtype, (L.batch, L.n_kv_heads, L.head_dim))
     ptrs = cache.ptrs
     _check(lib().kvbfp_append_decode_attention(C.byref(L), C.byref(ptrs), n_q_heads, _dev_ptr(k_new), _dev_ptr(v_new),
-                                               k_new.stride(0), k_new.stride(1), _dev_ptr(q), _TORCH_DT[q.dtype],
+                                               stride_b, stride_h, _dev_ptr(q), _TORCH_DT[q.dtype],
                                                _dev_ptr(seq_len_dev, torch.int32), int(max_len), float(softmax_scale),
                                                _dev_ptr(perm_k, torch.int32), _dev_ptr(perm_v, torch.int32),
                                                int(q_mant_bits), _dev_ptr(out), _dev_ptr(workspace), workspace.numel(),
