@@ -703,6 +703,10 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     a.n_splits = sp.n_splits;
     a.spread = (fast || wide || rope_fast) && seq_len_dev && L->batch > 1 && sp.n_splits > 1 &&
                ((max_len + (1 << log2_tile) - 1) >> log2_tile) > sp.n_splits;
+    // One split: nothing to merge, the split pass writes the output itself and the combine pass is not launched: an appended
+    // step over 250 tokens 15.6 -> 8.2 us, 128 sequences x 1000 tokens (1024 units) 36.6 -> 33.0 us.  (Not in the passes for
+    // many heads: their merge has no registers to spare, 20 heads over 12000 tokens 44.7 -> 45.7 us with the branch in it.)
+    a.direct = sp.n_splits == 1 && (rope_fast || (fast && !wide));
     a.part_ml = a.part_o + (size_t)L->batch * n_q_heads * sp.n_splits * kD;
     const dim3 grid1((unsigned)sp.n_splits, (unsigned)(a.H_kv * gg), (unsigned)L->batch);
     a.g_base = 0;
@@ -776,7 +780,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         launch_split();
     }
     if (kernel_ms) (void)hipEventRecord(ev[1], s);
-    for (int r = 0; r < reps && err == hipSuccess; ++r) {
+    for (int r = 0; r < reps && err == hipSuccess && !a.direct; ++r) {
         // few (batch, head) pairs with many splits: 32 channels per workgroup (16 slices x 8 loads cover 128 splits)
         if (sp.n_splits > 32 && (int64_t)n_q_heads * L->batch < 256) {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, kD / 32);

@@ -27,6 +27,7 @@ struct DecodeArgs {
     // s of a kv-head is query token s / real_G, real head kvh * real_G + s % real_G, and may attend
     // to n_q_tokens - 1 - s / real_G tokens fewer than the sequence holds (causal order of the new tokens).
     int32_t H_kv, H_q, G, n_splits, log2_block;
+    int32_t direct;           // 1: one split and no combine pass, the split pass writes the output itself
     int32_t spread;           // 1: where the lengths differ, the n_splits * B workgroups of a kv-head are shared out by them
     int32_t n_q_tokens, real_Hq, real_G;
     int32_t g_base, g_cnt;    // matrix-core passes: this launch serves virtual heads [g_base, g_base + g_cnt) of every kv-head;

@@ -88,9 +88,27 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
+    const int kvh = blockIdx.y;
+    // the queries and their permutation are requested ahead of everything (loads return in order), before the sequence
+    // lengths have arrived
+    const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
+    constexpr int kQPerThread = NH * kD / 256;
+    uint32_t q_bits[kQPerThread];
+    auto request_queries = [&](const int seq) {
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) {
+            const int i = tid + 256 * k;
+            const int64_t idx = kvbfp::query_row(a, seq, kvh, a.g_base + min(i / kD, a.g_cnt - 1)) * kD + i % kD;   // clamped: heads beyond the count are zeroed below
+            q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
+        }
+    };
+    request_queries(blockIdx.z);
+    const int perm_c = a.perm_k ? (a.perm_k[kvh * kD + tid % kD] & (kD - 1)) : tid % kD;       // masked: device data the host cannot check
+    __builtin_amdgcn_sched_barrier(0);
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, blockIdx.y * a.G + a.g_base, a.g_cnt, span)) return;
-    const int split = span.split, kvh = blockIdx.y, b = span.b;
+    if (!kvbfp::spans::take(a, len0, 8, kvh * a.G + a.g_base, a.g_cnt, span)) return;
+    if (span.b != (int)blockIdx.z) request_queries(span.b);
+    const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
     const int64_t L = span.L;
@@ -100,8 +118,10 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     const int64_t t_end = L;
 
     if (t_begin >= t_end) {   // nothing cached in this split
-        for (int i = tid; i < a.g_cnt * kD; i += 256)
-            a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
+        for (int i = tid; i < a.g_cnt * kD; i += 256) {
+            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
+        }
         if (tid < a.g_cnt) {
             float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
@@ -188,14 +208,19 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     // q' = permuted query (optionally cast to BFP) * softmax_scale*log2(e) * 2^kShift; head slots beyond G are zero
     {
         const float two_k = (float)(1 << kShift);
-        for (int i = tid; i < NH * kD; i += 256) {
-            const int g = i / kD, c = i % kD;
-            float v = 0.f;
-            if (g < a.g_cnt) {
-                const int src = a.perm_k ? (a.perm_k[kvh * kD + c] & (kD - 1)) : c;
-                v = load_as_float(a.q, dt, kvbfp::query_row(a, b, kvh, a.g_base + g) * kD + src);
-            }
-            q_s[g][c] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
+        float* const raw = &o_s[0][0][0];           // [NH][kD], original channel order
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) {
+            const int i = tid + 256 * k;
+            const float f = dt == KVBFP_F32 ? __uint_as_float(q_bits[k]) : load_as_float(&q_bits[k], dt, 0);
+            raw[i] = i / kD < a.g_cnt ? f : 0.f;
+        }
+        lds_only_barrier();
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) {
+            const int g = (tid + 256 * k) / kD;
+            const float v = raw[g * kD + perm_c];
+            q_s[g][tid % kD] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
         }
         lds_only_barrier();
         if (a.q_mant_bits) {
@@ -404,9 +429,17 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        a.part_o[span.row(h0 + g) * kD + c] = acc;
+        if (a.direct) {
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                if (ml_s[w][g][0] > -INFINITY) den = fmaf(exp2f(ml_s[w][g][0] - M), ml_s[w][g][1], den);
+            kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + g, c, acc, den);
+        } else {
+            a.part_o[span.row(h0 + g) * kD + c] = acc;
+        }
     }
-    if (tid < a.g_cnt) {
+    if (!a.direct && tid < a.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll

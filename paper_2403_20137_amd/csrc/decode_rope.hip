@@ -148,8 +148,10 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
     const int64_t t_end = L;
 
     if (t_begin >= t_end) {
-        for (int i = tid; i < a.g_cnt * kD; i += 256)
-            a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
+        for (int i = tid; i < a.g_cnt * kD; i += 256) {
+            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
+        }
         if (tid < a.g_cnt) {
             float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
@@ -531,9 +533,17 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        a.part_o[span.row(h0 + g) * kD + c] = acc;
+        if (a.direct) {
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w)
+                if (ml_s[w][g][0] > -INFINITY) den = fmaf(exp2f(ml_s[w][g][0] - M), ml_s[w][g][1], den);
+            kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + g, c, acc, den);
+        } else {
+            a.part_o[span.row(h0 + g) * kD + c] = acc;
+        }
     }
-    if (tid < a.g_cnt) {
+    if (!a.direct && tid < a.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll

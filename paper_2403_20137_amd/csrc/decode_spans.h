@@ -20,6 +20,7 @@
 #include <cstdint>
 
 #include "decode_args.h"
+#include "kvbfp.h"
 
 namespace kvbfp {
 namespace spans {
@@ -155,6 +156,23 @@ __device__ __forceinline__ Parts listed_parts(const DecodeArgs& a, int batch, in
             return p;
         }
         before = __builtin_amdgcn_readlane(upto, 63);
+    }
+}
+
+// One split (a.direct): the merged o of channel c (cache order) of virtual head s of kv-head kvh, normalised by l and
+// rounded once to the output's type, goes where the combine pass would put it.
+__device__ __forceinline__ void write_output(const DecodeArgs& a, int dt, int b, int kvh, int s, int c, float o, float l) {
+    const int to = a.perm_v ? (a.perm_v[kvh * 128 + c] & 127) : c;       // masked: the store stays inside the row
+    const int64_t i = query_row(a, b, kvh, s) * 128 + to;
+    const float r = l > 0.f ? o / l : 0.f;
+    if (dt == KVBFP_F32) {
+        ((float*)a.out)[i] = r;
+    } else if (dt == KVBFP_F16) {
+        ((uint16_t*)a.out)[i] = __builtin_bit_cast(unsigned short, (_Float16)r);
+    } else {
+        uint32_t u = __float_as_uint(r);
+        u += 0x7FFFu + ((u >> 16) & 1u);
+        ((uint16_t*)a.out)[i] = (uint16_t)(u >> 16);
     }
 }
 

@@ -75,3 +75,21 @@ def test_append_inside_the_pass(p, G):
     b = kvbfp.decode_attention(two, q.cuda(), S, 0.1, seq_len_dev=lens_t, perm_k=pkd, perm_v=pvd)
     torch.cuda.synchronize()
     assert torch.equal(a, b) and all(torch.equal(x, y) for x, y in zip(one.planes(), two.planes()))
+
+
+@pytest.mark.parametrize("dtype,p,n,G", [
+    (torch.bfloat16, 4, 32, 1), (torch.float16, 8, 64, 6), (torch.float32, 4, 16, 4), (torch.float32, 8, 128, 5),
+    (torch.bfloat16, 4, 16, 12),                 # many heads: keeps the combine pass
+])
+def test_one_split_writes_the_output_itself(dtype, p, n, G):
+    # 256 tokens and fewer are one tile, so one split; a full tile, one token, none, a ragged tile
+    k, v, q, pk, pv = make_small(dtype, B=4, S=256, Hkv=2, G=G, seed=700 + G)
+    got, want = run_both(k, v, q, n, p, [256, 1, 0, 200], 128 ** -0.5, pk, pv)
+    assert_attention_close(got, want, dtype)
+    assert bool((got[2] == 0).all())
+
+
+def test_one_split_of_the_rotation_at_read():
+    k, v, q, pk, pv = make_small(torch.bfloat16, B=3, S=256, Hkv=2, G=6, seed=710)
+    got, want = run_rope(k, v, q, 32, 4, [256, 0, 130], 128 ** -0.5, pk, pv, 1)
+    assert_attention_close(got, want, torch.bfloat16)
