@@ -361,7 +361,8 @@ int kvbfp_decode_attention_multi_paged(const kvbfp_layout* pool, const kvbfp_cac
  * kvbfp_decode_attention_qbfp (Sec. III; same arguments, same result in `out`) with HIP events
  * recorded on `hip_stream` before the split pass, between the two passes and after the combine
  * pass, waits for the last one and returns the two durations in milliseconds:
- *   kernel_ms : HOST float[2]; [0] = split pass (the kernel that streams the cache), [1] = combine.
+ *   kernel_ms : HOST float[2]; [0] = split pass (the kernel that streams the cache), [1] = combine (about 0 where
+ *               there is one split, whose pass writes the output itself).
  * Creates and destroys three events per call; not meant for a serving loop.
  * Errors: as kvbfp_decode_attention_qbfp, plus INVALID_ARG for a NULL kernel_ms. */
 int kvbfp_decode_attention_profile(const kvbfp_layout* layout, const kvbfp_cache* cache,
