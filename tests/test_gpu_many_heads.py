@@ -127,93 +127,6 @@ def test_every_exponent_byte(p, n, which, byte):
         assert_attention_close(got, want, torch.bfloat16, "%s %d" % (which, byte))
 
 
-@pytest.mark.parametrize("p", [4, 8])
-@pytest.mark.parametrize("n", [16, 32, 64, 128])
-@pytest.mark.parametrize("byte,beside", [(1, None), (2, None), (1, 20), (3, None)])
-def test_keys_with_the_smallest_exponent_bytes_up_to_32_heads(p, n, byte, beside):
-    """Keys are exact at every byte a finite row can have, as in the passes for up to 8 heads: with the scale to match, the
-    scores come out as anywhere else.  beside: the first 16 tokens of every 40 hold larger ones."""
-    B, Hkv, G, S = 1, 1, 12, 200
-    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
-    planes = oracle_cache(k, v, n, p, S, 0)
-    planes[1][:] = byte + (np.arange(planes[1].size).reshape(planes[1].shape) % 2)
-    if beside:
-        planes[1][:, :, np.arange(S) % 40 < 16] = beside
-    q, scale = (q.float() * 2.0 ** 60).bfloat16(), float(np.float32(2.0 ** (60 if not beside else 44)))
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
-    for t, w in zip(cache.planes(), planes):
-        t.copy_(torch.from_numpy(w))
-    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
-    torch.cuda.synchronize()
-    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
-
-
-@pytest.mark.parametrize("p,top", [(4, 254), (4, 253), (4, 252), (8, 251), (8, 250), (8, 249)])
-@pytest.mark.parametrize("n", [16, 32, 64, 128])
-def test_keys_with_the_largest_exponent_bytes_up_to_32_heads(p, n, top):
-    """Every third token's rows at the last bytes the pass takes and around them, the others 2^20 smaller."""
-    B, Hkv, G, S = 1, 1, 12, 200
-    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
-    planes = oracle_cache(k, v, n, p, S, 0)
-    planes[1][:] = top - 20
-    planes[1][:, :, ::3] = top
-    q, scale = (q.float() * 2.0 ** -60).bfloat16(), float(np.float32(2.0 ** -(top - 127 - 60)) * np.float32(0.05))
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
-    for t, w in zip(cache.planes(), planes):
-        t.copy_(torch.from_numpy(w))
-    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
-    torch.cuda.synchronize()
-    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
-
-
-@pytest.mark.parametrize("dt", ["bf16", "f16"])
-@pytest.mark.parametrize("p,n", [(4, 16), (4, 32), (8, 32)])
-@pytest.mark.parametrize("G", [40, 100, 130])
-def test_partial_results_above_32_heads_are_fp32(dt, p, n, G):
-    """More than 32 heads: probabilities keep their 24 bits.  The workspace holds the partial results in fp32; merged here
-    in 64 bits they are as far from the oracle as fp32 sums over the scores' rounding are: 2100 products of weights
-    whose base-2 scores of magnitude up to 16 carry 2^-24 of it each, 16 * 2^-24 = 1e-6 times a few for the sum of
-    128 products behind a score."""
-    B, S, Hkv = 2, 2100, 1
-    k, v, q, pk, _ = _inputs(dt, Hkv, S, B, 5, Hkv * G)
-    planes = oracle_cache(k, v, n, p, S, 0, pk, None)
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S, perm_k=pk)
-    scale, Hq = float(np.float32(D ** -0.5)), Hkv * G
-    need = kvbfp.decode_workspace_bytes(cache.layout, Hq, S)
-    splits = need // (B * Hq * (D + 2) * 4)
-    ws = torch.zeros((need,), dtype=torch.uint8, device="cuda")
-    kvbfp.decode_attention(cache, q.cuda(), S, scale, perm_k=dev_i32(pk), workspace=ws)
-    torch.cuda.synchronize()
-    f = ws.view(torch.float32).cpu().double().numpy()
-    po, ml = f[:B * Hq * splits * D].reshape(B, Hq, splits, D), f[B * Hq * splits * D:].reshape(B, Hq, splits, 2)
-    assert (ml[..., 1] > 0).all()
-    w = np.exp2(ml[..., 0] - ml[..., 0].max(axis=-1, keepdims=True))
-    merged = (w[..., None] * po).sum(axis=2) / (w * ml[..., 1]).sum(axis=-1)[..., None]
-    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S, S], scale, pk, None)
-    err = np.linalg.norm(merged - want, axis=-1) / np.linalg.norm(want, axis=-1)
-    assert err.max() <= 6e-6 and err.mean() <= 6e-7, (err.max(), err.mean())
-
-
-@pytest.mark.parametrize("p", [4, 8])
-@pytest.mark.parametrize("dt,q_exp,s_exp", [("bf16", -120, -12), ("f16", -12, -120), ("bf16", -60, -72)])
-def test_query_far_below_one_times_a_small_scale(p, dt, q_exp, s_exp):
-    """q * softmax_scale around 2^-132, where fp32 itself is short of bits, against keys around 2^124: the scores count."""
-    B, Hkv, G, S, n = 1, 1, 40, 300, 32
-    gen = torch.Generator().manual_seed(8)
-    k, v = (torch.randn(B, S, Hkv, D, generator=gen) * f for f in (2.0 ** 124, 1.0))
-    k, v = k.clamp(-2.0 ** 126, 2.0 ** 126).bfloat16(), v.bfloat16()
-    q = (torch.randn(B, Hkv * G, D, generator=gen) * 2.0 ** q_exp).to(DT[dt])
-    planes = oracle_cache(k, v, n, p, S, 0)
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
-    scale = float(np.float32(2.0 ** s_exp))
-    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale)
-    flat = O.decode_attention(*planes, D, n, p, 0 * synth.to_f32_numpy(q), [S], scale)
-    assert np.linalg.norm(want - flat) > 0.02 * np.linalg.norm(want)
-    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
-    torch.cuda.synchronize()
-    assert_attention_close(got, want, DT[dt])
-
-
 def test_query_and_output_at_any_address():
     B, Hkv, G, S = 1, 1, 40, 200
     k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
