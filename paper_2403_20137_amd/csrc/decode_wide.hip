@@ -41,6 +41,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kRows = 32;                      // virtual heads per wavefront
+constexpr uint32_t kKeyUp = 2;                 // decode_split_few: added to the keys' exponent bytes
 
 // packs the upper halves of two fp32 patterns: (lo, hi) -> one register of two bf16
 __device__ __forceinline__ uint32_t pack_hi(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
@@ -613,7 +614,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 template <int P, int N, int QL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
-    constexpr int kShift = P == 4 ? 7 : 3;
+    constexpr int kShift = P == 4 ? 7 : 3;             // of the values; keys are value * 2^-(kShift - kKeyUp)
     constexpr int kDepth = P == 8 ? 1 : 2;
     constexpr int NB = kD / N;
     constexpr int kRowB = kD * P / 8;
@@ -785,7 +786,19 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
                 }
             }
         }
-        // ---- S^T
+        // ---- S^T.  The keys' exponent bytes are raised by kKeyUp: bf16 then holds the smallest blocks too (bytes 1 and 2).
+        // Where a byte of the tile has no room for that, all of them stay as they are and the scores make up for it
+        // (the look at them costs 1 % of the instructions).
+        constexpr uint32_t kRaise = kKeyUp * 0x01010101u;
+        bool above = false;
+#pragma unroll
+        for (int i = 0; i < (N == 16 ? 2 : 1); ++i)
+            above |= (((r.ke[i] & 0x7F7F7F7Fu) + (0x7Fu - (ExpRange<P>::kTop - kKeyUp - 128u)) * 0x01010101u) & r.ke[i] & 0x80808080u) != 0;
+        const bool raised = __builtin_amdgcn_ballot_w64(above) == 0;
+        if (raised) {
+#pragma unroll
+            for (int i = 0; i < (N == 16 ? 2 : 1); ++i) r.ke[i] += kRaise;
+        }
         f32x16 s;
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = 0.f;
@@ -806,6 +819,10 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
             const bf16x8 ka = __builtin_bit_cast(bf16x8, kw);
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, q_op[0][m], s, 0, 0, 0);
             if (QL == 2) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, q_op[QL - 1][m], s, 0, 0, 0);
+        }
+        if (!raised) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] *= (float)(1 << kKeyUp);
         }
         // the rows are used up: the tile kDepth ahead is requested into the same registers
         if (T0 + kDepth * step < L) {
@@ -933,10 +950,11 @@ hipError_t launch_decode_split_wide(const DecodeArgs& a, int mant_bits, int dtyp
     int e = 0;
     const float f = std::frexp(std::fabs(a.scale_log2e), &e);
     const int at = std::abs(e - 1) <= 8 ? 0 : std::max(-119, std::min(119, e - 1));
-    const int shift = mant_bits == 4 ? 7 : 3;
+    const bool few = w.row_tiles == 1 && w.groups == 1;
+    const int shift = (mant_bits == 4 ? 7 : 3) - (few ? (int)kKeyUp : 0);
     const float score_mul = a.scale_log2e != 0.f ? std::ldexp(2.f * f, e - 1 - at + shift) : 1.f;
     const float query_mul = a.scale_log2e != 0.f ? std::copysign(std::ldexp(1.0f, at), a.scale_log2e) : 0.f;
-    if (w.row_tiles == 1 && w.groups == 1) {
+    if (few) {
         if (mant_bits == 4) launch_few<4>(a, dtype, block, grid, score_mul, query_mul, s);
         else launch_few<8>(a, dtype, block, grid, score_mul, query_mul, s);
     } else if (mant_bits == 4 && block == 16) launch_rg<4, true>(a, dtype, grid, w.row_tiles, w.groups, score_mul, query_mul, s);

@@ -127,6 +127,27 @@ def test_every_exponent_byte(p, n, which, byte):
         assert_attention_close(got, want, torch.bfloat16, "%s %d" % (which, byte))
 
 
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+@pytest.mark.parametrize("byte,beside", [(1, None), (2, None), (1, 20), (3, None)])
+def test_keys_with_the_smallest_exponent_bytes_up_to_32_heads(p, n, byte, beside):
+    """Keys are exact at every byte a finite row can have, as in the passes for up to 8 heads: with the scale to match, the
+    scores come out as anywhere else.  beside: the first 16 tokens of every 40 hold larger ones."""
+    B, Hkv, G, S = 1, 1, 12, 200
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    planes[1][:] = byte + (np.arange(planes[1].size).reshape(planes[1].shape) % 2)
+    if beside:
+        planes[1][:, :, np.arange(S) % 40 < 16] = beside
+    q, scale = (q.float() * 2.0 ** 60).bfloat16(), float(np.float32(2.0 ** (60 if not beside else 44)))
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
+
+
 def test_query_and_output_at_any_address():
     B, Hkv, G, S = 1, 1, 40, 200
     k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
