@@ -13,9 +13,10 @@
 //     of the wavefront, and the registers that hold S^T are, converted, the second operand of the value product -- the
 //     order of the tokens in its reduction is free, and V^T is laid out in LDS in the order S^T leaves them in.
 //   * The query is not rounded: a bf16 query (or one cast to BFP) is one bf16 operand, an fp16 query is two (8 + 3
-//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities are two bf16 limbs (16 bits), as in the other passes for 16-bit I/O.
-// Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 48 MFMAs of 32 cycles,
-// some 320 vector instructions of softmax and 110 of decoding, 4 cycles each).  256 virtual heads (64 query tokens, groups of
+//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads are three bf16 limbs, all of
+//     their 24 bits; up to 32 two (16 bits), as in the other passes for 16-bit I/O.
+// Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 64 MFMAs of 32 cycles,
+// some 390 vector instructions of softmax and limbs and 110 of decoding, 4 cycles each).  256 virtual heads (64 query tokens, groups of
 // 4) over 4 x 8192 tokens x 8 kv-heads: 63 us against 1470 us in the general pass.  Up to 32 heads: vector ALUs 70 % busy (490
 // instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us, 2.6 TB/s, against 65 us in two launches.
 #include <hip/hip_runtime.h>
@@ -531,34 +532,19 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             const float m_ref = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = exp2_raw(m_run - m_ref);
             const float m_p = m_ref - (float)kShift;               // probabilities carry 2^kShift
-            uint32_t p_hi[CB][8], p_lo[CB][8];
             float psum = 0.f;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                for (int i = 0; i < 16; i += 2) {
-                    const float p0 = exp2_raw(fmaf(s[cb][i], score_mul, -m_p));
-                    const float p1 = exp2_raw(fmaf(s[cb][i + 1], score_mul, -m_p));
-                    psum += p0;
-                    psum += p1;
-                    p_hi[cb][i / 2] = pack_hi(__float_as_uint(p0), __float_as_uint(p1));
-                    bf16x2 lo;
-                    lo[0] = (__bf16)(p0 - __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u));
-                    lo[1] = (__bf16)(p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
-                    p_lo[cb][i / 2] = bits(lo);
+                for (int i = 0; i < 16; ++i) {
+                    s[cb][i] = exp2_raw(fmaf(s[cb][i], score_mul, -m_p));
+                    psum += s[cb][i];
                 }
             if (any_mode != 0) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                    for (int i = 0; i < 16; i += 2) {
-                        const float u = ExpRange<P>::undo((mode_at(cb, i) >> 4) & 0xFu);
-                        auto scaled = [&](uint32_t w) {
-                            return pack_hi(__float_as_uint(__uint_as_float(w << 16) * u), __float_as_uint(__uint_as_float(w & 0xFFFF0000u) * u));
-                        };
-                        p_hi[cb][i / 2] = scaled(p_hi[cb][i / 2]);
-                        p_lo[cb][i / 2] = scaled(p_lo[cb][i / 2]);
-                    }
+                    for (int i = 0; i < 16; ++i) s[cb][i] *= ExpRange<P>::undo((mode_at(cb, i) >> 4) & 0xFu);
             }
             l_run = l_run * alpha + psum;
             m_run = m_new;
@@ -571,15 +557,26 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
-                    const bf16x8 ph = __builtin_bit_cast(bf16x8, u32x4{p_hi[cb][4 * kk], p_hi[cb][4 * kk + 1], p_hi[cb][4 * kk + 2], p_hi[cb][4 * kk + 3]});
-                    const bf16x8 pl = __builtin_bit_cast(bf16x8, u32x4{p_lo[cb][4 * kk], p_lo[cb][4 * kk + 1], p_lo[cb][4 * kk + 2], p_lo[cb][4 * kk + 3]});
+                    // three bf16 limbs of 8 bits each: the probability as it is
+                    u32x4 limb[3];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float x = s[cb][8 * kk + 2 * j], y = s[cb][8 * kk + 2 * j + 1];
+#pragma unroll
+                        for (int l = 0; l < 3; ++l) {
+                            limb[l][j] = pack_hi(__float_as_uint(x), __float_as_uint(y));
+                            x -= __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
+                            y -= __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
+                        }
+                    }
                     const int place = 2 * (my_tok0 / 16 + 2 * cb + kk) + half;
 #pragma unroll
                     for (int ct = 0; ct < 4; ++ct) {
                         const int ch = 32 * ct + l32;
                         const bf16x8 va = *(const bf16x8*)(v_lds + value_at(ch, place));
-                        o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, ph, o[ct], 0, 0, 0);
-                        o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pl, o[ct], 0, 0, 0);
+#pragma unroll
+                        for (int l = 0; l < 3; ++l)
+                            o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, limb[l]), o[ct], 0, 0, 0);
                     }
                 }
         }

@@ -148,6 +148,34 @@ def test_keys_with_the_smallest_exponent_bytes_up_to_32_heads(p, n, byte, beside
     assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
 
 
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("p,n", [(4, 16), (4, 32), (8, 32)])
+@pytest.mark.parametrize("G", [40, 100, 130])
+def test_partial_results_above_32_heads_are_fp32(dt, p, n, G):
+    """More than 32 heads: probabilities keep their 24 bits.  The workspace holds the partial results in fp32; merged here
+    in 64 bits they are as far from the oracle as fp32 sums over the scores' rounding are: 2100 products of weights
+    whose base-2 scores of magnitude up to 16 carry 2^-24 of it each, 16 * 2^-24 = 1e-6 times a few for the sum of
+    128 products behind a score."""
+    B, S, Hkv = 2, 2100, 1
+    k, v, q, pk, _ = _inputs(dt, Hkv, S, B, 5, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0, pk, None)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S, perm_k=pk)
+    scale, Hq = float(np.float32(D ** -0.5)), Hkv * G
+    need = kvbfp.decode_workspace_bytes(cache.layout, Hq, S)
+    splits = need // (B * Hq * (D + 2) * 4)
+    ws = torch.zeros((need,), dtype=torch.uint8, device="cuda")
+    kvbfp.decode_attention(cache, q.cuda(), S, scale, perm_k=dev_i32(pk), workspace=ws)
+    torch.cuda.synchronize()
+    f = ws.view(torch.float32).cpu().double().numpy()
+    po, ml = f[:B * Hq * splits * D].reshape(B, Hq, splits, D), f[B * Hq * splits * D:].reshape(B, Hq, splits, 2)
+    assert (ml[..., 1] > 0).all()
+    w = np.exp2(ml[..., 0] - ml[..., 0].max(axis=-1, keepdims=True))
+    merged = (w[..., None] * po).sum(axis=2) / (w * ml[..., 1]).sum(axis=-1)[..., None]
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S, S], scale, pk, None)
+    err = np.linalg.norm(merged - want, axis=-1) / np.linalg.norm(want, axis=-1)
+    assert err.max() <= 6e-6 and err.mean() <= 6e-7, (err.max(), err.mean())
+
+
 def test_query_and_output_at_any_address():
     B, Hkv, G, S = 1, 1, 40, 200
     k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
