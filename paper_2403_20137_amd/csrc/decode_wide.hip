@@ -119,9 +119,10 @@ struct QueryRows {
             }
         }
     }
-    // smem: ROWS * 256 bytes, inv_s: kD ints.  Called by the whole workgroup; ends with a barrier.
+    // smem: ROWS * 256 bytes, inv_s: kD ints.  Called by the whole workgroup; ends with a barrier.  Returns what the scores
+    // of this lane's head are to be multiplied with on top of score_mul.
     template <int P, int QL, class Group>
-    __device__ __forceinline__ void build(const DecodeArgs& a, int dt, int used, int row0, uint8_t* smem, int* inv_s, float query_mul,
+    __device__ __forceinline__ float build(const DecodeArgs& a, int dt, int used, int row0, uint8_t* smem, int* inv_s, float query_mul,
                                           Group&& group, bf16x8 (&q_op)[QL][8]) {
         const int tid = threadIdx.x, l32 = tid & 31, half = (tid >> 5) & 1;
         // cache position of every channel; position c goes to slot order inside its group of 8
@@ -148,7 +149,7 @@ struct QueryRows {
         if (QL == 1 && dt == KVBFP_BF16 && a.q_mant_bits == 0 && query_mul == 1.0f) {      // the operand as it is
 #pragma unroll
             for (int m = 0; m < 8; ++m) q_op[0][m] = __builtin_bit_cast(bf16x8, raw[m]);
-            return;
+            return 1.f;
         }
         auto value = [&](int m, int k) {
             const uint32_t h = (raw[m][k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
@@ -179,6 +180,20 @@ struct QueryRows {
                 cast_e[m] = (amax == 0 ? 0 : (int)max(bumped, 1u)) - 127 - (a.q_mant_bits - 2);
             }
         }
+        // A small power of two is folded in as far as the head's largest element stays above 2^-8, the rest of it multiplies
+        // the scores: below 2^-126 bf16 loses bits.  (No sum of 128 products then reaches the end of the fp32 range.)
+        float lift = 1.f;
+        if (fabsf(query_mul) < 1.f && query_mul != 0.f) {
+            float top = 0.f;
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) top = fmaxf(top, fabsf(value(m, k)));
+            int e = 0;
+            (void)frexpf(fmaxf(top, other_half(top)) * fabsf(query_mul), &e);
+            lift = ldexpf(1.f, min(max(-8 - e, 0), -ilogbf(query_mul)));
+        }
+        query_mul *= lift;
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
 #pragma unroll
@@ -192,6 +207,7 @@ struct QueryRows {
             }
             __builtin_amdgcn_sched_barrier(0);          // one group of 8 at a time: the rows in flight hold the registers
         }
+        return 1.f / lift;
     }
 };
 
@@ -462,7 +478,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     fetch(t_first, raw);
 
     bf16x8 q_op[QL][8];
-    query.template build<P, QL>(a, dt, s_count, rg * kRows, smem, perm_s, query_mul, [](int m, int h) { return 2 * m + h; }, q_op);
+    const float mul = score_mul * query.template build<P, QL>(a, dt, s_count, rg * kRows, smem, perm_s, query_mul, [](int m, int h) { return 2 * m + h; }, q_op);
 
     const int64_t lim = L - kvbfp::hidden_tokens(a, my_s);         // this head sees tokens below
     const int64_t all_see = L - (a.n_q_tokens - 1);                // every head does
@@ -527,7 +543,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, s[cb][i]);
-            tmax = fmaxf(tmax, other_half(tmax)) * score_mul;      // -inf only if this head sees none of the tile
+            tmax = fmaxf(tmax, other_half(tmax)) * mul;      // -inf only if this head sees none of the tile
             const float m_new = fmaxf(m_run, tmax);
             const float m_ref = m_new == -INFINITY ? 0.f : m_new;
             const float alpha = exp2_raw(m_run - m_ref);
@@ -537,7 +553,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    s[cb][i] = exp2_raw(fmaf(s[cb][i], score_mul, -m_p));
+                    s[cb][i] = exp2_raw(fmaf(s[cb][i], mul, -m_p));
                     psum += s[cb][i];
                 }
             if (any_mode != 0) {
@@ -736,7 +752,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     // MFMA m multiplies the 8 channels of key group group_of(m, half)
     auto group_of = [](int m, int h) { return P == 4 ? 8 * (m >> 2) + 4 * h + (m & 3) : 4 * (m >> 1) + 2 * h + (m & 1); };
     bf16x8 q_op[QL][8];
-    query.template build<P, QL>(a, dt, a.G, 0, smem, perm_s, query_mul, group_of, q_op);
+    const float mul = score_mul * query.template build<P, QL>(a, dt, a.G, 0, smem, perm_s, query_mul, group_of, q_op);
 
     // [128 channels][4 groups of 8 tokens], row and place exchanged with the channel's bits so that neither the writes (equal
     // bits 0-2) nor the reads (16 neighbouring channels) meet in a bank
@@ -833,7 +849,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         float tmax = s[0];
 #pragma unroll
         for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-        tmax = fmaxf(tmax, other_half(tmax)) * score_mul;          // -inf only if this head sees none of the tile
+        tmax = fmaxf(tmax, other_half(tmax)) * mul;          // -inf only if this head sees none of the tile
         const float m_new = fmaxf(m_run, tmax);
         const float m_ref = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = exp2_raw(m_run - m_ref);
@@ -842,8 +858,8 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         float psum = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
-            const float p0 = exp2_raw(fmaf(s[i], score_mul, -m_p));
-            const float p1 = exp2_raw(fmaf(s[i + 1], score_mul, -m_p));
+            const float p0 = exp2_raw(fmaf(s[i], mul, -m_p));
+            const float p1 = exp2_raw(fmaf(s[i + 1], mul, -m_p));
             psum += p0;
             psum += p1;
             p_hi[i / 2] = pack_hi(__float_as_uint(p0), __float_as_uint(p1));

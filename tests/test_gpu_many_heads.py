@@ -148,6 +148,24 @@ def test_keys_with_the_smallest_exponent_bytes_up_to_32_heads(p, n, byte, beside
     assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
 
 
+@pytest.mark.parametrize("p,top", [(4, 254), (4, 253), (4, 252), (8, 251), (8, 250), (8, 249)])
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+def test_keys_with_the_largest_exponent_bytes_up_to_32_heads(p, n, top):
+    """Every third token's rows at the last bytes the pass takes and around them, the others 2^20 smaller."""
+    B, Hkv, G, S = 1, 1, 12, 200
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    planes[1][:] = top - 20
+    planes[1][:, :, ::3] = top
+    q, scale = (q.float() * 2.0 ** -60).bfloat16(), float(np.float32(2.0 ** -(top - 127 - 60)) * np.float32(0.05))
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale), torch.bfloat16)
+
+
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
 @pytest.mark.parametrize("p,n", [(4, 16), (4, 32), (8, 32)])
 @pytest.mark.parametrize("G", [40, 100, 130])
@@ -174,6 +192,26 @@ def test_partial_results_above_32_heads_are_fp32(dt, p, n, G):
     want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S, S], scale, pk, None)
     err = np.linalg.norm(merged - want, axis=-1) / np.linalg.norm(want, axis=-1)
     assert err.max() <= 6e-6 and err.mean() <= 6e-7, (err.max(), err.mean())
+
+
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("dt,q_exp,s_exp", [("bf16", -120, -12), ("f16", -12, -120), ("bf16", -60, -72)])
+def test_query_far_below_one_times_a_small_scale(p, dt, q_exp, s_exp):
+    """q * softmax_scale around 2^-132, where fp32 itself is short of bits, against keys around 2^124: the scores count."""
+    B, Hkv, G, S, n = 1, 1, 40, 300, 32
+    gen = torch.Generator().manual_seed(8)
+    k, v = (torch.randn(B, S, Hkv, D, generator=gen) * f for f in (2.0 ** 124, 1.0))
+    k, v = k.clamp(-2.0 ** 126, 2.0 ** 126).bfloat16(), v.bfloat16()
+    q = (torch.randn(B, Hkv * G, D, generator=gen) * 2.0 ** q_exp).to(DT[dt])
+    planes = oracle_cache(k, v, n, p, S, 0)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    scale = float(np.float32(2.0 ** s_exp))
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale)
+    flat = O.decode_attention(*planes, D, n, p, 0 * synth.to_f32_numpy(q), [S], scale)
+    assert np.linalg.norm(want - flat) > 0.02 * np.linalg.norm(want)
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert_attention_close(got, want, DT[dt])
 
 
 def test_query_and_output_at_any_address():
