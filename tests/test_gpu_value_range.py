@@ -71,3 +71,16 @@ def test_queries_at_the_ends_of_the_range_with_the_matching_softmax_scale(dtype,
     if dtype == torch.float16:
         q_shift = -10 if q_shift < 0 else 4
     _run(dtype, n, p, 0, 0, q_shift)
+
+
+@pytest.mark.parametrize("S", [1500, 1024, 700, 300])
+def test_sums_beyond_the_range_are_infinite_whatever_the_number_of_splits(S):
+    # the value sums of a split leave fp32 before the division by the normaliser: an infinity, and no NaN from a
+    # split that is not there (6, 4, 3 and 2 splits here)
+    v = torch.full((2, S, 2, D), 2.0 ** 125, dtype=torch.bfloat16)
+    k = synth.kv_rows(2, S, 2, D, "bf16", synth.outlier_gains(5, 0, 2, D), 5, 2)
+    q = synth.queries(2, 8, D, "bf16", 5, 4)
+    cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
+    got = kvbfp.decode_attention(cache, q.cuda(), S, 1e-3)
+    torch.cuda.synchronize()
+    assert bool(torch.isposinf(got).all())
