@@ -30,7 +30,11 @@ struct Span {
     int64_t L;                  // cached tokens of the sequence
     int64_t row0, row_step;     // partial results of head h: row0 + h * row_step
     bool listed;                // the lengths differ: a place of the list
-    __device__ float mark(float l) const { return listed ? -l : l; }      // l >= 0, 0 included
+    // bit 31 set or cleared whatever l is: a NaN, from inputs that are not finite, comes with either sign
+    __device__ float mark(float l) const {
+        const uint32_t m = __float_as_uint(l) & 0x7FFFFFFFu;
+        return __uint_as_float(listed ? m | 0x80000000u : m);
+    }
     __device__ int64_t row(int64_t h) const { return row0 + h * row_step; }
 };
 

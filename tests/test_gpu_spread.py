@@ -93,3 +93,32 @@ def test_one_split_of_the_rotation_at_read():
     k, v, q, pk, pv = make_small(torch.bfloat16, B=3, S=256, Hkv=2, G=6, seed=710)
     got, want = run_rope(k, v, q, 32, 4, [256, 0, 130], 128 ** -0.5, pk, pv, 1)
     assert_attention_close(got, want, torch.bfloat16)
+
+
+@pytest.mark.parametrize("dtype,p,G,B,Hkv,S", [
+    (torch.bfloat16, 4, 4, 24, 8, 1100),         # 4 splits: a wavefront of the combine pass per head
+    (torch.float32, 4, 1, 24, 8, 1100),
+    (torch.bfloat16, 4, 12, 24, 8, 1100),        # 9 to 32 heads
+    (torch.bfloat16, 8, 40, 12, 8, 1100),        # more
+    (torch.bfloat16, 4, 4, 2, 8, 13000),         # 48 splits: a workgroup of it per head
+    (torch.float32, 4, 4, 2, 8, 13000),
+])
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("bits", [0xFFC00000, 0x7FC00000])
+def test_a_query_that_is_not_a_number_stays_in_its_sequence(dtype, p, G, B, Hkv, S, ragged, bits):
+    # whatever its sign: the form of the partial results is not told by what is computed
+    lens = dev_i32(_lens(B, S, 21) if ragged else [S] * B)
+    k, v, q, _, _ = make_small(dtype, B=B, S=S, Hkv=Hkv, G=G, seed=640)
+    cache = gpu_cache(k.cuda(), v.cuda(), 32, p, S)
+    want = kvbfp.decode_attention(cache, q.cuda(), S, 0.1, seq_len_dev=lens)
+    bad = q.clone()
+    if dtype == torch.float32:
+        bad[1] = torch.tensor(bits - (1 << 32 if bits >> 31 else 0), dtype=torch.int32).view(torch.float32)
+    else:
+        bad.view(torch.int16)[1] = (bits >> 16) - (1 << 16 if bits >> 31 else 0)
+    assert bool(bad[1].isnan().all())
+    got = kvbfp.decode_attention(cache, bad.cuda(), S, 0.1, seq_len_dev=lens)
+    torch.cuda.synchronize()
+    keep = [b for b in range(B) if b != 1]
+    assert torch.equal(got[keep], want[keep])
+    assert bool((got[1].isnan() | (got[1] == 0)).all())
