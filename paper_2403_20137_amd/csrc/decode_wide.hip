@@ -288,9 +288,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float score_mul, float query_mul) {
     constexpr int kShift = P == 4 ? 7 : 3;             // decoded values are value * 2^-kShift
     constexpr int TG = 4 / RG;                         // wavefronts that share the tokens of a tile
-    constexpr int kLog2Tile = 6, TT = 1 << kLog2Tile;  // tokens per tile
+    constexpr int kLog2Tile = 6, TT = 1 << kLog2Tile;  // tokens per tile; every wavefront decodes 16 of them
     constexpr int CB = TT / 32 / TG;                   // blocks of 32 tokens per wavefront
-    constexpr int SP = TT / 64;                        // decode passes: a wavefront decodes 16 tokens of every 64
     constexpr int kRowB = kD * P / 8;
     constexpr int kKeyChunks = P == 4 ? 1 : 2;         // 16-byte chunks of a key row per thread and pass
     constexpr int kValWords = P == 4 ? 1 : 2;          // dwords (8 channels) of a value row per thread
@@ -307,7 +306,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     constexpr int kSmem = kSmemA > kQueryBytes ? kSmemA : kQueryBytes;
     __shared__ __align__(16) uint8_t smem[kSmem];
     __shared__ int perm_s[kD];
-    __shared__ uint32_t modes_s[SP];                   // ExpMode of the tile's 16-token stages, one byte each: keys | values << 4
+    __shared__ uint32_t modes_s;                       // ExpMode of the tile's 16-token stages, one byte each: keys | values << 4
     uint8_t* const k_lds = smem;
     uint8_t* const v_lds = smem + kKeyBytes;
 
@@ -340,13 +339,13 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     QueryRows<RG * kRows> query;
     query.request(a, b, kvh, s_first, s_count);
 
-    // ---- packed rows of one tile, as loaded: this wavefront's 16 tokens of every 64
+    // ---- packed rows of one tile, as loaded: this wavefront's 16 tokens
     const int log2_nb = 7 - a.log2_block;              // exponent bytes per row
     struct Raw {
-        u32x4 k[SP][kKeyChunks];
-        uint32_t ke[SP][2];
-        uint32_t v[SP][4][kValWords];
-        uint32_t ve[SP][4];
+        u32x4 k[kKeyChunks];
+        uint32_t ke[2];
+        uint32_t v[4][kValWords];
+        uint32_t ve[4];
     };
     const int k_tok = lane >> 2, k_chunk = lane & 3;   // keys: token of the stage, 16-byte chunk (8-bit: and chunk + 4)
     const int v_quad = lane >> 4, v_word = lane & 15;  // values: tokens 4 v_quad .. + 3, channels 8 v_word .. + 7
@@ -354,118 +353,112 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     const uint32_t ke_at1 = P == 4 ? ke_at0 + 1 : (uint32_t)((64 + 16 * k_chunk) >> a.log2_block);
     const uint32_t ve_at = (uint32_t)((8 * v_word) >> a.log2_block);
     auto fetch = [&](const int64_t T0, Raw& r) {
+        int64_t st = T0 + 16 * wave;               // first token of the stage, wave-uniform
+        if (st >= L) st = (L - 1) & ~(int64_t)15;  // beyond the end: rows that are not used
+        const int last = (int)min((int64_t)15, L - 1 - st);
+        const int64_t row0 = kvbfp::cache_row(a, b, kvh, st);
+        const uint8_t* __restrict__ km = a.k_mant + row0 * kRowB;
+        const uint8_t* __restrict__ vm = a.v_mant + row0 * kRowB;
+        const uint8_t* __restrict__ kx = a.k_exp + (row0 << log2_nb);
+        const uint8_t* __restrict__ vx = a.v_exp + (row0 << log2_nb);
+        const uint32_t kr = (uint32_t)min(k_tok, last);
 #pragma unroll
-        for (int p = 0; p < SP; ++p) {
-            int64_t st = T0 + 64 * p + 16 * wave;      // first token of the stage, wave-uniform
-            if (st >= L) st = (L - 1) & ~(int64_t)15;  // beyond the end: rows that are not used
-            const int last = (int)min((int64_t)15, L - 1 - st);
-            const int64_t row0 = kvbfp::cache_row(a, b, kvh, st);
-            const uint8_t* __restrict__ km = a.k_mant + row0 * kRowB;
-            const uint8_t* __restrict__ vm = a.v_mant + row0 * kRowB;
-            const uint8_t* __restrict__ kx = a.k_exp + (row0 << log2_nb);
-            const uint8_t* __restrict__ vx = a.v_exp + (row0 << log2_nb);
-            const uint32_t kr = (uint32_t)min(k_tok, last);
+        for (int i = 0; i < kKeyChunks; ++i)
+            r.k[i] = __builtin_nontemporal_load((const u32x4*)(km + (kr * kRowB + k_chunk * 16 + i * 64)));
+        if (P == 4 && N16) {
+            r.ke[0] = *(const uint16_t*)(kx + ((kr << log2_nb) + ke_at0));
+        } else {
+            r.ke[0] = kx[(kr << log2_nb) + ke_at0];
+            if (P == 8) r.ke[1] = kx[(kr << log2_nb) + ke_at1];
+        }
 #pragma unroll
-            for (int i = 0; i < kKeyChunks; ++i)
-                r.k[p][i] = __builtin_nontemporal_load((const u32x4*)(km + (kr * kRowB + k_chunk * 16 + i * 64)));
-            if (P == 4 && N16) {
-                r.ke[p][0] = *(const uint16_t*)(kx + ((kr << log2_nb) + ke_at0));
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t vr = (uint32_t)min(4 * v_quad + i, last);
+            if constexpr (P == 4) {
+                r.v[i][0] = __builtin_nontemporal_load((const uint32_t*)(vm + (vr * kRowB + v_word * 4)));
             } else {
-                r.ke[p][0] = kx[(kr << log2_nb) + ke_at0];
-                if (P == 8) r.ke[p][1] = kx[(kr << log2_nb) + ke_at1];
+                const u32x2 w = __builtin_nontemporal_load((const u32x2*)(vm + (vr * kRowB + v_word * 8)));
+                r.v[i][0] = w[0];
+                r.v[i][kValWords - 1] = w[1];
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t vr = (uint32_t)min(4 * v_quad + i, last);
-                if constexpr (P == 4) {
-                    r.v[p][i][0] = __builtin_nontemporal_load((const uint32_t*)(vm + (vr * kRowB + v_word * 4)));
-                } else {
-                    const u32x2 w = __builtin_nontemporal_load((const u32x2*)(vm + (vr * kRowB + v_word * 8)));
-                    r.v[p][i][0] = w[0];
-                    r.v[p][i][kValWords - 1] = w[1];
-                }
-                r.ve[p][i] = vx[(vr << log2_nb) + ve_at];
-            }
+            r.ve[i] = vx[(vr << log2_nb) + ve_at];
         }
     };
     // decoded to bf16 in LDS
     auto decode = [&](Raw& r) {
-#pragma unroll
-        for (int p = 0; p < SP; ++p) {
-            using R = ExpRange<P>;
-            const uint32_t ke[2] = {P == 4 && N16 ? (r.ke[p][0] & 0xFFu) : r.ke[p][0], P == 4 ? (N16 ? r.ke[p][0] >> 8 : r.ke[p][0]) : r.ke[p][1]};
-            const uint32_t top = max(max(max(r.ve[p][0], r.ve[p][1]), max(r.ve[p][2], r.ve[p][3])), max(ke[0], ke[1]));
-            const uint32_t low = min(min(min(r.ve[p][0], r.ve[p][1]), min(r.ve[p][2], r.ve[p][3])), min(ke[0], ke[1]));
-            int mode_k = kExpPlain, mode_v = kExpPlain;
-            if (__builtin_amdgcn_ballot_w64(top > R::kTop || low <= 2u) != 0) {     // (also where a block is all zero)
-                constexpr uint32_t kLowTop = R::kTop - R::kUp;
-                auto tiny = [](uint32_t E) { return E - 1u < 2u; };
-                const uint32_t kt = max(ke[0], ke[1]);
-                mode_k = exp_mode<P>(kt > R::kTop, kt > kLowTop, tiny(ke[0]) || tiny(ke[1]));
-                const uint32_t vt = max(max(r.ve[p][0], r.ve[p][1]), max(r.ve[p][2], r.ve[p][3]));
-                mode_v = exp_mode<P>(vt > R::kTop, vt > kLowTop, tiny(r.ve[p][0]) || tiny(r.ve[p][1]) || tiny(r.ve[p][2]) || tiny(r.ve[p][3]));
-                if constexpr (P == 4) {
-                    r.ke[p][0] = N16 ? (R::operand(ke[0], mode_k) | (R::operand(ke[1], mode_k) << 8)) : R::operand(ke[0], mode_k);
-                } else {
-                    r.ke[p][0] = R::operand(ke[0], mode_k);
-                    r.ke[p][1] = R::operand(ke[1], mode_k);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) r.ve[p][i] = R::operand(r.ve[p][i], mode_v);
-            }
-            if (lane == 0) ((uint8_t*)&modes_s[p])[wave] = (uint8_t)(mode_k | (mode_v << 4));
-            const int tok = 64 * p + 16 * wave + k_tok;
-            uint8_t* const krow = k_lds + tok * 256;
-#pragma unroll
-            for (int i = 0; i < kKeyChunks; ++i) {
-                if constexpr (P == 4) {
-                    const float s0 = __uint_as_float((N16 ? (r.ke[p][0] & 0xFFu) : r.ke[p][0]) << 23);
-                    const float s1 = N16 ? __uint_as_float((r.ke[p][0] >> 8) << 23) : s0;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        uint32_t q[4];
-                        unpack8_p4(r.k[p][i][d], d < 2 ? s0 : s1, q);
-                        *(u32x4*)(krow + (((4 * k_chunk + d) ^ (tok & 15)) * 16)) = u32x4{q[0], q[1], q[2], q[3]};
-                    }
-                } else {
-#pragma unroll
-                    for (int d = 0; d < 2; ++d) {
-                        float x[4], y[4];
-                        unpack4_p8(r.k[p][i][2 * d], r.ke[p][i] << 23, x);
-                        unpack4_p8(r.k[p][i][2 * d + 1], r.ke[p][i] << 23, y);
-                        const u32x4 w = {pack_hi(__float_as_uint(x[0]), __float_as_uint(x[1])), pack_hi(__float_as_uint(x[2]), __float_as_uint(x[3])),
-                                         pack_hi(__float_as_uint(y[0]), __float_as_uint(y[1])), pack_hi(__float_as_uint(y[2]), __float_as_uint(y[3]))};
-                        *(u32x4*)(krow + (((8 * i + 2 * k_chunk + d) ^ (tok & 15)) * 16)) = w;
-                    }
-                }
-            }
-            // values: the four tokens of each channel side by side.  In a group of 16 tokens the quads 0 and 2 make the
-            // first 16 bytes and 1 and 3 the second: the order in which S^T leaves them in the two halves of a wavefront.
-            const int place = 2 * (4 * p + wave) + (v_quad & 1);
-            auto put = [&](const int c, const uint32_t t01, const uint32_t t23) {      // c = channel % 8
-                const int ch = 8 * v_word + c;
-                *(u32x2*)(v_lds + value_at(ch, place) + (v_quad >> 1) * 8) = u32x2{t01, t23};
-            };
+        using R = ExpRange<P>;
+        const uint32_t ke[2] = {P == 4 && N16 ? (r.ke[0] & 0xFFu) : r.ke[0], P == 4 ? (N16 ? r.ke[0] >> 8 : r.ke[0]) : r.ke[1]};
+        const uint32_t top = max(max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3])), max(ke[0], ke[1]));
+        const uint32_t low = min(min(min(r.ve[0], r.ve[1]), min(r.ve[2], r.ve[3])), min(ke[0], ke[1]));
+        int mode_k = kExpPlain, mode_v = kExpPlain;
+        if (__builtin_amdgcn_ballot_w64(top > R::kTop || low <= 2u) != 0) {     // (also where a block is all zero)
+            constexpr uint32_t kLowTop = R::kTop - R::kUp;
+            auto tiny = [](uint32_t E) { return E - 1u < 2u; };
+            const uint32_t kt = max(ke[0], ke[1]);
+            mode_k = exp_mode<P>(kt > R::kTop, kt > kLowTop, tiny(ke[0]) || tiny(ke[1]));
+            const uint32_t vt = max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3]));
+            mode_v = exp_mode<P>(vt > R::kTop, vt > kLowTop, tiny(r.ve[0]) || tiny(r.ve[1]) || tiny(r.ve[2]) || tiny(r.ve[3]));
             if constexpr (P == 4) {
-                uint32_t q[4][4];
+                r.ke[0] = N16 ? (R::operand(ke[0], mode_k) | (R::operand(ke[1], mode_k) << 8)) : R::operand(ke[0], mode_k);
+            } else {
+                r.ke[0] = R::operand(ke[0], mode_k);
+                r.ke[1] = R::operand(ke[1], mode_k);
+            }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) unpack8_p4(r.v[p][i][0], __uint_as_float(r.ve[p][i] << 23), q[i]);
+            for (int i = 0; i < 4; ++i) r.ve[i] = R::operand(r.ve[i], mode_v);
+        }
+        if (lane == 0) ((uint8_t*)&modes_s)[wave] = (uint8_t)(mode_k | (mode_v << 4));
+        const int tok = 16 * wave + k_tok;
+        uint8_t* const krow = k_lds + tok * 256;
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {          // pair x: channels (0,2), (4,6), (1,3), (5,7)
-                    const int c = x < 2 ? 4 * x : 4 * (x - 2) + 1;
-                    put(c, pack_lo(q[0][x], q[1][x]), pack_lo(q[2][x], q[3][x]));
-                    put(c + 2, pack_hi(q[0][x], q[1][x]), pack_hi(q[2][x], q[3][x]));
+        for (int i = 0; i < kKeyChunks; ++i) {
+            if constexpr (P == 4) {
+                const float s0 = __uint_as_float((N16 ? (r.ke[0] & 0xFFu) : r.ke[0]) << 23);
+                const float s1 = N16 ? __uint_as_float((r.ke[0] >> 8) << 23) : s0;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    uint32_t q[4];
+                    unpack8_p4(r.k[i][d], d < 2 ? s0 : s1, q);
+                    *(u32x4*)(krow + (((4 * k_chunk + d) ^ (tok & 15)) * 16)) = u32x4{q[0], q[1], q[2], q[3]};
                 }
             } else {
 #pragma unroll
-                for (int w = 0; w < kValWords; ++w) {
-                    float x[4][4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack4_p8(r.v[p][i][w], r.ve[p][i] << 23, x[i]);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        put(4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
+                for (int d = 0; d < 2; ++d) {
+                    float x[4], y[4];
+                    unpack4_p8(r.k[i][2 * d], r.ke[i] << 23, x);
+                    unpack4_p8(r.k[i][2 * d + 1], r.ke[i] << 23, y);
+                    const u32x4 w = {pack_hi(__float_as_uint(x[0]), __float_as_uint(x[1])), pack_hi(__float_as_uint(x[2]), __float_as_uint(x[3])),
+                                     pack_hi(__float_as_uint(y[0]), __float_as_uint(y[1])), pack_hi(__float_as_uint(y[2]), __float_as_uint(y[3]))};
+                    *(u32x4*)(krow + (((8 * i + 2 * k_chunk + d) ^ (tok & 15)) * 16)) = w;
                 }
+            }
+        }
+        // values: the four tokens of each channel side by side.  In a group of 16 tokens the quads 0 and 2 make the
+        // first 16 bytes and 1 and 3 the second: the order in which S^T leaves them in the two halves of a wavefront.
+        const int place = 2 * wave + (v_quad & 1);
+        auto put = [&](const int c, const uint32_t t01, const uint32_t t23) {      // c = channel % 8
+            const int ch = 8 * v_word + c;
+            *(u32x2*)(v_lds + value_at(ch, place) + (v_quad >> 1) * 8) = u32x2{t01, t23};
+        };
+        if constexpr (P == 4) {
+            uint32_t q[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) unpack8_p4(r.v[i][0], __uint_as_float(r.ve[i] << 23), q[i]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {          // pair x: channels (0,2), (4,6), (1,3), (5,7)
+                const int c = x < 2 ? 4 * x : 4 * (x - 2) + 1;
+                put(c, pack_lo(q[0][x], q[1][x]), pack_lo(q[2][x], q[3][x]));
+                put(c + 2, pack_hi(q[0][x], q[1][x]), pack_hi(q[2][x], q[3][x]));
+            }
+        } else {
+#pragma unroll
+            for (int w = 0; w < kValWords; ++w) {
+                float x[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) unpack4_p8(r.v[i][w], r.ve[i] << 23, x[i]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    put(4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
             }
         }
     };
@@ -512,17 +505,10 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
                 }
             }
             // register i of a block: token 8 (i / 4) + 4 half + i % 4
-            uint32_t modes[SP];
-            uint32_t any_mode = 0;
-#pragma unroll
-            for (int p = 0; p < SP; ++p) any_mode |= modes[p] = __builtin_amdgcn_readfirstlane(modes_s[p]);
-            auto mode_at = [&](int cb, int i) {            // of the stage of 16 tokens this register's token lies in
-                const int st = my_tok0 / 16 + 2 * cb + (i >> 3);
-                uint32_t w = modes[0];
-                if constexpr (SP == 2) w = st >= 4 ? modes[SP - 1] : w;
-                return w >> (8 * (st & 3));
-            };
-            if (any_mode != 0) {
+            const uint32_t modes = __builtin_amdgcn_readfirstlane(modes_s);
+            // of the stage of 16 tokens this register's token lies in
+            auto mode_at = [&](int cb, int i) { return modes >> (8 * (my_tok0 / 16 + 2 * cb + (i >> 3))); };
+            if (modes != 0) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -556,7 +542,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
                     s[cb][i] = exp2_raw(fmaf(s[cb][i], mul, -m_p));
                     psum += s[cb][i];
                 }
-            if (any_mode != 0) {
+            if (modes != 0) {
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
