@@ -73,24 +73,21 @@ __device__ __forceinline__ void unpack4_p8(uint32_t w, uint32_t field, float (&x
 }
 
 // Exponent bytes at the ends of their range.  The conversions take the byte as their scale operand, which fits all but the
-// largest ones, and leave value * 2^-kShift in bf16, which holds all but the smallest blocks exactly.  A 16-token stage
-// with such a byte is converted at another power of two, and what its scores and probabilities are multiplied with makes
-// up for it; the general pass, which has no such limits, is not needed for them.
-enum ExpMode { kExpPlain = 0, kExpHigh = 1, kExpLow = 2 };
+// largest ones, and leave value * 2^-kShift in bf16, which holds all but the smallest blocks exactly.  A 16-token stage with
+// one of the smallest is converted at kUp powers of two more, which its scores and probabilities make up for; a block whose byte
+// is then too large for the operand is converted at kDown fewer and its bf16 numbers are raised where they lie (bf16 itself
+// holds them: code 127 at byte 255 + kUp is below 2^128).  So every byte is exact beside every other.
 template <int P>
 struct ExpRange {
     static constexpr uint32_t kTop = P == 4 ? 254u : 251u;         // largest byte whose scale operand (8-bit: + 3) is finite
-    static constexpr uint32_t kDown = P == 4 ? 1u : 8u, kUp = 2u;  // taken off / added to the byte at the two ends
-    __device__ static uint32_t operand(uint32_t E, int mode) {
-        return mode == kExpPlain ? E : (mode == kExpHigh ? E - min(E, kDown) : E + kUp);
-    }
-    __device__ static float undo(uint32_t mode) { return mode == kExpPlain ? 1.f : (mode == kExpHigh ? (float)(1u << kDown) : 0.25f); }
+    static constexpr uint32_t kUp = 2u, kDown = 8u;
+    __device__ static bool tiny(uint32_t E) { return E - 1u < 2u; }
+    __device__ static bool high(uint32_t E, uint32_t up) { return E + up > kTop; }
+    __device__ static uint32_t operand(uint32_t E, uint32_t up) { return high(E, up) ? E + up - kDown : E + up; }
 };
-// mode of the stage whose bytes the lanes of a wavefront hold (any number of calls or-ed together)
-template <int P>
-__device__ __forceinline__ int exp_mode(bool above_top, bool above_low, bool tiny) {
-    if (__builtin_amdgcn_ballot_w64(above_top) != 0) return kExpHigh;
-    return __builtin_amdgcn_ballot_w64(tiny) != 0 && __builtin_amdgcn_ballot_w64(above_low) == 0 ? kExpLow : kExpPlain;
+// a pair of bf16 numbers times 2^kDown (normal numbers and zeros)
+__device__ __forceinline__ uint32_t raise_pair(uint32_t w, bool lo, bool hi) {
+    return w + (lo && (w & 0x7FFFu) ? 8u << 7 : 0u) + (hi && (w & 0x7FFF0000u) ? 8u << 23 : 0u);
 }
 
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32); }
@@ -306,7 +303,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     constexpr int kSmem = kSmemA > kQueryBytes ? kSmemA : kQueryBytes;
     __shared__ __align__(16) uint8_t smem[kSmem];
     __shared__ int perm_s[kD];
-    __shared__ uint32_t modes_s;                       // ExpMode of the tile's 16-token stages, one byte each: keys | values << 4
+    __shared__ uint32_t modes_s;                       // the tile's 16-token stages, one byte each: bit 0 keys, bit 4 values raised by kUp
     uint8_t* const k_lds = smem;
     uint8_t* const v_lds = smem + kKeyBytes;
 
@@ -390,24 +387,25 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         const uint32_t ke[2] = {P == 4 && N16 ? (r.ke[0] & 0xFFu) : r.ke[0], P == 4 ? (N16 ? r.ke[0] >> 8 : r.ke[0]) : r.ke[1]};
         const uint32_t top = max(max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3])), max(ke[0], ke[1]));
         const uint32_t low = min(min(min(r.ve[0], r.ve[1]), min(r.ve[2], r.ve[3])), min(ke[0], ke[1]));
-        int mode_k = kExpPlain, mode_v = kExpPlain;
+        uint32_t up_k = 0, up_v = 0;                   // wave-uniform
+        uint32_t raise = 0;                            // this lane's blocks converted at kDown fewer: keys bits 0, 1, values 4 + token
         if (__builtin_amdgcn_ballot_w64(top > R::kTop || low <= 2u) != 0) {     // (also where a block is all zero)
-            constexpr uint32_t kLowTop = R::kTop - R::kUp;
-            auto tiny = [](uint32_t E) { return E - 1u < 2u; };
-            const uint32_t kt = max(ke[0], ke[1]);
-            mode_k = exp_mode<P>(kt > R::kTop, kt > kLowTop, tiny(ke[0]) || tiny(ke[1]));
-            const uint32_t vt = max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3]));
-            mode_v = exp_mode<P>(vt > R::kTop, vt > kLowTop, tiny(r.ve[0]) || tiny(r.ve[1]) || tiny(r.ve[2]) || tiny(r.ve[3]));
+            up_k = __builtin_amdgcn_ballot_w64(R::tiny(ke[0]) || R::tiny(ke[1])) != 0 ? R::kUp : 0;
+            up_v = __builtin_amdgcn_ballot_w64(R::tiny(r.ve[0]) || R::tiny(r.ve[1]) || R::tiny(r.ve[2]) || R::tiny(r.ve[3])) != 0 ? R::kUp : 0;
+            raise = (R::high(ke[0], up_k) ? 1u : 0u) | (R::high(ke[1], up_k) ? 2u : 0u);
             if constexpr (P == 4) {
-                r.ke[0] = N16 ? (R::operand(ke[0], mode_k) | (R::operand(ke[1], mode_k) << 8)) : R::operand(ke[0], mode_k);
+                r.ke[0] = N16 ? (R::operand(ke[0], up_k) | (R::operand(ke[1], up_k) << 8)) : R::operand(ke[0], up_k);
             } else {
-                r.ke[0] = R::operand(ke[0], mode_k);
-                r.ke[1] = R::operand(ke[1], mode_k);
+                r.ke[0] = R::operand(ke[0], up_k);
+                r.ke[1] = R::operand(ke[1], up_k);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) r.ve[i] = R::operand(r.ve[i], mode_v);
+            for (int i = 0; i < 4; ++i) {
+                raise |= R::high(r.ve[i], up_v) ? 16u << i : 0u;
+                r.ve[i] = R::operand(r.ve[i], up_v);
+            }
         }
-        if (lane == 0) ((uint8_t*)&modes_s)[wave] = (uint8_t)(mode_k | (mode_v << 4));
+        if (lane == 0) ((uint8_t*)&modes_s)[wave] = (uint8_t)((up_k ? 1u : 0u) | (up_v ? 16u : 0u));
         const int tok = 16 * wave + k_tok;
         uint8_t* const krow = k_lds + tok * 256;
 #pragma unroll
@@ -461,6 +459,22 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
                     put(4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
             }
         }
+        if (__builtin_amdgcn_ballot_w64(raise != 0) != 0) {        // what this lane wrote above
+#pragma unroll 1
+            for (int g = 0; g < 4; ++g) {
+                const bool up = (raise >> (g >> 1)) & 1u;
+                const int group = P == 4 ? 4 * k_chunk + g : 8 * (g >> 1) + 2 * k_chunk + (g & 1);
+                u32x4* const at = (u32x4*)(krow + ((group ^ (tok & 15)) * 16));
+                const u32x4 w = *at;
+                *at = u32x4{raise_pair(w[0], up, up), raise_pair(w[1], up, up), raise_pair(w[2], up, up), raise_pair(w[3], up, up)};
+            }
+#pragma unroll 1
+            for (int c = 0; c < 8; ++c) {
+                u32x2* const at = (u32x2*)(v_lds + value_at(8 * v_word + c, place) + (v_quad >> 1) * 8);
+                const u32x2 w = *at;
+                *at = u32x2{raise_pair(w[0], raise & 16u, raise & 32u), raise_pair(w[1], raise & 64u, raise & 128u)};
+            }
+        }
     };
 
     // the current token (one row tile only): by the wavefront that decodes its row
@@ -512,7 +526,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) s[cb][i] *= ExpRange<P>::undo(mode_at(cb, i) & 0xFu);
+                    for (int i = 0; i < 16; ++i) s[cb][i] *= (mode_at(cb, i) & 1u) ? 0.25f : 1.f;
             }
             if (T0 + TT > all_see) {
 #pragma unroll
@@ -546,7 +560,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) s[cb][i] *= ExpRange<P>::undo((mode_at(cb, i) >> 4) & 0xFu);
+                    for (int i = 0; i < 16; ++i) s[cb][i] *= (mode_at(cb, i) & 16u) ? 0.25f : 1.f;
             }
             l_run = l_run * alpha + psum;
             m_run = m_new;

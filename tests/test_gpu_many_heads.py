@@ -214,6 +214,45 @@ def test_query_far_below_one_times_a_small_scale(p, dt, q_exp, s_exp):
     assert_attention_close(got, want, DT[dt])
 
 
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("n", [16, 32, 64])
+@pytest.mark.parametrize("G", [40, 100])
+@pytest.mark.parametrize("which", ["k", "v"])
+@pytest.mark.parametrize("top,byte", [(255, 1), (255, 6), (252, 2), (252, 7)])
+def test_largest_exponent_bytes_beside_the_smallest(p, n, G, which, top, byte):
+    """Block 0 of two tokens of every 16 holds the largest numbers (code 1 or 17, so that their mean stays in fp32), all
+    other blocks the smallest: every block is exact whatever stands beside it."""
+    B, Hkv, S = 1, 1, 200
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    mant, exps = (planes[0], planes[1]) if which == "k" else (planes[2], planes[3])
+    exps[:] = byte
+    for t in (0, 5):
+        exps[0, 0, t::16, 0] = top
+        mant[0, 0, t::16, :n * p // 8] = 0x11
+    scale = float(np.float32(0.09))
+    if which == "k":    # what is large meets a query of zeros there, what is small one that is large
+        q = q.float() * 2.0 ** 60
+        q[..., :n] = 0
+        q, scale = q.bfloat16(), float(np.float32(2.0 ** (60 - byte)))
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale)
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    assert np.isfinite(want).all() and np.abs(want).max() < 2.0 ** 127
+    if which == "k":
+        assert_attention_close(got, want, torch.bfloat16)
+        return
+    # by element: bf16 outputs below 2^-126 have an absolute step of 2^-133
+    diff = np.abs(got.cpu().double().numpy() - want)
+    slack = np.empty_like(diff)
+    for part in (slice(0, n), slice(n, D)):
+        slack[..., part] = 3e-4 * np.abs(want[..., part]).max(axis=-1, keepdims=True)
+    assert (diff <= 2.0 ** -134 + 2.0 ** -8 * np.abs(want) + slack).all(), (diff / np.abs(want)).max()
+
+
 def test_query_and_output_at_any_address():
     B, Hkv, G, S = 1, 1, 40, 200
     k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
