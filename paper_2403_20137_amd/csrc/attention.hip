@@ -357,8 +357,8 @@ __device__ __forceinline__ uint16_t narrow_bf16(float v) {
 // at the end.  Few (batch, head) pairs with many splits -- one long sequence -- take the 32-channel form: four
 // times the workgroups, a quarter of the bytes through each compute unit.
 constexpr int kCombineThreads = 512;
-template <int kCombineBatch, int kChan>
-__global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, int dt, int log2_tile) {
+template <int kCombineBatch, int kChan, bool SHARED>
+__global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, int dt) {
     constexpr int kSlices = kCombineThreads / kChan;
     constexpr int kMaxLds = 1024;
     __shared__ float m_s[kMaxLds];
@@ -368,6 +368,11 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
     const int jl = threadIdx.x % kChan, sl = threadIdx.x / kChan;
     const int j = blockIdx.z * kChan + jl;      // channel (cache order)
     const int h = blockIdx.x, b = blockIdx.y;
+    int at = -1, count = 0;
+    if (SHARED) {
+        at = a.places[2 * b];
+        count = a.places[2 * b + 1];
+    }
     kvbfp::spans::Parts parts = kvbfp::spans::parts_of(a, b, h);
 
     // where this channel goes in the output row: requested with the partial outputs, not after the sums (a load here
@@ -383,9 +388,8 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
         }
     };
     first_batch();
-    // (requested where they are if the lengths are equal; the mark of the first row tells whether they are)
-    if (a.spread && signbit(a.part_ml[parts.first * 2 + 1])) {
-        parts = kvbfp::spans::listed_parts(a, gridDim.y, b, h, log2_tile);
+    if (SHARED && at >= 0) {                    // (requested where they are if nothing was shared out, without waiting for the table)
+        parts = kvbfp::spans::shared_parts(a, at, count, h);
         first_batch();
     }
     const float* const ml = a.part_ml + parts.first * 2;
@@ -396,12 +400,12 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
         for (int i = threadIdx.x; i < n; i += kCombineThreads) {
             const float2 t = *(const float2*)(ml + 2 * i * parts.step);
             m_s[i] = t.x;
-            l_s[i] = fabsf(t.y);
+            l_s[i] = t.y;
         }
         __syncthreads();
     }
     auto m_of = [&](int i) { return staged ? m_s[i] : ml[2 * i * parts.step]; };
-    auto l_of = [&](int i) { return staged ? l_s[i] : fabsf(ml[2 * i * parts.step + 1]); };
+    auto l_of = [&](int i) { return staged ? l_s[i] : ml[2 * i * parts.step + 1]; };
     // Each slice works relative to the maximum of its own splits (a short, unrolled scan instead of
     // one long serial loop over all of them); the slices are brought to the common maximum at the end.
     float mk[kCombineBatch];
@@ -461,8 +465,8 @@ __global__ __launch_bounds__(kCombineThreads) void decode_combine(DecodeArgs a, 
 // partial outputs are tens of megabytes and this is a streaming pass: bound by memory there (8192 heads, 8 splits, 34 MB:
 // 20.6 us with a 512-thread workgroup per head, 8.2 us with this one), by the launch and one round trip otherwise (4.6 us).
 constexpr int kRowSplits = 32;
-template <bool SPREAD>
-__global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt, int batch, int log2_tile) {
+template <bool SHARED>
+__global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt, int batch) {
     __shared__ float out_s[4][kD];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int bh = blockIdx.x * 4 + wave;       // b * H_q + h
@@ -470,6 +474,11 @@ __global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt,
     const int b = bh / a.H_q, h = bh % a.H_q;
     const int kvh = h / a.G;
     const int n = a.n_splits;                   // <= kRowSplits
+    int at = -1, count_all = 0;                 // (requested with the rows: where nothing was shared out it costs no time)
+    if (SHARED) {
+        at = a.places[2 * b];
+        count_all = a.places[2 * b + 1];
+    }
     const float2 ml = lane < n ? ((const float2*)a.part_ml)[(int64_t)bh * n + lane] : make_float2(-INFINITY, 0.f);
     const float2* const po = (const float2*)(a.part_o + (int64_t)bh * n * kD) + lane;
     float2 v[kRowSplits];
@@ -492,7 +501,7 @@ __global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt,
         const float ref = M_new > -INFINITY ? M_new : 0.f;
         const float w = exp2f(t.x - ref);                // 0 for a split without cached tokens
         const float was = exp2f(M - ref);
-        den = den * was + wave_sum(w * fabsf(t.y));
+        den = den * was + wave_sum(w * t.y);
         n0 *= was;
         n1 *= was;
         M = M_new;
@@ -509,9 +518,9 @@ __global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt,
             }
         }
     };
-    if (SPREAD && __builtin_amdgcn_ballot_w64(signbit(ml.y)) != 0) {
-        // the lengths differ: other rows, and more than 32 of them for a long sequence among short ones
-        const kvbfp::spans::Parts p = kvbfp::spans::listed_parts(a, batch, b, h, log2_tile);
+    if (SHARED && at >= 0) {
+        // other rows, and more than 32 of them for a long sequence among short ones
+        const kvbfp::spans::Parts p = kvbfp::spans::shared_parts(a, at, count_all, h);
         for (int i0 = 0; i0 < p.n; i0 += kRowSplits) {
             const int count = min(p.n - i0, kRowSplits);
             const int64_t r0 = p.first + i0 * p.step;
@@ -563,6 +572,34 @@ using namespace kvbfp;
 
 extern "C" {
 
+// Workspace: the partial results of the splits, and behind them the table of places (DecodeArgs::places) where it may be used.
+static size_t rows_bytes(const kvbfp_layout* L, int32_t n_q_heads, int32_t n_splits) {
+    return (size_t)L->batch * (size_t)n_q_heads * (size_t)n_splits * (size_t)(kD + 2) * sizeof(float);
+}
+static size_t places_bytes(const kvbfp_layout* L) { return (size_t)L->batch * 2 * sizeof(int32_t); }
+// Tiles of a sequence above which the workgroups are shared out by the lengths (0: nowhere).  A split of the longest sequence
+// has T / n_splits tiles, and with B sequences sharing out leaves it at best a B-th of them; what it has to save for that to
+// pay (`tiles`) depends on the time of a tile, see share_from.
+static int64_t share_above(const kvbfp_layout* L, int32_t n_splits, int64_t max_len, int log2_tile, float tiles) {
+    if (L->batch < 2 || L->batch > kvbfp::kMaxShared || n_splits < 2) return 0;
+    const int64_t above = (int64_t)(tiles * (float)n_splits * (float)L->batch / (float)(L->batch - 1));
+    return ((max_len + (1 << log2_tile) - 1) >> log2_tile) > above ? above : 0;
+}
+// Lengths log-uniform from 16, one call, kept -> shared out: 4-bit mantissas 3 x 16384 tokens, 32 kv-heads (saves 5.3 tiles)
+// 22.5 -> 25.4 us, 8 x 16384 (4.7) 17.1 -> 19.0, 12 x 16384 (7.3) 22.7 -> 20.7, 48 x 4096 (7.8) 22.2 -> 19.4; 8 bits 20 x 1024
+// (1.3) 15.1 -> 14.6, 20 x 2048 (2.5) 19.1 -> 15.5; rotation 20 x 1024 (1.3) 24.8 -> 23.3, 8 x 4096 (1.8) 23.4 -> 20.1; fp32 8 x
+// 4096 (1.2) 14.8 -> 15.0, 20 x 2048 (1.9) 19.6 -> 17.6; 12 heads 3 x 4096 (1.3) 15.9 -> 18.7, 8 x 2048 (1.8) 15.9 -> 15.2;
+// 128 heads, tiles of 64, 3 x 8192 (4.1) 37.9 -> 40.1, 20 x 1024 (5.1) 41.3 -> 39.7.  With more than 16 splits the longest
+// sequence gets more places than the combine pass merges at once: 8 bits 3 x 16384 (2.0) 19.1 -> 22.2, 12 heads 3 x 8192 (2.0)
+// 20.9 -> 24.2.
+static float share_from(bool f32, int mant_bits, int G, bool rope, int32_t n_splits) {
+    if (G > 32 && !rope && !f32) return 4.2f;
+    if (!rope && !f32 && G <= 8 && mant_bits == 4) return 6.0f;
+    if (n_splits > 16) return 2.1f;
+    if (f32 && G <= 4) return 1.85f;
+    return G > 8 && !rope && !f32 ? 1.5f : 1.2f;
+}
+
 size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* L, int32_t n_q_heads, int64_t max_len) {
     clear_error();
     if (check_device_layout(L) != KVBFP_OK) return 0;
@@ -571,7 +608,11 @@ size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* L, int32_t n_q_heads, in
         return 0;
     }
     const SplitPlan sp = plan_splits(L, n_q_heads, max_len);
-    return (size_t)L->batch * (size_t)n_q_heads * (size_t)sp.n_splits * (size_t)(kD + 2) * sizeof(float);
+    // (a pass that takes fewer splits than these has room for the table anyway)
+    const int G = n_q_heads / L->n_kv_heads;
+    const int log2_tile = G > 8 ? plan_wide(G, 1, 1, 1).log2_tile : 8;
+    const bool may_share = share_above(L, sp.n_splits, max_len, log2_tile, 1.2f) != 0;     // (the least of share_from: the I/O type is not known here)
+    return rows_bytes(L, n_q_heads, sp.n_splits) + (may_share ? places_bytes(L) : 0);
 }
 
 // What the variants of the decode call add to the plain one; the defaults are the plain call.
@@ -638,7 +679,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // from here on "heads" are virtual heads: every query token brings its own set (see DecodeArgs)
     const int32_t real_heads = n_q_heads;
     n_q_heads *= n_q_tokens;
-    const size_t need = kvbfp_decode_workspace_bytes(L, n_q_heads, max_len);
+    // (the partial results alone will do: without room for the table nothing is shared out)
+    const size_t need = kvbfp_decode_workspace_bytes(L, n_q_heads, max_len) ? rows_bytes(L, n_q_heads, plan_splits(L, n_q_heads, max_len).n_splits) : 0;
     if (!workspace || workspace_bytes < need)
         return fail(KVBFP_ERR_WORKSPACE, "decode_attention: workspace of %zu bytes needed, %zu given", need,
                     workspace ? workspace_bytes : (size_t)0);
@@ -682,8 +724,6 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     const bool wide = !rope && a.G > 8 && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
     if (wide) sp.n_splits = wp.n_splits;
-    // tokens of a tile, and whether the splits are shared out by the lengths (decode_spans.h): where there are lengths and
-    // a sequence can have more tiles than splits (otherwise no split has more than one).  The general pass does not.
     const int log2_tile = wide ? wp.log2_tile : 8;
     // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
     const bool rope_fast = rope && !paging && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 &&
@@ -702,8 +742,12 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         else if (rope_fast && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }
     a.n_splits = sp.n_splits;
-    a.spread = (fast || wide || rope_fast) && seq_len_dev && L->batch > 1 && sp.n_splits > 1 &&
-               ((max_len + (1 << log2_tile) - 1) >> log2_tile) > sp.n_splits;
+    // by the lengths where there are any (not in the general pass) and the workspace has room for the table
+    const size_t rows = rows_bytes(L, n_q_heads, sp.n_splits);
+    if ((fast || wide || rope_fast) && seq_len_dev && workspace_bytes >= rows + places_bytes(L)) {
+        a.share_above = (int32_t)share_above(L, sp.n_splits, max_len, log2_tile, share_from(dtype == KVBFP_F32, L->mant_bits, a.G, rope, sp.n_splits));
+        a.places = (int32_t*)((char*)workspace + rows);
+    }
     // One split: nothing to merge, the split pass writes the output itself and the combine pass is not launched: an appended
     // step over 250 tokens 15.6 -> 8.2 us, 128 sequences x 1000 tokens (1024 units) 36.6 -> 33.0 us.  (Not in the passes for
     // many heads: their merge has no registers to spare, 20 heads over 12000 tokens 44.7 -> 45.7 us with the branch in it.)
@@ -785,14 +829,16 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         // few (batch, head) pairs with many splits: 32 channels per workgroup (16 slices x 8 loads cover 128 splits)
         if (sp.n_splits > 32 && (int64_t)n_q_heads * L->batch < 256) {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, kD / 32);
-            decode_combine<8, 32><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype, log2_tile);
+            if (a.share_above) decode_combine<8, 32, true><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
+            else decode_combine<8, 32, false><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
         } else if (sp.n_splits <= kRowSplits) {
             const dim3 grid2((unsigned)((n_q_heads * L->batch + 3) / 4));
-            if (a.spread) decode_combine_rows<true><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch, log2_tile);
-            else decode_combine_rows<false><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch, log2_tile);
+            if (a.share_above) decode_combine_rows<true><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch);
+            else decode_combine_rows<false><<<grid2, 256, 0, s>>>(a, (int)dtype, L->batch);
         } else {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, 1);
-            decode_combine<32, kD><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype, log2_tile);
+            if (a.share_above) decode_combine<32, kD, true><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
+            else decode_combine<32, kD, false><<<grid2, kCombineThreads, 0, s>>>(a, (int)dtype);
         }
         err = hipGetLastError();
     }
@@ -939,7 +985,9 @@ int kvbfp_decode_attention_multi_paged(const kvbfp_layout* pool, const kvbfp_cac
 // ---- kvbfp_decode_attention_noalloc: the partial results of the splits live in a file-scope device
 // array instead of a caller's workspace.  Every GPU holds its own copy of the array; its address on a
 // device is asked for once, with that device current, and kept.
-static __device__ __align__(256) unsigned char scratch[KVBFP_NOALLOC_SCRATCH_BYTES];
+// (the table of places has room of its own: what fits the scratch is a matter of the partial results)
+constexpr size_t kScratchBytes = KVBFP_NOALLOC_SCRATCH_BYTES + kvbfp::kMaxShared * 2 * sizeof(int32_t);
+static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -973,7 +1021,7 @@ int kvbfp_decode_attention_noalloc(const kvbfp_layout* L, const kvbfp_cache* cac
                                    const int32_t* perm_v, int32_t q_mant_bits, void* out, void* hip_stream) {
     clear_error();
     // the size check comes first: a geometry that does not fit is refused before anything else happens
-    const size_t need = kvbfp_decode_workspace_bytes(L, n_q_heads, max_len);
+    const size_t need = kvbfp_decode_workspace_bytes(L, n_q_heads, max_len) ? rows_bytes(L, n_q_heads, plan_splits(L, n_q_heads, max_len).n_splits) : 0;
     if (need == 0) return fail(KVBFP_ERR_INVALID_ARG, "decode_attention_noalloc: bad layout, n_q_heads or max_len");
     if (need > (size_t)KVBFP_NOALLOC_SCRATCH_BYTES)
         return fail(KVBFP_ERR_WORKSPACE,
@@ -985,7 +1033,7 @@ int kvbfp_decode_attention_noalloc(const kvbfp_layout* L, const kvbfp_cache* cac
     DecodeExtras x;
     x.q_mant_bits = q_mant_bits;
     return decode_impl(L, cache, n_q_heads, q, dtype, seq_len_dev, max_len, softmax_scale, perm_k, perm_v, out, ws,
-                       (size_t)KVBFP_NOALLOC_SCRATCH_BYTES, hip_stream, x);
+                       kScratchBytes, hip_stream, x);
 }
 
 int kvbfp_decode_attention_profile(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t n_q_heads,

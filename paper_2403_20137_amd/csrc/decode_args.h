@@ -7,6 +7,8 @@
 
 namespace kvbfp {
 
+constexpr int kMaxShared = 768;      // sequences: with more of them there is one split
+
 struct DecodeArgs {
     const uint8_t* k_mant;
     const uint8_t* k_exp;
@@ -28,7 +30,9 @@ struct DecodeArgs {
     // to n_q_tokens - 1 - s / real_G tokens fewer than the sequence holds (causal order of the new tokens).
     int32_t H_kv, H_q, G, n_splits, log2_block;
     int32_t direct;           // 1: one split and no combine pass, the split pass writes the output itself
-    int32_t spread;           // 1: where the lengths differ, the n_splits * B workgroups of a kv-head are shared out by them
+    int32_t share_above;      // not 0: where the lengths differ and a sequence has more tiles than this, the n_splits * B
+                              // workgroups of a kv-head are shared out by them (decode_spans.h)
+    int32_t* places;          // [B][2], where share_above is not 0: the first place of a sequence (-1: not shared out) and their number
     int32_t n_q_tokens, real_Hq, real_G;
     int32_t g_base, g_cnt;    // matrix-core passes: this launch serves virtual heads [g_base, g_base + g_cnt) of every kv-head;
                               // g_cnt <= 8

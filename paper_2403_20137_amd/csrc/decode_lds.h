@@ -284,7 +284,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     __builtin_amdgcn_sched_barrier(0);
 
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, len0, 8, kvh * a.G + a.g_base, a.g_cnt, span)) return;
+    if (!kvbfp::spans::take(a, len0, 8, span)) return;
     if (span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
@@ -1179,7 +1179,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         }
         float* ml = a.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
-        ml[1] = span.mark(lsum);
+        ml[1] = lsum;
     }
 }
 

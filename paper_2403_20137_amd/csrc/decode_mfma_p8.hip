@@ -106,7 +106,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     const int perm_c = a.perm_k ? (a.perm_k[kvh * kD + tid % kD] & (kD - 1)) : tid % kD;       // masked: device data the host cannot check
     __builtin_amdgcn_sched_barrier(0);
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, len0, 8, kvh * a.G + a.g_base, a.g_cnt, span)) return;
+    if (!kvbfp::spans::take(a, len0, 8, span)) return;
     if (span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
@@ -452,7 +452,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
         }
         float* ml = a.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
-        ml[1] = span.mark(lsum);
+        ml[1] = lsum;
     }
 }
 

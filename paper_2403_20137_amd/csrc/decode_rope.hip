@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;    // scalar: tile bases stay in SGPRs
     const int j = lane & 15, kg = lane >> 4;
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, blockIdx.y * a.G + a.g_base, a.g_cnt, span)) return;
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, span)) return;
     const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G + a.g_base;
 
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
         }
         float* ml = a.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
-        ml[1] = span.mark(lsum);
+        ml[1] = lsum;
     }
 }
 

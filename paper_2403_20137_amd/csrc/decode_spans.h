@@ -4,14 +4,15 @@
 // blockIdx (s, ., b) and takes the tiles s, s + n_splits, ... of the sequence; so it is where the host passes no lengths.
 // With lengths that differ, that leaves the workgroups of a short sequence without work while those of the longest one
 // carry n_splits-ths of it: 48 sequences spread log-uniformly from 64 to 16384 tokens (8 kv-heads, two splits, 16-token pages,
-// 168 MB) took 74 us a call, as many tokens in equal lengths 40.  There (a.spread, set by the host where a sequence can have more tiles than splits) the
-// n_splits * B workgroups of a kv-head are one list: a sequence of T tiles gets n = ceil(T / c) of them, c the smallest
-// value found for which the list is long enough.  Every wavefront of either pass works c out for itself from the
-// lengths, one sequence per lane, which takes less time than any exchange between workgroups; equal tile counts (one
-// compare) keep the first form (51.9 us a call on 8 x 32769 tokens with lengths passed, 51.8 without the look at them).  The
-// call above takes 46 us: the longest place has 9 tiles, 6.3 would be even.  The partial results of place x of the list are the rows x * H_q + h, and the l of every row
-// (also of a place without work) carries a sign bit there, by which the combine pass knows the form without having
-// waited for the lengths.
+// 168 MB) took 74 us a call, as many tokens in equal lengths 40.  There the n_splits * B workgroups of a kv-head are one
+// list: a sequence of T tiles gets n = ceil(T / c) of them, c the smallest value found for which the list is long enough.
+// Every wavefront of the split pass works c out for itself from the lengths, which takes less time than any exchange between
+// workgroups.  The partial results of place x of the list are the rows x * H_q + h, and the workgroups (0, 0, b) leave the
+// place and count of sequence b (or that nothing was shared out) in a.places for the combine pass.
+//
+// Sharing out costs 2 to 4 us: the search, more workgroups with a set-up, and in the combine pass a round trip for the table
+// ahead of the rows.  So sequences keep their splits, decided on the lengths, where all have as many tiles as each other or
+// none has more than a.share_above of them (which the host sets by the pass, with the figures there).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,29 +29,17 @@ namespace spans {
 struct Span {
     int b, split, n;            // sequence; this workgroup takes its tiles split, split + n, split + 2 n, ...
     int64_t L;                  // cached tokens of the sequence
-    int64_t row0, row_step;     // partial results of head h: row0 + h * row_step
-    bool listed;                // the lengths differ: a place of the list
-    // bit 31 set or cleared whatever l is: a NaN, from inputs that are not finite, comes with either sign
-    __device__ float mark(float l) const {
-        const uint32_t m = __float_as_uint(l) & 0x7FFFFFFFu;
-        return __uint_as_float(listed ? m | 0x80000000u : m);
-    }
-    __device__ int64_t row(int64_t h) const { return row0 + h * row_step; }
+    int row0, row_step;         // partial results of head h: row0 + h * row_step (a row is 520 bytes: fewer than 2^31 fit memory)
+    __device__ int64_t row(int h) const { return row0 + h * row_step; }
 };
 
 __device__ __forceinline__ int64_t clamped_len(const DecodeArgs& a, int64_t len) {
     return len < 0 ? 0 : (len > a.max_len ? a.max_len : len);
 }
-// The lengths of the first 64 sequences, one per lane: requested ahead of a kernel's other loads (they return in order, and
+// The lengths of up to 64 sequences, one per lane: requested ahead of a kernel's other loads (they return in order, and
 // nothing can start without them).
 __device__ __forceinline__ int request_lengths(const DecodeArgs& a, int batch) {
-    return a.spread ? a.seq_len[min((int)(threadIdx.x & 63), batch - 1)] : 0;
-}
-// tiles of the sequence this lane looks at in the group of 64 that starts at b0 (0 beyond the last one)
-__device__ __forceinline__ int lane_tiles(const DecodeArgs& a, int len0, int batch, int b0, int lane, int log2_tile) {
-    const int b = b0 + lane;
-    if (b >= batch) return 0;
-    return (int)((clamped_len(a, b0 == 0 ? len0 : a.seq_len[b]) + ((1 << log2_tile) - 1)) >> log2_tile);
+    return a.share_above ? a.seq_len[min((int)(threadIdx.x & 63), batch - 1)] : 0;
 }
 // inclusive prefix sum over the 64 lanes
 __device__ __forceinline__ int wave_scan(int v) {
@@ -66,72 +55,112 @@ __device__ __forceinline__ int wave_scan(int v) {
 __device__ __forceinline__ int places(int T, float inv) {
     return T == 0 ? 0 : min(T, max(1, (int)ceilf((float)T * inv - 1.0f / 1024.0f)));
 }
-// 1 / c, or 0 where all sequences have as many tiles as each other
-__device__ __forceinline__ float inverse_share(const DecodeArgs& a, int len0, int batch, int lane, int log2_tile) {
-    const int t0 = lane_tiles(a, len0, batch, 0, lane, log2_tile);
-    const int first = __builtin_amdgcn_readfirstlane(t0);
-    bool same = t0 == first || lane >= batch;
-    int total = t0;
-    for (int b0 = 64; b0 < batch; b0 += 64) {
-        const int t = lane_tiles(a, len0, batch, b0, lane, log2_tile);
-        same = same && (t == first || b0 + lane >= batch);
-        total += t;
+// 1 / c for the tiles of this lane's K sequences (from K * lane on), or 0 where the sequences keep their splits
+template <int K>
+__device__ __forceinline__ float inverse_share(const DecodeArgs& a, const int (&tiles)[K], int batch) {
+    const int lane = threadIdx.x & 63;
+    const int first = __builtin_amdgcn_readfirstlane(tiles[0]);
+    bool differ = false, longer = false;
+    int total = 0;
+#pragma unroll
+    for (int g = 0; g < K; ++g) {
+        differ = differ || (tiles[g] != first && K * lane + g < batch);
+        longer = longer || tiles[g] > a.share_above;
+        total += tiles[g];
     }
-    if (__builtin_amdgcn_ballot_w64(!same) == 0) return 0.f;
+    if (__builtin_amdgcn_ballot_w64(differ) == 0 || __builtin_amdgcn_ballot_w64(longer) == 0) return 0.f;
     const int list = a.n_splits * batch;
     total = __builtin_amdgcn_readlane(wave_scan(total), 63);
-    // total / list is the least it can be; in steps of 1/16 the list suffices soon after (at the latest with the
-    // longest sequence's tiles, one place each)
-    float c = fmaxf(1.0f, (float)total / (float)list);
-    for (;;) {
-        const float inv = 1.0f / c;
-        int sum = places(t0, inv);
-        for (int b0 = 64; b0 < batch; b0 += 64) sum += places(lane_tiles(a, len0, batch, b0, lane, log2_tile), inv);
-        if (__builtin_amdgcn_readlane(wave_scan(sum), 63) <= list) return inv;
-        c *= 1.0625f;
+    // c0 = total / list is the least it can be, and 2 c0 is enough: there are fewer than total / c + batch places then, and
+    // the list has two per sequence or more.  The smallest of c0 * 2^(k/16) that does, by halves.
+    const float inv0 = __builtin_amdgcn_rcpf(fmaxf(1.0f, (float)total / (float)list));
+    auto fits = [&](float inv) {
+        int sum = 0;
+#pragma unroll
+        for (int g = 0; g < K; ++g) sum += places(tiles[g], inv);
+        return __builtin_amdgcn_readlane(wave_scan(sum), 63) <= list;
+    };
+    if (fits(inv0)) return inv0;
+    int lo = 1, hi = 16;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (fits(inv0 * __builtin_amdgcn_exp2f((float)mid * -0.0625f))) hi = mid;
+        else lo = mid + 1;
     }
+    return inv0 * __builtin_amdgcn_exp2f((float)hi * -0.0625f);
 }
 
-// The work of this workgroup (grid (n_splits, ., B)); false: none, and the marks of its `heads` heads from `h0` on are written.
-__device__ __forceinline__ bool take(const DecodeArgs& a, int len0, int log2_tile, int h0, int heads, Span& s) {
+// take() with K sequences per lane; len0: request_lengths
+template <int K>
+__device__ __forceinline__ bool take_shared(const DecodeArgs& a, int len0, int log2_tile, Span& s) {
+    const int batch = gridDim.z, lane = threadIdx.x & 63;
+    int len[K], tiles[K], n[K];
+#pragma unroll
+    for (int g = 0; g < K; ++g) len[g] = K == 1 ? len0 : a.seq_len[min(K * lane + g, batch - 1)];
+#pragma unroll
+    for (int g = 0; g < K; ++g)
+        tiles[g] = K * lane + g < batch ? (int)((clamped_len(a, len[g]) + ((1 << log2_tile) - 1)) >> log2_tile) : 0;
+    const float inv = inverse_share<K>(a, tiles, batch);
+    const bool writer = blockIdx.x == 0 && blockIdx.y == 0;
+    if (inv == 0.f) {
+        if (writer && threadIdx.x == 0) a.places[2 * s.b] = -1;
+        s.L = clamped_len(a, K == 1 ? __builtin_amdgcn_readlane(len0, s.b) : a.seq_len[s.b]);
+        return true;
+    }
+    int mine = 0;
+#pragma unroll
+    for (int g = 0; g < K; ++g) mine += n[g] = places(tiles[g], inv);
+    const int upto = wave_scan(mine);
+    if (writer) {
+        const int of = s.b / K;
+        int at = __builtin_amdgcn_readlane(upto - mine, of), count = 0;
+#pragma unroll
+        for (int g = 0; g < K; ++g) {
+            const int here = __builtin_amdgcn_readlane(n[g], of);
+            if (K * of + g < s.b) at += here;
+            if (K * of + g == s.b) count = here;
+        }
+        if (threadIdx.x == 0) {
+            a.places[2 * s.b] = at;
+            a.places[2 * s.b + 1] = count;
+        }
+    }
+    const int x = blockIdx.z * a.n_splits + blockIdx.x;
+    s.row0 = x * a.H_q;
+    s.row_step = 1;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(x < upto);
+    if (m == 0) return false;                   // beyond the last place: its rows are not read
+    const int of = __builtin_ctzll(m);
+    int at = __builtin_amdgcn_readlane(upto - mine, of);
+    bool found = false;
+#pragma unroll
+    for (int g = 0; g < K; ++g) {
+        const int here = __builtin_amdgcn_readlane(n[g], of);
+        if (!found && x < at + here) {
+            found = true;
+            s.b = K * of + g;
+            s.n = here;
+            s.split = x - at;
+            s.L = clamped_len(a, __builtin_amdgcn_readlane(len[g], of));
+        }
+        at += here;
+    }
+    return true;
+}
+
+// The work of this workgroup (grid (n_splits, ., B)); false: none.
+__device__ __forceinline__ bool take(const DecodeArgs& a, int len0, int log2_tile, Span& s) {
     s.b = blockIdx.z;
     s.split = blockIdx.x;
     s.n = a.n_splits;
-    s.row0 = (int64_t)s.b * a.H_q * a.n_splits + s.split;
+    s.row0 = s.b * a.H_q * a.n_splits + s.split;
     s.row_step = a.n_splits;
-    s.listed = false;
-    if (a.spread) {
-        const int batch = gridDim.z, lane = threadIdx.x & 63;
-        const float inv = inverse_share(a, len0, batch, lane, log2_tile);
-        if (inv != 0.f) {
-            const int x = blockIdx.z * a.n_splits + blockIdx.x;
-            s.listed = true;
-            s.row0 = (int64_t)x * a.H_q;
-            s.row_step = 1;
-            int before = 0;
-            for (int b0 = 0; b0 < batch; b0 += 64) {
-                const int n = places(lane_tiles(a, len0, batch, b0, lane, log2_tile), inv);
-                const int upto = before + wave_scan(n);
-                const uint64_t m = __builtin_amdgcn_ballot_w64(x < upto);
-                if (m != 0) {
-                    const int l = __builtin_ctzll(m);
-                    s.b = b0 + l;
-                    s.n = __builtin_amdgcn_readlane(n, l);
-                    s.split = x - (__builtin_amdgcn_readlane(upto, l) - s.n);
-                    s.L = clamped_len(a, b0 == 0 ? __builtin_amdgcn_readlane(len0, l) : a.seq_len[s.b]);
-                    return true;
-                }
-                before = __builtin_amdgcn_readlane(upto, 63);
-            }
-            for (int i = threadIdx.x; i < heads; i += blockDim.x) {
-                float* const ml = a.part_ml + s.row(h0 + i) * 2;
-                ml[0] = -INFINITY;
-                ml[1] = s.mark(0.f);
-            }
-            return false;
-        }
+    if (a.share_above) {
+        if (gridDim.z <= 64) return take_shared<1>(a, len0, log2_tile, s);
+        if (gridDim.z <= 256) return take_shared<4>(a, len0, log2_tile, s);
+        return take_shared<kMaxShared / 64>(a, len0, log2_tile, s);
     }
-    s.L = !a.seq_len ? a.max_len : clamped_len(a, a.spread && gridDim.z <= 64 ? __builtin_amdgcn_readlane(len0, s.b) : a.seq_len[s.b]);
+    s.L = !a.seq_len ? a.max_len : clamped_len(a, a.seq_len[s.b]);
     return true;
 }
 
@@ -143,24 +172,9 @@ struct Parts {
 __device__ __forceinline__ Parts parts_of(const DecodeArgs& a, int b, int h) {
     return Parts{((int64_t)b * a.H_q + h) * a.n_splits, 1, a.n_splits};
 }
-// the same where the marks say that the lengths differ
-__device__ __forceinline__ Parts listed_parts(const DecodeArgs& a, int batch, int b, int h, int log2_tile) {
-    Parts p;
-    const int lane = threadIdx.x & 63;
-    const int len0 = request_lengths(a, batch);
-    const float inv = inverse_share(a, len0, batch, lane, log2_tile);
-    int before = 0;
-    for (int b0 = 0;; b0 += 64) {
-        const int n = places(lane_tiles(a, len0, batch, b0, lane, log2_tile), inv);
-        const int upto = before + wave_scan(n);
-        if (b < b0 + 64) {
-            p.n = __builtin_amdgcn_readlane(n, b - b0);
-            p.first = (int64_t)(__builtin_amdgcn_readlane(upto, b - b0) - p.n) * a.H_q + h;
-            p.step = a.H_q;
-            return p;
-        }
-        before = __builtin_amdgcn_readlane(upto, 63);
-    }
+// the same where the workgroups were shared out: at, n as the split pass left them in a.places
+__device__ __forceinline__ Parts shared_parts(const DecodeArgs& a, int at, int n, int h) {
+    return Parts{(int64_t)at * a.H_q + h, a.H_q, n};
 }
 
 // One split (a.direct): the merged o of channel c (cache order) of virtual head s of kv-head kvh, normalised by l and

