@@ -510,10 +510,10 @@ __global__ __launch_bounds__(256) void decode_combine_rows(DecodeArgs a, int dt,
             if (i < count) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
+                    if (k > 0 && i + k >= count) break;      // (not by a weight of 0: a sum beyond fp32 is infinite)
                     const float wi = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), i + k));
-                    const bool there = i + k < count;    // (not by a weight of 0: a sum beyond fp32 is infinite)
-                    n0 = fmaf(wi, there ? v[i + k].x : 0.f, n0);
-                    n1 = fmaf(wi, there ? v[i + k].y : 0.f, n1);
+                    n0 = fmaf(wi, v[i + k].x, n0);
+                    n1 = fmaf(wi, v[i + k].y, n1);
                 }
             }
         }

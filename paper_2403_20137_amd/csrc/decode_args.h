@@ -32,7 +32,6 @@ struct DecodeArgs {
     int32_t direct;           // 1: one split and no combine pass, the split pass writes the output itself
     int32_t share_above;      // not 0: where the lengths differ and a sequence has more tiles than this, the n_splits * B
                               // workgroups of a kv-head are shared out by them (decode_spans.h)
-    int32_t* places;          // [B][2], where share_above is not 0: the first place of a sequence (-1: not shared out) and their number
     int32_t n_q_tokens, real_Hq, real_G;
     int32_t g_base, g_cnt;    // matrix-core passes: this launch serves virtual heads [g_base, g_base + g_cnt) of every kv-head;
                               // g_cnt <= 8
@@ -57,6 +56,7 @@ struct DecodeArgs {
     const int32_t* block_table;
     int64_t table_stride;
     int32_t log2_page, n_pages;
+    int32_t* places;          // [B][2], where share_above is not 0: the first place of a sequence (-1: not shared out) and their number
 };
 
 // Row index (one row = one token of one kv-head) of token t of sequence b in the four planes.  Page

@@ -195,7 +195,9 @@ constexpr int vmcnt_imm(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | ((
 // QI8 (8-bit mantissas, blocks of 32 and wider, query cast to 8-bit BFP): the score product on the integer
 // datapath of Sec. II-B -- v_mfma_i32_16x16x64_i8 on the signed codes of query and keys, one accumulator per 32
 // channels, and the two block exponents added and applied to the integer sums afterwards.
-template <int P, int N, int HG, bool PAGED, bool QI8 = false>
+// SHARE: the instantiation for calls whose workgroups may be shared out by the lengths (which have splits to merge).  A branch on it
+// costs the others 0.3 us of a call (1024 units x 1024 tokens, one split: 17.6 us with it, 17.0 without).
+template <int P, int N, int HG, bool PAGED, bool SHARE, bool QI8 = false>
 __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const int dt) {
     static_assert(P == 4 || P == 8, "mantissa widths of the format");
     static_assert(!QI8 || (P == 8 && N >= 32), "integer score product: 8-bit codes, one key exponent per 32 channels");
@@ -256,7 +258,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     const int lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
     const int kvh = blockIdx.y;
-    const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
+    const int len0 = SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0;
     // ---- the query and its permutation are requested ahead of everything, before the sequence lengths have arrived, the
     // first tile of this wavefront right after them, and only then does anybody wait: issued later, these small loads
     // would queue behind the first tiles of every workgroup of the grid (tens of megabytes).
@@ -284,8 +286,8 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     __builtin_amdgcn_sched_barrier(0);
 
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, len0, 8, span)) return;
-    if (span.b != (int)blockIdx.z) request_queries(span.b);
+    if (!kvbfp::spans::take<SHARE>(a, len0, 8, span)) return;
+    if (SHARE && span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
@@ -299,7 +301,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256) {
-            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            if (!SHARE && a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
         if (tid < a.g_cnt) {
@@ -1143,7 +1145,8 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         }
     }
     __syncthreads();
-    for (int i = tid; i < a.g_cnt * kD; i += 256) {
+    const DecodeArgs& e = kvbfp::spans::arguments_again();
+    for (int i = tid; i < e.g_cnt * kD; i += 256) {
         const int g = i / kD, c = i % kD;
         float M = -INFINITY;
 #pragma unroll
@@ -1154,19 +1157,19 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[(w * NH + g) * kD + c], acc);
         }
-        if (a.direct) {
+        if (!SHARE && e.direct) {
             float den = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 const float mw = ml_s[(w * NH + g) * 2];
                 if (mw > -INFINITY) den = fmaf(exp2f(mw - M), ml_s[(w * NH + g) * 2 + 1], den);
             }
-            kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + g, c, acc, den);
+            kvbfp::spans::write_output(e, dt, b, kvh, e.g_base + g, c, acc, den);
         } else {
-            a.part_o[span.row(h0 + g) * kD + c] = acc;
+            e.part_o[span.row(h0 + g) * kD + c] = acc;
         }
     }
-    if (!a.direct && tid < a.g_cnt) {
+    if ((SHARE || !e.direct) && tid < e.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll
@@ -1177,7 +1180,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) lsum = fmaf(exp2f(mw - M), ml_s[(w * NH + g) * 2 + 1], lsum);
         }
-        float* ml = a.part_ml + span.row(h0 + g) * 2;
+        float* ml = e.part_ml + span.row(h0 + g) * 2;
         ml[0] = M;
         ml[1] = lsum;
     }

@@ -413,10 +413,10 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 
 
 // The LDS-DMA pipeline (decode_lds.h) for 4-bit mantissas.
-template <int N, int HG, bool PAGED>
+template <int N, int HG, bool PAGED, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((N != 32 && HG == 2) ? 2 : 3, 4)))
 void decode_split_lds_p4(DecodeArgs a, int dt) {
-    kvbfp::lds::decode_split_lds_body<4, N, HG, PAGED>(a, dt);
+    kvbfp::lds::decode_split_lds_body<4, N, HG, PAGED, SHARE>(a, dt);
 }
 
 // 16-bit I/O: the LDS pipeline, every block size.  fp32 I/O: the register-staged pass with three probability
@@ -432,15 +432,20 @@ hipError_t launch_reg(const DecodeArgs& a, int dt, int block, dim3 grid, hipStre
     return hipGetLastError();
 }
 
+template <int HG, bool PAGED, bool SHARE>
+hipError_t launch_lds(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+    if (block == 16) decode_split_lds_p4<16, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 32) decode_split_lds_p4<32, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 64) decode_split_lds_p4<64, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 128) decode_split_lds_p4<128, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 template <int HG, bool PAGED>
 hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
     if (dt == KVBFP_F32) return launch_reg<HG, PAGED>(a, dt, block, grid, s);
-    if (block == 16) decode_split_lds_p4<16, HG, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 32) decode_split_lds_p4<32, HG, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 64) decode_split_lds_p4<64, HG, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 128) decode_split_lds_p4<128, HG, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    return a.share_above ? launch_lds<HG, PAGED, true>(a, dt, block, grid, s) : launch_lds<HG, PAGED, false>(a, dt, block, grid, s);
 }
 
 }  // namespace

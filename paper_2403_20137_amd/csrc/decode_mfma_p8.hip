@@ -469,39 +469,50 @@ hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream
 
 // The LDS-DMA pipeline (decode_lds.h) for 8-bit mantissas: 16-bit I/O.  Its staging area is twice that of the 4-bit
 // pipeline (68 KB per workgroup), so two workgroups share a compute unit.
-template <int N, int HG, bool PAGED>
+template <int N, int HG, bool PAGED, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void decode_split_lds_p8(DecodeArgs a, int dt) {
-    kvbfp::lds::decode_split_lds_body<8, N, HG, PAGED>(a, dt);
+    kvbfp::lds::decode_split_lds_body<8, N, HG, PAGED, SHARE>(a, dt);
 }
 
 // The same with the query cast to 8-bit BFP and blocks of 32 and wider: the score product on the integer datapath
 // (v_mfma_i32_16x16x64_i8 on the codes, block exponents added afterwards; Sec. II-B).
-template <int N, int HG, bool PAGED>
+template <int N, int HG, bool PAGED, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void decode_split_lds_p8_qi8(DecodeArgs a, int dt) {
-    kvbfp::lds::decode_split_lds_body<8, N, HG, PAGED, true>(a, dt);
+    kvbfp::lds::decode_split_lds_body<8, N, HG, PAGED, SHARE, true>(a, dt);
 }
 
-template <int HG, bool PAGED>
+template <int HG, bool PAGED, bool SHARE>
 hipError_t launch_lds_qi8(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
     switch (block) {
-        case 32: decode_split_lds_p8_qi8<32, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        case 64: decode_split_lds_p8_qi8<64, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        default: decode_split_lds_p8_qi8<128, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
+        case 32: decode_split_lds_p8_qi8<32, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        case 64: decode_split_lds_p8_qi8<64, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        default: decode_split_lds_p8_qi8<128, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
     }
     return hipGetLastError();
 }
 
-template <int HG, bool PAGED>
+template <int HG, bool PAGED, bool SHARE>
 hipError_t launch_lds(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
     switch (block) {
-        case 16: decode_split_lds_p8<16, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        case 32: decode_split_lds_p8<32, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        case 64: decode_split_lds_p8<64, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        default: decode_split_lds_p8<128, HG, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
+        case 16: decode_split_lds_p8<16, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        case 32: decode_split_lds_p8<32, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        case 64: decode_split_lds_p8<64, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        default: decode_split_lds_p8<128, HG, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
     }
     return hipGetLastError();
+}
+
+// one instantiation per head groups, paging and sharing out
+template <bool SHARE>
+hipError_t launch_16(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+    if (a.q_mant_bits == 8 && block >= 32) {      // 8-bit query codes x 8-bit key codes: integer matrix product
+        if (a.block_table) return a.g_cnt <= 4 ? launch_lds_qi8<1, true, SHARE>(a, dt, block, grid, s) : launch_lds_qi8<2, true, SHARE>(a, dt, block, grid, s);
+        return a.g_cnt <= 4 ? launch_lds_qi8<1, false, SHARE>(a, dt, block, grid, s) : launch_lds_qi8<2, false, SHARE>(a, dt, block, grid, s);
+    }
+    if (a.block_table) return a.g_cnt <= 4 ? launch_lds<1, true, SHARE>(a, dt, block, grid, s) : launch_lds<2, true, SHARE>(a, dt, block, grid, s);
+    return a.g_cnt <= 4 ? launch_lds<1, false, SHARE>(a, dt, block, grid, s) : launch_lds<2, false, SHARE>(a, dt, block, grid, s);
 }
 
 template <int HG, int PL>
@@ -517,12 +528,7 @@ hipError_t launch_decode_split_mfma_p8(const DecodeArgs& a, int dtype, int block
     const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
     // fp32 outputs take three probability limbs (24 bits), 16-bit outputs two
     if (dtype == KVBFP_F32) return a.g_cnt <= 4 ? launch_p<1, 3>(a, dtype, block, grid, s) : launch_p<2, 3>(a, dtype, block, grid, s);
-    if (a.q_mant_bits == 8 && block >= 32) {      // 8-bit query codes x 8-bit key codes: integer matrix product
-        if (a.block_table) return a.g_cnt <= 4 ? launch_lds_qi8<1, true>(a, dtype, block, grid, s) : launch_lds_qi8<2, true>(a, dtype, block, grid, s);
-        return a.g_cnt <= 4 ? launch_lds_qi8<1, false>(a, dtype, block, grid, s) : launch_lds_qi8<2, false>(a, dtype, block, grid, s);
-    }
-    if (a.block_table) return a.g_cnt <= 4 ? launch_lds<1, true>(a, dtype, block, grid, s) : launch_lds<2, true>(a, dtype, block, grid, s);
-    return a.g_cnt <= 4 ? launch_lds<1, false>(a, dtype, block, grid, s) : launch_lds<2, false>(a, dtype, block, grid, s);
+    return a.share_above ? launch_16<true>(a, dtype, block, grid, s) : launch_16<false>(a, dtype, block, grid, s);
 }
 
 }  // namespace kvbfp

@@ -148,14 +148,15 @@ __device__ __forceinline__ bool take_shared(const DecodeArgs& a, int len0, int l
     return true;
 }
 
-// The work of this workgroup (grid (n_splits, ., B)); false: none.
+// The work of this workgroup (grid (n_splits, ., B)); false: none.  SHARE false: for calls without share_above.
+template <bool SHARE = true>
 __device__ __forceinline__ bool take(const DecodeArgs& a, int len0, int log2_tile, Span& s) {
     s.b = blockIdx.z;
     s.split = blockIdx.x;
     s.n = a.n_splits;
     s.row0 = s.b * a.H_q * a.n_splits + s.split;
     s.row_step = a.n_splits;
-    if (a.share_above) {
+    if (SHARE && a.share_above) {
         if (gridDim.z <= 64) return take_shared<1>(a, len0, log2_tile, s);
         if (gridDim.z <= 256) return take_shared<4>(a, len0, log2_tile, s);
         return take_shared<kMaxShared / 64>(a, len0, log2_tile, s);
@@ -175,6 +176,15 @@ __device__ __forceinline__ Parts parts_of(const DecodeArgs& a, int b, int h) {
 // the same where the workgroups were shared out: at, n as the split pass left them in a.places
 __device__ __forceinline__ Parts shared_parts(const DecodeArgs& a, int at, int n, int h) {
     return Parts{(int64_t)at * a.H_q + h, a.H_q, n};
+}
+
+// The arguments of a split kernel (its first parameter) again, for what comes after its main loop: read there, they are not
+// held in scalar registers through it, where those that do not fit take vector registers.  Blocks of 32, two groups of four
+// heads over pages: the three wavefronts per SIMD leave 168, and 4 were spilled; 8 heads, 8 x 8192 tokens 27.2 -> 26.3 us.
+__device__ __forceinline__ const DecodeArgs& arguments_again() {
+    const __attribute__((address_space(4))) DecodeArgs* p = (const __attribute__((address_space(4))) DecodeArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));                 // (not the same to the compiler)
+    return *(const DecodeArgs*)p;
 }
 
 // One split (a.direct): the merged o of channel c (cache order) of virtual head s of kv-head kvh, normalised by l and
