@@ -611,7 +611,9 @@ size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* L, int32_t n_q_heads, in
     // (a pass that takes fewer splits than these has room for the table anyway)
     const int G = n_q_heads / L->n_kv_heads;
     const int log2_tile = G > 8 ? plan_wide(G, 1, 1, 1).log2_tile : 8;
-    const bool may_share = share_above(L, sp.n_splits, max_len, log2_tile, 1.2f) != 0;     // (the least of share_from: the I/O type is not known here)
+    // (the I/O type and the rotation are not known here: the least of share_from; above 32 heads one pass shares)
+    const float from = G > 32 ? share_from(false, L->mant_bits, G, false, sp.n_splits) : 1.2f;
+    const bool may_share = share_above(L, sp.n_splits, max_len, log2_tile, from) != 0;
     return rows_bytes(L, n_q_heads, sp.n_splits) + (may_share ? places_bytes(L) : 0);
 }
 
