@@ -251,23 +251,30 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
         ml_s[(wave * kRows + l32) * 2 + 1] = l_run;
     }
     lds_only_barrier();
-    for (int i = threadIdx.x; i < count * kD; i += kThreads) {
-        const int g = i / kD, c = i % kD;
+    // four channels per thread (a head's weights are worked out once for them): 64 heads over 300 tokens 21.4 us a call with
+    // one, 15.0 with four; 32 heads over 4 x 3000 26.0 and 20.0
+    for (int i = threadIdx.x; i < count * (kD / 4); i += kThreads) {
+        const int g = i / (kD / 4), c = 4 * (i % (kD / 4));
         const int w0 = g / kRows, r = g % kRows;
-        float M = -INFINITY;
-#pragma unroll
-        for (int t = 0; t < 4 / RG; ++t) M = fmaxf(M, ml_s[((w0 + t * RG) * kRows + r) * 2]);
-        float acc = 0.f, lsum = 0.f;
+        float m[4 / RG], M = -INFINITY;
 #pragma unroll
         for (int t = 0; t < 4 / RG; ++t) {
-            const float mw = ml_s[((w0 + t * RG) * kRows + r) * 2];
-            if (mw > -INFINITY) {
-                const float f = exp2f(mw - M);
-                acc = fmaf(f, o_s[((w0 + t * RG) * kRows + r) * kOStride + c], acc);
+            m[t] = ml_s[((w0 + t * RG) * kRows + r) * 2];
+            M = fmaxf(M, m[t]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float lsum = 0.f;
+#pragma unroll
+        for (int t = 0; t < 4 / RG; ++t) {
+            if (m[t] > -INFINITY) {
+                const float f = exp2f(m[t] - M);
+                const f32x4 x = *(const f32x4*)(o_s + ((w0 + t * RG) * kRows + r) * kOStride + c);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) acc[k] = fmaf(f, x[k], acc[k]);
                 lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 2 + 1], lsum);
             }
         }
-        a.part_o[span.row(h + g) * kD + c] = acc;
+        *(f32x4*)(a.part_o + span.row(h + g) * kD + c) = acc;
         if (c == 0) {
             float* ml = a.part_ml + span.row(h + g) * 2;
             ml[0] = M;
