@@ -630,12 +630,13 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 // The four wavefronts take 32 tokens each of a tile of 128 and share nothing until the merge: keys go from memory to
 // registers, where they are the first operand of S^T = K Q^T as they are decoded (a lane holds half of a token's row);
 // values are transposed through 8 KB of LDS of the wavefront's own.  No barrier in the loop, and kDepth tiles per wavefront
-// in flight (one for 8-bit mantissas, whose rows take twice the registers: with two the variants spill, 76 -> 68 us).
+// in flight (one for 8-bit mantissas, whose rows take twice the registers, and for fp16 queries, whose second limb takes 32:
+// with two those variants spill, 8 bits 76 -> 68 us, 12 heads with fp16 I/O over 8 x 12000 tokens 46.1 -> 42.4 us).
 template <int P, int N, int QL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     constexpr int kShift = P == 4 ? 7 : 3;             // of the values; keys are value * 2^-(kShift - kKeyUp)
-    constexpr int kDepth = P == 8 ? 1 : 2;
+    constexpr int kDepth = P == 8 || QL == 2 ? 1 : 2;
     constexpr int NB = kD / N;
     constexpr int kRowB = kD * P / 8;
     constexpr int kKeyChunks = kRowB / 32;             // 16-byte chunks of a key row per lane (every other one)
