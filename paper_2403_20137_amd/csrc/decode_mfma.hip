@@ -137,7 +137,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     // 10 x 8000 tokens, blocks of 32 35.3 against 55.1 (2.5 TB/s).  168 registers keep three workgroups per compute unit.
     struct Rows {
         u32x4 k[4];
-        uint32_t ke[4], v[4][4], ve[4][4];
+        uint32_t ke[4], v[4][4], ve[4][N == 128 ? 1 : 4];      // (one exponent a row: that of row 16u + j, handed over where it is used)
     };
     auto fetch_keys = [&](const int T0, Rows& r) {
         kvbfp::StageBases sb{};
@@ -167,8 +167,9 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             for (int i = 0; i < 4; ++i) {
                 const uint32_t row = (uint32_t)min(16 * u + 4 * kg + i, left - 1);
                 r.v[u][i] = __builtin_nontemporal_load((const uint32_t*)(vp + (row * 64u + 4u * (uint32_t)j)));
-                r.ve[u][i] = vep[row * NB + (uint32_t)((8 * j) / N)];
+                if constexpr (N != 128) r.ve[u][N == 128 ? 0 : i] = vep[row * NB + (uint32_t)((8 * j) / N)];
             }
+            if constexpr (N == 128) r.ve[u][0] = vep[min(16 * u + j, left - 1)];
         }
     };
     const int T_first = wave * kSuper, T_step = span.n * kWaves * kSuper;     // this wavefront's tiles
@@ -316,7 +317,10 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
         for (int u = 0; u < 4; ++u) {
             Unpacked vv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vv[i] = unpack8(rows.v[u][i], scale_operand(rows.ve[u][i]));
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t E = N == 128 ? (uint32_t)__shfl((int)rows.ve[u][0], 20 * kg + i) : rows.ve[u][N == 128 ? 0 : i];
+                vv[i] = unpack8(rows.v[u][i], scale_operand(E));
+            }
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) {
                 // probabilities of tokens 16u + 4kg .. +3 for this lane's row (head, parity, limb); a third
