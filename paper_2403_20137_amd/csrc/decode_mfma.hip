@@ -73,7 +73,7 @@ __device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 
 // PL = bf16 limbs of a probability: 2 (16 bits, enough for 16-bit outputs) or 3 (24 bits, fp32 outputs).
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
-template <int N, int HG, int PL, bool PAGED>
+template <int N, int HG, int PL, bool PAGED, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 1 ? 3 : 2, 4)))
 void decode_split_mfma_p4(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
@@ -87,7 +87,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     const int wave = tid >> 6, lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, span)) return;
+    if (!kvbfp::spans::take<SHARE>(a, SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0, 8, span)) return;
     const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
@@ -99,7 +99,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256) {
-            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            if (!SHARE && a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
         if (tid < a.g_cnt) {
@@ -388,7 +388,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        if (a.direct) {
+        if (!SHARE && a.direct) {
             float den = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w)
@@ -398,7 +398,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             a.part_o[span.row(h0 + g) * kD + c] = acc;
         }
     }
-    if (!a.direct && tid < a.g_cnt) {
+    if ((SHARE || !a.direct) && tid < a.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll
@@ -426,12 +426,12 @@ void decode_split_lds_p4(DecodeArgs a, int dt) {
 // 16-bit I/O: the LDS pipeline, every block size.  fp32 I/O: the register-staged pass with three probability
 // limbs and the three-limb bf16 query (the FP8 query limbs of the LDS pipeline carry 16 bits, too few for the
 // 1e-5 bar).
-template <int HG, bool PAGED>
+template <int HG, bool PAGED, bool SHARE>
 hipError_t launch_reg(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
-    if (block == 16) decode_split_mfma_p4<16, HG, 3, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 32) decode_split_mfma_p4<32, HG, 3, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 64) decode_split_mfma_p4<64, HG, 3, PAGED><<<grid, 256, 0, s>>>(a, dt);
-    else if (block == 128) decode_split_mfma_p4<128, HG, 3, PAGED><<<grid, 256, 0, s>>>(a, dt);
+    if (block == 16) decode_split_mfma_p4<16, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 32) decode_split_mfma_p4<32, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 64) decode_split_mfma_p4<64, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
+    else if (block == 128) decode_split_mfma_p4<128, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -448,7 +448,7 @@ hipError_t launch_lds(const DecodeArgs& a, int dt, int block, dim3 grid, hipStre
 
 template <int HG, bool PAGED>
 hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
-    if (dt == KVBFP_F32) return launch_reg<HG, PAGED>(a, dt, block, grid, s);
+    if (dt == KVBFP_F32) return a.share_above ? launch_reg<HG, PAGED, true>(a, dt, block, grid, s) : launch_reg<HG, PAGED, false>(a, dt, block, grid, s);
     return a.share_above ? launch_lds<HG, PAGED, true>(a, dt, block, grid, s) : launch_lds<HG, PAGED, false>(a, dt, block, grid, s);
 }
 

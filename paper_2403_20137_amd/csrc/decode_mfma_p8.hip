@@ -75,7 +75,7 @@ __device__ __forceinline__ Pieces unpack4(uint32_t w, float s_hi, float s_lo) {
 // PL = bf16 limbs of a probability: 2 (16 bits, enough for 16-bit outputs) or 3 (24 bits, fp32 outputs).
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
-template <int N, int HG, int PL, bool PAGED>
+template <int N, int HG, int PL, bool PAGED, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void decode_split_mfma_p8(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
@@ -91,7 +91,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     const int kvh = blockIdx.y;
     // the queries and their permutation are requested ahead of everything (loads return in order), before the sequence
     // lengths have arrived
-    const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
+    const int len0 = SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0;
     constexpr int kQPerThread = NH * kD / 256;
     uint32_t q_bits[kQPerThread];
     auto request_queries = [&](const int seq) {
@@ -106,8 +106,8 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     const int perm_c = a.perm_k ? (a.perm_k[kvh * kD + tid % kD] & (kD - 1)) : tid % kD;       // masked: device data the host cannot check
     __builtin_amdgcn_sched_barrier(0);
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, len0, 8, span)) return;
-    if (span.b != (int)blockIdx.z) request_queries(span.b);
+    if (!kvbfp::spans::take<SHARE>(a, len0, 8, span)) return;
+    if (SHARE && span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
@@ -119,7 +119,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256) {
-            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            if (!SHARE && a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
         if (tid < a.g_cnt) {
@@ -429,7 +429,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        if (a.direct) {
+        if (!SHARE && a.direct) {
             float den = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w)
@@ -439,7 +439,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
             a.part_o[span.row(h0 + g) * kD + c] = acc;
         }
     }
-    if (!a.direct && tid < a.g_cnt) {
+    if ((SHARE || !a.direct) && tid < a.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll
@@ -456,13 +456,13 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
     }
 }
 
-template <int HG, int PL, bool PAGED>
+template <int HG, int PL, bool PAGED, bool SHARE>
 hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
     switch (block) {
-        case 16: decode_split_mfma_p8<16, HG, PL, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        case 32: decode_split_mfma_p8<32, HG, PL, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        case 64: decode_split_mfma_p8<64, HG, PL, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
-        default: decode_split_mfma_p8<128, HG, PL, PAGED><<<grid, 256, 0, s>>>(a, dt); break;
+        case 16: decode_split_mfma_p8<16, HG, PL, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        case 32: decode_split_mfma_p8<32, HG, PL, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        case 64: decode_split_mfma_p8<64, HG, PL, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
+        default: decode_split_mfma_p8<128, HG, PL, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt); break;
     }
     return hipGetLastError();
 }
@@ -517,7 +517,8 @@ hipError_t launch_16(const DecodeArgs& a, int dt, int block, dim3 grid, hipStrea
 
 template <int HG, int PL>
 hipError_t launch_p(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
-    return a.block_table ? launch_n<HG, PL, true>(a, dt, block, grid, s) : launch_n<HG, PL, false>(a, dt, block, grid, s);
+    if (a.share_above) return a.block_table ? launch_n<HG, PL, true, true>(a, dt, block, grid, s) : launch_n<HG, PL, false, true>(a, dt, block, grid, s);
+    return a.block_table ? launch_n<HG, PL, true, false>(a, dt, block, grid, s) : launch_n<HG, PL, false, false>(a, dt, block, grid, s);
 }
 
 }  // namespace
