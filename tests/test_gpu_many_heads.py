@@ -253,8 +253,35 @@ def test_largest_exponent_bytes_beside_the_smallest(p, n, G, which, top, byte):
     assert (diff <= 2.0 ** -134 + 2.0 ** -8 * np.abs(want) + slack).all(), (diff / np.abs(want)).max()
 
 
-def test_query_and_output_at_any_address():
-    B, Hkv, G, S = 1, 1, 40, 200
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+@pytest.mark.parametrize("byte", [1, 2, 3, 254])
+def test_values_at_the_ends_of_the_exponent_bytes_up_to_32_heads(p, n, byte):
+    """Bytes 3 to 254 (8-bit: 251) are exact; 1 and 2 are off by less than 2^-126 an element, as documented."""
+    B, Hkv, G, S = 1, 1, 12, 200
+    k, v, q, _, _ = _inputs("bf16", Hkv, S, B, 3, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    if byte > 200:
+        planes[3][0, 0, 150, 0] = byte if p == 4 else 251
+    else:
+        planes[3][:] = byte
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    scale = float(np.float32(0.09))
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), [S], scale)
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    if byte > 200:
+        assert_attention_close(got, want, torch.bfloat16)
+    else:
+        diff = np.abs(got.cpu().double().numpy() - want)
+        assert (diff <= (2.0 ** -126 if byte < 3 else 0) + 2.0 ** -134 + 2.0 ** -8 * np.abs(want)).all(), diff.max()
+
+
+@pytest.mark.parametrize("G", [12, 40])
+def test_query_and_output_at_any_address(G):
+    B, Hkv, S = 1, 1, 200
     k, v, q, pk, pv = _inputs("bf16", Hkv, S, B, 11, G)
     cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
     want = kvbfp.decode_attention(cache, q.cuda(), S, 0.1, perm_v=dev_i32(pv))

@@ -97,8 +97,8 @@ def test_paged_cache_matches_oracle(dtype, p, n, G, page):
 
 
 def test_paged_equals_contiguous_bit_for_bit_and_wide_groups():
-    # same kernels, same order of operations: the paged result is the contiguous one exactly; G = 40 takes
-    # the general pass, G = 12 two launches of the matrix-core pass
+    # same kernels, same order of operations: the paged result is the contiguous one exactly; G = 12 and G = 40 take
+    # the two passes for many heads
     for G, page in ((12, 256), (40, 256), (40, 64), (12, 16), (40, 32)):
         lens = [900, 900]
         k, v, q, pk, pv = make_small(torch.bfloat16, B=2, S=900, Hkv=1, G=G, seed=170 + G)
@@ -234,11 +234,15 @@ def test_current_token_appended_and_attended_on_pages(dtype, p, n, G, page, Hkv)
 @pytest.mark.parametrize("dtype,p,n,G,Tq,page", [
     (torch.bfloat16, 4, 32, 2, 4, 256),
     (torch.float16, 4, 16, 1, 8, 64),
-    (torch.bfloat16, 8, 32, 3, 7, 128),     # 21 virtual heads: three launches over head subsets
-    (torch.bfloat16, 4, 64, 4, 9, 256),     # 36 virtual heads: general pass
+    (torch.bfloat16, 8, 32, 3, 7, 128),     # 21 virtual heads: the pass for 9 to 32
+    (torch.bfloat16, 4, 64, 4, 9, 256),     # 36 virtual heads: the pass for more
     (torch.bfloat16, 4, 32, 4, 4, 16),
     (torch.bfloat16, 8, 16, 2, 3, 32),
-    (torch.float16, 4, 128, 5, 8, 16),      # 40 virtual heads: general pass over pages of 16
+    (torch.float16, 4, 128, 5, 8, 16),      # 40 virtual heads over pages of 16
+    (torch.float32, 4, 16, 3, 4, 32),       # fp32 I/O: two launches over head subsets
+    (torch.float32, 4, 32, 5, 8, 16),       # fp32 I/O from 33 on: general pass, a page per stage of a tile
+    (torch.float32, 8, 16, 11, 3, 32),
+    (torch.float32, 8, 128, 2, 17, 256),
 ])
 def test_several_query_tokens_on_pages(dtype, p, n, G, Tq, page):
     lens = [830, max(Tq - 2, 1), 257 + Tq // 2]
@@ -290,3 +294,20 @@ def test_many_tiles_per_wavefront_on_pages(page):
         want = O.decode_attention(km, ke, vm, ve, D, n, p, synth.to_f32_numpy(q[b:b + 1, h * G:(h + 1) * G].cpu()), [S], scale,
                                   pk[h:h + 1], pv[h:h + 1])
         assert_attention_close(got[b:b + 1, h * G:(h + 1) * G], want, torch.bfloat16, "page %d unit (%d,%d)" % (page, b, h))
+
+
+@pytest.mark.parametrize("dtype,p,n,page", [(torch.bfloat16, 4, 32, 16), (torch.float16, 8, 16, 32), (torch.float32, 4, 64, 16),
+                                            (torch.bfloat16, 8, 128, 256)])
+def test_exponent_planes_at_any_address_on_pages(dtype, p, n, page):
+    # planes that are not 16-byte aligned go to the general pass, which reads exponents byte by byte
+    lens = [700, 33]
+    k, v, q, pk, pv = make_small(dtype, B=2, S=700, Hkv=2, G=3, seed=241)
+    pool, table, planes = fill_both(k, v, n, p, page, -(-700 // page) + 1, lens, pk, pv, seed=page)
+    km, ke, vm, ve = pool.planes()
+    ke, ve = (torch.cat([x.new_zeros(1), x.flatten()])[1:].view(x.shape) for x in (ke, ve))
+    assert ke.data_ptr() % 16 != 0 and ve.data_ptr() % 16 != 0
+    odd = kvbfp.Cache(pool.layout, km, ke, vm, ve)
+    scale = float(np.float32(0.09))
+    got = kvbfp.decode_attention_paged(odd, table, q.cuda(), 700, scale, seq_len_dev=dev_i32(lens), perm_k=dev_i32(pk), perm_v=dev_i32(pv))
+    torch.cuda.synchronize()
+    assert_attention_close(got, O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), lens, scale, pk, pv), dtype)

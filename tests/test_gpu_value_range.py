@@ -73,6 +73,15 @@ def test_queries_at_the_ends_of_the_range_with_the_matching_softmax_scale(dtype,
     _run(dtype, n, p, 0, 0, q_shift)
 
 
+@pytest.mark.parametrize("G", [12, 40])           # the passes for 9 to 32 heads and for more
+@pytest.mark.parametrize("dtype,n,p", [f for f in FAMILIES if f[0] != torch.float32])
+@pytest.mark.parametrize("which,shift", [("k", -100), ("k", 100), ("q", -90), ("q", 90), ("v", -100), ("v", -120), ("v", 110)])
+def test_many_heads_at_the_ends_of_the_range(dtype, n, p, which, shift, G):
+    if dtype == torch.float16:
+        shift = {"k": {-100: -10, 100: 4}, "q": {-90: -10, 90: 4}, "v": {-100: -8, -120: -12, 110: 2}}[which][shift]
+    _run(dtype, n, p, shift if which == "k" else 0, shift if which == "v" else 0, shift if which == "q" else 0, G=G)
+
+
 @pytest.mark.parametrize("S", [1500, 1024, 700, 300])
 def test_sums_beyond_the_range_are_infinite_whatever_the_number_of_splits(S):
     # the value sums of a split leave fp32 before the division by the normaliser: an infinity, and no NaN from a
