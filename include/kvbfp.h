@@ -160,7 +160,9 @@ int kvbfp_dequantize(const kvbfp_layout* layout, const kvbfp_cache* cache, int32
                      void* hip_stream);
 
 /* Bytes of DEVICE workspace kvbfp_decode_attention needs for up to max_len cached tokens
- * (partial results of the sequence splits).  Returns 0 on invalid arguments. */
+ * (partial results of the sequence splits, and a table of 8 bytes a sequence where lengths that differ may be shared out
+ * over the splits; without room for the table a call is taken all the same, and not shared out).  Returns 0 on
+ * invalid arguments. */
 size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* layout, int32_t n_q_heads, int64_t max_len);
 
 /* DEVICE, asynchronous.  One decode step of attention over the packed cache (Sec. III: the cached
@@ -178,15 +180,18 @@ size_t kvbfp_decode_workspace_bytes(const kvbfp_layout* layout, int32_t n_q_head
  *   workspace   : DEVICE, at least kvbfp_decode_workspace_bytes(layout, n_q_heads, max_len) bytes,
  *                 256-byte aligned; contents are scratch.
  * Accumulation is fp32; the output is rounded once to `dtype`.
- * Range: up to 32 query heads per kv-head the products run on the matrix cores, whose 16-bit operand
- * format holds every cached block with an exponent byte from 3 to 254 (4-bit mantissas) or 3 to 251
- * (8-bit mantissas) exactly, i.e. magnitudes from 2^-126 to 2^124.  Blocks with exponent byte 1 or 2
- * (every magnitude below 2^-124) lose low-order bits there, an absolute error under 2^-126 per element;
- * blocks above the upper end are not supported there.  The scaled query q * softmax_scale * log2(e) must
- * stay between 2^-100 and 2^100 in magnitude wherever it matters to the scores.  Wider groups, and exponent
- * planes that are not 16-byte aligned, take the general pass (fp32 multiply-adds), which has no such limits
- * beyond those of fp32 itself; with 16-bit I/O and 16-byte aligned planes wider groups run on the matrix cores as
- * well, with the exponent bytes at the ends of the range handled apart.
+ * Range, by the pass a call takes (heads: query heads per kv-head, times the query tokens of kvbfp_decode_attention_multi):
+ *   - up to 32 heads, 16-byte aligned exponent planes: matrix cores, whose 16-bit operand format holds every cached
+ *     block with an exponent byte from 3 to 254 (4-bit mantissas) or 3 to 251 (8-bit mantissas) exactly, i.e.
+ *     magnitudes from 2^-126 to 2^124.  Blocks with exponent byte 1 or 2 (every magnitude below 2^-124) lose
+ *     low-order bits there, an absolute error under 2^-126 per element; blocks above the upper end are not supported
+ *     there.  The scaled query q * softmax_scale * log2(e) must stay between 2^-100 and 2^100 in magnitude wherever
+ *     it matters to the scores.
+ *   - more heads, 16-bit I/O, 16-byte aligned exponent planes: matrix cores, every exponent byte exact beside every
+ *     other, probabilities with all their 24 bits.  A power of two of softmax_scale far from 1 is folded into the
+ *     query as far as its largest element stays above 2^-8; below 2^-126 elements of a bf16 query lose bits.
+ *   - more heads with fp32 I/O, and exponent planes that are not 16-byte aligned: the general pass (fp32
+ *     multiply-adds), with no limits beyond those of fp32 itself.
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP. */
 int kvbfp_decode_attention(const kvbfp_layout* layout, const kvbfp_cache* cache, int32_t n_q_heads,
                            const void* q, kvbfp_dtype dtype, const int32_t* seq_len_dev,

@@ -22,8 +22,9 @@ struct DecodeArgs {
     float* part_ml;           // [rows][2]  (m in base-2 units, l), rows of the partial results: [B][H_q][n_splits], or as
     float* part_o;            // [rows][D]   decode_spans.h has them where the lengths differ
     int64_t max_seq, max_len;
-    // Work division: the sequence is cut into 256-token tiles and split s (blockIdx.x) takes tiles
-    // s, s + n_splits, s + 2 n_splits, ...; each split leaves one partial result for the combine pass.
+    // Work division: the sequence is cut into tiles (of 256 tokens; 128 and 64 in the passes for more than 8 and more than 32
+    // heads) and split s (blockIdx.x) takes tiles s, s + n_splits, s + 2 n_splits, ... or, where the splits are shared out by the
+    // lengths, its part of them (decode_spans.h); each split leaves one partial result for the combine pass.
     // With several query tokens per sequence (kvbfp_decode_attention_multi) the kernels see "virtual
     // heads": H_q = n_q_tokens * real_Hq per batch and G = n_q_tokens * real_G per kv-head; virtual head
     // s of a kv-head is query token s / real_G, real head kvh * real_G + s % real_G, and may attend

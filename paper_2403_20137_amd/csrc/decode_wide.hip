@@ -17,8 +17,9 @@
 //     their 24 bits; up to 32 two (16 bits), as in the other passes for 16-bit I/O.
 // Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 64 MFMAs of 32 cycles,
 // some 390 vector instructions of softmax and limbs and 110 of decoding, 4 cycles each).  256 virtual heads (64 query tokens, groups of
-// 4) over 4 x 8192 tokens x 8 kv-heads: 63 us against 1470 us in the general pass.  Up to 32 heads: vector ALUs 70 % busy (490
-// instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us, 2.6 TB/s, against 65 us in two launches.
+// 4) over 4 x 8192 tokens x 8 kv-heads: 79 us a call against 1490 us in the general pass.  Up to 32 heads: vector ALUs 70 % busy (490
+// instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us a call, against 66 us in two launches.
+// Registers: with fp16 queries and more than 64 heads 14 (8 bits: 23) of them are spilled, the second limb of the query.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -951,7 +952,9 @@ WidePlan plan_wide(int G, int64_t units, int64_t max_len, int max_splits) {
     const int groups = (G + kRows - 1) / kRows;
     w.row_tiles = (groups + 3) / 4;
     w.groups = (groups + w.row_tiles - 1) / w.row_tiles;
-    // two workgroups fit a compute unit; as many splits as fill one round of them, not more than there are tiles
+    // two workgroups fit a compute unit; as many splits as fill one round of them, not more than there are tiles.  (Down to
+    // one, which leaves slots empty from 257 to 511 workgroups: 40 sequences x 4096 tokens, 5 query tokens x 4 heads, 320
+    // workgroups, take 83 us a call in equal and 60 in log-uniform lengths, 122 and 70 in the passes that served them before.)
     const int tile = w.groups > 1 ? 64 : 128;
     const int64_t tiles = (max_len + tile - 1) / tile;
     int64_t n = 512 / (units * w.row_tiles);

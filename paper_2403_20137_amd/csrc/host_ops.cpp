@@ -74,13 +74,13 @@ int check_paging(const kvbfp_layout* pool, const Paging& pg, kvbfp_layout* logic
 
 SplitPlan plan_splits(const kvbfp_layout* L, int32_t n_q_heads, int64_t max_len) {
     // Enough workgroups to fill 256 compute units with as many as are resident per unit - three, or two
-    // with 8-bit mantissas (the passes for more than 8 heads also keep two; the workspace of callers counts on
-    // these figures, a pass takes fewer splits where it wants them) - but no more splits than there are
+    // with 8-bit mantissas and for more than 8 heads with blocks of 16 and 32 - but no more splits than there are
     // 256-token tiles: the tiles are dealt out round-robin over the splits.
     const int64_t units = (int64_t)L->batch * L->n_kv_heads;
     const int64_t tiles = (max_len + kTokenTile - 1) / kTokenTile;
-    const bool sixteen = L->mant_bits == 4 && L->block <= 32 && n_q_heads / L->n_kv_heads > 8;
-    const bool two_per_cu = sixteen || L->mant_bits == 8;      // 8-bit mantissas: twice the staging area per workgroup
+    // (the size of a workspace follows from this; a pass takes fewer splits where it wants them, see WidePlan)
+    const bool many = L->mant_bits == 4 && L->block <= 32 && n_q_heads / L->n_kv_heads > 8;
+    const bool two_per_cu = many || L->mant_bits == 8;      // 8-bit mantissas: twice the staging area per workgroup
     const int64_t target_wgs = 256 * (two_per_cu ? 2 : 3);
     int64_t want = (target_wgs + units - 1) / units;
     if (want > tiles) want = tiles;
