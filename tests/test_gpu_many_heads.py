@@ -291,3 +291,46 @@ def test_query_and_output_at_any_address(G):
     got = kvbfp.decode_attention(cache, shifted[1:].view(q.shape), S, 0.1, perm_v=dev_i32(pv), out=out[1:].view(q.shape))
     torch.cuda.synchronize()
     assert torch.equal(got, want) and float(out[0]) == 0.0
+
+
+@pytest.mark.parametrize("dt,p,n,G", [("bf16", 4, 32, 33), ("f16", 4, 16, 70), ("bf16", 8, 16, 33), ("f16", 8, 64, 70)])
+def test_exponents_that_leave_the_range_of_the_first_tile(dt, p, n, G):
+    """Two workgroups a sequence, four tiles each: the pass starts with values relative to the largest exponent of its first tile
+    and has to go on in another way from the first tile that does not fit it, with the sums it has.  Block 0 (and the keys)
+    of one sequence each: nothing; one value 2^30 above; 2^40 below; 2^40 below from the start on, then as it was; zero rows at
+    the start; one value 2^10 above in the last token; keys at the smallest byte; up by 2^6 and down by 2^24, the last that fit."""
+    B, Hkv, S = 64, 4, 450
+    k, v, q, _, _ = _inputs(dt, Hkv, S, B, 17 + G, Hkv * G)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    ke, ve = planes[1], planes[3]
+    for b in range(B):
+        t = 128 + 64 * (b // 8 % 4) + b % 16               # second to fifth tile
+        e = ve[b, ..., 0].astype(np.int64)
+        kind = b % 8
+        if kind == 1: e[:, t] += 30
+        elif kind == 2: e[:, t] -= 40
+        elif kind == 3: e[:, :t] -= 40
+        elif kind == 4: ve[b, :, :t], planes[2][b, :, :t] = 0, 0
+        elif kind == 5: e[:, S - 1] += 10
+        elif kind == 6: ke[b, :, t:t + 16] = 1
+        elif kind == 7:
+            e[:, t] += 6
+            e[:, t + 9] -= 24
+        if kind != 4:
+            ve[b, ..., 0] = e
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w))
+    scale = float(np.float32(0.02))
+    want = O.decode_attention(*(np.ascontiguousarray(x[:, 1:2]) for x in planes), D, n, p, synth.to_f32_numpy(q[:, G:2 * G]), [S] * B, scale)   # one kv-head
+    if dt == "f16":                                        # block 0 of the values out of its range: compared as it is stored
+        want = np.where(np.abs(want) < 65520, want, np.inf * np.sign(want))
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)[:, G:2 * G]
+    torch.cuda.synchronize()
+    for part in (slice(0, n), slice(n, D)):                # apart: what is large in block 0 says nothing about the others
+        g, w = got[..., part], want[..., part]
+        fits = np.isfinite(w).all(axis=-1)
+        assert bool((torch.isinf(g).cpu() == torch.from_numpy(np.isinf(w))).all())
+        for b in range(B):
+            if fits[b].any():
+                assert_attention_close(g[b, fits[b]], w[b, fits[b]], DT[dt], "sequence %d" % b)
