@@ -50,6 +50,10 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kThreads = 256;
 constexpr int kRows = 32;                      // virtual heads per wavefront
 constexpr uint32_t kKeyUp = 2;                 // decode_split_few: added to the keys' exponent bytes
+// The sums are relative to a reference that a score may exceed by kSlack before they are rescaled (a branch and 64 products nearly
+// every tile otherwise), so a sum of weighted values may be 2^kSlack above the values: not for values with a byte above kOrdinary.
+constexpr float kSlack = 4.f;
+constexpr int kOrdinary = 240;
 
 // packs the upper halves of two fp32 patterns: (lo, hi) -> one register of two bf16
 __device__ __forceinline__ uint32_t pack_hi(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
@@ -342,9 +346,8 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     constexpr int kValWords = P == 4 ? 1 : 2;          // dwords (8 channels) of a value row per thread
     // binary16: a code of byte E is m 2^(kUnit + E - ref); at most 127 2^(2 + 6) or 7 2^(6 + 6), exact down to 2^-22
     constexpr int kUnit = P == 4 ? 6 : 2, kSpanUp = 6, kSpanDown = 24;
-    // probabilities carry 2^kProb relative to a reference that a score may exceed by kSlack before the sums are rescaled (at most
-    // 2^15, and what is below 2^-25 is lost: 2^-36 of the reference)
-    constexpr float kProb = 11.f, kSlack = 4.f;
+    // probabilities carry 2^kProb: at most 2^(kProb + kSlack), and what is below 2^-25 is lost, 2^-36 of the reference
+    constexpr float kProb = 11.f;
     constexpr int kKeyBytes = TT * 256, kValBytes = kD * TT * 2, kTileBytes = kKeyBytes + kValBytes;
     constexpr int kOStride = kD + 4;
     constexpr int kMerge = TG > 1 ? 2 * kRows * kOStride * 4 : 0;          // two wavefronts' outputs
@@ -590,7 +593,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             const uint32_t v_low = min(min(r.ve[0] - 1u, r.ve[1] - 1u), min(r.ve[2] - 1u, r.ve[3] - 1u));
             const int v_top = (int)max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3]));
             const uint32_t k_low = min(key_byte(r, 0) - 1u, key_byte(r, 1) - 1u), k_top = max(key_byte(r, 0), key_byte(r, 1));
-            const bool beyond = v_low < (uint32_t)max(lo - 1, 0) || v_top > ref + kSpanUp || k_low < 2u || k_top > ExpRange<P>::kTop;
+            const bool beyond = v_low < (uint32_t)max(lo - 1, 0) || v_top > min(ref + kSpanUp, kOrdinary) || k_low < 2u || k_top > ExpRange<P>::kTop;
             if (__builtin_amdgcn_ballot_w64(beyond) != 0 && lane == 0) beyond_s[at] = 1;
         };
         auto decode_all = [&](const Raw& r, uint8_t* const tile, const int at) {
@@ -1005,6 +1008,12 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
 
     auto tile = [&](const int64_t T0, Raw& r) {
+        uint32_t v_top = 0;
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v_top = max(v_top, r.ve[st][i]);
+        const float slack = __builtin_amdgcn_ballot_w64(v_top > kOrdinary) != 0 ? 0.f : kSlack;
         // ---- values to LDS, the four tokens of a quad side by side per channel; quads 0 and 2 of a stage make its first 16
         // bytes, 1 and 3 the second (the order in which S^T leaves the tokens)
 #pragma unroll
@@ -1086,11 +1095,24 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         float tmax = s[0];
 #pragma unroll
         for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-        tmax = fmaxf(tmax, other_half(tmax)) * mul;          // -inf only if this head sees none of the tile
-        const float m_new = fmaxf(m_run, tmax);
-        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2_raw(m_run - m_ref);
-        const float m_p = m_ref - (float)kShift;                   // probabilities carry 2^kShift
+        float alpha = 1.f;
+        if constexpr (P == 4) {
+            tmax = both_halves_max(tmax) * mul;              // -inf only if this head sees none of the tile
+            if (__builtin_amdgcn_ballot_w64(tmax > m_run + slack) != 0) {
+                const float m_new = fmaxf(m_run, tmax);
+                alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
+                l_run *= alpha;
+                m_run = m_new;
+#pragma unroll
+                for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+            }
+        } else {                                             // (bound by memory: the branch there costs as much as it saves)
+            tmax = fmaxf(tmax, other_half(tmax)) * mul;
+            const float m_new = fmaxf(m_run, tmax);
+            alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
+            m_run = m_new;
+        }
+        const float m_p = (m_run == -INFINITY ? 0.f : m_run) - (float)kShift;     // probabilities carry 2^kShift
         uint32_t p_hi[8], p_lo[8];
         float psum = 0.f;
 #pragma unroll
@@ -1105,11 +1127,14 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
             lo[1] = (__bf16)(p1 - __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u));
             p_lo[i / 2] = bits(lo);
         }
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+        if constexpr (P == 4) {
+            l_run += psum;
+        } else {
+            l_run = l_run * alpha + psum;
+            if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+                for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+            }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // the values were written by other lanes of this wavefront
         __builtin_amdgcn_wave_barrier();
