@@ -28,6 +28,11 @@
 //     Blocks of 16: a chunk holds two blocks; the one with the smaller exponent is scaled down by the
 //     difference inside the conversion (exact down to 2^-24 of the other block's unit).
 // Values, softmax and the merge of the four wavefronts are those of the register-staged plain pass.
+// Bound by vector ALUs: some 920 instructions a wavefront and tile of 64 tokens, 256 of them the table products, 320 the
+// unpacking of keys and values, 130 the operand rebuild; 90 % of the issue slots once the set-up (7 us, most of it sines and
+// cosines) is done.  8 x 16384 tokens x 8 kv-heads, 4 heads: 51 us a call; 58 with 64-bit addresses per row, accumulation registers
+// that were copied to and fro (the compiler's choice without the two wavefronts per SIMD stated) and a sine and a cosine per
+// table entry.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -115,7 +120,8 @@ __device__ __forceinline__ void static_for4(F&& f) {
 constexpr int kHeadStride = kD + 4;     // fp32 words per head of the normalised queries: four heads hit different banks
 
 template <int N>
-__global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void decode_split_rope_p4(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = 4;
     // cos/sin(tau Th[m]) in binary16 limbs: 16-byte entries [chunk][cos hi|sin hi|cos lo|sin lo][kg][tau / 16][tau % 16],
@@ -176,14 +182,10 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
         q2_s[g][c] = -a.rope_sign[kvh * kD + c] * q1_s[g][a.rope_partner[kvh * kD + c] & (kD - 1)];
     }
     __syncthreads();
-    if (tid < NH * 4) {     // per (head, chunk): the power of two that brings |A1|, |A2| <= |q| + |q2| below 2^14
-        const int g = tid >> 2, blk = tid & 3;
-        uint32_t mx = 0u;
-        for (int c = 0; c < 32; ++c) {
-            mx = max(mx, __float_as_uint(q1_s[g][32 * blk + c]) & 0x7FFFFFFFu);
-            mx = max(mx, __float_as_uint(q2_s[g][32 * blk + c]) & 0x7FFFFFFFu);
-        }
-        qe_s[g][blk] = (int)min(mx >> 23, 254u) - 139;          // mx < 2^(e - 126)  =>  |A| 2^-qe < 2^14
+    {       // per (head, chunk): the power of two that brings |A1|, |A2| <= |q| + |q2| below 2^14; a wavefront per head, 16 lanes per chunk
+        const float2 x = *(const float2*)&q1_s[wave][2 * lane], y = *(const float2*)&q2_s[wave][2 * lane];
+        const float top = row_max(fmaxf(fmaxf(fabsf(x.x), fabsf(x.y)), fmaxf(fabsf(y.x), fabsf(y.y))));
+        if (j == 0) qe_s[wave][kg] = (int)min(__float_as_uint(top) >> 23, 254u) - 139;          // top < 2^(e - 126)  =>  |A| 2^-qe < 2^14
     }
     __syncthreads();
     for (int i = tid; i < NH * kD; i += 256) {
@@ -193,34 +195,81 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
         q2n_s[g * kHeadStride + slot_index(c)] = ldexpf(q2_s[g][c], -e);
     }
     __syncthreads();        // the channel-order queries give way to the table
-    {
-        _Float16* tab_h = reinterpret_cast<_Float16*>(tab_raw);
-        for (int i = tid; i < kSuper * kD; i += 256) {
-            const int tau = i >> 7, c = i & (kD - 1);
-            float sn, cs;
-            sincosf((float)tau * a.rope_theta[kvh * kD + c], &sn, &cs);
-            const int blk = c >> 5, dw = (c >> 3) & 3, slot = slot_index(c) & 7;
-            const int e16 = ((blk * 4 * 4 + dw) * 4 + (tau >> 4)) * 16 + (tau & 15);    // 16-byte entry of the cosine's high limb
-            const _Float16 ch = (_Float16)(float)(__bf16)cs, sh = (_Float16)(float)(__bf16)sn;   // 8 significant bits
-            tab_h[e16 * 8 + slot] = ch;
-            tab_h[(e16 + kKind) * 8 + slot] = sh;
-            tab_h[(e16 + 2 * kKind) * 8 + slot] = (_Float16)(cs - (float)ch);
-            tab_h[(e16 + 3 * kKind) * 8 + slot] = (_Float16)(sn - (float)sh);
+    const int64_t tile_step = (int64_t)span.n * 256;
+    // A phasor at an angle of up to some tens, with what the angle lost when it was rounded put back.
+    auto phasor = [](const float tau, const float th, float& cs, float& sn) {
+        const float angle = tau * th, rest = fmaf(tau, th, -angle);
+        sincosf(angle, &sn, &cs);
+        const float c0 = cs;
+        cs = fmaf(-rest, sn, cs);
+        sn = fmaf(rest, c0, sn);
+    };
+    float* const p16_s = (float*)&p_s[0][0][0][0];                  // [2][kD]: phasors of 16 tokens
+    static_assert(sizeof(p_s) >= 2 * kD * sizeof(float), "they fit");
+    {       // In double precision, angles of up to 10^5: those of the wavefronts' first tiles, t_begin + 64 w, by one half of the
+            // threads, the latter three as products, that of the step from tile to tile by the other.
+        const int c = tid & (kD - 1), at = slot_index(c);
+        const float th = a.rope_theta[kvh * kD + c];
+        const bool first = tid < kD;
+        double sn, cs;
+        sincos((double)(first ? t_begin : tile_step) * (double)th, &sn, &cs);
+        if (first) {
+            double s64, c64;
+            sincos((double)kSuper * (double)th, &s64, &c64);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                ph_s[w][0][at] = (float)cs;
+                ph_s[w][1][at] = (float)sn;
+                const double next = cs * c64 - sn * s64;
+                sn = sn * c64 + cs * s64;
+                cs = next;
+            }
+        } else {
+            step_s[0][at] = (float)cs;
+            step_s[1][at] = (float)sn;
+            phasor(16.f, th, p16_s[c], p16_s[kD + c]);
         }
     }
-    const int64_t tile_step = (int64_t)span.n * 256;
-    if (tid < kD) {
-        const double th = (double)a.rope_theta[kvh * kD + tid];
-        const int at = slot_index(tid);
-        double sn, cs;
-        sincos((double)tile_step * th, &sn, &cs);
-        step_s[0][at] = (float)cs;
-        step_s[1][at] = (float)sn;
+    __syncthreads();
+    {
+        // The table: a thread takes the eight channels of an entry at tau = t, t + 16, .., so that it stores whole entries (a channel
+        // per thread is 32 sine/cosine pairs and 128 stores of two bytes that meet in the same banks).
+        const int t = tid & 15, group = tid >> 4;                    // group: 4 blk + dw
+        float cs[4], sn[4];
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {                       // (four channels at a time: the code of four sine/cosine pairs is enough)
+            float th[4];
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            sincos((double)(t_begin + w * kSuper) * th, &sn, &cs);
-            ph_s[w][0][at] = (float)cs;
-            ph_s[w][1][at] = (float)sn;
+            for (int x = 0; x < 4; ++x) th[x] = a.rope_theta[kvh * kD + 8 * group + 2 * x + half];      // slot 4 half + x
+#pragma unroll
+            for (int x = 0; x < 4; ++x) phasor((float)t, th[x], cs[x], sn[x]);
+            u32x2* const at = (u32x2*)tab_raw + (size_t)(((group >> 2) * 4 * 4 + (group & 3)) * 4 * 16 + t) * 2 + half;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                            // tau = t + 16 i
+                uint32_t w[4][2];
+#pragma unroll
+                for (int x = 0; x < 4; x += 2) {
+                    const f16x2 ch = {(_Float16)(float)(__bf16)cs[x], (_Float16)(float)(__bf16)cs[x + 1]};          // 8 significant bits
+                    const f16x2 sh = {(_Float16)(float)(__bf16)sn[x], (_Float16)(float)(__bf16)sn[x + 1]};
+                    const f16x2 cl = {(_Float16)(cs[x] - (float)ch[0]), (_Float16)(cs[x + 1] - (float)ch[1])};
+                    const f16x2 sl = {(_Float16)(sn[x] - (float)sh[0]), (_Float16)(sn[x + 1] - (float)sh[1])};
+                    w[0][x / 2] = __builtin_bit_cast(uint32_t, ch);
+                    w[1][x / 2] = __builtin_bit_cast(uint32_t, sh);
+                    w[2][x / 2] = __builtin_bit_cast(uint32_t, cl);
+                    w[3][x / 2] = __builtin_bit_cast(uint32_t, sl);
+                }
+#pragma unroll
+                for (int kind = 0; kind < 4; ++kind) at[(kind * kKind + 16 * i) * 2] = u32x2{w[kind][0], w[kind][1]};
+                if (i < 3) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        const float c16 = p16_s[8 * group + 2 * x + half], s16 = p16_s[kD + 8 * group + 2 * x + half];
+                        const float next = fmaf(cs[x], c16, -(sn[x] * s16));
+                        sn[x] = fmaf(sn[x], c16, cs[x] * s16);
+                        cs[x] = next;
+                    }
+                }
+            }
         }
     }
     __syncthreads();
@@ -228,7 +277,7 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
     // this lane's rows of every score MFMA belong to head kg
     int qe[4];
 #pragma unroll
-    for (int blk = 0; blk < 4; ++blk) qe[blk] = qe_s[kg][blk];
+    for (int blk = 0; blk < 4; ++blk) qe[blk] = qe_s[kg][blk] - 129;
 
     const int a_head = j >> 2, a_par = (j >> 1) & 1, a_limb = j & 1;
     const uint32_t sel_even = a_par ? 0x01000c0cu : 0x0c0c0100u;
@@ -247,6 +296,8 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
     for (int m = 0; m < 4; ++m) o_acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const uint4* tab = reinterpret_cast<const uint4*>(tab_raw);
+    float minus_one = -1.f;
+    asm volatile("" : "+s"(minus_one));          // (a product for the compiler: v_fma_mix takes the binary16 number as it is)
 
     // The rows of one 64-token tile as this lane loads them: key chunk kg of rows 16u + j with the row's
     // exponent bytes, requested before the tile's query operands are built; value dword j of rows
@@ -259,6 +310,8 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
         uint32_t vw[16];
         uint32_t vex[16];
     };
+    const uint32_t k_at = (uint32_t)j * 64u + (uint32_t)kg * 16u, kx_at = (uint32_t)j * NB;
+    const uint32_t v_at = (uint32_t)kg * 256u + (uint32_t)j * 4u, vx_at = (uint32_t)(4 * kg * NB + (8 * j) / N);
     auto fetch = [&](const int T0, auto full_tag, KeyRows& d) {
         constexpr bool FULL = decltype(full_tag)::value;
         const size_t R0 = (size_t)T0;   // wave-uniform
@@ -267,17 +320,20 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
         const int left = n_tok - T0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const uint32_t r = FULL ? (uint32_t)(16 * u + j) : (uint32_t)min(16 * u + j, left - 1);
-            d.kw[u] = __builtin_nontemporal_load((const u32x4*)(kp + r * 64u + (uint32_t)kg * 16u));
+            // a complete tile: one offset per lane, the stage as an immediate
+            const uint32_t r = (uint32_t)min(16 * u + j, left - 1);
+            const uint8_t* const km = FULL ? kp + 1024 * u + k_at : kp + (r * 64u + (uint32_t)kg * 16u);
+            const uint8_t* const kx = FULL ? kep + 16 * u * NB + kx_at : kep + r * NB;
+            d.kw[u] = __builtin_nontemporal_load((const u32x4*)km);
             if constexpr (N == 16) {
-                const u32x2 e2 = *(const u32x2*)(kep + r * 8u);
+                const u32x2 e2 = *(const u32x2*)kx;
                 d.kex[u][0] = e2[0]; d.kex[u][1] = e2[1];
             } else if constexpr (N == 32) {
-                d.kex[u][0] = *(const uint32_t*)(kep + r * 4u);
+                d.kex[u][0] = *(const uint32_t*)kx;
             } else if constexpr (N == 64) {
-                d.kex[u][0] = *(const uint16_t*)(kep + r * 2u);
+                d.kex[u][0] = *(const uint16_t*)kx;
             } else {
-                d.kex[u][0] = kep[r];
+                d.kex[u][0] = *kx;
             }
         }
     };
@@ -316,7 +372,8 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
                 // cut again: the pair carries 22 bits whichever way each part is rounded
                 const f16x2 h1 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(a1[0], a1[1]));
                 const f16x2 h2 = __builtin_bit_cast(f16x2, __builtin_amdgcn_cvt_pkrtz(a2[0], a2[1]));
-                const f32x2 r1 = a1 - __builtin_convertvector(h1, f32x2), r2 = a2 - __builtin_convertvector(h2, f32x2);
+                const f32x2 r1 = {fmaf((float)h1[0], minus_one, a1[0]), fmaf((float)h1[1], minus_one, a1[1])};
+                const f32x2 r2 = {fmaf((float)h2[0], minus_one, a2[0]), fmaf((float)h2[1], minus_one, a2[1])};
                 hi1[i / 2] = __builtin_bit_cast(uint32_t, h1);
                 hi2[i / 2] = __builtin_bit_cast(uint32_t, h2);
                 lo1[i / 2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(r1[0], r1[1]));
@@ -329,8 +386,8 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
             uint32_t ze1[4], zo1[4], ze2[4], zo2[4];       // for even / odd blk
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const uint32_t x1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo1[r], 0xB1, 0xF, 0xF, false);   // quad_perm [1,0,3,2]
-                const uint32_t x2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo2[r], 0xB1, 0xF, 0xF, false);
+                const uint32_t x1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo1[r], 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2] (bound_ctrl: no old value to bring)
+                const uint32_t x2 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo2[r], 0xB1, 0xF, 0xF, true);
                 ze1[r] = odd ? x1 : hi1[r];
                 zo1[r] = odd ? hi1[r] : x1;
                 ze2[r] = odd ? x2 : hi2[r];
@@ -342,8 +399,8 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
                 uint32_t p1[4], p2[4];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    p1[r] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)((blk & 1) ? zo1[r] : ze1[r]), ctrl, 0xF, 0xF, false);
-                    p2[r] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)((blk & 1) ? zo2[r] : ze2[r]), ctrl, 0xF, 0xF, false);
+                    p1[r] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)((blk & 1) ? zo1[r] : ze1[r]), ctrl, 0xF, 0xF, true);
+                    p2[r] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)((blk & 1) ? zo2[r] : ze2[r]), ctrl, 0xF, 0xF, true);
                 }
                 A1[blk] = __builtin_bit_cast(f16x8, u32x4{p1[0], p1[1], p1[2], p1[3]});
                 A2[blk] = __builtin_bit_cast(f16x8, u32x4{p2[0], p2[1], p2[2], p2[3]});
@@ -371,9 +428,9 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
             for (int u = 0; u < 4; ++u)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const uint32_t r = FULL ? (uint32_t)(16 * u + 4 * kg + i) : (uint32_t)min(16 * u + 4 * kg + i, left - 1);
-                    dv.vw[4 * u + i] = __builtin_nontemporal_load((const uint32_t*)(vp + r * 64u + 4u * (uint32_t)j));
-                    dv.vex[4 * u + i] = vep[r * NB + (uint32_t)((8 * j) / N)];
+                    const uint32_t r = (uint32_t)min(16 * u + 4 * kg + i, left - 1);
+                    dv.vw[4 * u + i] = __builtin_nontemporal_load((const uint32_t*)(FULL ? vp + (1024 * u + 64 * i) + v_at : vp + (r * 64u + 4u * (uint32_t)j)));
+                    dv.vex[4 * u + i] = *(FULL ? vep + (16 * u + i) * NB + vx_at : vep + (r * NB + (uint32_t)((8 * j) / N)));
                 }
         }
 
@@ -392,11 +449,11 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
             float acc_s = 0.f;
             // the partial sums of a step are picked up one step later, when its MFMAs have long finished
             f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-            float post_scale[2] = {0.f, 0.f};
+            int post_scale[2] = {0, 0};
             auto finish = [&](const int c) {                // step c: scale by the powers of two, add, close a stage
                 const int u = c >> 2, blk = c & 3;
                 if (blk == 0) acc_s = 0.f;
-                acc_s = fmaf(acc[c & 1][0] + acc[c & 1][1], post_scale[c & 1], acc_s);
+                acc_s += ldexpf(acc[c & 1][0] + acc[c & 1][1], post_scale[c & 1]);
                 if (blk == 3) s[u] = (FULL || 16 * u + j < left) ? acc_s : -INFINITY;
             };
 #pragma unroll
@@ -434,8 +491,7 @@ __global__ __launch_bounds__(256) void decode_split_rope_p4(DecodeArgs a, int dt
                 }
                 acc[c & 1] = a4;
                 // code m of exponent byte E is m 2^(E - 129); the query was divided by 2^qe
-                const int F = min(max((int)Ec + qe[blk] - 2, 0), 254);
-                post_scale[c & 1] = __uint_as_float((uint32_t)F << 23);
+                post_scale[c & 1] = (int)Ec + qe[blk];
                 if (c > 0) finish(c - 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
