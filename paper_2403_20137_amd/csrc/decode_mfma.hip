@@ -78,7 +78,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 1 ? 3
 void decode_split_mfma_p4(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
-    __shared__ float q_s[NH][kD];                               // scaled, permuted queries
+    constexpr int kQStride = kD + 4;                            // (four heads side by side are read from different banks)
+    __shared__ __align__(16) float q_s[NH][kQStride];           // scaled, permuted queries
     __shared__ __align__(16) uint16_t p_s[kWaves][HG][PL][4][kSuper];  // probabilities, bf16 limbs
     __shared__ float o_s[kWaves][NH][kD];                       // per-wavefront outputs for the merge
     __shared__ float ml_s[kWaves][NH][2];
@@ -86,8 +87,9 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int j = lane & 15, kg = lane >> 4;
+    const int len0 = SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0;
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take<SHARE>(a, SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0, 8, span)) return;
+    if (!kvbfp::spans::take<SHARE>(a, len0, 8, span)) return;
     const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
@@ -174,6 +176,17 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
         }
     };
     const int T_first = wave * kSuper, T_step = span.n * kWaves * kSuper;     // this wavefront's tiles
+    // The query as it lies in memory and its permutation ahead of the first tile's rows: loads return in order, and a load through
+    // the permutation would be a round trip behind them.
+    constexpr int kQPerThread = NH * kD / 256;
+    uint32_t q_bits[kQPerThread];
+#pragma unroll
+    for (int k = 0; k < kQPerThread; ++k) {
+        const int i = tid + 256 * k, g = i / kD;
+        const int64_t idx = kvbfp::query_row(a, b, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + i % kD;   // clamped: rows beyond the count are zeroed below
+        q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
+    }
+    const int perm_c = a.perm_k ? (a.perm_k[kvh * kD + tid % kD] & (kD - 1)) : tid % kD;
     Rows rows;
     if (T_first < n_tok) {
         fetch_keys(T_first, rows);
@@ -183,21 +196,29 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     // q' = permuted query (optionally cast to BFP) * softmax_scale*log2(e) * 2^kShift; head slots beyond G are zero
     {
         const float two_k = (float)(1 << kShift);
-        for (int i = tid; i < NH * kD; i += 256) {
-            const int g = i / kD, c = i % kD;
-            float v = 0.f;
-            if (g < a.g_cnt) {
-                const int src = a.perm_k ? (a.perm_k[kvh * kD + c] & (kD - 1)) : c;
-                v = load_as_float(a.q, dt, kvbfp::query_row(a, b, kvh, a.g_base + g) * kD + src);
-            }
-            q_s[g][c] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
+        float* const raw = &o_s[0][0][0];           // [NH][kD], original channel order
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) {
+            const int i = tid + 256 * k;
+            const float f = dt == KVBFP_F32 ? __uint_as_float(q_bits[k]) : load_as_float(&q_bits[k], dt, 0);
+            raw[i] = i / kD < a.g_cnt ? f : 0.f;
         }
         lds_only_barrier();
+        float v[kQPerThread];
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) v[k] = raw[((tid + 256 * k) / kD) * kD + perm_c];
         if (a.q_mant_bits) {
-            bfp_round_queries(&q_s[0][0], (uint32_t*)&o_s[0][0][0], NH, a.log2_block, a.q_mant_bits);
-            for (int i = tid; i < NH * kD; i += 256) (&q_s[0][0])[i] = ((&q_s[0][0])[i] * a.scale_log2e) * two_k;
+            float* const cast = &o_s[1][0][0];      // [NH][kD], cache channel order
+#pragma unroll
+            for (int k = 0; k < kQPerThread; ++k) cast[tid + 256 * k] = v[k];
             lds_only_barrier();
+            bfp_round_queries(cast, (uint32_t*)&o_s[2][0][0], NH, a.log2_block, a.q_mant_bits);
+#pragma unroll
+            for (int k = 0; k < kQPerThread; ++k) v[k] = cast[tid + 256 * k];
         }
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) q_s[(tid + 256 * k) / kD][tid % kD] = (v[k] * a.scale_log2e) * two_k;
+        lds_only_barrier();
     }
 
     // A operands of the score product: row r = lane%16 = 4*head + limb, k-slot (kg, x) of MFMA d
@@ -208,10 +229,12 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg)
 #pragma unroll
-            for (int d = 0; d < 4; ++d)
+            for (int d = 0; d < 4; ++d) {
+                const f32x4 q0 = *(const f32x4*)&q_s[hg * 4 + gi][32 * kg + 8 * d], q1 = *(const f32x4*)&q_s[hg * 4 + gi][32 * kg + 8 * d + 4];
 #pragma unroll
                 for (int x = 0; x < 8; ++x) {
-                    const float f = q_s[hg * 4 + gi][32 * kg + 8 * d + slot_channel(x)];
+                    const int c = slot_channel(x);
+                    const float f = c < 4 ? q0[c & 3] : q1[c & 3];
                     const __bf16 l0 = (__bf16)f;
                     const float r1 = f - (float)l0;
                     const __bf16 l1 = (__bf16)r1;
@@ -219,6 +242,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
                     const __bf16 l2 = (__bf16)r2;
                     aq[hg][d][x] = limb == 0 ? l0 : (limb == 1 ? l1 : (limb == 2 ? l2 : (__bf16)0.0f));
                 }
+            }
     }
 
     // selectors that place a probability in the low (parity 0) or high (parity 1) half of an

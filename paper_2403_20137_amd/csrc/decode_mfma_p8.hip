@@ -80,7 +80,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
 void decode_split_mfma_p8(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
-    __shared__ float q_s[NH][kD];                               // scaled, permuted queries
+    constexpr int kQStride = kD + 4;                            // (four heads side by side are read from different banks)
+    __shared__ __align__(16) float q_s[NH][kQStride];           // scaled, permuted queries
     __shared__ __align__(16) uint16_t p_s[kWaves][HG][PL][4][kSuper];  // probabilities, bf16 limbs
     __shared__ float o_s[kWaves][NH][kD];                       // per-wavefront outputs for the merge
     __shared__ float ml_s[kWaves][NH][2];
@@ -216,18 +217,21 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
             raw[i] = i / kD < a.g_cnt ? f : 0.f;
         }
         lds_only_barrier();
+        float v[kQPerThread];
 #pragma unroll
-        for (int k = 0; k < kQPerThread; ++k) {
-            const int g = (tid + 256 * k) / kD;
-            const float v = raw[g * kD + perm_c];
-            q_s[g][tid % kD] = a.q_mant_bits ? v : (v * a.scale_log2e) * two_k;
-        }
-        lds_only_barrier();
+        for (int k = 0; k < kQPerThread; ++k) v[k] = raw[((tid + 256 * k) / kD) * kD + perm_c];
         if (a.q_mant_bits) {
-            bfp_round_queries(&q_s[0][0], (uint32_t*)&o_s[0][0][0], NH, a.log2_block, a.q_mant_bits);
-            for (int i = tid; i < NH * kD; i += 256) (&q_s[0][0])[i] = ((&q_s[0][0])[i] * a.scale_log2e) * two_k;
+            float* const cast = &o_s[1][0][0];      // [NH][kD], cache channel order
+#pragma unroll
+            for (int k = 0; k < kQPerThread; ++k) cast[tid + 256 * k] = v[k];
             lds_only_barrier();
+            bfp_round_queries(cast, (uint32_t*)&o_s[2][0][0], NH, a.log2_block, a.q_mant_bits);
+#pragma unroll
+            for (int k = 0; k < kQPerThread; ++k) v[k] = cast[tid + 256 * k];
         }
+#pragma unroll
+        for (int k = 0; k < kQPerThread; ++k) q_s[(tid + 256 * k) / kD][tid % kD] = (v[k] * a.scale_log2e) * two_k;
+        lds_only_barrier();
     }
 
     // A operands of the score product: row r = lane%16 = 4*head + limb; MFMA d (0..7) reduces over
@@ -239,10 +243,11 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg)
 #pragma unroll
-            for (int d = 0; d < 8; ++d)
+            for (int d = 0; d < 8; ++d) {
+                const f32x4 q4 = *(const f32x4*)&q_s[hg * 4 + gi][64 * (d >> 2) + 16 * kg + 4 * (d & 3)];
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    const float f = q_s[hg * 4 + gi][64 * (d >> 2) + 16 * kg + 4 * (d & 3) + x];
+                    const float f = q4[x];
                     const __bf16 l0 = (__bf16)f;
                     const float r1 = f - (float)l0;
                     const __bf16 l1 = (__bf16)r1;
@@ -252,6 +257,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
                     aq[hg][d][x] = v;
                     aq[hg][d][4 + x] = v;
                 }
+            }
     }
 
     // selectors that place a probability in the low (parity 0) or high (parity 1) half of an
