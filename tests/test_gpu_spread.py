@@ -8,11 +8,12 @@ import torch
 
 from test_gpu_attention import make_small, run_both
 from test_gpu_rope_at_read import run_both as run_rope
-from util import assert_attention_close, dev_i32, gpu_cache, rel_l2_per_head
+from util import assert_attention_close, dev_i32, gpu_cache, oracle_cache, rel_l2_per_head
 from oracle import kvbfp_oracle as O
 from paper_2403_20137_amd import kvbfp, synth
 
 pytestmark = pytest.mark.gpu
+D = 128
 
 
 def _lens(B, S, seed, long_only=False):
@@ -236,3 +237,28 @@ def test_a_query_that_is_not_a_number_stays_in_its_sequence(dtype, p, G, B, Hkv,
     keep = [b for b in range(B) if b != 1]
     assert torch.equal(got[keep], want[keep])
     assert bool((got[1].isnan() | (got[1] == 0)).all())
+
+
+@pytest.mark.parametrize("dt,p,B,rope", [("bf16", 4, 24, False), ("f32", 4, 24, False), ("bf16", 8, 16, False), ("f32", 8, 16, False), ("f16", 4, 16, True)])
+@pytest.mark.parametrize("given", [False, True])
+def test_five_tiles_where_four_splits_fit(dt, p, B, rope, given):
+    """Three splits of two, two and one tile take their place: whole tiles, one token in the last, none in it, none at all."""
+    Hkv, S, n = 8, 1200, 32
+    lens = np.resize(np.asarray([1200, 1025, 1024, 512, 1, 0, 769], np.int32), B) if given else np.full(B, S, np.int32)
+    torch_dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dt]
+    k, v = (synth.kv_rows(B, S, Hkv, D, dt, synth.outlier_gains(61, t, Hkv, D), 61, 2 + t) for t in (0, 1))
+    q = synth.queries(B, Hkv, D, dt, 61, 4)
+    planes = oracle_cache(k, v, n, p, S, 0)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    scale = float(np.float32(D ** -0.5))
+    lens_dev = dev_i32(lens) if given else None
+    if rope:
+        theta = (10000.0 ** (-np.arange(0, D, 2, dtype=np.float64) / D)).astype(np.float32)
+        r = kvbfp.permute_rope(theta, np.tile(np.arange(D, dtype=np.int32), (Hkv, 1)))
+        got = kvbfp.decode_attention_rope(cache, q.cuda(), S, scale, *(torch.as_tensor(np.ascontiguousarray(x)).cuda() for x in r), seq_len_dev=lens_dev)
+        want = O.decode_attention_rope(*planes, D, n, p, synth.to_f32_numpy(q), lens, scale, *r)
+    else:
+        got = kvbfp.decode_attention(cache, q.cuda(), S, scale, seq_len_dev=lens_dev)
+        want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), lens, scale)
+    torch.cuda.synchronize()
+    assert_attention_close(got, want, torch_dt, "%s p=%d B=%d" % (dt, p, B))
