@@ -144,9 +144,28 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;    // scalar: tile bases stay in SGPRs
     const int j = lane & 15, kg = lane >> 4;
+    const int kvh = blockIdx.y;
+    // what the set-up reads ahead of everything else but the lengths, before those have arrived: the query as it lies in memory, the
+    // vectors of this thread's channel (a load through the permutation would be one more round trip)
+    const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
+    const int my_c = tid & (kD - 1);
+    uint32_t q_bits[NH * kD / 256];
+    auto request_queries = [&](const int seq) {
+#pragma unroll
+        for (int k = 0; k < NH * kD / 256; ++k) {
+            const int g = (tid + 256 * k) / kD;
+            q_bits[k] = ((const uint16_t*)a.q)[kvbfp::query_row(a, seq, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + my_c];
+        }
+    };
+    request_queries(blockIdx.z);
+    const int perm_c = a.perm_k ? (a.perm_k[kvh * kD + my_c] & (kD - 1)) : my_c;       // masked: device data the host cannot check
+    const int partner_c = a.rope_partner[kvh * kD + my_c] & (kD - 1);
+    const float sign_c = a.rope_sign[kvh * kD + my_c], th = a.rope_theta[kvh * kD + my_c];
+    __builtin_amdgcn_sched_barrier(0);
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take(a, kvbfp::spans::request_lengths(a, gridDim.z), 8, span)) return;
-    const int split = span.split, kvh = blockIdx.y, b = span.b;
+    if (!kvbfp::spans::take(a, len0, 8, span)) return;
+    if (span.b != (int)blockIdx.z) request_queries(span.b);
+    const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;
 
     const int64_t L = span.L;
@@ -167,19 +186,24 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
     }
 
     // ---------------- set-up
-    for (int i = tid; i < NH * kD; i += 256) {
-        const int g = i / kD, c = i % kD;
-        float v = 0.f;
-        if (g < a.g_cnt) {
-            const int src = a.perm_k ? (a.perm_k[kvh * kD + c] & (kD - 1)) : c;
-            v = load_as_float(a.q, dt, kvbfp::query_row(a, b, kvh, a.g_base + g) * kD + src) * a.scale_log2e;
-        }
-        q1_s[g][c] = v;
+    float (*raw)[kD] = q2_s + NH;                                // [NH][kD], original channel order
+#pragma unroll
+    for (int k = 0; k < NH * kD / 256; ++k) {
+        const int g = (tid + 256 * k) / kD;
+        const float f = dt == KVBFP_F16 ? (float)__builtin_bit_cast(_Float16, (unsigned short)q_bits[k]) : __uint_as_float(q_bits[k] << 16);
+        raw[g][my_c] = g < a.g_cnt ? f : 0.f;
     }
     __syncthreads();
-    for (int i = tid; i < NH * kD; i += 256) {
-        const int g = i / kD, c = i % kD;
-        q2_s[g][c] = -a.rope_sign[kvh * kD + c] * q1_s[g][a.rope_partner[kvh * kD + c] & (kD - 1)];
+#pragma unroll
+    for (int k = 0; k < NH * kD / 256; ++k) {
+        const int g = (tid + 256 * k) / kD;
+        q1_s[g][my_c] = raw[g][perm_c] * a.scale_log2e;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NH * kD / 256; ++k) {
+        const int g = (tid + 256 * k) / kD;
+        q2_s[g][my_c] = -sign_c * q1_s[g][partner_c];
     }
     __syncthreads();
     {       // per (head, chunk): the power of two that brings |A1|, |A2| <= |q| + |q2| below 2^14; a wavefront per head, 16 lanes per chunk
@@ -205,15 +229,16 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
         sn = fmaf(rest, c0, sn);
     };
     float* const p16_s = (float*)&p_s[0][0][0][0];                  // [2][kD]: phasors of 16 tokens
-    static_assert(sizeof(p_s) >= 2 * kD * sizeof(float), "they fit");
+    float* const theta_s = p16_s + 2 * kD;                          // [kD]
+    static_assert(sizeof(p_s) >= 3 * kD * sizeof(float), "they fit");
     {       // In double precision, angles of up to 10^5: those of the wavefronts' first tiles, t_begin + 64 w, by one half of the
             // threads, the latter three as products, that of the step from tile to tile by the other.
-        const int c = tid & (kD - 1), at = slot_index(c);
-        const float th = a.rope_theta[kvh * kD + c];
+        const int c = my_c, at = slot_index(c);
         const bool first = tid < kD;
         double sn, cs;
         sincos((double)(first ? t_begin : tile_step) * (double)th, &sn, &cs);
         if (first) {
+            theta_s[c] = th;
             double s64, c64;
             sincos((double)kSuper * (double)th, &s64, &c64);
 #pragma unroll
@@ -238,11 +263,8 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
         float cs[4], sn[4];
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {                       // (four channels at a time: the code of four sine/cosine pairs is enough)
-            float th[4];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) th[x] = a.rope_theta[kvh * kD + 8 * group + 2 * x + half];      // slot 4 half + x
-#pragma unroll
-            for (int x = 0; x < 4; ++x) phasor((float)t, th[x], cs[x], sn[x]);
+            for (int x = 0; x < 4; ++x) phasor((float)t, theta_s[8 * group + 2 * x + half], cs[x], sn[x]);      // slot 4 half + x
             u32x2* const at = (u32x2*)tab_raw + (size_t)(((group >> 2) * 4 * 4 + (group & 3)) * 4 * 16 + t) * 2 + half;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {                            // tau = t + 16 i
