@@ -135,9 +135,10 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     // 16u + 4kg + i, each with its exponent bytes.  The rows of the wavefront's next tile are requested as soon as these are
     // used up, keys before the softmax and values at the end of a tile, and those of the first tile before the set-up
     // (which waits for LDS only): a round trip to memory takes longer than the arithmetic of a tile.  4 x 8192 tokens, 8
-    // kv-heads, blocks of 16, fp32 I/O: a call takes 22.2 us, with every tile's rows requested when they are needed 32.6;
-    // 10 x 8000 tokens, blocks of 32 35.3 against 55.1 (2.5 TB/s).  168 registers keep three workgroups per compute unit; 6 to 9
-    // more are spilled in regions with blocks of 16 to 64 (loop invariants, the figures above are with them).
+    // kv-heads, blocks of 16, fp32 I/O: a call took 22.2 us with it, 32.6 with every tile's rows requested when they are needed (20.2 now,
+    // with the query ahead of the rows and two tiles for every split); 10 x 8000 tokens, blocks of 32 35.3 against 55.1 (2.5 TB/s).
+    // 168 registers keep three workgroups per compute unit; 8 to 12 more are spilled in regions with blocks of 16 to 64 (loop
+    // invariants, the figures above are with them).
     struct Rows {
         u32x4 k[4];
         uint32_t ke[4], v[4][4], ve[4][N == 128 ? 1 : 4];      // (one exponent a row: that of row 16u + j, handed over where it is used)
