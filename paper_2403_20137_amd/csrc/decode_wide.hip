@@ -13,8 +13,9 @@
 //     of the wavefront, and the registers that hold S^T are, converted, the second operand of the value product -- the
 //     order of the tokens in its reduction is free, and V^T is laid out in LDS in the order S^T leaves them in.
 //   * The query is not rounded: a bf16 query (or one cast to BFP) is one bf16 operand, an fp16 query is two (8 + 3
-//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads keep all of their 24 bits, as
-//     two binary16 limbs where the exponents of the cached values allow it and three bf16 ones elsewhere; up to 32 heads they
+//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads keep 24 bits: as two binary16
+//     limbs where the exponents of the cached values allow it (those below 2^-11 of the reference 2^-36 of it, absolutely, less
+//     than the rounding of the sums they go into), as three bf16 ones elsewhere; up to 32 heads they
 //     are two bf16 limbs (16 bits), as in the other passes for 16-bit I/O.
 // Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 48 MFMAs of 32 cycles and
 // some 430 vector instructions of 4 cycles, 32 exponentials of 8 among them).  256 virtual heads (64 query tokens, groups of
@@ -51,9 +52,10 @@ constexpr int kThreads = 256;
 constexpr int kRows = 32;                      // virtual heads per wavefront
 constexpr uint32_t kKeyUp = 2;                 // decode_split_few: added to the keys' exponent bytes
 // The sums are relative to a reference that a score may exceed by kSlack before they are rescaled (a branch and 64 products nearly
-// every tile otherwise), so a sum of weighted values may be 2^kSlack above the values: not for values with a byte above kOrdinary.
+// every tile otherwise), so a sum of weighted values may be 2^kSlack above what it is with the largest score as the reference: not for
+// values with a byte above kOrdinary, whose sum over all tokens a sequence can have would not fit fp32 with that.
 constexpr float kSlack = 4.f;
-constexpr int kOrdinary = 240;
+constexpr int kOrdinary = 200;
 
 // packs the upper halves of two fp32 patterns: (lo, hi) -> one register of two bf16
 __device__ __forceinline__ uint32_t pack_hi(uint32_t lo, uint32_t hi) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }

@@ -334,3 +334,25 @@ def test_exponents_that_leave_the_range_of_the_first_tile(dt, p, n, G):
         for b in range(B):
             if fits[b].any():
                 assert_attention_close(g[b, fits[b]], w[b, fits[b]], DT[dt], "sequence %d" % b)
+
+
+@pytest.mark.parametrize("p,top", [(4, 240), (8, 240), (4, 201)])
+@pytest.mark.parametrize("G", [12, 40])
+def test_sums_of_large_values_while_the_scores_rise(p, top, G):
+    """4096 tokens of one weight, near what their sum can be in fp32, behind some whose scores are 3.5 powers of two lower: the
+    reference of the sums may not be the one of those."""
+    B, Hkv, S, n = 64, 4, 4096, 32
+    layout = kvbfp.make_layout(D, n, p, Hkv, B, S)
+    cache = kvbfp.alloc_cache(layout, "cuda", fill=0)
+    one, seven = (0x11, 0x77) if p == 4 else (0x10, 0x70)
+    cache.k_mant[:, :, 256:] = one
+    cache.k_exp[:] = 129
+    cache.v_mant[:] = seven
+    cache.v_exp[:] = top
+    key = 1.0 if p == 4 else 2.0 ** -4 * 16             # a code times 2^(129 - 127 - (p - 2))
+    value = 7.0 * 2.0 ** (top - 129) if p == 4 else 112.0 * 2.0 ** (top - 133)
+    assert S * value < 2.0 ** 128
+    q = torch.ones((B, Hkv * G, D), dtype=torch.bfloat16, device="cuda")
+    got = kvbfp.decode_attention(cache, q, S, float(np.float32(3.5 / (D * key * np.log2(np.e)))))
+    torch.cuda.synchronize()
+    assert bool((got.double() / value - 1).abs().max() < 2.0 ** -8)
