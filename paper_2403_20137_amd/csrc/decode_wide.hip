@@ -13,15 +13,14 @@
 //     of the wavefront, and the registers that hold S^T are, converted, the second operand of the value product -- the
 //     order of the tokens in its reduction is free, and V^T is laid out in LDS in the order S^T leaves them in.
 //   * The query is not rounded: a bf16 query (or one cast to BFP) is one bf16 operand, an fp16 query is two (8 + 3
-//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads keep 24 bits: as two binary16
-//     limbs where the exponents of the cached values allow it (those below 2^-11 of the reference 2^-36 of it, absolutely, less
-//     than the rounding of the sums they go into), as three bf16 ones elsewhere; up to 32 heads they
-//     are two bf16 limbs (16 bits), as in the other passes for 16-bit I/O.
-// Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 48 MFMAs of 32 cycles and
-// some 430 vector instructions of 4 cycles, 32 exponentials of 8 among them).  256 virtual heads (64 query tokens, groups of
-// 4) over 4 x 8192 tokens x 8 kv-heads: 66 us a call (79 with three bf16 limbs and one half of LDS, fp16 I/O 77 and 123; 1490 in the
-// general pass).  Every instruction left out counts: without the value products 11 us less, without those for the scores 8,
-// without decoding 8, without exponentials 4.  Requesting the rows two tiles ahead changed nothing (70.3, 70.5 us).
+//     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads are three bf16 limbs, all of
+//     their 24 bits; up to 32 two (16 bits), as in the other passes for 16-bit I/O.  (Not two binary16 limbs, which take two thirds
+//     of the matrix instructions and a third of the vector instructions, 256 heads below 67 us: they have an absolute step, 2^-36 of
+//     the largest probability, and where the heaviest token's values are zero the output is the sum of the light ones alone.)
+// Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 64 MFMAs of 32 cycles and
+// some 530 vector instructions of 4 cycles, 32 exponentials of 8 among them).  256 virtual heads (64 query tokens, groups of
+// 4) over 4 x 8192 tokens x 8 kv-heads: 76 us a call, fp16 I/O 86 (80 and 125 with one half of LDS, decoding and products one after
+// the other; 1490 in the general pass).
 // Up to 32 heads: vector ALUs 70 % busy (490 instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us a
 // call, against 66 us in two launches.
 #include <hip/hip_runtime.h>
@@ -30,6 +29,7 @@
 #include <cmath>
 #include <cstdint>
 #include <type_traits>
+#include <utility>
 
 #include "decode_args.h"
 #include "decode_dev.h"
@@ -45,8 +45,6 @@ using namespace kvbfp::dev;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kThreads = 256;
 constexpr int kRows = 32;                      // virtual heads per wavefront
@@ -84,24 +82,6 @@ __device__ __forceinline__ void unpack4_p8(uint32_t w, uint32_t field, float (&x
     x[0] = h01[0] + l01[0]; x[1] = h01[1] + l01[1];
     x[2] = h23[0] + l23[0]; x[3] = h23[1] + l23[1];
 }
-// The same codes -> binary16, times 2^(field - 136): the field in the exponent bits of `scale`, and the sum of the two pieces of
-// an 8-bit code formed in binary16 (8 significant bits).
-__device__ __forceinline__ void unpack8_p4_f16(uint32_t w, float scale, uint32_t (&p)[4]) {
-    const uint32_t lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);
-    const uint32_t hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);
-    p[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, false));
-    p[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, true));
-    p[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, scale, false));
-    p[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, scale, true));
-}
-__device__ __forceinline__ void unpack4_p8_f16(uint32_t w, float scale, uint32_t& p01, uint32_t& p23) {
-    const float up = __uint_as_float(__float_as_uint(scale) + (3u << 23));
-    const uint32_t hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u), lo = w & 0x87878787u;
-    const f16x2 a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, up, false), b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, up, true);
-    const f16x2 c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, false), d = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, true);
-    p01 = __builtin_bit_cast(uint32_t, a + c);
-    p23 = __builtin_bit_cast(uint32_t, b + d);
-}
 
 // Exponent bytes at the ends of their range.  The conversions take the byte as their scale operand, which fits all but the
 // largest ones, and leave value * 2^-kShift in bf16, which holds all but the smallest blocks exactly.  A 16-token stage with
@@ -121,15 +101,16 @@ __device__ __forceinline__ uint32_t raise_pair(uint32_t w, bool lo, bool hi) {
     return w + (lo && (w & 0x7FFFu) ? 8u << 7 : 0u) + (hi && (w & 0x7FFF0000u) ? 8u << 23 : 0u);
 }
 
+// f(0) .. f(N - 1), the argument a constant of the type's (arrays it indexes stay in registers)
+template <class F, int... I>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for(std::make_integer_sequence<int, N>{}, f); }
+
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32); }
 __device__ __forceinline__ float both_halves_max(float v) {
     const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(x[0]), __uint_as_float(x[1]));
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int d = 1; d < 64; d *= 2) v = max(v, (uint32_t)__shfl_xor((int)v, d));
-    return v;
 }
 
 // The query operand: lane (head l32, half), MFMA m: the 8 channels of group `group(m, half)`, in key slot order, QL bf16
@@ -328,14 +309,9 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
 // grid = (n_splits, H_kv * row_tiles, B), block = 256; a workgroup takes the heads of `groups` (<= RG) groups of 32,
 // and every n_splits-th tile of TT tokens.
 //
-// Two loops.  The first one is for cached values whose exponent bytes lie within kSpanDown below and kSpanUp above the
-// largest byte of the workgroup's first tile (`ref`), which is what they do in earnest: a value is then an integer code times a
-// power of two that binary16 holds exactly relative to that byte, and a probability is two binary16 limbs, rounded to nearest:
-// 24 bits, as three bf16 limbs carry, in two thirds of the matrix instructions and a third of the vector instructions.  The
-// first tile with a byte elsewhere (or a key block whose byte the conversion cannot take as it is) ends it, for good: the sums are
-// brought to their own scale and the second loop goes on in bf16, which holds every exponent.
-// The first loop decodes the next tile into the other half of the LDS while it multiplies with this one, so that the vector
-// instructions of one wavefront fill the time of its own matrix instructions.
+// The next tile is decoded into the other half of the LDS while this one is multiplied with, and the next probabilities are formed
+// between the value products, so that the vector instructions of a wavefront fill the time of its own matrix instructions.
+// Registers: with fp16 queries and more than 64 heads 1 (8 bits: 4) of them is spilled.
 template <int P, bool N16, int RG, int QL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float score_mul, float query_mul) {
@@ -346,10 +322,8 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     constexpr int kRowB = kD * P / 8;
     constexpr int kKeyChunks = P == 4 ? 1 : 2;         // 16-byte chunks of a key row per thread and pass
     constexpr int kValWords = P == 4 ? 1 : 2;          // dwords (8 channels) of a value row per thread
-    // binary16: a code of byte E is m 2^(kUnit + E - ref); at most 127 2^(2 + 6) or 7 2^(6 + 6), exact down to 2^-22
-    constexpr int kUnit = P == 4 ? 6 : 2, kSpanUp = 6, kSpanDown = 24;
-    // probabilities carry 2^kProb: at most 2^(kProb + kSlack), and what is below 2^-25 is lost, 2^-36 of the reference
-    constexpr float kProb = 11.f;
+    // marks of a stage of 16 tokens: keys, values raised by kUp; a value byte above kOrdinary
+    constexpr uint32_t kKeysUp = 1, kValuesUp = 2, kLarge = 4;
     constexpr int kKeyBytes = TT * 256, kValBytes = kD * TT * 2, kTileBytes = kKeyBytes + kValBytes;
     constexpr int kOStride = kD + 4;
     constexpr int kMerge = TG > 1 ? 2 * kRows * kOStride * 4 : 0;          // two wavefronts' outputs
@@ -359,9 +333,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     __shared__ __align__(1024) uint8_t smem_odd[kSmem];
     __shared__ float ml_s[TG > 1 ? 4 * kRows * 2 : 1];
     __shared__ int perm_s[kD];
-    __shared__ uint32_t modes_s;                       // second loop: the tile's 16-token stages, one byte each: bit 0 keys, bit 4 values raised by kUp
-    __shared__ uint32_t beyond_s[2];                   // first loop: not 0 where the tile in that half ends it
-    __shared__ uint32_t ref_s[4];
+    __shared__ uint32_t marks_s[2];                    // of the tile in either half of the LDS: its four stages, one byte each
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -391,7 +363,6 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
 
     QueryRows<RG * kRows> query;
     query.request(a, b, kvh, s_first, s_count);
-    if (tid < 2) beyond_s[tid] = 0;
 
     // ---- packed rows of one tile, as loaded: this wavefront's 16 tokens
     const int log2_nb = 7 - a.log2_block;              // exponent bytes per row
@@ -457,13 +428,14 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     // step n, block of channels ct: ^ 32 (n ^ 2 (ct & 1)) ^ 128 (ct >> 1), + 4096 ct
     uint32_t val_get = kKeyBytes + l32 * 128 + (((4 * tg * (CB & 1) + half) ^ (l32 & 7) ^ (l32 >> 3)) * 16);
     // keys to bf16 in LDS, a quarter of what this lane holds of them
-    auto decode_keys = [&](const Raw& r, uint8_t* const tile, const int d) {
+    auto decode_keys = [&](const Raw& r, uint8_t* const tile, auto quarter) {
+        constexpr int d = decltype(quarter)::value;
         if constexpr (P == 4) {
             uint32_t q[4];
             unpack8_p4(r.k[0][d], __uint_as_float(key_byte(r, d >> 1) << 23), q);
             *(u32x4*)(tile + (key_put ^ (16 * d))) = u32x4{q[0], q[1], q[2], q[3]};
         } else {
-            const int i = (d >> 1) * (kKeyChunks - 1), e = d & 1;
+            constexpr int i = (d >> 1) * (kKeyChunks - 1), e = d & 1;
             float x[4], y[4];
             unpack4_p8(r.k[i][2 * e], r.ke[i] << 23, x);
             unpack4_p8(r.k[i][2 * e + 1], r.ke[i] << 23, y);
@@ -515,21 +487,19 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         bf16x8 ka[2][CB];
         auto read = [&](const int m) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                ka[m & 1][cb] = *(const bf16x8*)(tile + (key_get ^ (32 * m)) + 8192 * cb);
-            }
+            for (int cb = 0; cb < CB; ++cb) ka[m & 1][cb] = *(const bf16x8*)(tile + (key_get ^ (32 * m)) + 8192 * cb);
         };
         read(0);
-#pragma unroll
-        for (int m = 0; m < 8; ++m) {
+        static_for<8>([&](auto at) {
+            constexpr int m = decltype(at)::value;
             if (m < 7) read(m + 1);
 #pragma unroll
             for (int l = 0; l < QL; ++l)
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) s[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[m & 1][cb], q_op[l][m], s[cb], 0, 0, 0);
-            meanwhile(m);
+            meanwhile(at);
             __builtin_amdgcn_sched_barrier(0);
-        }
+        });
     };
     auto hide = [&](const int64_t T0, f32x16 (&s)[CB]) {           // what a head must not see
         const int sees = (int)min((int64_t)TT, max((int64_t)0, lim - T0)) - my_tok0 - 4 * half;
@@ -549,296 +519,185 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     };
 
     int64_t T0 = t_first;
-    int back;                                                      // the first loop's sums are 2^-back of the true ones
-    {
-        // ---- first loop: values in binary16 relative to `ref`
-        uint32_t top = wave_max_u32(max(max(raw.ve[0], raw.ve[1]), max(raw.ve[2], raw.ve[3])));
-        if (lane == 0) ref_s[wave] = top;
-        lds_only_barrier();
-        top = max(max(ref_s[0], ref_s[1]), max(ref_s[2], ref_s[3]));
-        const int ref = __builtin_amdgcn_readfirstlane((int)(top ? top : 127u));
-        back = ref - kUnit - 127 - (P - 2) - (int)kProb;
-        const int lo = ref - kSpanDown;                            // (bytes below it: all-zero blocks only)
-        const int to_field = 127 + 9 + kUnit - ref;                // a code is the FP8 number m 2^-9
-        float minus_one = -1.f;
-        asm volatile("" : "+s"(minus_one));                        // (a product for the compiler: v_fma_mix takes the binary16 number as it is)
-        // the tile's values as they are decoded: by pair of channels and token
-        struct Values { uint32_t q[4][4]; };
-        // pieces 0-3: keys, 4-7: values
-        auto decode = [&](const Raw& r, uint8_t* const tile, Values& v, const int piece) {
-            if (piece < 4) {
-                decode_keys(r, tile, piece);
-                return;
-            }
-            const int i = piece - 4;
-            const float field = __uint_as_float((uint32_t)(max((int)r.ve[i], lo) + to_field) << 23);
+    // A tile's exponent bytes, made operands of the conversions in place (see ExpRange), and what its stage is marked with.  Returns this
+    // lane's blocks that were converted at kDown fewer: keys bits 0, 1, values 4 + token.
+    auto mark = [&](Raw& r, const int at) -> uint32_t {
+        using R = ExpRange<P>;
+        const uint32_t ke[2] = {key_byte(r, 0), key_byte(r, 1)};
+        const uint32_t v_top = max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3])), top = max(v_top, max(ke[0], ke[1]));
+        const uint32_t low = min(min(min(r.ve[0], r.ve[1]), min(r.ve[2], r.ve[3])), min(ke[0], ke[1]));
+        uint32_t marks = 0, raise = 0;                 // marks: wave-uniform
+        if (__builtin_amdgcn_ballot_w64(top > (uint32_t)kOrdinary || low <= 2u) != 0) {      // (also where a block is all zero)
+            const uint32_t up_k = __builtin_amdgcn_ballot_w64(R::tiny(ke[0]) || R::tiny(ke[1])) != 0 ? R::kUp : 0;
+            const uint32_t up_v = __builtin_amdgcn_ballot_w64(R::tiny(r.ve[0]) || R::tiny(r.ve[1]) || R::tiny(r.ve[2]) || R::tiny(r.ve[3])) != 0 ? R::kUp : 0;
+            marks = (up_k ? kKeysUp : 0u) | (up_v ? kValuesUp : 0u) | (__builtin_amdgcn_ballot_w64(v_top > (uint32_t)kOrdinary) != 0 ? kLarge : 0u);
+            raise = (R::high(ke[0], up_k) ? 1u : 0u) | (R::high(ke[1], up_k) ? 2u : 0u);
             if constexpr (P == 4) {
-                unpack8_p4_f16(r.v[i][0], field, v.q[i]);
+                r.ke[0] = N16 ? (R::operand(ke[0], up_k) | (R::operand(ke[1], up_k) << 8)) : R::operand(ke[0], up_k);
             } else {
-                unpack4_p8_f16(r.v[i][0], field, v.q[i][0], v.q[i][1]);
-                unpack4_p8_f16(r.v[i][kValWords - 1], field, v.q[i][2], v.q[i][3]);
+                r.ke[0] = R::operand(ke[0], up_k);
+                r.ke[1] = R::operand(ke[1], up_k);
             }
-        };
-        auto store_values = [&](uint8_t* const tile, const Values& v) {
-            if constexpr (P == 4) {
-                put_pairs(tile, v.q);
-            } else {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    put(tile, 2 * c, pack_lo(v.q[0][c], v.q[1][c]), pack_lo(v.q[2][c], v.q[3][c]));
-                    put(tile, 2 * c + 1, pack_hi(v.q[0][c], v.q[1][c]), pack_hi(v.q[2][c], v.q[3][c]));
-                }
+            for (int i = 0; i < 4; ++i) {
+                raise |= R::high(r.ve[i], up_v) ? 16u << i : 0u;
+                r.ve[i] = R::operand(r.ve[i], up_v);
             }
-        };
-        auto check = [&](const Raw& r, const int at) {
-            // zero bytes (all-zero blocks) are below everything and above nothing once 1 is subtracted
-            const uint32_t v_low = min(min(r.ve[0] - 1u, r.ve[1] - 1u), min(r.ve[2] - 1u, r.ve[3] - 1u));
-            const int v_top = (int)max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3]));
-            const uint32_t k_low = min(key_byte(r, 0) - 1u, key_byte(r, 1) - 1u), k_top = max(key_byte(r, 0), key_byte(r, 1));
-            const bool beyond = v_low < (uint32_t)max(lo - 1, 0) || v_top > min(ref + kSpanUp, kOrdinary) || k_low < 2u || k_top > ExpRange<P>::kTop;
-            if (__builtin_amdgcn_ballot_w64(beyond) != 0 && lane == 0) beyond_s[at] = 1;
-        };
-        auto decode_all = [&](const Raw& r, uint8_t* const tile, const int at) {
-            Values v;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) decode(r, tile, v, i);
-            store_values(tile, v);
-            check(r, at);
-        };
-        // sums relative to m_run; a score may exceed it by kSlack
-        auto raise = [&](const float tmax) {
-            if (__builtin_amdgcn_ballot_w64(tmax > m_run + kSlack) != 0) {
-                const float m_new = fmaxf(m_run, tmax);
-                const float alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
-                l_run *= alpha;
-                m_run = m_new;
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
-            }
-        };
-        auto products = [&](const uint8_t* const tile, f32x16 (&s)[CB]) {
-            const float m_p = (m_run == -INFINITY ? 0.f : m_run) - kProb;
-            float psum = 0.f;
-            u32x4 hi[2], low[2];
-            f16x8 va[4];
-            // two of the eight probabilities of step n (16 tokens)
-            auto limbs = [&](const int n, const int j) {
-                const float x = exp2_raw(fmaf(s[n >> 1][8 * (n & 1) + 2 * j], mul, -m_p));
-                const float y = exp2_raw(fmaf(s[n >> 1][8 * (n & 1) + 2 * j + 1], mul, -m_p));
-                psum += x;
-                psum += y;
-                const f16x2 h = __builtin_convertvector((f32x2{x, y}), f16x2);
-                const f32x2 rest = {fmaf((float)h[0], minus_one, x), fmaf((float)h[1], minus_one, y)};
-                hi[n & 1][j] = __builtin_bit_cast(uint32_t, h);
-                low[n & 1][j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, f16x2));
-            };
-            auto read = [&](const int n, const int ct) {
-                va[ct] = *(const f16x8*)(tile + value_get(n, ct));
-            };
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) read(0, ct);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) limbs(0, j);
-#pragma unroll
-            for (int n = 0; n < 2 * CB; ++n) {
-                const f16x8 ph = __builtin_bit_cast(f16x8, hi[n & 1]), pr = __builtin_bit_cast(f16x8, low[n & 1]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {      // two products, and vector instructions of the next step for their time
-                    const int ct = j & 2;
-                    o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[ct], (j & 1) ? pr : ph, o[ct], 0, 0, 0);
-                    o[ct + 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(va[ct + 1], (j & 1) ? pr : ph, o[ct + 1], 0, 0, 0);
-                    if (n + 1 < 2 * CB) {
-                        if (j & 1) {
-                            read(n + 1, ct);
-                            read(n + 1, ct + 1);
-                        }
-                        limbs(n + 1, j);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            l_run += psum;
-        };
-
-        decode_all(raw, smem, 0);
-        if (T0 + step < L) fetch(T0 + step, raw);
-        // One tile from half AT of the LDS, the next one decoded into the other.  False: the loop ends here.
-        auto tile_of = [&](auto AT) -> bool {
-            constexpr int at = decltype(AT)::value;
-            uint8_t* const tile = at ? smem_odd : smem;
-            uint8_t* const next = at ? smem : smem_odd;
-            asm volatile("" : "+v"(key_put), "+v"(val_put), "+v"(key_get), "+v"(val_get));
-            lds_only_barrier();
-            if (T0 >= L || __builtin_amdgcn_readfirstlane(beyond_s[at]) != 0) return false;
-            if (active) {
-                f32x16 s[CB];
-                Values v;
-                scores(tile, s, [&](const int m) { decode(raw, next, v, m); });    // (behind the last tile: once more what it holds, for nobody)
-                store_values(next, v);
-                check(raw, at ^ 1);
-                if (T0 + 2 * step < L) fetch(T0 + 2 * step, raw);
-                if (T0 + TT > all_see) hide(T0, s);
-                raise(largest(s));
-                products(tile, s);
-            } else if (T0 + step < L) {
-                decode_all(raw, next, at ^ 1);
-                if (T0 + 2 * step < L) fetch(T0 + 2 * step, raw);
-            }
-            T0 += step;
-            return true;
-        };
-        while (tile_of(std::integral_constant<int, 0>{}) && tile_of(std::integral_constant<int, 1>{})) {}
-        if (T0 < L) {                                              // the sums at their own scale, with the second loop's 2^kShift
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[ct][i] = ldexpf(o[ct][i], back);
-            l_run *= exp2f((float)kShift - kProb);
-            back = 0;
+        }
+        if (lane == 0) ((uint8_t*)&marks_s[at])[wave] = (uint8_t)marks;
+        return raise;
+    };
+    // A quarter of the keys (pieces 0-3) or values (4-7) to bf16 in LDS.  Values wait in q for the rest of their words: 4 bits,
+    // pairs of channels by token, stored by finish(); 8 bits, channels of tokens 0 and 1 of a word, stored with those of tokens 2 and 3.
+    struct Values {
+        uint32_t q[4][P == 4 ? 4 : 1];
+        u32x4 two;
+    };
+    auto decode = [&](const Raw& r, uint8_t* const tile, Values& v, auto part) {
+        constexpr int piece = decltype(part)::value;
+        if constexpr (piece < 4) {
+            decode_keys(r, tile, part);
+        } else if constexpr (P == 4) {
+            unpack8_p4(r.v[piece - 4][0], __uint_as_float(r.ve[piece - 4] << 23), v.q[piece - 4]);
         } else {
-            l_run *= exp2f(-kProb);
+            constexpr int w = (piece - 4) >> 1, h = (piece - 4) & 1;
+            float x[4], y[4];
+            unpack4_p8(r.v[2 * h][w], r.ve[2 * h] << 23, x);
+            unpack4_p8(r.v[2 * h + 1][w], r.ve[2 * h + 1] << 23, y);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t two = pack_hi(__float_as_uint(x[c]), __float_as_uint(y[c]));
+                if constexpr (h == 0) v.two[c] = two;
+                else put(tile, 4 * w + c, v.two[c], two);
+            }
         }
-    }
-    if (T0 < L) {
-        // ---- second loop: any exponent byte, everything in bf16
-        auto decode = [&](Raw& r) {
-            using R = ExpRange<P>;
-            const uint32_t ke[2] = {key_byte(r, 0), key_byte(r, 1)};
-            const uint32_t top = max(max(max(r.ve[0], r.ve[1]), max(r.ve[2], r.ve[3])), max(ke[0], ke[1]));
-            const uint32_t low = min(min(min(r.ve[0], r.ve[1]), min(r.ve[2], r.ve[3])), min(ke[0], ke[1]));
-            uint32_t up_k = 0, up_v = 0;                   // wave-uniform
-            uint32_t raise = 0;                            // this lane's blocks converted at kDown fewer: keys bits 0, 1, values 4 + token
-            if (__builtin_amdgcn_ballot_w64(top > R::kTop || low <= 2u) != 0) {     // (also where a block is all zero)
-                up_k = __builtin_amdgcn_ballot_w64(R::tiny(ke[0]) || R::tiny(ke[1])) != 0 ? R::kUp : 0;
-                up_v = __builtin_amdgcn_ballot_w64(R::tiny(r.ve[0]) || R::tiny(r.ve[1]) || R::tiny(r.ve[2]) || R::tiny(r.ve[3])) != 0 ? R::kUp : 0;
-                raise = (R::high(ke[0], up_k) ? 1u : 0u) | (R::high(ke[1], up_k) ? 2u : 0u);
-                if constexpr (P == 4) {
-                    r.ke[0] = N16 ? (R::operand(ke[0], up_k) | (R::operand(ke[1], up_k) << 8)) : R::operand(ke[0], up_k);
-                } else {
-                    r.ke[0] = R::operand(ke[0], up_k);
-                    r.ke[1] = R::operand(ke[1], up_k);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    raise |= R::high(r.ve[i], up_v) ? 16u << i : 0u;
-                    r.ve[i] = R::operand(r.ve[i], up_v);
-                }
-            }
-            if (lane == 0) ((uint8_t*)&modes_s)[wave] = (uint8_t)((up_k ? 1u : 0u) | (up_v ? 16u : 0u));
-#pragma unroll
-            for (int d = 0; d < 4; ++d) decode_keys(r, smem, d);
-            if constexpr (P == 4) {
-                uint32_t q[4][4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) unpack8_p4(r.v[i][0], __uint_as_float(r.ve[i] << 23), q[i]);
-                put_pairs(smem, q);
-            } else {
-#pragma unroll
-                for (int w = 0; w < kValWords; ++w) {
-                    float x[4][4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) unpack4_p8(r.v[i][w], r.ve[i] << 23, x[i]);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        put(smem, 4 * w + c, pack_hi(__float_as_uint(x[0][c]), __float_as_uint(x[1][c])), pack_hi(__float_as_uint(x[2][c]), __float_as_uint(x[3][c])));
-                }
-            }
-            if (__builtin_amdgcn_ballot_w64(raise != 0) != 0) {        // what this lane wrote above
+    };
+    auto finish = [&](uint8_t* const tile, const Values& v, const uint32_t raise) {
+        if constexpr (P == 4) put_pairs(tile, v.q);
+        if (__builtin_amdgcn_ballot_w64(raise != 0) != 0) {        // what this lane wrote
 #pragma unroll 1
-                for (int g = 0; g < 4; ++g) {
-                    const bool up = (raise >> (g >> 1)) & 1u;
-                    u32x4* const at = (u32x4*)(smem + (key_put ^ (16 * (P == 4 ? g : 8 * (g >> 1) + (g & 1)))));
-                    const u32x4 w = *at;
-                    *at = u32x4{raise_pair(w[0], up, up), raise_pair(w[1], up, up), raise_pair(w[2], up, up), raise_pair(w[3], up, up)};
-                }
-#pragma unroll 1
-                for (int c = 0; c < 8; ++c) {
-                    u32x2* const at = (u32x2*)(smem + (val_put ^ (144 * c)));
-                    const u32x2 w = *at;
-                    *at = u32x2{raise_pair(w[0], raise & 16u, raise & 32u), raise_pair(w[1], raise & 64u, raise & 128u)};
-                }
+            for (int g = 0; g < 4; ++g) {
+                const bool up = (raise >> (g >> 1)) & 1u;
+                u32x4* const at = (u32x4*)(tile + (key_put ^ (16 * (P == 4 ? g : 8 * (g >> 1) + (g & 1)))));
+                const u32x4 w = *at;
+                *at = u32x4{raise_pair(w[0], up, up), raise_pair(w[1], up, up), raise_pair(w[2], up, up), raise_pair(w[3], up, up)};
             }
+#pragma unroll 1
+            for (int c = 0; c < 8; ++c) {
+                u32x2* const at = (u32x2*)(tile + (val_put ^ (144 * c)));
+                const u32x2 w = *at;
+                *at = u32x2{raise_pair(w[0], raise & 16u, raise & 32u), raise_pair(w[1], raise & 64u, raise & 128u)};
+            }
+        }
+    };
+    auto decode_all = [&](Raw& r, uint8_t* const tile, const int at) {
+        const uint32_t raise = mark(r, at);
+        Values v;
+        static_for<8>([&](auto i) { decode(r, tile, v, i); });
+        finish(tile, v, raise);
+    };
+    // sums relative to m_run; a score may exceed it by `slack`
+    auto raise_reference = [&](const float tmax, const float slack) {
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run + slack) != 0) {
+            const float m_new = fmaxf(m_run, tmax);
+            const float alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
+            l_run *= alpha;
+            m_run = m_new;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+        }
+    };
+    // O^T += V^T P^T, 16 tokens a step.  A probability is three bf16 limbs, all of its 24 bits at every size (a token whose values
+    // are zero takes any weight, and what is left is the sum of the others).
+    auto products = [&](const uint8_t* const tile, f32x16 (&s)[CB], const uint32_t marks) {
+        const float m_p = (m_run == -INFINITY ? 0.f : m_run) - (float)kShift;      // probabilities carry 2^kShift
+        u32x4 limb[2][3];
+        bf16x8 va[4];
+        float psum = 0.f;
+        // of step n: values of a stage that was raised by kUp take probabilities that are lower by as much
+        auto up_of = [&](const int n) { return (marks >> (8 * (my_tok0 / 16 + n))) & kValuesUp; };
+        float part, m_n;
+        // two of the eight probabilities of step n
+        auto limbs = [&](const int n, const int j) {
+            if (j == 0) {
+                part = 0.f;
+                m_n = m_p + (up_of(n) ? (float)ExpRange<P>::kUp : 0.f);
+            }
+            float x = exp2_raw(fmaf(s[n >> 1][8 * (n & 1) + 2 * j], mul, -m_n));
+            float y = exp2_raw(fmaf(s[n >> 1][8 * (n & 1) + 2 * j + 1], mul, -m_n));
+            part += x;
+            part += y;
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                limb[n & 1][l][j] = pack_hi(__float_as_uint(x), __float_as_uint(y));
+                x -= __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
+                y -= __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
+            }
+            if (j == 3) psum = fmaf(part, up_of(n) ? (float)(1 << ExpRange<P>::kUp) : 1.f, psum);
         };
-        lds_only_barrier();                                        // every wavefront has left the first loop
-#pragma unroll 1
-        for (; T0 < L; T0 += step) {
-            fetch(T0, raw);
-            decode(raw);
-            lds_only_barrier();
-            if (active) {
-                f32x16 s[CB];
-                scores(smem, s, [](int) {});
-                const uint32_t modes = __builtin_amdgcn_readfirstlane(modes_s);
-                // of the stage of 16 tokens this register's token lies in
-                auto mode_at = [&](int cb, int i) { return modes >> (8 * (my_tok0 / 16 + 2 * cb + (i >> 3))); };
-                if (modes != 0) {
+        auto read = [&](const int n, const int ct) { va[ct] = *(const bf16x8*)(tile + value_get(n, ct)); };
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
+        for (int ct = 0; ct < 4; ++ct) read(0, ct);
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) s[cb][i] *= (mode_at(cb, i) & 1u) ? 0.25f : 1.f;
+        for (int j = 0; j < 4; ++j) limbs(0, j);
+#pragma unroll
+        for (int n = 0; n < 2 * CB; ++n) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {          // three products of a pair of blocks of channels, and vector instructions of the next step for their time
+#pragma unroll
+                for (int k = 3 * (j & 1); k < 3 * (j & 1) + 3; ++k) {
+                    const int ct = (j & 2) + (k & 1);
+                    o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ct], __builtin_bit_cast(bf16x8, limb[n & 1][k >> 1]), o[ct], 0, 0, 0);
                 }
-                if (T0 + TT > all_see) hide(T0, s);
-                // ---- online softmax, base 2
-                const float m_new = fmaxf(m_run, largest(s));
-                const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-                const float alpha = exp2_raw(m_run - m_ref);
-                const float m_p = m_ref - (float)kShift;               // probabilities carry 2^kShift
-                float psum = 0.f;
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        s[cb][i] = exp2_raw(fmaf(s[cb][i], mul, -m_p));
-                        psum += s[cb][i];
+                if (n + 1 < 2 * CB) {
+                    if (j & 1) {
+                        read(n + 1, j & 2);
+                        read(n + 1, (j & 2) + 1);
                     }
-                if (modes != 0) {
-#pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) s[cb][i] *= (mode_at(cb, i) & 16u) ? 0.25f : 1.f;
+                    limbs(n + 1, j);
                 }
-                l_run = l_run * alpha + psum;
-                m_run = m_new;
-                if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-                    for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
-                }
-                // ---- O^T += V^T P^T
-#pragma unroll
-                for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk) {
-                        // three bf16 limbs of 8 bits each: the probability as it is
-                        u32x4 limb[3];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            float x = s[cb][8 * kk + 2 * j], y = s[cb][8 * kk + 2 * j + 1];
-#pragma unroll
-                            for (int l = 0; l < 3; ++l) {
-                                limb[l][j] = pack_hi(__float_as_uint(x), __float_as_uint(y));
-                                x -= __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
-                                y -= __uint_as_float(__float_as_uint(y) & 0xFFFF0000u);
-                            }
-                        }
-#pragma unroll
-                        for (int ct = 0; ct < 4; ++ct) {
-                            const bf16x8 va = *(const bf16x8*)(smem + value_get(2 * cb + kk, ct));
-#pragma unroll
-                            for (int l = 0; l < 3; ++l)
-                                o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, limb[l]), o[ct], 0, 0, 0);
-                        }
-                    }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            lds_only_barrier();                                        // the next tile overwrites this one
         }
-        l_run *= 1.0f / (float)(1 << kShift);
-    } else {
+        l_run += psum;
+    };
+
+    decode_all(raw, smem, 0);
+    if (T0 + step < L) fetch(T0 + step, raw);
+    // One tile from half AT of the LDS, the next one decoded into the other.  False: there is none.
+    auto tile_of = [&](auto AT) -> bool {
+        constexpr int at = decltype(AT)::value;
+        uint8_t* const tile = at ? smem_odd : smem;
+        uint8_t* const next = at ? smem : smem_odd;
+        asm volatile("" : "+v"(key_put), "+v"(val_put), "+v"(key_get), "+v"(val_get));
+        lds_only_barrier();
+        if (T0 >= L) return false;
+        if (active) {
+            const uint32_t marks = __builtin_amdgcn_readfirstlane(marks_s[at]);
+            f32x16 s[CB];
+            Values v;
+            const uint32_t raise = mark(raw, at ^ 1);
+            scores(tile, s, [&](auto m) { decode(raw, next, v, m); });    // (behind the last tile: once more what it holds, for nobody)
+            finish(next, v, raise);
+            if (T0 + 2 * step < L) fetch(T0 + 2 * step, raw);
+            if (marks & (0x01010101u * kKeysUp)) {                 // of the stage of 16 tokens a register's token lies in
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
+                for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) o[ct][i] = ldexpf(o[ct][i], back);
-        lds_only_barrier();                                        // the merge reuses the tiles
-    }
+                    for (int i = 0; i < 16; ++i) s[cb][i] *= ((marks >> (8 * (my_tok0 / 16 + 2 * cb + (i >> 3)))) & kKeysUp) ? 0.25f : 1.f;
+            }
+            if (T0 + TT > all_see) hide(T0, s);
+            raise_reference(largest(s), (marks & (0x01010101u * kLarge)) ? 0.f : kSlack);
+            products(tile, s, marks);
+        } else if (T0 + step < L) {
+            decode_all(raw, next, at ^ 1);
+            if (T0 + 2 * step < L) fetch(T0 + 2 * step, raw);
+        }
+        T0 += step;
+        return true;
+    };
+    while (tile_of(std::integral_constant<int, 0>{}) && tile_of(std::integral_constant<int, 1>{})) {}
+    l_run *= 1.0f / (float)(1 << kShift);
     l_run += other_half(l_run);
 
     // ---- partial result of this split: registers 4i .. 4i+3 of block ct are channels 32 ct + 8 i + 4 half ..

@@ -356,3 +356,50 @@ def test_sums_of_large_values_while_the_scores_rise(p, top, G):
     got = kvbfp.decode_attention(cache, q, S, float(np.float32(3.5 / (D * key * np.log2(np.e)))))
     torch.cuda.synchronize()
     assert bool((got.double() / value - 1).abs().max() < 2.0 ** -8)
+
+
+@pytest.mark.parametrize("heavy", ["zero row", "zero channels", "small blocks"])
+@pytest.mark.parametrize("gap", [20.3, 30.7, 40.2])
+@pytest.mark.parametrize("p,n,G", [(4, 16, 40), (4, 32, 100), (8, 32, 40), (8, 64, 100)])
+def test_light_tokens_beside_a_heavy_one_above_32_heads(p, n, G, gap, heavy):
+    """One token's score is `gap` powers of two above the others and its value row holds nothing, nothing in every other channel,
+    or blocks 2^24 below the others': what the light tokens sum to there keeps the bits of an fp32 sum.  The one split's
+    partial results, compared by channel with what weights off by 40 * 2^-24 times a few (the rounding of a score) make of
+    the sum of the magnitudes."""
+    B, Hkv, S = 128, 4, 300                             # 512 units: one split
+    rng = np.random.default_rng(int(gap * 10) + p + G)
+    ms, es = O.plane_shapes(1, 1, D, n, p, S)
+    km, ke, vm, ve = np.zeros(ms, np.uint8), np.full(es, 127, np.uint8), np.zeros(ms, np.uint8), np.full(es, 127, np.uint8)
+    one = 0x11 if p == 4 else 0x10
+    km[0, 0, :, :2] = rng.integers(0, 256, (S, 2)) & (0x33 if p == 4 else 0x1F)      # light scores a little apart
+    vm[:] = rng.integers(0, 256, ms)
+    ve[:] = 127 + rng.integers(-3, 4, es)
+    km[0, 0, 3] = one
+    if heavy == "zero row":
+        vm[0, 0, 3], ve[0, 0, 3] = 0, 0
+    elif heavy == "zero channels":
+        if p == 4:
+            vm[0, 0, 3] &= 0xF0
+        else:
+            vm[0, 0, 3, ::2] = 0
+    else:
+        vm[0, 0, 3], ve[0, 0, 3] = one, 127 - 24
+    planes = [km, ke, vm, ve]
+    cache = kvbfp.alloc_cache(kvbfp.make_layout(D, n, p, Hkv, B, S), "cuda", fill=0)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w).expand(t.shape))
+    q = (1 + 0.1 * torch.rand((1, Hkv * G, D), generator=torch.Generator().manual_seed(3))).bfloat16()
+    scale = float(np.float32(gap / (1.05 * D * 0.25 * np.log2(np.e))))           # a code of one is 2^-2
+    Hq = Hkv * G
+    ws = torch.zeros((max(kvbfp.decode_workspace_bytes(cache.layout, Hq, S), B * Hq * (D + 2) * 4),), dtype=torch.uint8, device="cuda")
+    kvbfp.decode_attention(cache, q.expand(B, Hq, D).contiguous().cuda(), S, scale, workspace=ws)
+    torch.cuda.synchronize()
+    f = ws.view(torch.float32)
+    po, ml = f[:B * Hq * D].view(B, Hq, D), f[B * Hq * D:B * Hq * (D + 2)].view(B, Hq, 2)
+    assert torch.equal(po[:1].expand_as(po)[..., :G, :], po[..., :G, :])
+    got = (po[-1, :G].double() / ml[-1, :G, 1:].double()).cpu().numpy()
+    qf = synth.to_f32_numpy(q[:, :G])
+    want = O.decode_attention(*planes, D, n, p, qf, [S], scale)[0]
+    size = O.decode_attention(km, ke, vm & (0x77 if p == 4 else 0x7F), ve, D, n, p, qf, [S], scale)[0]
+    err = np.abs(got - want) / np.where(size > 0, size, 1)
+    assert err.max() <= 2e-5, (err.max(), np.unravel_index(err.argmax(), err.shape))
