@@ -50,8 +50,10 @@ constexpr int kThreads = 256;
 constexpr int kRows = 32;                      // virtual heads per wavefront
 constexpr uint32_t kKeyUp = 2;                 // decode_split_few: added to the keys' exponent bytes
 // The sums are relative to a reference that a score may exceed by kSlack before they are rescaled (a branch and 64 products nearly
-// every tile otherwise), so a sum of weighted values may be 2^kSlack above what it is with the largest score as the reference: not for
-// values with a byte above kOrdinary, whose sum over all tokens a sequence can have would not fit fp32 with that.
+// every tile otherwise), so a sum of weighted values may be 2^kSlack above what it is with the largest score as the reference.  Values
+// with bytes up to kOrdinary bear that with room to spare (those up to 218 would: below 2^92 each, times 2^kSlack, times the
+// 2^31 tokens a sequence can have at most, is below 2^128).  From the first larger byte on a wavefront's reference is its largest score,
+// and what wavefronts and workgroups hand on is relative to that in any case.
 constexpr float kSlack = 4.f;
 constexpr int kOrdinary = 200;
 
@@ -255,10 +257,11 @@ __device__ __forceinline__ void append_row(const DecodeArgs& a, int dt, int b, i
 }
 
 // Merges the 4 / RG wavefronts that hold the same heads over different tokens (wavefront w: heads 32 (w % RG) ..) and
-// writes this split's partial result for `count` heads from head `h` on.  LDS: o_s, o_s2 [2][32][kD + 4] floats each, ml_s [4][32][2].
+// writes this split's partial result for `count` heads from head `h` on.  LDS: o_s, o_s2 [2][32][kD + 4] floats each, ml_s [4][32][3].
+// The sums are relative to m_run, what is written to the largest score, m_top.
 template <int RG>
 __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::spans::Span& span, int h, int count, float* o_s, float* o_s2, float* ml_s,
-                                            int wave, int lane, const f32x16 (&o)[4], float m_run, float l_run) {
+                                            int wave, int lane, const f32x16 (&o)[4], float m_run, float m_top, float l_run) {
     constexpr int kOStride = kD + 4;
     const int half = lane >> 5, l32 = lane & 31;
     auto row_of = [&](int w, int r) { return (w < 2 ? o_s : o_s2) + ((w & 1) * kRows + r) * kOStride; };
@@ -268,8 +271,9 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
         for (int i = 0; i < 4; ++i)
             *(f32x4*)(row_of(wave, l32) + 32 * ct + 8 * i + 4 * half) = f32x4{o[ct][4 * i], o[ct][4 * i + 1], o[ct][4 * i + 2], o[ct][4 * i + 3]};
     if (half == 0) {
-        ml_s[(wave * kRows + l32) * 2] = m_run;
-        ml_s[(wave * kRows + l32) * 2 + 1] = l_run;
+        ml_s[(wave * kRows + l32) * 3] = m_run;
+        ml_s[(wave * kRows + l32) * 3 + 1] = l_run;
+        ml_s[(wave * kRows + l32) * 3 + 2] = m_top;
     }
     lds_only_barrier();
     // four channels per thread (a head's weights are worked out once for them): 64 heads over 300 tokens 21.4 us a call with
@@ -280,8 +284,8 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
         float m[4 / RG], M = -INFINITY;
 #pragma unroll
         for (int t = 0; t < 4 / RG; ++t) {
-            m[t] = ml_s[((w0 + t * RG) * kRows + r) * 2];
-            M = fmaxf(M, m[t]);
+            m[t] = ml_s[((w0 + t * RG) * kRows + r) * 3];
+            M = fmaxf(M, ml_s[((w0 + t * RG) * kRows + r) * 3 + 2]);
         }
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         float lsum = 0.f;
@@ -292,7 +296,7 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
                 const f32x4 x = *(const f32x4*)(row_of(w0 + t * RG, r) + c);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) acc[k] = fmaf(f, x[k], acc[k]);
-                lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 2 + 1], lsum);
+                lsum = fmaf(f, ml_s[((w0 + t * RG) * kRows + r) * 3 + 1], lsum);
             }
         }
         *(f32x4*)(a.part_o + span.row(h + g) * kD + c) = acc;
@@ -311,7 +315,7 @@ __device__ __forceinline__ void merge_waves(const DecodeArgs& a, const kvbfp::sp
 //
 // The next tile is decoded into the other half of the LDS while this one is multiplied with, and the next probabilities are formed
 // between the value products, so that the vector instructions of a wavefront fill the time of its own matrix instructions.
-// Registers: with fp16 queries and more than 64 heads 1 (8 bits: 4) of them is spilled.
+// Registers: with 8-bit mantissas, fp16 queries and more than 64 heads 4 of them are spilled.
 template <int P, bool N16, int RG, int QL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float score_mul, float query_mul) {
@@ -331,7 +335,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     static_assert(RG * kRows * 256 <= kSmem, "the raw queries of the set-up fit");
     __shared__ __align__(1024) uint8_t smem[kSmem];    // (two arrays: the compiler then knows that what it writes to one is not read from the other)
     __shared__ __align__(1024) uint8_t smem_odd[kSmem];
-    __shared__ float ml_s[TG > 1 ? 4 * kRows * 2 : 1];
+    __shared__ float ml_s[TG > 1 ? 4 * kRows * 3 : 1];
     __shared__ int perm_s[kD];
     __shared__ uint32_t marks_s[2];                    // of the tile in either half of the LDS: its four stages, one byte each
 
@@ -374,9 +378,6 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
     };
     const int k_tok = lane >> 2, k_chunk = lane & 3;   // keys: token of the stage, 16-byte chunk (8-bit: and chunk + 4)
     const int v_quad = lane >> 4, v_word = lane & 15;  // values: tokens 4 v_quad .. + 3, channels 8 v_word .. + 7
-    const uint32_t ke_at0 = P == 4 ? (uint32_t)((32 * k_chunk) >> a.log2_block) : (uint32_t)((16 * k_chunk) >> a.log2_block);
-    const uint32_t ke_at1 = P == 4 ? ke_at0 + 1 : (uint32_t)((64 + 16 * k_chunk) >> a.log2_block);
-    const uint32_t ve_at = (uint32_t)((8 * v_word) >> a.log2_block);
     auto fetch = [&](const int64_t T0, Raw& r) {
         int64_t st = T0 + 16 * wave;               // first token of the stage, wave-uniform
         if (st >= L) st = (L - 1) & ~(int64_t)15;  // beyond the end: rows that are not used
@@ -386,10 +387,18 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         const uint8_t* __restrict__ vm = a.v_mant + row0 * kRowB;
         const uint8_t* __restrict__ kx = a.k_exp + (row0 << log2_nb);
         const uint8_t* __restrict__ vx = a.v_exp + (row0 << log2_nb);
-        const uint32_t kr = (uint32_t)min(k_tok, last);
+        // what follows from the lane is worked out here each time: held through the loop, it spills with two limbs of the query, and
+        // the requests then wait for it (256 heads, fp16 I/O, 4 x 8192 tokens: 92 us a call)
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        const int chunk = l & 3, word = l & 15;
+        const uint32_t ke_at0 = (uint32_t)((P == 4 ? 32 : 16) * chunk) >> a.log2_block;
+        const uint32_t ke_at1 = (uint32_t)(64 + 16 * chunk) >> a.log2_block;        // (8 bits)
+        const uint32_t ve_at = (uint32_t)(8 * word) >> a.log2_block;
+        const uint32_t kr = (uint32_t)min(l >> 2, last);
 #pragma unroll
         for (int i = 0; i < kKeyChunks; ++i)
-            r.k[i] = __builtin_nontemporal_load((const u32x4*)(km + (kr * kRowB + k_chunk * 16 + i * 64)));
+            r.k[i] = __builtin_nontemporal_load((const u32x4*)(km + (kr * kRowB + chunk * 16 + i * 64)));
         if (P == 4 && N16) {
             r.ke[0] = *(const uint16_t*)(kx + ((kr << log2_nb) + ke_at0));
         } else {
@@ -398,11 +407,11 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t vr = (uint32_t)min(4 * v_quad + i, last);
+            const uint32_t vr = (uint32_t)min(4 * (l >> 4) + i, last);
             if constexpr (P == 4) {
-                r.v[i][0] = __builtin_nontemporal_load((const uint32_t*)(vm + (vr * kRowB + v_word * 4)));
+                r.v[i][0] = __builtin_nontemporal_load((const uint32_t*)(vm + (vr * kRowB + word * 4)));
             } else {
-                const u32x2 w = __builtin_nontemporal_load((const u32x2*)(vm + (vr * kRowB + v_word * 8)));
+                const u32x2 w = __builtin_nontemporal_load((const u32x2*)(vm + (vr * kRowB + word * 8)));
                 r.v[i][0] = w[0];
                 r.v[i][kValWords - 1] = w[1];
             }
@@ -596,13 +605,16 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         static_for<8>([&](auto i) { decode(r, tile, v, i); });
         finish(tile, v, raise);
     };
-    // sums relative to m_run; a score may exceed it by `slack`
-    auto raise_reference = [&](const float tmax, const float slack) {
-        if (__builtin_amdgcn_ballot_w64(tmax > m_run + slack) != 0) {
-            const float m_new = fmaxf(m_run, tmax);
-            const float alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
+    // sums relative to m_run; the largest score may exceed it by kSlack
+    float m_top = -INFINITY;
+    uint32_t seen = 0;                                             // marks of the tiles so far
+    auto raise_reference = [&](const float tmax, const uint32_t marks) {
+        m_top = fmaxf(m_top, tmax);
+        seen |= marks;
+        if (__builtin_amdgcn_ballot_w64(m_top > m_run + ((seen & (0x01010101u * kLarge)) ? 0.f : kSlack)) != 0) {
+            const float alpha = exp2_raw(m_run - (m_top == -INFINITY ? 0.f : m_top));
             l_run *= alpha;
-            m_run = m_new;
+            m_run = m_top;
 #pragma unroll
             for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
         }
@@ -687,7 +699,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
                     for (int i = 0; i < 16; ++i) s[cb][i] *= ((marks >> (8 * (my_tok0 / 16 + 2 * cb + (i >> 3)))) & kKeysUp) ? 0.25f : 1.f;
             }
             if (T0 + TT > all_see) hide(T0, s);
-            raise_reference(largest(s), (marks & (0x01010101u * kLarge)) ? 0.f : kSlack);
+            raise_reference(largest(s), marks);
             products(tile, s, marks);
         } else if (T0 + step < L) {
             decode_all(raw, next, at ^ 1);
@@ -697,6 +709,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
         return true;
     };
     while (tile_of(std::integral_constant<int, 0>{}) && tile_of(std::integral_constant<int, 1>{})) {}
+    if constexpr (TG == 1) raise_reference(-INFINITY, kLarge);     // (the merge of wavefronts does it otherwise)
     l_run *= 1.0f / (float)(1 << kShift);
     l_run += other_half(l_run);
 
@@ -715,7 +728,7 @@ void decode_split_wide(DecodeArgs a, int dt, int row_tiles, int groups, float sc
             ml[1] = l_run;
         }
     } else {       // merge the wavefronts that shared the tokens
-        merge_waves<RG>(a, span, h0 + s_first, s_count, (float*)smem, (float*)smem_odd, ml_s, wave, lane, o, m_run, l_run);
+        merge_waves<RG>(a, span, h0 + s_first, s_count, (float*)smem, (float*)smem_odd, ml_s, wave, lane, o, m_run, m_top, l_run);
     }
 }
 
@@ -736,7 +749,7 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
     constexpr int kValWords = P / 4;                   // dwords (8 channels) of a value row per lane
     constexpr int TT = 32;                             // tokens per wavefront and tile
     constexpr int kOStride = kD + 4;
-    constexpr int kMerge = 4 * kRows * kOStride * 4 + 4 * kRows * 2 * 4;
+    constexpr int kMerge = 4 * kRows * kOStride * 4 + 4 * kRows * 3 * 4;
     __shared__ __align__(16) uint8_t smem[kMerge];     // queries, then the transposed values (8 KB per wavefront), then the merge
     __shared__ int perm_s[kD];
 
@@ -868,13 +881,23 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) o[ct][i] = 0.f;
 
+    float m_top = -INFINITY, slack = kSlack;                       // 4 bits: see kSlack
+    auto raise_reference = [&] {
+        if (__builtin_amdgcn_ballot_w64(m_top > m_run + slack) != 0) {
+            const float alpha = exp2_raw(m_run - (m_top == -INFINITY ? 0.f : m_top));
+            l_run *= alpha;
+            m_run = m_top;
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
+        }
+    };
     auto tile = [&](const int64_t T0, Raw& r) {
         uint32_t v_top = 0;
 #pragma unroll
         for (int st = 0; st < 2; ++st)
 #pragma unroll
             for (int i = 0; i < 4; ++i) v_top = max(v_top, r.ve[st][i]);
-        const float slack = __builtin_amdgcn_ballot_w64(v_top > kOrdinary) != 0 ? 0.f : kSlack;
+        if (__builtin_amdgcn_ballot_w64(v_top > kOrdinary) != 0) slack = 0.f;
         // ---- values to LDS, the four tokens of a quad side by side per channel; quads 0 and 2 of a stage make its first 16
         // bytes, 1 and 3 the second (the order in which S^T leaves the tokens)
 #pragma unroll
@@ -958,15 +981,8 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
         float alpha = 1.f;
         if constexpr (P == 4) {
-            tmax = both_halves_max(tmax) * mul;              // -inf only if this head sees none of the tile
-            if (__builtin_amdgcn_ballot_w64(tmax > m_run + slack) != 0) {
-                const float m_new = fmaxf(m_run, tmax);
-                alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
-                l_run *= alpha;
-                m_run = m_new;
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) o[ct] *= alpha;
-            }
+            m_top = fmaxf(m_top, both_halves_max(tmax) * mul);         // -inf only if this head has seen no token
+            raise_reference();
         } else {                                             // (bound by memory: the branch there costs as much as it saves)
             tmax = fmaxf(tmax, other_half(tmax)) * mul;
             const float m_new = fmaxf(m_run, tmax);
@@ -1024,11 +1040,12 @@ void decode_split_few(DecodeArgs a, int dt, float score_mul, float query_mul) {
         for (int d = 0; d < kDepth; ++d)
             if (T0 + d * step < L) tile(T0 + d * step, raw[d]);
     }
+    if constexpr (P == 8) m_top = m_run;
     l_run = (l_run + other_half(l_run)) * (1.0f / (float)(1 << kShift));
 
     // ---- merge the four wavefronts
     lds_only_barrier();
-    merge_waves<1>(a, span, h0, a.G, (float*)smem, (float*)smem + 2 * kRows * kOStride, (float*)smem + 4 * kRows * kOStride, wave, lane, o, m_run, l_run);
+    merge_waves<1>(a, span, h0, a.G, (float*)smem, (float*)smem + 2 * kRows * kOStride, (float*)smem + 4 * kRows * kOStride, wave, lane, o, m_run, m_top, l_run);
 }
 
 template <int P, bool N16, int RG>

@@ -340,7 +340,8 @@ def test_exponents_that_leave_the_range_of_the_first_tile(dt, p, n, G):
 @pytest.mark.parametrize("G", [12, 40])
 def test_sums_of_large_values_while_the_scores_rise(p, top, G):
     """4096 tokens of one weight, near what their sum can be in fp32, behind some whose scores are 3.5 powers of two lower: the
-    reference of the sums may not be the one of those."""
+    reference of the sums may not be the one of those.  (Byte 201 is the first on that path; its sums would fit either way.  12 heads
+    with 8 bits rescale at every new maximum.)"""
     B, Hkv, S, n = 64, 4, 4096, 32
     layout = kvbfp.make_layout(D, n, p, Hkv, B, S)
     cache = kvbfp.alloc_cache(layout, "cuda", fill=0)
@@ -403,3 +404,41 @@ def test_light_tokens_beside_a_heavy_one_above_32_heads(p, n, G, gap, heavy):
     size = O.decode_attention(km, ke, vm & (0x77 if p == 4 else 0x7F), ve, D, n, p, qf, [S], scale)[0]
     err = np.abs(got - want) / np.where(size > 0, size, 1)
     assert err.max() <= 2e-5, (err.max(), np.unravel_index(err.argmax(), err.shape))
+
+
+# (tiles of (score in units of 3.5 powers of two, large values) per quarter of a tile; splits)
+@pytest.mark.parametrize("name,tiles,splits", [
+    ("large values behind a rise", [[(0, 0)] * 4, [(1, 0)] * 4, [(0, 1)] * 4], 1),
+    ("large values ahead of a rise", [[(0, 1)] * 4, [(1, 0)] * 4], 1),
+    ("a rise in another wavefront", [[(0, 1)] * 3 + [(0, 0)], [(-7, 0)] * 3 + [(1, 0)]], 1),
+    ("a rise in another split", [[(0, 1)] * 4] * 3 + [[(0, 0)] * 4] + [[(-7, 0)] * 4] * 11 + [[(1, 0)] * 4], 4),
+])
+@pytest.mark.parametrize("p,G", [(4, 12), (8, 12), (4, 40), (8, 40), (4, 100), (8, 100)])
+def test_sums_of_large_values_where_the_scores_rose(p, G, name, tiles, splits):
+    """Sums of values near the end of fp32 relative to the largest score so far fit; relative to one 3.5 powers of two lower they do
+    not, in a wavefront, in the merge of its workgroup or in that of the splits."""
+    TT = 128 if G <= 32 else 64
+    B, Hkv, S, n = 512 // splits // 4, 4, TT * len(tiles), 32
+    # as many as a wavefront (where all four hold values, its sum alone fits) or a split has: 7 2^(byte - 129) each, below 2^128 in all
+    together = TT if splits > 1 or G > 64 else 32
+    byte = 254 - int(np.log2(together))
+    ms, es = O.plane_shapes(1, 1, D, n, p, S)
+    km, ke, vm, ve = np.zeros(ms, np.uint8), np.full(es, 127, np.uint8), np.zeros(ms, np.uint8), np.full(es, 127, np.uint8)
+    codes = {0: 0, 1: 0x11, -7: 0xFF} if p == 4 else {0: 0, 1: 0x10, -7: 0xF0}
+    for i, tile in enumerate(tiles):
+        for j, (score, large) in enumerate(tile):
+            part = slice(i * TT + j * TT // 4, i * TT + (j + 1) * TT // 4)
+            km[0, 0, part] = codes[score]
+            vm[0, 0, part] = 0x77 if p == 4 else 0x70
+            ve[0, 0, part] = byte if large else 127
+    planes = [km, ke, vm, ve]
+    cache = kvbfp.alloc_cache(kvbfp.make_layout(D, n, p, Hkv, B, S), "cuda", fill=0)
+    for t, w in zip(cache.planes(), planes):
+        t.copy_(torch.from_numpy(w).expand(t.shape))
+    q = torch.ones((B, Hkv * G, D), dtype=torch.bfloat16)
+    scale = float(np.float32(3.5 / (D * 0.25 * np.log2(np.e))))                  # a code of one is 2^-2
+    got = kvbfp.decode_attention(cache, q.cuda(), S, scale)
+    torch.cuda.synchronize()
+    want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q[:1, :1]), [S], scale)[0, 0, 0]
+    assert 2.0 ** 100 < want < 2.0 ** 127
+    assert bool((got.double() / want - 1).abs().max() < 2.0 ** -8), (name, float(got.double().max()), want)
