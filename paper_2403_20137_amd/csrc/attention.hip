@@ -745,11 +745,19 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     }
     // Where up to half of the splits would take a second tile, all take two instead and there are fewer of them (to set up, to run
     // beside each other and to merge).  8 kv-heads, one call, as many splits as fit -> two tiles each: fp32 4 x 8192 tokens (24 splits for 32
-    // tiles) 22.0 -> 20.6 us, 6 x 5000 25.5 -> 21.3; 4 bits 6 x 5000 16.5 -> 14.7, 1 x 30000 16.4 -> 15.4, 8 bits 2 x 9000 17.9 ->
-    // 17.3; with more than half no more: 4 bits 8 x 5000 (12 splits for 20) 16.6 -> 17.1, 8 bits 32 kv-heads 1 x 7500 (16 for 30) 17.1 -> 18.0.
-    if ((fast && !wide) || rope_fast) {
-        const int64_t tiles = (max_len + 255) / 256;
-        if (sp.n_splits < tiles && 2 * tiles <= 3 * (int64_t)sp.n_splits) sp.n_splits = (int32_t)((tiles + 1) / 2);
+    // tiles) 21.9 -> 20.5 us, 6 x 5000 25.5 -> 21.3; 4 bits 6 x 5000 17.1 -> 15.2, 1 x 30000 16.8 -> 15.9, 8 bits 2 x 9000 18.4 ->
+    // 17.8; with more than half no more: 4 bits 8 x 5000 (12 splits for 20) 16.6 -> 17.1, 8 bits 32 kv-heads 1 x 7500 (16 for 30) 17.1 -> 18.0;
+    // nor with the rotation: 4 x 5600 23.5 and 23.3, 6 x 3000 21.1 -> 22.8.
+    // Lengths on the device may be anything up to max_len.  Of 0.6 to 0.8 of it the fewer splits take two tiles where the others took
+    // one: 8 bits 2 x 9000 15.7 -> 17.6, 8 heads 8 x 2500 18.8 -> 21.8, fp32 8 heads 4 x 5600 19.4 -> 22.9.  So 8 bits keep
+    // their splits there, and fp32 I/O with 4 bits launches them all and decides by the length of each sequence (4 x 8192: 20.9 where they are max_len,
+    // 18.6 against 20.5 at 0.6; 6 x 5000, whose 6 idle splits of 16 leave some of the dies with less work than others, 24.8).  16-bit I/O with 4 bits
+    // goes by max_len: 3 % less to 7 % more at 0.6 to 0.8 (32 kv-heads 2 x 4000 12.7 -> 13.2, 16-token pages 2 x 15000 16.1 -> 17.1), 4 to
+    // 14 % less at max_len, 20 % less to 8 % more below a half.
+    if (fast && !wide) {
+        const int32_t paired = kvbfp::spans::paired_splits(sp.n_splits, (max_len + 255) / 256);
+        if (!seq_len_dev || (L->mant_bits == 4 && dtype != KVBFP_F32)) sp.n_splits = paired;
+        else if (L->mant_bits == 4 && paired != sp.n_splits) a.direct = kvbfp::kPaired;
     }
     a.n_splits = sp.n_splits;
     // by the lengths where there are any (not in the general pass) and the workspace has room for the table
@@ -761,7 +769,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // One split: nothing to merge, the split pass writes the output itself and the combine pass is not launched: an appended
     // step over 250 tokens 15.6 -> 8.2 us, 128 sequences x 1000 tokens (1024 units) 36.6 -> 33.0 us.  (Not in the passes for
     // many heads: their merge has no registers to spare, 20 heads over 12000 tokens 44.7 -> 45.7 us with the branch in it.)
-    a.direct = sp.n_splits == 1 && (rope_fast || (fast && !wide));
+    if (sp.n_splits == 1 && (rope_fast || (fast && !wide))) a.direct = 1;
     a.part_ml = a.part_o + (size_t)L->batch * n_q_heads * sp.n_splits * kD;
     const dim3 grid1((unsigned)sp.n_splits, (unsigned)(a.H_kv * gg), (unsigned)L->batch);
     a.g_base = 0;
@@ -835,7 +843,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         launch_split();
     }
     if (kernel_ms) (void)hipEventRecord(ev[1], s);
-    for (int r = 0; r < reps && err == hipSuccess && !a.direct; ++r) {
+    for (int r = 0; r < reps && err == hipSuccess && a.direct != 1; ++r) {
         // few (batch, head) pairs with many splits: 32 channels per workgroup (16 slices x 8 loads cover 128 splits)
         if (sp.n_splits > 32 && (int64_t)n_q_heads * L->batch < 256) {
             const dim3 grid2((unsigned)n_q_heads, (unsigned)L->batch, kD / 32);

@@ -9,6 +9,9 @@ namespace kvbfp {
 
 constexpr int kMaxShared = 768;      // sequences: with more of them there is one split
 
+constexpr int kPaired = 2;           // value of DecodeArgs::direct (a field of its own would put the last argument of the launches
+                                     // into one more cache line: 1.5 % of the shortest calls)
+
 struct DecodeArgs {
     const uint8_t* k_mant;
     const uint8_t* k_exp;
@@ -30,7 +33,8 @@ struct DecodeArgs {
     // s of a kv-head is query token s / real_G, real head kvh * real_G + s % real_G, and may attend
     // to n_q_tokens - 1 - s / real_G tokens fewer than the sequence holds (causal order of the new tokens).
     int32_t H_kv, H_q, G, n_splits, log2_block;
-    int32_t direct;           // 1: one split and no combine pass, the split pass writes the output itself
+    int32_t direct;           // 1: one split and no combine pass, the split pass writes the output itself; kPaired (register-staged
+                              // pass for 4-bit mantissas only): a sequence takes two tiles a split where paired_splits() says so
     int32_t share_above;      // not 0: where the lengths differ and a sequence has more tiles than this, the n_splits * B
                               // workgroups of a kv-head are shared out by them (decode_spans.h)
     int32_t n_q_tokens, real_Hq, real_G;

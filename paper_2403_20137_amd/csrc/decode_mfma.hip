@@ -89,7 +89,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     const int j = lane & 15, kg = lane >> 4;
     const int len0 = SHARE ? kvbfp::spans::request_lengths(a, gridDim.z) : 0;
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take<SHARE>(a, len0, 8, span)) return;
+    if (!kvbfp::spans::take<SHARE, true>(a, len0, 8, span)) return;
     const int split = span.split, kvh = blockIdx.y, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
@@ -101,7 +101,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 
     if (t_begin >= t_end) {   // nothing cached in this split
         for (int i = tid; i < a.g_cnt * kD; i += 256) {
-            if (!SHARE && a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+            if (!SHARE && a.direct == 1) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
         if (tid < a.g_cnt) {
@@ -414,7 +414,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             const float mw = ml_s[w][g][0];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[w][g][c], acc);
         }
-        if (!SHARE && a.direct) {
+        if (!SHARE && a.direct == 1) {
             float den = 0.f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w)
@@ -424,7 +424,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             a.part_o[span.row(h0 + g) * kD + c] = acc;
         }
     }
-    if ((SHARE || !a.direct) && tid < a.g_cnt) {
+    if ((SHARE || a.direct != 1) && tid < a.g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll

@@ -90,8 +90,21 @@ __device__ __forceinline__ float inverse_share(const DecodeArgs& a, const int (&
     return inv0 * __builtin_amdgcn_exp2f((float)hi * -0.0625f);
 }
 
+// Where up to half of the splits would take a second tile, all take two instead and there are fewer of them: how many, for a
+// sequence of so many tiles (when, and the figures: attention.hip).
+__host__ __device__ __forceinline__ int paired_splits(int n, int64_t tiles) {
+    return n < tiles && 2 * tiles <= 3 * (int64_t)n ? (int)((tiles + 1) / 2) : n;
+}
+// The same by the actual length (kPaired): the grid has all splits, and those that are not needed have nothing to do.
+__device__ __forceinline__ void pair_up(const DecodeArgs& a, int log2_tile, Span& s) {
+    if (a.direct != kPaired) return;
+    const int tiles = (int)((s.L + ((1 << log2_tile) - 1)) >> log2_tile);
+    s.n = paired_splits(a.n_splits, tiles);
+    if (s.split >= s.n) s.split = tiles;        // beyond the end
+}
+
 // take() with K sequences per lane; len0: request_lengths
-template <int K>
+template <bool PAIR, int K>
 __device__ __forceinline__ bool take_shared(const DecodeArgs& a, int len0, int log2_tile, Span& s) {
     const int batch = gridDim.z, lane = threadIdx.x & 63;
     int len[K], tiles[K], n[K];
@@ -105,6 +118,7 @@ __device__ __forceinline__ bool take_shared(const DecodeArgs& a, int len0, int l
     if (inv == 0.f) {
         if (writer && threadIdx.x == 0) a.places[2 * s.b] = -1;
         s.L = clamped_len(a, K == 1 ? __builtin_amdgcn_readlane(len0, s.b) : a.seq_len[s.b]);
+        if (PAIR) pair_up(a, log2_tile, s);
         return true;
     }
     int mine = 0;
@@ -148,8 +162,9 @@ __device__ __forceinline__ bool take_shared(const DecodeArgs& a, int len0, int l
     return true;
 }
 
-// The work of this workgroup (grid (n_splits, ., B)); false: none.  SHARE false: for calls without share_above.
-template <bool SHARE = true>
+// The work of this workgroup (grid (n_splits, ., B)); false: none.  SHARE false: for calls without share_above; PAIR: for the
+// pass that may have kPaired.
+template <bool SHARE = true, bool PAIR = false>
 __device__ __forceinline__ bool take(const DecodeArgs& a, int len0, int log2_tile, Span& s) {
     s.b = blockIdx.z;
     s.split = blockIdx.x;
@@ -157,11 +172,12 @@ __device__ __forceinline__ bool take(const DecodeArgs& a, int len0, int log2_til
     s.row0 = s.b * a.H_q * a.n_splits + s.split;
     s.row_step = a.n_splits;
     if (SHARE && a.share_above) {
-        if (gridDim.z <= 64) return take_shared<1>(a, len0, log2_tile, s);
-        if (gridDim.z <= 256) return take_shared<4>(a, len0, log2_tile, s);
-        return take_shared<kMaxShared / 64>(a, len0, log2_tile, s);
+        if (gridDim.z <= 64) return take_shared<PAIR, 1>(a, len0, log2_tile, s);
+        if (gridDim.z <= 256) return take_shared<PAIR, 4>(a, len0, log2_tile, s);
+        return take_shared<PAIR, kMaxShared / 64>(a, len0, log2_tile, s);
     }
     s.L = !a.seq_len ? a.max_len : clamped_len(a, a.seq_len[s.b]);
+    if (PAIR) pair_up(a, log2_tile, s);
     return true;
 }
 
@@ -187,7 +203,7 @@ __device__ __forceinline__ const DecodeArgs& arguments_again() {
     return *(const DecodeArgs*)p;
 }
 
-// One split (a.direct): the merged o of channel c (cache order) of virtual head s of kv-head kvh, normalised by l and
+// One split (a.direct = 1): the merged o of channel c (cache order) of virtual head s of kv-head kvh, normalised by l and
 // rounded once to the output's type, goes where the combine pass would put it.
 __device__ __forceinline__ void write_output(const DecodeArgs& a, int dt, int b, int kvh, int s, int c, float o, float l) {
     const int to = a.perm_v ? (a.perm_v[kvh * 128 + c] & 127) : c;       // masked: the store stays inside the row

@@ -262,3 +262,27 @@ def test_five_tiles_where_four_splits_fit(dt, p, B, rope, given):
         want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), lens, scale)
     torch.cuda.synchronize()
     assert_attention_close(got, want, torch_dt, "%s p=%d B=%d" % (dt, p, B))
+
+
+@pytest.mark.parametrize("dt,p,B,rope,five", [("f32", 4, 24, False, 3), ("bf16", 8, 16, False, 4), ("f32", 8, 16, False, 4), ("f16", 4, 16, True, 4)])
+def test_the_splits_follow_the_lengths_and_not_max_len(dt, p, B, rope, five):
+    """Planned for five tiles, four splits fit.  Lengths of four tiles and fewer have a split for every tile; five tiles
+    take three (two, two and one) with fp32 I/O and 4 bits, four elsewhere."""
+    Hkv, S, n, Hq = 8, 1200, 32, 8
+    layout = kvbfp.make_layout(D, n, p, Hkv, B, S)
+    cache = kvbfp.alloc_cache(layout, "cuda", fill=0)
+    q = torch.zeros((B, Hq, D), dtype={"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dt], device="cuda")
+    ws = torch.zeros((kvbfp.decode_workspace_bytes(layout, Hq, S) + 4096,), dtype=torch.uint8, device="cuda")
+    if rope:
+        theta = (10000.0 ** (-np.arange(0, D, 2, dtype=np.float64) / D)).astype(np.float32)
+        r = [torch.as_tensor(np.ascontiguousarray(x)).cuda() for x in kvbfp.permute_rope(theta, np.tile(np.arange(D, dtype=np.int32), (Hkv, 1)))]
+    for length, busy in ((1200, five), (1024, 4), (700, 3), (512, 2), (1, 1)):
+        kw = dict(seq_len_dev=dev_i32(np.full(B, length)), workspace=ws)
+        if rope:
+            kvbfp.decode_attention_rope(cache, q, S, 0.1, *r, **kw)
+        else:
+            kvbfp.decode_attention(cache, q, S, 0.1, **kw)
+        torch.cuda.synchronize()
+        rows = B * Hq * 4
+        weight = ws.view(torch.float32)[rows * D:rows * (D + 2)].view(B, Hq, 4, 2)[..., 1]      # of a row: as many as it has tokens
+        assert bool((weight.sum(-1) == length).all()) and bool(((weight > 0).sum(-1) == busy).all()), (length, weight[0, 0].tolist())
