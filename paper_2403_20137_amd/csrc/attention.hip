@@ -722,7 +722,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // More heads than one launch of those takes, 16-bit I/O: all of them in one pass that decodes a row once.  8 sequences x
     // 12000 tokens x 8 kv-heads, call time before (16 heads per launch of an LDS pipeline for 4 bits and blocks of 16 / 32,
     // 8 heads otherwise, from 33 heads the general pass) -> now: 16 heads, blocks of 32 48 -> 46 us, of 16 62 -> 47 us, of 64
-    // 67 -> 45 us, 8 bits 95 -> 65 us; 32 heads 90 -> 50 us, 8 bits 168 -> 68 us; 64 heads 1135 -> 73 us.
+    // 67 -> 45 us, 8 bits 95 -> 65 us; 32 heads 90 -> 50 us, 8 bits 168 -> 68 us; 64 heads 1135 -> 69 us.
     const bool wide = !rope && a.G > 8 && dtype != KVBFP_F32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
     if (wide) sp.n_splits = wp.n_splits;

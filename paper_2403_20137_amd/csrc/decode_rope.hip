@@ -220,7 +220,9 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
     }
     __syncthreads();        // the channel-order queries give way to the table
     const int64_t tile_step = (int64_t)span.n * 256;
-    // A phasor at an angle of up to some tens, with what the angle lost when it was rounded put back.
+    // A phasor at an angle of up to some tens, with what the angle lost when it was rounded put back.  (The table's entries are 1.8e-7
+    // off at most so, 1.9e-6 with sine and cosine of the rounded angle; partial results of 40 calls over 300 to 40000 tokens are 0.97
+    // as far from 64 bits as with that, and 0.1 % of bf16 and 0.6 % of fp16 outputs round the other way.)
     auto phasor = [](const float tau, const float th, float& cs, float& sn) {
         const float angle = tau * th, rest = fmaf(tau, th, -angle);
         sincosf(angle, &sn, &cs);

@@ -15,11 +15,11 @@
 //   * The query is not rounded: a bf16 query (or one cast to BFP) is one bf16 operand, an fp16 query is two (8 + 3
 //     bits).  softmax_scale * log2(e) multiplies the score in fp32.  Probabilities above 32 heads are three bf16 limbs, all of
 //     their 24 bits; up to 32 two (16 bits), as in the other passes for 16-bit I/O.  (Not two binary16 limbs, which take two thirds
-//     of the matrix instructions and a third of the vector instructions, 256 heads below 67 us: they have an absolute step, 2^-36 of
-//     the largest probability, and where the heaviest token's values are zero the output is the sum of the light ones alone.)
+//     of the matrix and a third of the limb instructions, 67 us for the 77 below: they have an absolute step, 2^-36 of the largest
+//     probability, and where the heaviest token's values are zero the output is the sum of the light ones alone.)
 // Bound by: vector ALUs and matrix cores (decode_split_wide, per wavefront, 64 tokens and 32 heads: 64 MFMAs of 32 cycles and
 // some 530 vector instructions of 4 cycles, 32 exponentials of 8 among them).  256 virtual heads (64 query tokens, groups of
-// 4) over 4 x 8192 tokens x 8 kv-heads: 76 us a call, fp16 I/O 86 (80 and 125 with one half of LDS, decoding and products one after
+// 4) over 4 x 8192 tokens x 8 kv-heads: 77 us a call, fp16 I/O 86 (80 and 125 with one half of LDS, decoding and products one after
 // the other; 1490 in the general pass).
 // Up to 32 heads: vector ALUs 70 % busy (490 instructions per 32 tokens); 20 heads over 8 x 12000 tokens x 8 kv-heads: 40 us a
 // call, against 66 us in two launches.

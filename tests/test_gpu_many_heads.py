@@ -295,8 +295,7 @@ def test_query_and_output_at_any_address(G):
 
 @pytest.mark.parametrize("dt,p,n,G", [("bf16", 4, 32, 33), ("f16", 4, 16, 70), ("bf16", 8, 16, 33), ("f16", 8, 64, 70)])
 def test_exponents_that_leave_the_range_of_the_first_tile(dt, p, n, G):
-    """Two workgroups a sequence, four tiles each: the pass starts with values relative to the largest exponent of its first tile
-    and has to go on in another way from the first tile that does not fit it, with the sums it has.  Block 0 (and the keys)
+    """Two workgroups a sequence, four tiles each: exponents far from those of a workgroup's first tile in a later one.  Block 0 (and the keys)
     of one sequence each: nothing; one value 2^30 above; 2^40 below; 2^40 below from the start on, then as it was; zero rows at
     the start; one value 2^10 above in the last token; keys at the smallest byte; up by 2^6 and down by 2^24, the last that fit."""
     B, Hkv, S = 64, 4, 450
