@@ -60,28 +60,11 @@ __device__ __forceinline__ float code_value(uint32_t c) {
 // four per workgroup; larger groups re-read the cache).  The fallback for what the matrix-core passes
 // do not take: more than 32 (virtual) heads per kv-head with fp32 I/O, planes that are not 16-byte aligned.
 // grid = (n_splits, H_kv * ceil(G/4), B), block = 256.
-//
-// ROPE: the keys were cached before the rotary embedding and are rotated here, at token index m = their
-// position in the cache (Sec. III; Alg. 1 step 5 for the reordered parameters Theta', i', s').  With
-// k_rot[j] = k'[j] cos(m Theta'[j]) + s'[j] k'[i'[j]] sin(m Theta'[j]) and the structure of the three
-// vectors (i' an involution, equal Theta' and opposite s' within a pair) the score is
-//     q'.k_rot = sum_j k'[j] ( q'[j] cos(m Theta'[j]) + q''[j] sin(m Theta'[j]) ),  q''[j] = -s'[j] q'[i'[j]],
-// so no cached element has to meet its partner.  m = tile0 + r: the tile's angle is folded into the two
-// query vectors once per tile (A = q' ch + q'' sh, B = q'' ch - q' sh), and the phasor of the offset r
-// = 16 a + b inside the tile is the product of two 16-entry tables per channel.  Tables and the tile
-// phasor are built in double precision from the fp32 frequencies (one sincos of Theta'[j], one of
-// t_begin Theta'[j] and of the tile step, then complex products), so that angles of 10^5 radians keep
-// fp32 accuracy.
-template <int P, bool ROPE>
+template <int P>
 __global__ __launch_bounds__(kTile) void decode_split_generic(DecodeArgs a, int dt) {
     constexpr int kRowBytes = kD * P / 8;
     constexpr int kRowVec = kRowBytes / 16;
-    __shared__ float qs[kHeadsPerWg][kD];                      // ROPE: A of the current tile
-    __shared__ float qb[ROPE ? kHeadsPerWg : 1][kD];           // B of the current tile
-    __shared__ float q1[ROPE ? kHeadsPerWg : 1][kD];           // q'
-    __shared__ float q2[ROPE ? kHeadsPerWg : 1][kD];           // q''
-    __shared__ float2 ph_lo[ROPE ? kD : 1][16];                // (cos, sin)(b Theta'[j]),    b < 16
-    __shared__ float2 ph_mid[ROPE ? kD : 1][16];               // (cos, sin)(16 a Theta'[j]), a < 16
+    __shared__ float qs[kHeadsPerWg][kD];
     __shared__ float sc[kHeadsPerWg][kTile];
     __shared__ float alpha_s[kHeadsPerWg];
     __shared__ float ored[4][kHeadsPerWg][kD];
@@ -134,40 +117,6 @@ __global__ __launch_bounds__(kTile) void decode_split_generic(DecodeArgs a, int 
         __syncthreads();
     }
 
-    double hi_c = 1.0, hi_s = 0.0, step_c = 1.0, step_s = 0.0;   // thread j < D: phasor of tile0 Theta'[j], of the tile step
-    if (ROPE) {
-        for (int i = tid; i < kHeadsPerWg * kD; i += kTile) (&q1[0][0])[i] = (&qs[0][0])[i];
-        __syncthreads();
-        for (int i = tid; i < kHeadsPerWg * kD; i += kTile) {
-            const int g = i / kD, j = i % kD;
-            q2[g][j] = -a.rope_sign[kvh * kD + j] * q1[g][a.rope_partner[kvh * kD + j] & (kD - 1)];
-        }
-        if (tid < kD) {
-            const double th = (double)a.rope_theta[kvh * kD + tid];
-            double c1, s1;
-            sincos(th, &s1, &c1);
-            double pc = 1.0, ps = 0.0;
-            for (int k = 0; k < 16; ++k) {
-                ph_lo[tid][k] = make_float2((float)pc, (float)ps);
-                const double nc = pc * c1 - ps * s1;
-                ps = ps * c1 + pc * s1;
-                pc = nc;
-            }
-            const double c16 = pc, s16 = ps;
-            pc = 1.0;
-            ps = 0.0;
-            for (int k = 0; k < 16; ++k) {
-                ph_mid[tid][k] = make_float2((float)pc, (float)ps);
-                const double nc = pc * c16 - ps * s16;
-                ps = ps * c16 + pc * s16;
-                pc = nc;
-            }
-            sincos((double)tile_step * th, &step_s, &step_c);     // from one of this workgroup's tiles to its next
-            sincos((double)t_begin * th, &hi_s, &hi_c);
-        }
-        __syncthreads();
-    }
-
     float m_run = -INFINITY, l_run = 0.f;          // wave g owns head g0+g (uniform per wave)
     float o[kHeadsPerWg][2];
 #pragma unroll
@@ -175,21 +124,6 @@ __global__ __launch_bounds__(kTile) void decode_split_generic(DecodeArgs a, int 
     const int cp = lane;                            // V phase: channels 2cp, 2cp+1
 
     for (int64_t tile0 = t_begin; tile0 < t_end; tile0 += tile_step) {
-        if (ROPE) {   // the queries of this tile (nobody reads qs / qb between the end of a tile and here)
-            if (tid < kD) {
-                const float ch = (float)hi_c, sh = (float)hi_s;
-#pragma unroll
-                for (int g = 0; g < kHeadsPerWg; ++g) {
-                    const float x = q1[g][tid], y = q2[g][tid];
-                    qs[g][tid] = x * ch + y * sh;
-                    qb[g][tid] = y * ch - x * sh;
-                }
-                const double nc = hi_c * step_c - hi_s * step_s;
-                hi_s = hi_s * step_c + hi_c * step_s;
-                hi_c = nc;
-            }
-            __syncthreads();
-        }
         // rows of the planes are addressed as base + token; a paged cache with pages of 64 tokens or more has one
         // base per 64 tokens, the share of a wavefront in both phases below; with smaller pages every token looks
         // up its own row
@@ -229,29 +163,12 @@ __global__ __launch_bounds__(kTile) void decode_split_generic(DecodeArgs a, int 
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v[i] = code_value<8>((w[i / 4] >> (8 * (i % 4))) & 0xFFu);
                 }
-                if (ROPE) {
-                    float acc[kHeadsPerWg];
 #pragma unroll
-                    for (int g = 0; g < kHeadsPerWg; ++g) acc[g] = 0.f;
+                for (int g = 0; g < kHeadsPerWg; ++g) {
+                    float acc = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int j = c * 16 + i;
-                        const float2 pm = ph_mid[j][tid >> 4], pl = ph_lo[j][tid & 15];
-                        const float kc = v[i] * (pm.x * pl.x - pm.y * pl.y);     // k' cos((16a + b) Theta')
-                        const float ks = v[i] * (pm.y * pl.x + pm.x * pl.y);     // k' sin(...)
-#pragma unroll
-                        for (int g = 0; g < kHeadsPerWg; ++g) acc[g] = fmaf(qs[g][j], kc, fmaf(qb[g][j], ks, acc[g]));
-                    }
-#pragma unroll
-                    for (int g = 0; g < kHeadsPerWg; ++g) s[g] = fmaf(scale, acc[g], s[g]);
-                } else {
-#pragma unroll
-                    for (int g = 0; g < kHeadsPerWg; ++g) {
-                        float acc = 0.f;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) acc = fmaf(qs[g][c * 16 + i], v[i], acc);
-                        s[g] = fmaf(scale, acc, s[g]);
-                    }
+                    for (int i = 0; i < 16; ++i) acc = fmaf(qs[g][c * 16 + i], v[i], acc);
+                    s[g] = fmaf(scale, acc, s[g]);
                 }
             }
         }
@@ -727,21 +644,21 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     const WidePlan wp = plan_wide(a.G, (int64_t)L->batch * L->n_kv_heads, max_len, sp.n_splits);
     if (wide) sp.n_splits = wp.n_splits;
     const int log2_tile = wide ? wp.log2_tile : 8;
-    // rotation at read: the matrix-core pass takes 4-bit mantissas with 16-bit I/O, four heads per launch
-    const bool rope_fast = rope && !paging && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 &&
-                           aligned16(a.k_exp) && aligned16(a.v_exp);
+    // rotation at read: 4-bit mantissas with 16-bit I/O go through binary16 operands, everything else through fp32 ones
+    // (8 sequences x 16384 tokens, 4 bits, bf16: 51.4 us, 64.9 in fp32)
+    const bool rope_halves = rope && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas,
     // for more than four heads with fp32 I/O and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
     // others.  8 kv-heads, 8000 tokens, one call with the splits rounded up -> down: 10 sequences 26.5 -> 23.0 us, 13 29.4 ->
     // 26.5, 30 51.3 -> 49.8; 8 bits, 7 sequences 33.8 -> 28.5; rotation, 7 sequences 50.4 -> 39.0.  Not down to one split: lengths
     // that differ need two to be shared out (50 ragged sequences 32.6 us with two, 45.1 with one), and 65 equal ones took
     // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).
-    if (rope_fast || (fast && !wide)) {
+    if (rope || (fast && !wide)) {
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
-        const bool two = rope_fast || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
+        const bool two = rope || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
         const int64_t round = 256 * (two ? 2 : 3) / units;
         if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
-        else if (rope_fast && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
+        else if (rope && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }
     // Where up to half of the splits would take a second tile, all take two instead and there are fewer of them (to set up, to run
     // beside each other and to merge).  8 kv-heads, one call, as many splits as fit -> two tiles each: fp32 4 x 8192 tokens (24 splits for 32
@@ -762,14 +679,14 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     a.n_splits = sp.n_splits;
     // by the lengths where there are any (not in the general pass) and the workspace has room for the table
     const size_t rows = rows_bytes(L, n_q_heads, sp.n_splits);
-    if ((fast || wide || rope_fast) && seq_len_dev && workspace_bytes >= rows + places_bytes(L)) {
+    if ((fast || wide || rope) && seq_len_dev && workspace_bytes >= rows + places_bytes(L)) {
         a.share_above = (int32_t)share_above(L, sp.n_splits, max_len, log2_tile, share_from(dtype == KVBFP_F32, L->mant_bits, a.G, rope, sp.n_splits));
         a.places = (int32_t*)((char*)workspace + rows);
     }
     // One split: nothing to merge, the split pass writes the output itself and the combine pass is not launched: an appended
     // step over 250 tokens 15.6 -> 8.2 us, 128 sequences x 1000 tokens (1024 units) 36.6 -> 33.0 us.  (Not in the passes for
     // many heads: their merge has no registers to spare, 20 heads over 12000 tokens 44.7 -> 45.7 us with the branch in it.)
-    if (sp.n_splits == 1 && (rope_fast || (fast && !wide))) a.direct = 1;
+    if (sp.n_splits == 1 && (rope || (fast && !wide))) a.direct = 1;
     a.part_ml = a.part_o + (size_t)L->batch * n_q_heads * sp.n_splits * kD;
     const dim3 grid1((unsigned)sp.n_splits, (unsigned)(a.H_kv * gg), (unsigned)L->batch);
     a.g_base = 0;
@@ -817,20 +734,16 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
                                         : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, s);
                 a.k_new = a.v_new = nullptr;       // the current token is cast by the first launch only
             }
-        } else if (rope_fast) {
+        } else if (rope) {                                                         // four heads per launch
             for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += 4) {
                 a.g_base = g0;
                 a.g_cnt = a.G - g0 < 4 ? a.G - g0 : 4;
-                err = launch_decode_split_rope(a, (int)dtype, L->block, L->batch, s);
+                err = rope_halves ? launch_decode_split_rope(a, (int)dtype, L->block, L->batch, s)
+                                  : launch_decode_split_rope_f32(a, L->mant_bits, (int)dtype, L->block, L->batch, s);
             }
         } else {
-            if (rope) {
-                if (L->mant_bits == 4) decode_split_generic<4, true><<<grid1, kTile, 0, s>>>(a, (int)dtype);
-                else decode_split_generic<8, true><<<grid1, kTile, 0, s>>>(a, (int)dtype);
-            } else {
-                if (L->mant_bits == 4) decode_split_generic<4, false><<<grid1, kTile, 0, s>>>(a, (int)dtype);
-                else decode_split_generic<8, false><<<grid1, kTile, 0, s>>>(a, (int)dtype);
-            }
+            if (L->mant_bits == 4) decode_split_generic<4><<<grid1, kTile, 0, s>>>(a, (int)dtype);
+            else decode_split_generic<8><<<grid1, kTile, 0, s>>>(a, (int)dtype);
             err = hipGetLastError();
         }
     };

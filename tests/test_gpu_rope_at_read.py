@@ -114,3 +114,65 @@ def test_profile_variant_returns_the_same_result_and_two_durations():
     (got, split_ms, combine_ms), want = run_both(k, v, q, 16, 4, [600, 1], 0.09, pk, pv, 0, profile=True)
     assert_attention_close(got, want, torch.bfloat16)
     assert split_ms > 0 and combine_ms > 0
+
+
+# ---- the pass in fp32 (8-bit mantissas, fp32 I/O, exponent planes of any alignment)
+
+@pytest.mark.parametrize("dtype,p,n", [(torch.float32, 4, 16), (torch.float32, 4, 64), (torch.float32, 8, 32), (torch.float32, 8, 128), (torch.bfloat16, 8, 16), (torch.float16, 8, 32)])
+@pytest.mark.parametrize("lens,G", [([1, 63], 4), ([64, 65], 1), ([255, 257], 5), ([512, 0], 3), ([1025, 960], 2)])
+def test_fp32_pass_at_the_edges_of_its_tiles(dtype, p, n, lens, G):
+    # 64 tokens to a wavefront, 256 to a workgroup; one to five heads (four to a launch); an empty sequence
+    k, v, q, pk, pv = make_small(dtype, B=2, S=max(lens), Hkv=2, G=G, seed=160 + G)
+    got, want = run_both(k, v, q, n, p, lens, 0.13, pk, pv, G & 1, S_max=max(lens) + 3)
+    assert_attention_close(got, want, dtype, "p=%d n=%d lengths %s" % (p, n, lens))
+
+
+@pytest.mark.parametrize("dtype,p,n", [(torch.float32, 4, 32), (torch.float32, 8, 16), (torch.bfloat16, 8, 64)])
+@pytest.mark.parametrize("k_shift,q_shift,v_shift", [(-100, 0, 0), (100, 0, 0), (0, 90, 0), (0, -90, 0), (-60, -50, 0), (0, 0, -120), (0, 0, -126), (0, 0, 110)])
+def test_fp32_pass_at_the_ends_of_the_range(dtype, p, n, k_shift, q_shift, v_shift):
+    # queries beyond 2^60 are normalised; value blocks with exponent bytes 1 and 2 (v 2^-126) take fp32 multiply-adds
+    B, S, Hkv, G = 2, 300, 2, 4
+    g = synth.outlier_gains(7, 0, Hkv, D)
+    mk = lambda t, sh: (t * 2.0 ** sh).to(dtype)
+    k = mk(synth.kv_rows(B, S, Hkv, D, "f32", g, 7, 2), k_shift)
+    v = mk(synth.kv_rows(B, S, Hkv, D, "f32", g, 7, 3), v_shift)
+    q = mk(synth.queries(B, Hkv * G, D, "f32", 7, 4), q_shift)
+    scale = float(np.float32(D ** -0.5) * np.float32(2.0 ** (-(k_shift + q_shift))))
+    got, want = run_both(k, v, q, n, p, [S, 131], scale, None, None, 1)
+    assert bool(torch.isfinite(got).all())
+    if v_shift == -126 and dtype == torch.float32:      # subnormal outputs: the step of fp32 there on top of the bar
+        err = np.abs(got.double().cpu().numpy() - want)
+        assert np.all(err <= 2.0 ** -149 + 1e-5 * np.abs(want).max(axis=-1, keepdims=True))
+    else:
+        assert_attention_close(got, want, dtype, "p=%d n=%d shifts k %d q %d v %d" % (p, n, k_shift, q_shift, v_shift))
+
+
+@pytest.mark.parametrize("n", [16, 128])
+def test_fp32_pass_takes_the_largest_exponent_bytes(n):
+    # three tokens with values of 2^125 (8 bits: bytes 252 and up do not fit the conversion to bf16)
+    g = torch.Generator().manual_seed(9)
+    k, q = torch.randn(1, 3, 2, D, generator=g), torch.randn(1, 8, D, generator=g)
+    v = (torch.rand(1, 3, 2, D, generator=g) - 0.5) * 2.0 ** 125
+    v[..., ::16] = 2.0 ** 125.5
+    got, want = run_both(k, v, q, n, 8, [3], 0.2, None, None, 0)
+    assert_attention_close(got, want, torch.float32)
+
+
+@pytest.mark.parametrize("dtype,p,n", [(torch.bfloat16, 4, 16), (torch.bfloat16, 4, 32), (torch.float32, 8, 64), (torch.float32, 4, 128)])
+def test_rotation_over_exponent_planes_of_any_alignment(dtype, p, n):
+    k, v, q, pk, pv = make_small(dtype, B=2, S=300, Hkv=2, G=4, seed=170)
+    planes = oracle_cache(k, v, n, p, 300, 0, pk, pv)
+    whole = gpu_cache(k.cuda(), v.cuda(), n, p, 300, perm_k=pk, perm_v=pv)
+    moved = []
+    for e in (whole.k_exp, whole.v_exp):
+        room = torch.zeros(e.numel() + 16, dtype=torch.uint8, device="cuda")
+        room[1:1 + e.numel()] = e.reshape(-1)
+        moved.append(room[1:1 + e.numel()].reshape(e.shape))
+        assert moved[-1].data_ptr() % 16 == 1
+    cache = kvbfp.Cache(whole.layout, whole.k_mant, moved[0], whole.v_mant, moved[1])
+    r = O.permute_rope(llama_theta(), pk, 0)
+    want = O.decode_attention_rope(*planes, D, n, p, synth.to_f32_numpy(q), [300, 70], 0.1, *r, perm_k=pk, perm_v=pv)
+    got = kvbfp.decode_attention_rope(cache, q.cuda(), 300, float(np.float32(0.1)), *(torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in r),
+                                      seq_len_dev=dev_i32([300, 70]), perm_k=dev_i32(pk), perm_v=dev_i32(pv))
+    torch.cuda.synchronize()
+    assert_attention_close(got, want, dtype, "p=%d n=%d" % (p, n))
