@@ -29,9 +29,10 @@
 //     difference inside the conversion (exact down to 2^-24 of the other block's unit).
 // Values, softmax and the merge of the four wavefronts are those of the register-staged plain pass.
 // Bound by vector ALUs: some 920 instructions a wavefront and tile of 64 tokens, 256 of them the table products, 320 the
-// unpacking of keys and values, 130 the operand rebuild; 90 % of the issue slots once the set-up (7 us, most of it sines and
-// cosines) is done.  8 x 16384 tokens x 8 kv-heads, 4 heads: 51 us a call; 58 with 64-bit addresses per row, accumulation registers
-// that were copied to and fro (the compiler's choice without the two wavefronts per SIMD stated) and a sine and a cosine per
+// unpacking of keys and values, 130 the operand rebuild; 90 % of the issue slots once the set-up (5 to 6 us) is done.  8 x 16384
+// tokens x 8 kv-heads, 4 heads: 51.1 us a call, 64 x 300 tokens 16.9; 51.7 and 17.2 with the library's sines and cosines in the set-up
+// (the table's entries are 3e-7 off at most before they are cut to 19 bits, 2e-6); 58 with 64-bit addresses per row, accumulation
+// registers that were copied to and fro (the compiler's choice without the two wavefronts per SIMD stated) and a sine and a cosine per
 // table entry.
 #include <hip/hip_runtime.h>
 
@@ -220,16 +221,6 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
     }
     __syncthreads();        // the channel-order queries give way to the table
     const int64_t tile_step = (int64_t)span.n * 256;
-    // A phasor at an angle of up to some tens, with what the angle lost when it was rounded put back.  (The table's entries are 1.8e-7
-    // off at most so, 1.9e-6 with sine and cosine of the rounded angle; partial results of 40 calls over 300 to 40000 tokens are 0.97
-    // as far from 64 bits as with that, and 0.1 % of bf16 and 0.6 % of fp16 outputs round the other way.)
-    auto phasor = [](const float tau, const float th, float& cs, float& sn) {
-        const float angle = tau * th, rest = fmaf(tau, th, -angle);
-        sincosf(angle, &sn, &cs);
-        const float c0 = cs;
-        cs = fmaf(-rest, sn, cs);
-        sn = fmaf(rest, c0, sn);
-    };
     float* const p16_s = (float*)&p_s[0][0][0][0];                  // [2][kD]: phasors of 16 tokens
     float* const theta_s = p16_s + 2 * kD;                          // [kD]
     static_assert(sizeof(p_s) >= 3 * kD * sizeof(float), "they fit");
@@ -238,11 +229,11 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
         const int c = my_c, at = slot_index(c);
         const bool first = tid < kD;
         double sn, cs;
-        sincos((double)(first ? t_begin : tile_step) * (double)th, &sn, &cs);
+        phasor((double)(first ? t_begin : tile_step), (double)th, cs, sn);
         if (first) {
             theta_s[c] = th;
             double s64, c64;
-            sincos((double)kSuper * (double)th, &s64, &c64);
+            phasor((double)kSuper, (double)th, c64, s64);
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) {
                 ph_s[w][0][at] = (float)cs;
