@@ -660,6 +660,24 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
         else if (rope && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }
+    // Short sequences, 16-bit I/O: one workgroup of eight wavefronts a sequence and kv-head instead of splits and a combine pass, as
+    // long as the tiles of 512 tokens that it takes one after the other cost less than that launch.  With many units the splits
+    // are busy for longer, so the line moves up with them; beyond 256 units the workgroups would not be spread evenly over the
+    // compute units.  8 kv-heads, one call in a graph, splits -> one workgroup: 4 bits, 1 x 900 tokens 10.4 -> 9.7 us, 8 x 512 9.5 -> 7.3,
+    // 8 x 1024 10.0 -> 9.5 (8 x 2048 12.0 -> 13.0), 16 x 1536 14.0 -> 11.3, 24 x 2048 16.6 -> 13.6, ragged 14.8 -> 13.7 (24 x 3072 16.6 ->
+    // 16.9); 5 to 8 heads, 8 x 768 12.6 -> 12.2 (8 x 1024 12.7 -> 13.7), 16 x 1024 15.2 -> 13.8, 24 x 1536 ragged 18.6 -> 16.1; 8 bits, 8 x
+    // 512 10.0 -> 8.8 (8 x 1024 11.2 -> 12.9), 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5 (20 x 1536 14.6 -> 15.3); 8 bits and 5 to 8
+    // heads 8 x 512 13.5 -> 13.1 (8 x 768 13.9 -> 14.7).
+    int waves = 4;
+    if (fast && !wide && dtype != KVBFP_F32 && sp.n_splits > 1) {
+        const int64_t units = (int64_t)L->batch * L->n_kv_heads;
+        const bool p4 = L->mant_bits == 4, one_group = a.G <= 4;
+        const int64_t few_units = p4 && one_group ? 1024 : p4 || one_group ? 768 : 512;
+        if (units <= 256 && max_len <= std::max(few_units, (p4 ? one_group ? 12 : 10 : 7) * units)) {
+            sp.n_splits = 1;
+            waves = 8;
+        }
+    }
     // Where up to half of the splits would take a second tile, all take two instead and there are fewer of them (to set up, to run
     // beside each other and to merge).  8 kv-heads, one call, as many splits as fit -> two tiles each: fp32 4 x 8192 tokens (24 splits for 32
     // tiles) 21.9 -> 20.5 us, 6 x 5000 25.5 -> 21.3; 4 bits 6 x 5000 17.1 -> 15.2, 1 x 30000 16.8 -> 15.9, 8 bits 2 x 9000 18.4 ->
@@ -730,8 +748,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
             for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += a.g_cnt) {      // 8 heads per launch
                 a.g_base = g0;
                 a.g_cnt = a.G - g0 < 8 ? a.G - g0 : 8;
-                err = L->mant_bits == 4 ? launch_decode_split_mfma(a, (int)dtype, L->block, L->batch, s)
-                                        : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, s);
+                err = L->mant_bits == 4 ? launch_decode_split_mfma(a, (int)dtype, L->block, L->batch, waves, s)
+                                        : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, waves, s);
                 a.k_new = a.v_new = nullptr;       // the current token is cast by the first launch only
             }
         } else if (rope) {                                                         // four heads per launch

@@ -197,11 +197,14 @@ constexpr int vmcnt_imm(int n) { return (n & 0xF) | (0x7 << 4) | (0xF << 8) | ((
 // channels, and the two block exponents added and applied to the integer sums afterwards.
 // SHARE: the instantiation for calls whose workgroups may be shared out by the lengths (which have splits to merge).  A branch on it
 // costs the others 0.3 us of a call (1024 units x 1024 tokens, one split: 17.6 us with it, 17.0 without).
-template <int P, int N, int HG, bool PAGED, bool SHARE, bool QI8 = false>
+template <int P, int N, int HG, bool PAGED, bool SHARE, bool QI8 = false, int W = kWaves>
 __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const int dt) {
     static_assert(P == 4 || P == 8, "mantissa widths of the format");
     static_assert(!QI8 || (P == 8 && N >= 32), "integer score product: 8-bit codes, one key exponent per 32 channels");
     static_assert(HG <= 2, "one or two groups of four heads");
+    static_assert(W == 4 || W == 8, "wavefronts of a workgroup");
+    constexpr int kThreads = 64 * W;
+    constexpr int kLog2Wg = W == 8 ? 9 : 8, kWgTok = 1 << kLog2Wg;      // tokens of a workgroup's tile, 64 per wavefront
     // value conversions produce value * 2^-kShift (the stored exponent byte is their scale operand); the
     // probabilities carry the inverse
     constexpr int kShift = P == 4 ? 7 : 3;
@@ -228,30 +231,31 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     constexpr int kExpDma = kEt / 256;             // DMA instructions per exponent tile (2 for blocks of 16, else 1)
     // Keys go to the scaled FP8 x FP4 MFMA as raw nibbles: a block of 32 is exactly its MX block; a
     // block of 16 takes two products per 32 channels, each with the other block's nibbles zeroed.
-    constexpr int kRings = kWaves * kWaveBytes;
-    static_assert(kWaves * NH * kD * 4 + kWaves * NH * 8 <= kRings, "merge buffers alias the staging area");
+    constexpr int kRings = W * kWaveBytes;
+    static_assert(W * NH * kD * 4 + W * NH * 8 <= kRings, "merge buffers alias the staging area");
     // The DMA rings are an LDS object of their own: the compiler waits for every outstanding DMA
     // before it touches an object that a DMA may write, and the set-up must not wait for the first tile.
     // (padded so that at most three workgroups fit a compute unit: with four, placement over the units gets uneven)
-    constexpr int kSmem = kRings + HG * 4096 + NH * 16 >= 42 * 1024 ? kRings : 42 * 1024 - HG * 4096 - NH * 16;
+    constexpr int kSmem = W == 8 || kRings + HG * 4096 + NH * 16 >= 42 * 1024 ? kRings : 42 * 1024 - HG * 4096 - NH * 16;
     __shared__ __align__(16) uint8_t smem[kSmem];
     // probabilities of the current tile, bf16 hi/lo limbs: [wave][HG][2 limbs][4 heads][64 tokens].  A separate
     // LDS object, so the compiler can tell its reads apart from the DMA targets inside smem.
-    __shared__ __align__(16) uint16_t p_lds[kWaves][HG * 2 * 4 * kTileTok];
+    __shared__ __align__(16) uint16_t p_lds[W][HG * 2 * 4 * kTileTok];
     // Until the main loop starts the same bytes stage the query: q' as fp32 [NH][128] in the first half,
     // its FP8 limbs [NH*4 rows][128] in the second (the permutation and the block maxima of the BFP cast
     // pass through there before the limbs are written); the limbs' scale bytes [NH*4][4] sit beside.
-    static_assert(sizeof(p_lds) == NH * kD * 4 + NH * 4 * kD, "query staging fills the probability buffer exactly");
+    static_assert(sizeof(p_lds) >= NH * kD * 4 + NH * 4 * kD, "the query fits the probability buffer (and fills that of four wavefronts)");
     // where paging would push a three-wavefront variant with two head groups over its registers, the query operand does
     // not stay in registers between tiles; it lives in LDS, [NH * 4 limb rows][128], and every tile reads it back for its
     // score phase
     constexpr bool kQueryInLds = HG == 2 && PAGED && ((P == 4 && N == 32) || (P == 8 && N == 16));
     // One small LDS object either way: the limbs' scale bytes [NH * 4][4] of the set-up, or -- where the query
     // operand lives in LDS -- that operand; the scale bytes then sit at the end of the query staging area, whose
-    // second half the limbs do not need in that case.
+    // second half the limbs do not need in that case.  (With eight wavefronts half of the buffer is free: 81920 bytes with blocks of 16,
+    // and two workgroups fit a compute unit.)
     __shared__ __align__(16) uint8_t qaux_lds[kQueryInLds ? NH * 4 * kD : NH * 16];
     uint8_t* const qop_lds = qaux_lds;
-    uint8_t* const qsc_lds = kQueryInLds ? (uint8_t*)&p_lds[0][0] + sizeof(p_lds) - NH * 16 : qaux_lds;
+    uint8_t* const qsc_lds = kQueryInLds || W == 8 ? (uint8_t*)&p_lds[0][0] + sizeof(p_lds) - NH * 16 : qaux_lds;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS bases stay in scalar registers
@@ -265,12 +269,12 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // (Loaded as raw bits and widened later: a conversion right here would make the compiler wait for
     // each load in turn.  For the same reason the set-up below synchronises with LDS-only barriers:
     // __syncthreads() also waits for every vector-memory operation, i.e. for the whole first tile.)
-    constexpr int kQPerThread = NH * kD / 256;
+    constexpr int kQPerThread = NH * kD / kThreads;
     uint32_t q_bits[kQPerThread];
     auto request_queries = [&](const int seq) {
 #pragma unroll
         for (int k = 0; k < kQPerThread; ++k) {
-            const int i = tid + 256 * k, g = i / kD, c = i % kD;
+            const int i = tid + kThreads * k, g = i / kD, c = i % kD;
             const int64_t idx = kvbfp::query_row(a, seq, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + c;   // clamped: rows beyond the count are zeroed below
             q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
         }
@@ -286,21 +290,21 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     __builtin_amdgcn_sched_barrier(0);
 
     kvbfp::spans::Span span;
-    if (!kvbfp::spans::take<SHARE>(a, len0, 8, span)) return;
+    if (!kvbfp::spans::take<SHARE>(a, len0, kLog2Wg, span)) return;
     if (SHARE && span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
     const int h0 = kvh * a.G + a.g_base;      // first (virtual) head of this launch
 
     const int64_t L = span.L;
-    // Tiles are dealt out round-robin: split s takes the 256-token tiles s, s + n, s + 2 n, ...
+    // Tiles are dealt out round-robin: split s takes the 256-token tiles (512 with eight wavefronts) s, s + n, s + 2 n, ...
     // The workgroups of one (batch, kv-head) then sweep the sequence side by side instead of each
     // streaming a distant region of its own, which the memory system serves a few percent faster, and no
     // split is more than one tile longer than another.  "Split-relative" tokens below count from t_begin.
-    const int64_t t_begin = (int64_t)split * 256;
+    const int64_t t_begin = (int64_t)split * kWgTok;
     const int64_t t_end = L;
 
     if (t_begin >= t_end) {   // nothing cached in this split
-        for (int i = tid; i < a.g_cnt * kD; i += 256) {
+        for (int i = tid; i < a.g_cnt * kD; i += kThreads) {
             if (!SHARE && a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
@@ -320,8 +324,8 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // it, for the tiles 32..63 ahead, whenever the loop enters the other half.  (One variant's 80 KB of LDS leave no
     // room for the list: it looks its pages up tile by tile.)
     constexpr int kPreTiles = !PAGED || (P == 8 && HG == 2 && N == 16) ? 0 : 64;      // 4 KB of LDS per workgroup
-    __shared__ __align__(16) int32_t pt_lds[kPreTiles > 0 ? kWaves * kPreTiles * 4 : 4];
-    const int64_t tile_step = (int64_t)span.n * kWaves * kTileTok;
+    __shared__ __align__(16) int32_t pt_lds[kPreTiles > 0 ? W * kPreTiles * 4 : 4];
+    const int64_t tile_step = (int64_t)span.n * kWgTok;
     auto fetch_pages = [&](auto n_tag, const int first_tile) {    // tiles first_tile .. first_tile + n - 1, n = 32 or 64
         constexpr int n = decltype(n_tag)::value;
         int32_t got[n / 16];
@@ -356,9 +360,9 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // If that tile is the wavefront's first, it is requested only after the stores, the row's own round trip being over
     // by the end of the set-up (gathering, casting and storing the row ahead of the set-up: split pass 10.7 us on 901 tokens,
     // 13.4 on 4096 with 32 kv-heads; this way 8.8 and 10.5).
-    const bool appends = a.k_new != nullptr && (int)(((L - 1) >> 8) % span.n) == split &&
-                         (int)(((L - 1) & 255) >> 6) == wave;                       // wave-uniform
-    const bool appends_first = appends && (L - 1) < t_begin + 256;
+    const bool appends = a.k_new != nullptr && (int)(((L - 1) >> kLog2Wg) % span.n) == split &&
+                         (int)(((L - 1) & (kWgTok - 1)) >> 6) == wave;                       // wave-uniform
+    const bool appends_first = appends && (L - 1) < t_begin + kWgTok;
     const int nr_sub = lane & 7, nr_which = (lane >> 3) & 1;
     const bool nr_live = lane < 16;
     uint32_t nr_bits[16];
@@ -552,12 +556,12 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     int* const scratch = (int*)(qr + NH * kD);              // permutation, then block maxima of the cast
 #pragma unroll
     for (int k = 0; k < kQPerThread; ++k) {
-        const int g = (tid + 256 * k) / kD;
+        const int g = (tid + kThreads * k) / kD;
         float f;
         if (dt == KVBFP_F32) f = __uint_as_float(q_bits[k]);
         else if (dt == KVBFP_F16) f = (float)__builtin_bit_cast(_Float16, (unsigned short)q_bits[k]);
         else f = __uint_as_float(q_bits[k] << 16);
-        qr[tid + 256 * k] = g < a.g_cnt ? f : 0.f;
+        qr[tid + kThreads * k] = g < a.g_cnt ? f : 0.f;
     }
     perm_c &= kD - 1;                   // a valid permutation is unchanged; keeps LDS reads in range
 
@@ -600,18 +604,18 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         if (a.q_mant_bits) {               // query cast to BFP: reorder in LDS, cast there (blocks may span wavefronts)
             float q_perm[kQPerThread];
 #pragma unroll
-            for (int k = 0; k < kQPerThread; ++k) q_perm[k] = qr[((tid + 256 * k) / kD) * kD + perm_c];
+            for (int k = 0; k < kQPerThread; ++k) q_perm[k] = qr[((tid + kThreads * k) / kD) * kD + perm_c];
             lds_barrier();
 #pragma unroll
-            for (int k = 0; k < kQPerThread; ++k) qr[((tid + 256 * k) / kD) * kD + qchan] = q_perm[k];
+            for (int k = 0; k < kQPerThread; ++k) qr[((tid + kThreads * k) / kD) * kD + qchan] = q_perm[k];
             lds_barrier();
             bfp_round_queries(qr, (uint32_t*)scratch, NH, a.log2_block, a.q_mant_bits);
 #pragma unroll
-            for (int k = 0; k < kQPerThread; ++k) qv[k] = qr[((tid + 256 * k) / kD) * kD + qchan] * a.scale_log2e;
+            for (int k = 0; k < kQPerThread; ++k) qv[k] = qr[((tid + kThreads * k) / kD) * kD + qchan] * a.scale_log2e;
             lds_barrier();                 // the limbs below overwrite the scratch area
         } else {
 #pragma unroll
-            for (int k = 0; k < kQPerThread; ++k) qv[k] = qr[((tid + 256 * k) / kD) * kD + perm_c] * a.scale_log2e;
+            for (int k = 0; k < kQPerThread; ++k) qv[k] = qr[((tid + kThreads * k) / kD) * kD + perm_c] * a.scale_log2e;
         }
         uint8_t* q8 = kQueryInLds ? qop_lds : (uint8_t*)(qr + NH * kD);   // [NH * 4 limb rows][kD positions], beside the fp32 values
         uint8_t* qsc = qsc_lds;
@@ -623,7 +627,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
             const int c = tid & (kD - 1);
 #pragma unroll
             for (int k = 0; k < kQPerThread; ++k) {
-                const int g = (tid + 256 * k) / kD;
+                const int g = (tid + kThreads * k) / kD;
                 const float v = qr[g * kD + c];
                 float mx = row_max(fabsf(v));
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
@@ -651,7 +655,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         } else {
 #pragma unroll
         for (int k = 0; k < kQPerThread; ++k) {
-            const int g = (tid + 256 * k) / kD;
+            const int g = (tid + kThreads * k) / kD;
             float mx = row_max(fabsf(qv[k]));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             int e = 0;
@@ -745,7 +749,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         // one stage ahead of its arithmetic, so their latency is covered by the arithmetic of the stage before,
         // and a stage is re-filled for the wavefront's next tile as soon as its reads have returned.  The
         // exponent bytes of a whole tile are read with its first stage (and re-filled right after).
-        const int kStep = span.n * kWaves * kTileTok;      // this workgroup's next 256-token tile
+        const int kStep = span.n * kWgTok;      // this workgroup's next tile
         // (Where registers are short -- two head groups with blocks of 32, which keep three wavefronts per SIMD --
         // every stage issues its own reads and waits for them; the probabilities look ahead with one group only.)
         constexpr bool kPipe = HG == 1 || (HG == 2 && N != 32), kPipeP = HG == 1;
@@ -1125,8 +1129,8 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // ---- merge the four wavefronts (buffers alias the staging areas, all DMA has landed) ---------
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
-    float* const o_s = (float*)smem;                              // [kWaves][NH][kD]
-    float* const ml_s = (float*)(smem + kWaves * NH * kD * 4);    // [kWaves][NH][2]
+    float* const o_s = (float*)smem;                              // [W][NH][kD]
+    float* const ml_s = (float*)(smem + W * NH * kD * 4);    // [W][NH][2]
 #pragma unroll
     for (int hg = 0; hg < HG; ++hg) {
         const float lsum = row_sum(l_run[hg]);
@@ -1146,21 +1150,21 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     }
     __syncthreads();
     const DecodeArgs& e = kvbfp::spans::arguments_again();
-    for (int i = tid; i < e.g_cnt * kD; i += 256) {
+    for (int i = tid; i < e.g_cnt * kD; i += kThreads) {
         const int g = i / kD, c = i % kD;
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml_s[(w * NH + g) * 2]);
+        for (int w = 0; w < W; ++w) M = fmaxf(M, ml_s[(w * NH + g) * 2]);
         float acc = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < W; ++w) {
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) acc = fmaf(exp2f(mw - M), o_s[(w * NH + g) * kD + c], acc);
         }
         if (!SHARE && e.direct) {
             float den = 0.f;
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
+            for (int w = 0; w < W; ++w) {
                 const float mw = ml_s[(w * NH + g) * 2];
                 if (mw > -INFINITY) den = fmaf(exp2f(mw - M), ml_s[(w * NH + g) * 2 + 1], den);
             }
@@ -1173,10 +1177,10 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, ml_s[(w * NH + g) * 2]);
+        for (int w = 0; w < W; ++w) M = fmaxf(M, ml_s[(w * NH + g) * 2]);
         float lsum = 0.f;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < W; ++w) {
             const float mw = ml_s[(w * NH + g) * 2];
             if (mw > -INFINITY) lsum = fmaf(exp2f(mw - M), ml_s[(w * NH + g) * 2 + 1], lsum);
         }

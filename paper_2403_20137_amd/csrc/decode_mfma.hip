@@ -449,6 +449,13 @@ void decode_split_lds_p4(DecodeArgs a, int dt) {
     kvbfp::lds::decode_split_lds_body<4, N, HG, PAGED, SHARE>(a, dt);
 }
 
+// The same with eight wavefronts, for calls whose workgroups take a sequence each (attention.hip has when and the figures).
+template <int N, int HG, bool PAGED>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4)))
+void decode_split_lds_p4_w8(DecodeArgs a, int dt) {
+    kvbfp::lds::decode_split_lds_body<4, N, HG, PAGED, false, false, 8>(a, dt);
+}
+
 // 16-bit I/O: the LDS pipeline, every block size.  fp32 I/O: the register-staged pass with three probability
 // limbs and the three-limb bf16 query (the FP8 query limbs of the LDS pipeline carry 16 bits, too few for the
 // 1e-5 bar).
@@ -473,7 +480,18 @@ hipError_t launch_lds(const DecodeArgs& a, int dt, int block, dim3 grid, hipStre
 }
 
 template <int HG, bool PAGED>
-hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+hipError_t launch_lds_w8(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+    if (block == 16) decode_split_lds_p4_w8<16, HG, PAGED><<<grid, 512, 0, s>>>(a, dt);
+    else if (block == 32) decode_split_lds_p4_w8<32, HG, PAGED><<<grid, 512, 0, s>>>(a, dt);
+    else if (block == 64) decode_split_lds_p4_w8<64, HG, PAGED><<<grid, 512, 0, s>>>(a, dt);
+    else if (block == 128) decode_split_lds_p4_w8<128, HG, PAGED><<<grid, 512, 0, s>>>(a, dt);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+template <int HG, bool PAGED>
+hipError_t launch_n(const DecodeArgs& a, int dt, int block, int waves, dim3 grid, hipStream_t s) {
+    if (waves == 8) return launch_lds_w8<HG, PAGED>(a, dt, block, grid, s);
     if (dt == KVBFP_F32) return a.share_above ? launch_reg<HG, PAGED, true>(a, dt, block, grid, s) : launch_reg<HG, PAGED, false>(a, dt, block, grid, s);
     return a.share_above ? launch_lds<HG, PAGED, true>(a, dt, block, grid, s) : launch_lds<HG, PAGED, false>(a, dt, block, grid, s);
 }
@@ -482,10 +500,11 @@ hipError_t launch_n(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream
 
 namespace kvbfp {
 
-hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s) {
+hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, int waves, hipStream_t s) {
+    if (waves == 8 && (dtype == KVBFP_F32 || a.share_above)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
-    if (a.block_table) return a.g_cnt <= 4 ? launch_n<1, true>(a, dtype, block, grid, s) : launch_n<2, true>(a, dtype, block, grid, s);
-    return a.g_cnt <= 4 ? launch_n<1, false>(a, dtype, block, grid, s) : launch_n<2, false>(a, dtype, block, grid, s);
+    if (a.block_table) return a.g_cnt <= 4 ? launch_n<1, true>(a, dtype, block, waves, grid, s) : launch_n<2, true>(a, dtype, block, waves, grid, s);
+    return a.g_cnt <= 4 ? launch_n<1, false>(a, dtype, block, waves, grid, s) : launch_n<2, false>(a, dtype, block, waves, grid, s);
 }
 
 }  // namespace kvbfp

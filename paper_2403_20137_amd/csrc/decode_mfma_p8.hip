@@ -510,6 +510,32 @@ hipError_t launch_lds(const DecodeArgs& a, int dt, int block, dim3 grid, hipStre
     return hipGetLastError();
 }
 
+// Eight wavefronts, for calls whose workgroups take a sequence each.
+template <int N, int HG, bool PAGED, bool QI8>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 4)))
+void decode_split_lds_p8_w8(DecodeArgs a, int dt) {
+    kvbfp::lds::decode_split_lds_body<8, N, HG, PAGED, false, QI8, 8>(a, dt);
+}
+template <int HG, bool PAGED>
+hipError_t launch_w8(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+    const bool qi8 = a.q_mant_bits == 8;
+    switch (block) {
+        case 16: decode_split_lds_p8_w8<16, HG, PAGED, false><<<grid, 512, 0, s>>>(a, dt); break;
+        case 32:
+            if (qi8) decode_split_lds_p8_w8<32, HG, PAGED, true><<<grid, 512, 0, s>>>(a, dt);
+            else decode_split_lds_p8_w8<32, HG, PAGED, false><<<grid, 512, 0, s>>>(a, dt);
+            break;
+        case 64:
+            if (qi8) decode_split_lds_p8_w8<64, HG, PAGED, true><<<grid, 512, 0, s>>>(a, dt);
+            else decode_split_lds_p8_w8<64, HG, PAGED, false><<<grid, 512, 0, s>>>(a, dt);
+            break;
+        default:
+            if (qi8) decode_split_lds_p8_w8<128, HG, PAGED, true><<<grid, 512, 0, s>>>(a, dt);
+            else decode_split_lds_p8_w8<128, HG, PAGED, false><<<grid, 512, 0, s>>>(a, dt);
+            break;
+    }
+    return hipGetLastError();
+}
 // one instantiation per head groups, paging and sharing out
 template <bool SHARE>
 hipError_t launch_16(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
@@ -531,8 +557,13 @@ hipError_t launch_p(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream
 
 namespace kvbfp {
 
-hipError_t launch_decode_split_mfma_p8(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s) {
+hipError_t launch_decode_split_mfma_p8(const DecodeArgs& a, int dtype, int block, int batch, int waves, hipStream_t s) {
+    if (waves == 8 && (dtype == KVBFP_F32 || a.share_above)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
+    if (waves == 8) {
+        if (a.block_table) return a.g_cnt <= 4 ? launch_w8<1, true>(a, dtype, block, grid, s) : launch_w8<2, true>(a, dtype, block, grid, s);
+        return a.g_cnt <= 4 ? launch_w8<1, false>(a, dtype, block, grid, s) : launch_w8<2, false>(a, dtype, block, grid, s);
+    }
     // fp32 outputs take three probability limbs (24 bits), 16-bit outputs two
     if (dtype == KVBFP_F32) return a.g_cnt <= 4 ? launch_p<1, 3>(a, dtype, block, grid, s) : launch_p<2, 3>(a, dtype, block, grid, s);
     return a.share_above ? launch_16<true>(a, dtype, block, grid, s) : launch_16<false>(a, dtype, block, grid, s);
