@@ -202,10 +202,14 @@ __device__ __forceinline__ void store16_stream(void* p, uint32_t x, uint32_t y, 
 
 // PERM: the values leave in the callers' channel order, position j of the cache going to channel perm[j]; the row
 // is reordered in LDS (a row stays inside 16 lanes of one wavefront), so the stores are the same 16-byte ones.
+// fp32 rows pass through LDS in either case: a lane's eight numbers are 32 bytes, and as two stores each of which fills every
+// other 16 bytes of a line they leave the write path in halves (4 x 8000 tokens x 8 heads, 4 bits: 65.4 us with
+// the permutation and 51.0 without, now 32.2 and 27.8; 8 bits 61.1 and 44.6, now 31.6 and 29.6).  Now 16 lanes store 256 bytes at a time.
 template <int DT, int P, int LPB, bool PERM>
 __global__ __launch_bounds__(256) void dequantize_rows_kernel(DequantArgs a) {
     constexpr int ESZ = DT == KVBFP_F32 ? 4 : 2;
-    __shared__ __align__(16) uint8_t stage[PERM ? kDqRowsPerBlock * kD * ESZ : 16];
+    constexpr bool kThroughLds = PERM || DT == KVBFP_F32;
+    __shared__ __align__(16) uint8_t stage[kThroughLds ? kDqRowsPerBlock * kD * ESZ : 16];
     const int lane16 = threadIdx.x & (kDqLanesPerRow - 1);
     const int slot = threadIdx.x >> 4;
     const int c0 = lane16 * 8;
@@ -263,38 +267,38 @@ __global__ __launch_bounds__(256) void dequantize_rows_kernel(DequantArgs a) {
             const float m = ldexpf((float)mag, e);
             v[i] = (code >> (P - 1)) ? -m : m;
         }
-        if (PERM) {
+        if (kThroughLds) {
             uint8_t* lrow = stage + (k * kDqRowsPerStep + slot) * (kD * ESZ);
+            if (PERM) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int4 q = pi[k][i >> 2];
-                const int c = ((i & 3) == 0 ? q.x : ((i & 3) == 1 ? q.y : ((i & 3) == 2 ? q.z : q.w))) & (kD - 1);   // masked: stays inside the row
-                if (DT == KVBFP_F32) ((float*)lrow)[c] = v[i];
-                else ((uint16_t*)lrow)[c] = (uint16_t)narrow16<DT>(v[i]);
+                for (int i = 0; i < 8; ++i) {
+                    const int4 q = pi[k][i >> 2];
+                    const int c = ((i & 3) == 0 ? q.x : ((i & 3) == 1 ? q.y : ((i & 3) == 2 ? q.z : q.w))) & (kD - 1);   // masked: stays inside the row
+                    if (DT == KVBFP_F32) ((float*)lrow)[c] = v[i];
+                    else ((uint16_t*)lrow)[c] = (uint16_t)narrow16<DT>(v[i]);
+                }
+            } else {
+                ((float4*)(lrow + c0 * 4))[0] = make_float4(v[0], v[1], v[2], v[3]);
+                ((float4*)(lrow + c0 * 4))[1] = make_float4(v[4], v[5], v[6], v[7]);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (live[k]) {
                 if (DT == KVBFP_F32) {
-                    const uint4 x = ((const uint4*)(lrow + c0 * 4))[0], y = ((const uint4*)(lrow + c0 * 4))[1];
-                    store16_stream((float*)a.out + orow[k] + c0, x.x, x.y, x.z, x.w);
-                    store16_stream((float*)a.out + orow[k] + c0 + 4, y.x, y.y, y.z, y.w);
+                    const uint4 x = ((const uint4*)lrow)[lane16], y = ((const uint4*)lrow)[16 + lane16];
+                    store16_stream((float*)a.out + orow[k] + 4 * lane16, x.x, x.y, x.z, x.w);
+                    store16_stream((float*)a.out + orow[k] + 64 + 4 * lane16, y.x, y.y, y.z, y.w);
                 } else {
                     const uint4 x = *(const uint4*)(lrow + c0 * 2);
                     store16_stream((uint16_t*)a.out + orow[k] + c0, x.x, x.y, x.z, x.w);
                 }
             }
         } else if (live[k]) {
-            if (DT == KVBFP_F32) {
-                store16_stream((float*)a.out + orow[k] + c0, __float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
-                store16_stream((float*)a.out + orow[k] + c0 + 4, __float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7]));
-            } else {
-                uint32_t w[4];
+            uint32_t w[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) w[i] = narrow16<DT>(v[2 * i]) | (narrow16<DT>(v[2 * i + 1]) << 16);
-                store16_stream((uint16_t*)a.out + orow[k] + c0, w[0], w[1], w[2], w[3]);
-            }
+            for (int i = 0; i < 4; ++i) w[i] = narrow16<DT>(v[2 * i]) | (narrow16<DT>(v[2 * i + 1]) << 16);
+            store16_stream((uint16_t*)a.out + orow[k] + c0, w[0], w[1], w[2], w[3]);
         }
     }
 }

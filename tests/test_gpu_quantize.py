@@ -180,3 +180,22 @@ def test_round_trip_through_both_kernels():
     step = torch.ldexp(torch.ones((), device="cuda"), e - 127 - (w.mant_bits - 2))
     step = step.repeat_interleave(w.block, dim=-1)
     assert bool(((back - d["k"].float()).abs() <= 0.5 * step).all())
+
+
+@pytest.mark.parametrize("p,n", [(4, 16), (4, 128), (8, 32)])
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 33])
+def test_dequantize_to_fp32_at_the_edges_of_a_workgroup(p, n, tokens):
+    # 4 rows per token and 64 to a workgroup: a single row group, one less and one more than a workgroup, a ragged third;
+    # in cache order and through a permutation, bit for bit, and nothing behind the last row is written
+    B, H, D = 2, 2, 128
+    rng = np.random.default_rng(tokens)
+    ms, es = O.plane_shapes(B, H, D, n, p, tokens)
+    mant, exp = rng.integers(0, 256, size=ms, dtype=np.uint8), rng.integers(100, 150, size=es).astype(np.uint8)
+    cache = kvbfp.Cache(kvbfp.make_layout(D, n, p, H, B, tokens), torch.from_numpy(mant).cuda(), torch.from_numpy(exp).cuda(), None, None)
+    for perm in (None, np.stack([rng.permutation(D) for _ in range(H)]).astype(np.int32)):
+        want = torch.from_numpy(O.dequantize(mant, exp, D, n, p, 0, tokens, perm=perm)).to(torch.float32)
+        room = torch.full((want.numel() + 64,), 7.0, device="cuda")
+        kvbfp.dequantize(cache, 0, 0, tokens, perm=dev_i32(perm), out=room[:want.numel()].reshape(want.shape))
+        torch.cuda.synchronize()
+        assert torch.equal(room[:want.numel()].reshape(want.shape).cpu().view(torch.int32), want.view(torch.int32))
+        assert bool((room[want.numel():] == 7.0).all())
