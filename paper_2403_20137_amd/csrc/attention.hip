@@ -648,17 +648,28 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // (8 sequences x 16384 tokens, 4 bits, bf16: 51.4 us, 64.9 in fp32)
     const bool rope_halves = rope && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas,
-    // for more than four heads with fp32 I/O and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
+    // for fp32 I/O (not over pages or with blocks of 128, up to four heads) and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
     // others.  8 kv-heads, 8000 tokens, one call with the splits rounded up -> down: 10 sequences 26.5 -> 23.0 us, 13 29.4 ->
     // 26.5, 30 51.3 -> 49.8; 8 bits, 7 sequences 33.8 -> 28.5; rotation, 7 sequences 50.4 -> 39.0.  Not down to one split: lengths
     // that differ need two to be shared out (50 ragged sequences 32.6 us with two, 45.1 with one), and 65 equal ones took
-    // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).
+    // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).  fp32 I/O with 4 bits goes down to one (64 x 1024 tokens 32.7 ->
+    // 21.2, 70 ragged sequences of up to 4096 43.4 -> 39.5, but of up to 8192 59.0 -> 66.8: not where more than fit may differ by that).
     if (rope || (fast && !wide)) {
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
-        const bool two = rope || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
+        // fp32 I/O with 4 bits: two of the steady pass (decode_mfma.hip), but three of the other where all splits have one tile and fit as
+        // three, and where lengths on the device are to decide below whether they take two, unless two for each compute unit take no more
+        bool f32_two = dtype == KVBFP_F32 && !rope && L->mant_bits == 4 && a.G <= 4 && !paging && L->block != 128;
+        if (f32_two) {
+            const int64_t tiles = (max_len + 255) / 256, fit2 = 512 / units, fit3 = 768 / units;
+            const int32_t three = (int32_t)std::min<int64_t>(sp.n_splits, std::max<int64_t>(fit3, 1));
+            if (tiles > fit2 && tiles <= fit3) f32_two = false;
+            if (seq_len_dev && kvbfp::spans::paired_splits(three, tiles) != three && tiles > 2 * fit2) f32_two = false;
+        }
+        const bool two = rope || L->mant_bits == 8 || f32_two || (dtype == KVBFP_F32 && a.G > 4);
         const int64_t round = 256 * (two ? 2 : 3) / units;
         if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
-        else if (rope && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
+        else if ((rope || f32_two) && round < 2 && !(f32_two && units > 512 && seq_len_dev && max_len > 4096))
+            sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }
     // Short sequences, 16-bit I/O: one workgroup of eight wavefronts a sequence and kv-head instead of splits and a combine pass, as
     // long as the tiles of 512 tokens that it takes one after the other cost less than that launch.  With many units the splits

@@ -73,8 +73,13 @@ __device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 
 // PL = bf16 limbs of a probability: 2 (16 bits, enough for 16-bit outputs) or 3 (24 bits, fp32 outputs).
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
-template <int N, int HG, int PL, bool PAGED, bool SHARE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HG == 1 ? 3 : 2, 4)))
+// THREE: three wavefronts per SIMD.  Otherwise two (f32_two in attention.hip goes with it), whose registers hold the tiles in
+// two instantiations without a branch around the requests.  Three do better over pages and with blocks of 128, whose exponents pass
+// between lanes (12 x 8192 tokens over 16-token pages 41.8 us, 48.1 with two; blocks of 128 33.5 and 35.8), where a wavefront
+// has one tile and more workgroups than two per compute unit are there (96 x 128 tokens 13.2 and 14.9, 6 x 3000 18.9 and 20.0), and with the splits of
+// kPaired, which are planned for three (24 ragged sequences of up to 1536 20.8 and 22.5).
+template <int N, int HG, int PL, bool PAGED, bool SHARE, bool THREE = HG == 1 && (PAGED || N == 128)>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(THREE ? 3 : 2, 4)))
 void decode_split_mfma_p4(DecodeArgs a, int dt) {
     constexpr int NB = kD / N;
     constexpr int NH = HG * 4;
@@ -135,10 +140,8 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     // 16u + 4kg + i, each with its exponent bytes.  The rows of the wavefront's next tile are requested as soon as these are
     // used up, keys before the softmax and values at the end of a tile, and those of the first tile before the set-up
     // (which waits for LDS only): a round trip to memory takes longer than the arithmetic of a tile.  4 x 8192 tokens, 8
-    // kv-heads, blocks of 16, fp32 I/O: a call took 22.2 us with it, 32.6 with every tile's rows requested when they are needed (20.2 now,
-    // with the query ahead of the rows and two tiles for every split); 10 x 8000 tokens, blocks of 32 35.3 against 55.1 (2.5 TB/s).
-    // 168 registers keep three workgroups per compute unit; 8 to 12 more are spilled in regions with blocks of 16 to 64 (loop
-    // invariants, the figures above are with them).
+    // kv-heads, blocks of 16, fp32 I/O: a call took 22.2 us with it, 32.6 with every tile's rows requested when they are needed (18.4 now,
+    // with the query ahead of the rows, two tiles for every split and steady tiles); 10 x 8000 tokens, blocks of 32 35.3 against 55.1.
     struct Rows {
         u32x4 k[4];
         uint32_t ke[4], v[4][4], ve[4][N == 128 ? 1 : 4];      // (one exponent a row: that of row 16u + j, handed over where it is used)
@@ -264,6 +267,12 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 
     // One 64-token tile starting at token T0 of the split.  FULL: all 64 tokens are cached, no
     // clamping or masking; otherwise rows are clamped to the last cached token and masked.
+    // Steady: the next tile is requested from all tiles but the last, which is the other instantiation whether it is full or not,
+    // and so without a branch around the requests: with one the compiler cannot tell which of them are on their way, and waits
+    // for a tile's values where it needs the keys.  The scheduling barriers keep the requests behind the last use of their
+    // registers.  Blocks of 16, 8 kv-heads, 4 heads, with the branch and three wavefronts per SIMD (168 registers and spills) -> now:
+    // 4 x 8192 tokens 20.7 -> 18.4 us, 32 x 8192 76.8 -> 62.6, 20 ragged sequences of up to 16384 36.1 -> 30.7.
+    constexpr bool kSteady = !PAGED && !THREE;
     auto tile = [&](const int T0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int left = n_tok - T0;                 // cached tokens from T0 on (>= 1)
@@ -286,8 +295,10 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
                     s_acc[hg][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[hg][d], bk, s_acc[hg][u], 0, 0, 0);
             }
         }
-        const bool more = T0 + T_step < n_tok;       // wave-uniform
+        const bool more = kSteady ? FULL : T0 + T_step < n_tok;       // wave-uniform
+        if constexpr (kSteady) __builtin_amdgcn_sched_barrier(0);
         if (more) fetch_keys(T0 + T_step, rows);
+        if constexpr (kSteady) __builtin_amdgcn_sched_barrier(0);
 
         // ---------------- online softmax; lane (j, kg) owns head kg of each group, tokens 16u + j
 #pragma unroll
@@ -369,7 +380,9 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
                 }
             }
         }
+        if constexpr (kSteady) __builtin_amdgcn_sched_barrier(0);
         if (more) fetch_values(T0 + T_step, rows);
+        if constexpr (kSteady) __builtin_amdgcn_sched_barrier(0);
         // the next tile overwrites the probability buffer
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -378,7 +391,8 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
 
     {
         int T0 = T_first;
-        for (; T0 + kSuper <= n_full; T0 += T_step) tile(T0, std::true_type{});
+        // (a tile with another one 256 tokens or more behind it is seen whole by every head: at most 63 tokens are hidden from one)
+        for (; kSteady ? T0 + T_step < n_tok : T0 + kSuper <= n_full; T0 += T_step) tile(T0, std::true_type{});
         if (T0 < n_tok) tile(T0, std::false_type{});     // at most one ragged tile per wavefront
     }
 
@@ -461,6 +475,19 @@ void decode_split_lds_p4_w8(DecodeArgs a, int dt) {
 // 1e-5 bar).
 template <int HG, bool PAGED, bool SHARE>
 hipError_t launch_reg(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+    if constexpr (HG == 1 && !PAGED) {
+        const unsigned workgroups = grid.x * grid.y * grid.z;
+        // (the last: one split, lengths that differ; 96 ragged sequences of up to 1024 tokens 26.7 us, 28.5 with two)
+        const bool three = a.direct == kvbfp::kPaired || (a.max_len <= 256 * (int64_t)a.n_splits && workgroups > 512 && workgroups <= 768) ||
+                           (a.seq_len && a.n_splits == 1 && a.max_len <= 1280 && workgroups > 640 && workgroups <= 768);
+        if (three && block != 128) {
+            if (block == 16) decode_split_mfma_p4<16, 1, 3, false, SHARE, true><<<grid, 256, 0, s>>>(a, dt);
+            else if (block == 32) decode_split_mfma_p4<32, 1, 3, false, SHARE, true><<<grid, 256, 0, s>>>(a, dt);
+            else if (block == 64) decode_split_mfma_p4<64, 1, 3, false, SHARE, true><<<grid, 256, 0, s>>>(a, dt);
+            else return hipErrorInvalidValue;
+            return hipGetLastError();
+        }
+    }
     if (block == 16) decode_split_mfma_p4<16, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
     else if (block == 32) decode_split_mfma_p4<32, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
     else if (block == 64) decode_split_mfma_p4<64, HG, 3, PAGED, SHARE><<<grid, 256, 0, s>>>(a, dt);
