@@ -655,7 +655,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).  fp32 I/O with 4 bits goes down to one (64 x 1024 tokens 32.7 ->
     // 21.2, 70 ragged sequences of up to 4096 43.4 -> 39.5, but of up to 8192 59.0 -> 66.8: not where more than fit may differ by that).
     if (rope || (fast && !wide)) {
-        const int64_t units = (int64_t)L->batch * L->n_kv_heads;
+        // (workgroups of a split: the fp32 rotation has all groups of four heads in one launch)
+        const int64_t units = (int64_t)L->batch * L->n_kv_heads * (rope && !rope_halves ? gg : 1);
         // fp32 I/O with 4 bits: two of the steady pass (decode_mfma.hip), but three of the other where all splits have one tile and fit as
         // three, and where lengths on the device are to decide below whether they take two, unless two for each compute unit take no more
         bool f32_two = dtype == KVBFP_F32 && !rope && L->mant_bits == 4 && a.G <= 4 && !paging && L->block != 128;
@@ -763,13 +764,14 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
                                         : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, waves, s);
                 a.k_new = a.v_new = nullptr;       // the current token is cast by the first launch only
             }
-        } else if (rope) {                                                         // four heads per launch
+        } else if (rope_halves) {                                                  // four heads per launch
             for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += 4) {
                 a.g_base = g0;
                 a.g_cnt = a.G - g0 < 4 ? a.G - g0 : 4;
-                err = rope_halves ? launch_decode_split_rope(a, (int)dtype, L->block, L->batch, s)
-                                  : launch_decode_split_rope_f32(a, L->mant_bits, (int)dtype, L->block, L->batch, s);
+                err = launch_decode_split_rope(a, (int)dtype, L->block, L->batch, s);
             }
+        } else if (rope) {
+            err = launch_decode_split_rope_f32(a, L->mant_bits, (int)dtype, L->block, L->batch, s);
         } else {
             if (L->mant_bits == 4) decode_split_generic<4><<<grid1, kTile, 0, s>>>(a, (int)dtype);
             else decode_split_generic<8><<<grid1, kTile, 0, s>>>(a, (int)dtype);

@@ -112,8 +112,8 @@ hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, i
 // The same for 8-bit mantissas (decode_mfma_p8.hip: the LDS pipeline for 16-bit I/O, the register-staged pass
 // for fp32 I/O; a.g_cnt <= 8).
 hipError_t launch_decode_split_mfma_p8(const DecodeArgs& a, int dtype, int block, int batch, int waves, hipStream_t s);
-// Rotation at read (contiguous cache, a.g_cnt <= 4): 4-bit mantissas, 16-bit I/O (decode_rope.hip), and everything in fp32
-// (decode_rope_f32.hip: 8-bit mantissas, fp32 I/O, exponent planes of any alignment).
+// Rotation at read (contiguous cache): 4-bit mantissas, 16-bit I/O (decode_rope.hip, a.g_cnt <= 4), and everything in fp32
+// (decode_rope_f32.hip: 8-bit mantissas, fp32 I/O, exponent planes of any alignment; all heads in one launch).
 hipError_t launch_decode_split_rope(const DecodeArgs& a, int dtype, int block, int batch, hipStream_t s);
 hipError_t launch_decode_split_rope_f32(const DecodeArgs& a, int mant_bits, int dtype, int block, int batch, hipStream_t s);
 // Many (virtual) heads per kv-head, 16-bit I/O (decode_wide.hip): all of them in one launch.

@@ -81,7 +81,11 @@ __device__ __forceinline__ void transpose_rows(float (&v)[4]) {
     v[0] = __uint_as_float(c[0]); v[1] = __uint_as_float(c[1]); v[2] = __uint_as_float(d[0]); v[3] = __uint_as_float(d[1]);
 }
 
-// P = mantissa bits, N = block.  grid = (n_splits, H_kv, B), block = 256.
+// P = mantissa bits, N = block.  grid = (n_splits, ceil(G / 4) * H_kv, B), block = 256: a workgroup serves four heads of a kv-head (the last
+// ones maybe fewer), and all of a call are in one launch, since with few and short sequences a launch of four heads leaves most of the chip
+// idle and takes as long as one of all.  8 kv-heads, launches one after the other -> one (all products on the vector ALUs, four heads a
+// workgroup, before either): 1 x 1000 tokens, 8 heads, 8 bits 25.8 -> 14.7 us (24.3), 16 heads 48.2 -> 14.9 (24.6), 64 heads 185 -> 20.9
+// (29.3), 8 x 16384 tokens, 8 heads 175 -> 154 (469), fp32 4 x 8192, 8 heads 47.4 -> 39.3 (117).  The groups of heads of a kv-head, which read the same rows, are H_kv * n_splits workgroups apart: on the same die where that is a multiple of 8.
 template <int P, int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_split_rope_f32(DecodeArgs a, int dt) {
@@ -119,7 +123,12 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;    // scalar: tile bases stay in SGPRs
     const int j = lane & 15, kg = lane >> 4;
-    const int kvh = blockIdx.y;
+    int kvh = blockIdx.y, group = 0;
+    if (a.G > NH) {
+        group = kvh / a.H_kv;
+        kvh -= group * a.H_kv;
+    }
+    const int g_base = NH * group, g_cnt = min(NH, a.G - g_base);
     // what the set-up reads ahead of everything else but the lengths, before those have arrived: the query as it lies in memory, the
     // vectors of this thread's channel (a load through the permutation would be one more round trip)
     const int len0 = kvbfp::spans::request_lengths(a, gridDim.z);
@@ -129,7 +138,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
 #pragma unroll
         for (int k = 0; k < NH * kD / 256; ++k) {
             const int g = (tid + 256 * k) / kD;
-            const int64_t idx = kvbfp::query_row(a, seq, kvh, a.g_base + min(g, a.g_cnt - 1)) * kD + my_c;
+            const int64_t idx = kvbfp::query_row(a, seq, kvh, g_base + min(g, g_cnt - 1)) * kD + my_c;
             q_bits[k] = dt == KVBFP_F32 ? ((const uint32_t*)a.q)[idx] : (uint32_t)((const uint16_t*)a.q)[idx];
         }
     };
@@ -143,18 +152,18 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
     if (!kvbfp::spans::take(a, len0, 8, span)) return;
     if (span.b != (int)blockIdx.z) request_queries(span.b);
     const int split = span.split, b = span.b;
-    const int h0 = kvh * a.G + a.g_base;
+    const int h0 = kvh * a.G + g_base;
 
     const int64_t L = span.L;
     const int64_t t_begin = (int64_t)split * 256;
     const int64_t t_end = L;
 
     if (t_begin >= t_end) {
-        for (int i = tid; i < a.g_cnt * kD; i += 256) {
-            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + i / kD, i % kD, 0.f, 0.f);
+        for (int i = tid; i < g_cnt * kD; i += 256) {
+            if (a.direct) kvbfp::spans::write_output(a, dt, b, kvh, g_base + i / kD, i % kD, 0.f, 0.f);
             else a.part_o[span.row(h0 + i / kD) * kD + (i % kD)] = 0.f;
         }
-        if (!a.direct && tid < a.g_cnt) {
+        if (!a.direct && tid < g_cnt) {
             float* ml = a.part_ml + span.row(h0 + tid) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
@@ -213,7 +222,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
         const int g = (tid + 256 * k) / kD;
         const float f = dt == KVBFP_F32 ? __uint_as_float(q_bits[k])
                         : dt == KVBFP_F16 ? (float)__builtin_bit_cast(_Float16, (unsigned short)q_bits[k]) : __uint_as_float(q_bits[k] << 16);
-        raw[g][my_c] = g < a.g_cnt ? f : 0.f;
+        raw[g][my_c] = g < g_cnt ? f : 0.f;
     }
     lds_only_barrier();
 #pragma unroll
@@ -572,7 +581,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
     }
     __syncthreads();
 
-    for (int i = tid; i < a.g_cnt * kD; i += 256) {
+    for (int i = tid; i < g_cnt * kD; i += 256) {
         const int g = i / kD, c = i % kD;
         float M = -INFINITY;
 #pragma unroll
@@ -588,12 +597,12 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
 #pragma unroll
             for (int w = 0; w < kWaves; ++w)
                 if (ml_s[w][g][0] > -INFINITY) den = fmaf(exp2f(ml_s[w][g][0] - M), ml_s[w][g][1], den);
-            kvbfp::spans::write_output(a, dt, b, kvh, a.g_base + g, c, acc, den);
+            kvbfp::spans::write_output(a, dt, b, kvh, g_base + g, c, acc, den);
         } else {
             a.part_o[span.row(h0 + g) * kD + c] = acc;
         }
     }
-    if (!a.direct && tid < a.g_cnt) {
+    if (!a.direct && tid < g_cnt) {
         const int g = tid;
         float M = -INFINITY;
 #pragma unroll
@@ -624,10 +633,10 @@ hipError_t launch_rope(const DecodeArgs& a, int dt, int block, dim3 grid, hipStr
 
 namespace kvbfp {
 
-// Contiguous cache, a.g_cnt <= 4 heads [a.g_base, a.g_base + a.g_cnt) of every KV head per launch.
+// Contiguous cache, all heads (a.g_base and a.g_cnt are not read).
 hipError_t launch_decode_split_rope_f32(const DecodeArgs& a, int mant_bits, int dtype, int block, int batch, hipStream_t s) {
-    if (a.g_cnt > 4 || a.block_table || !a.rope_theta || !a.rope_partner || !a.rope_sign) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
+    if (a.block_table || !a.rope_theta || !a.rope_partner || !a.rope_sign) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)a.n_splits, (unsigned)((a.G + 3) / 4 * a.H_kv), (unsigned)batch);
     return mant_bits == 4 ? launch_rope<4>(a, dtype, block, grid, s) : launch_rope<8>(a, dtype, block, grid, s);
 }
 

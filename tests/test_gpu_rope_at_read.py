@@ -176,3 +176,40 @@ def test_rotation_over_exponent_planes_of_any_alignment(dtype, p, n):
                                       seq_len_dev=dev_i32([300, 70]), perm_k=dev_i32(pk), perm_v=dev_i32(pv))
     torch.cuda.synchronize()
     assert_attention_close(got, want, dtype, "p=%d n=%d" % (p, n))
+
+
+@pytest.mark.parametrize("dtype,p,n,G,lens,Hkv", [(torch.float32, 4, 32, 9, [700, 259], 2), (torch.bfloat16, 8, 16, 16, [300, 0], 3), (torch.float16, 4, 64, 35, [513, 64], 2)])
+def test_all_heads_of_a_call_in_one_launch(dtype, p, n, G, lens, Hkv):
+    # groups of four heads with a last one of fewer; more than 32 heads take the fp32 pass with 4 bits and 16-bit I/O too
+    k, v, q, pk, pv = make_small(dtype, B=2, S=max(lens), Hkv=Hkv, G=G, seed=180 + G)
+    got, want = run_both(k, v, q, n, p, lens, 0.11, pk, pv, 1)
+    assert_attention_close(got, want, dtype, "p=%d n=%d G=%d" % (p, n, G))
+
+
+def test_a_call_of_many_heads_over_short_sequences_costs_little_more_than_one_of_four():
+    # 16 heads are 32 workgroups in place of 8: launched one group after the other a call took 3.3 times as long
+    S, times = 300, {}
+    for G in (4, 16):
+        k, v, q, pk, pv = make_small(torch.bfloat16, B=1, S=S, Hkv=8, G=G, seed=190)
+        cache = gpu_cache(k.cuda(), v.cuda(), 32, 8, S, perm_k=pk, perm_v=pv)
+        r = [torch.from_numpy(x).cuda() for x in kvbfp.permute_rope(llama_theta(), pk, 1)]
+        qd, out = q.cuda(), torch.empty_like(q, device="cuda")
+        ws = torch.empty(kvbfp.decode_workspace_bytes(cache.layout, 8 * G, S), dtype=torch.uint8, device="cuda")
+        call = lambda: kvbfp.decode_attention_rope(cache, qd, S, 0.1, *r, perm_k=dpk, perm_v=dpv, out=out, workspace=ws)
+        dpk, dpv = dev_i32(pk), dev_i32(pv)
+        call()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(50):
+                call()
+        graph.replay()
+        got = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            got.append(a.elapsed_time(b))
+        times[G] = min(got)
+    assert times[16] < 2 * times[4], times
