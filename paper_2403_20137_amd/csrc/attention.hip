@@ -553,6 +553,38 @@ struct DecodeExtras {
     int32_t ring_len = 0, reps = 1;
 };
 
+// fp32 I/O, 4-bit mantissas, up to four heads, one region per sequence, blocks of up to 64: splits (at most the n that the workspace has room
+// for) of `units` (sequence, kv-head) pairs of `tiles` 256-token tiles; lengths: they may differ.  Two workgroups per compute unit with the
+// steady tiles of decode_mfma.hip, or (true) three of the form with a branch around the requests.  Two rounded down to one resident
+// round are faster nearly everywhere: 8 kv-heads, three -> two, all sequences full, 4 x 4352 tokens 18.2 -> 17.3 us, 4 x 9216 25.0 -> 21.1,
+// 8 x 4608 25.0 -> 20.4, 16 x 1536 19.8 -> 17.0, 20 x 16384 99 -> 79, lengths log-uniform 16 x 8192 25.7 -> 20.7.  But
+// - 171 to 192 units leave a quarter of the places empty as two and none as three: long sequences take three (24 x 16384, three and two:
+//   102 and 106, ragged 36.9 and 42.2, blocks of 16 96 and 108, 34.8 and 43.0; 24 x 8192, 32 tiles, 60.1 and 59.2, ragged 28.8 and 27.8).
+//   So do 5 and 6 tiles there with lengths, whose two-tile splits by the actual lengths (kPaired) a test holds: 24.2 and 20.4.
+// - 257 to 512 units would have a split each or two, which are more than fit: one while the longest place, which then is the longest sequence,
+//   is short (three, one, two splits: 48 x 1024 25.7, 21.3, 25.7, ragged 19.7, 17.3, 20.8; 64 x 2048 49.3, 35.4, 43.0, ragged 32.3, 28.7, 29.2), two
+//   beyond (33 x 4096 55.4, 55.8, 50.3, ragged 25.9, 35.1, 22.4; ragged 64 x 4096 40.4, 45.6, 36.5, 64 x 16384 83.8, 139, 70.9; ragged
+//   48 x 4096 30.8, 37.5, 32.1, full 60.2, 57.3, 53.2; 60 x 3072
+//   34.1, 35.5, 31.7, full 63.4, 46.6, 54.0).  Equal lengths of more than 384 units always take one (64 x 8192 143.7, 116.4, 120.5).
+// - More than 512 likewise, one up to 4096 tokens (ragged 65 x 3000 39.6, 32.0, 35.4, 65 x 4096 43.3, 39.5, 38.0, 88 x 4096 50.6, 51.4, 48.6, full
+//   108, 87, 97; ragged 65 x 8192 57.7, 68.4, 49.9).  Sequences of one tile that fit as three take three (65 x 128 11.8 and 14.1, 96 x 128 13.4
+//   and 14.9, ragged 96 x 256 15.0 and 16.8), and up to five where they are most and may differ (ragged 96 x 1024 26.8 and 28.6,
+//   88 x 768 22.2 and 23.4, 80 x 1024 26.5 and 22.0; full 96 x 1024 34.8 and 32.1).
+static bool plan_f32(int64_t units, int64_t tiles, bool lengths, int32_t& n) {
+    if (units > 512) {
+        if (!lengths || tiles <= 16) n = 1;
+        return n == 1 && units <= 768 && (tiles == 1 || (lengths && units > 640 && tiles <= 5));
+    }
+    if (units > 256) {
+        n = std::min(n, (lengths ? tiles <= units / 42 : units > 384 || tiles <= 8) ? 1 : 2);
+        return false;
+    }
+    const int32_t fit2 = (int32_t)(512 / units), fit3 = std::min(n, (int32_t)(768 / units));
+    const bool three = units * fit2 <= 384 && (tiles > 32 || (lengths && tiles > 2 * fit2 && kvbfp::spans::paired_splits(fit3, tiles) != fit3));
+    n = three ? fit3 : std::min(n, fit2);
+    return three;
+}
+
 static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t n_q_heads,
                        const void* q, kvbfp_dtype dtype, const int32_t* seq_len_dev,
                        int64_t max_len, float softmax_scale, const int32_t* perm_k,
@@ -648,29 +680,21 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // (8 sequences x 16384 tokens, 4 bits, bf16: 51.4 us, 64.9 in fp32)
     const bool rope_halves = rope && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas,
-    // for fp32 I/O (not over pages or with blocks of 128, up to four heads) and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which would run alone after the
-    // others.  8 kv-heads, 8000 tokens, one call with the splits rounded up -> down: 10 sequences 26.5 -> 23.0 us, 13 29.4 ->
+    // for more than four heads with fp32 I/O and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which
+    // would run alone after the others.  8 kv-heads, 8000 tokens, one call with the splits rounded up -> down: 10 sequences 26.5 -> 23.0 us, 13 29.4 ->
     // 26.5, 30 51.3 -> 49.8; 8 bits, 7 sequences 33.8 -> 28.5; rotation, 7 sequences 50.4 -> 39.0.  Not down to one split: lengths
     // that differ need two to be shared out (50 ragged sequences 32.6 us with two, 45.1 with one), and 65 equal ones took
-    // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).  fp32 I/O with 4 bits goes down to one (64 x 1024 tokens 32.7 ->
-    // 21.2, 70 ragged sequences of up to 4096 43.4 -> 39.5, but of up to 8192 59.0 -> 66.8: not where more than fit may differ by that).
+    // 105.8 against 117.9 us (50 equal ones would be 6 % faster with one).
+    const bool f32_steady = fast && dtype == KVBFP_F32 && L->mant_bits == 4 && a.G <= 4 && !paging && L->block != 128;
+    bool f32_three = false;
     if (rope || (fast && !wide)) {
         // (workgroups of a split: the fp32 rotation has all groups of four heads in one launch)
         const int64_t units = (int64_t)L->batch * L->n_kv_heads * (rope && !rope_halves ? gg : 1);
-        // fp32 I/O with 4 bits: two of the steady pass (decode_mfma.hip), but three of the other where all splits have one tile and fit as
-        // three, and where lengths on the device are to decide below whether they take two, unless two for each compute unit take no more
-        bool f32_two = dtype == KVBFP_F32 && !rope && L->mant_bits == 4 && a.G <= 4 && !paging && L->block != 128;
-        if (f32_two) {
-            const int64_t tiles = (max_len + 255) / 256, fit2 = 512 / units, fit3 = 768 / units;
-            const int32_t three = (int32_t)std::min<int64_t>(sp.n_splits, std::max<int64_t>(fit3, 1));
-            if (tiles > fit2 && tiles <= fit3) f32_two = false;
-            if (seq_len_dev && kvbfp::spans::paired_splits(three, tiles) != three && tiles > 2 * fit2) f32_two = false;
-        }
-        const bool two = rope || L->mant_bits == 8 || f32_two || (dtype == KVBFP_F32 && a.G > 4);
+        const bool two = rope || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
         const int64_t round = 256 * (two ? 2 : 3) / units;
-        if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
-        else if ((rope || f32_two) && round < 2 && !(f32_two && units > 512 && seq_len_dev && max_len > 4096))
-            sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
+        if (f32_steady) f32_three = plan_f32(units, (max_len + 255) / 256, seq_len_dev != nullptr, sp.n_splits);
+        else if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
+        else if (rope && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }
     // Short sequences, 16-bit I/O: one workgroup of eight wavefronts a sequence and kv-head instead of splits and a combine pass, as
     // long as the tiles of 512 tokens that it takes one after the other cost less than that launch.  With many units the splits
@@ -701,7 +725,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // 18.6 against 20.5 at 0.6; 6 x 5000, whose 6 idle splits of 16 leave some of the dies with less work than others, 24.8).  16-bit I/O with 4 bits
     // goes by max_len: 3 % less to 7 % more at 0.6 to 0.8 (32 kv-heads 2 x 4000 12.7 -> 13.2, 16-token pages 2 x 15000 16.1 -> 17.1), 4 to
     // 14 % less at max_len, 20 % less to 8 % more below a half.
-    if (fast && !wide) {
+    if (fast && !wide && !(f32_steady && !f32_three)) {
         const int32_t paired = kvbfp::spans::paired_splits(sp.n_splits, (max_len + 255) / 256);
         if (!seq_len_dev || (L->mant_bits == 4 && dtype != KVBFP_F32)) sp.n_splits = paired;
         else if (L->mant_bits == 4 && paired != sp.n_splits) a.direct = kvbfp::kPaired;
@@ -760,7 +784,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
             for (int g0 = 0; g0 < a.G && err == hipSuccess; g0 += a.g_cnt) {      // 8 heads per launch
                 a.g_base = g0;
                 a.g_cnt = a.G - g0 < 8 ? a.G - g0 : 8;
-                err = L->mant_bits == 4 ? launch_decode_split_mfma(a, (int)dtype, L->block, L->batch, waves, s)
+                err = L->mant_bits == 4 ? launch_decode_split_mfma(a, (int)dtype, L->block, L->batch, waves, f32_three || a.direct == kvbfp::kPaired, s)
                                         : launch_decode_split_mfma_p8(a, (int)dtype, L->block, L->batch, waves, s);
                 a.k_new = a.v_new = nullptr;       // the current token is cast by the first launch only
             }

@@ -107,7 +107,8 @@ __host__ __device__ inline int hidden_tokens(const DecodeArgs& a, int s) {
 // Matrix-core split pass for 4-bit mantissas (decode_mfma.hip).  Returns hipSuccess after
 // enqueuing; the caller has already validated the arguments.
 // waves: wavefronts of a workgroup, 4, or 8 (16-bit I/O, one split, no sharing out).
-hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, int waves, hipStream_t s);
+// three: with fp32 I/O, up to four heads, blocks of up to 64 and no pages, the form with three wavefronts per SIMD.
+hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, int waves, bool three, hipStream_t s);
 // (a.g_cnt <= 8 heads per launch; larger groups with fp32 I/O take several launches over head subsets.)
 // The same for 8-bit mantissas (decode_mfma_p8.hip: the LDS pipeline for 16-bit I/O, the register-staged pass
 // for fp32 I/O; a.g_cnt <= 8).

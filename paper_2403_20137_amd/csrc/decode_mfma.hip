@@ -73,11 +73,9 @@ __device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 
 // PL = bf16 limbs of a probability: 2 (16 bits, enough for 16-bit outputs) or 3 (24 bits, fp32 outputs).
 // PAGED: the planes are a pool of pages and every 16-token stage of a tile looks up its page (a separate instantiation: the
 // contiguous case keeps its 32-bit offsets from one scalar base).
-// THREE: three wavefronts per SIMD.  Otherwise two (f32_two in attention.hip goes with it), whose registers hold the tiles in
-// two instantiations without a branch around the requests.  Three do better over pages and with blocks of 128, whose exponents pass
-// between lanes (12 x 8192 tokens over 16-token pages 41.8 us, 48.1 with two; blocks of 128 33.5 and 35.8), where a wavefront
-// has one tile and more workgroups than two per compute unit are there (96 x 128 tokens 13.2 and 14.9, 6 x 3000 18.9 and 20.0), and with the splits of
-// kPaired, which are planned for three (24 ragged sequences of up to 1536 20.8 and 22.5).
+// THREE: three wavefronts per SIMD.  Otherwise two, whose registers hold the tiles in two instantiations without a branch around the
+// requests.  Three do better over pages and with blocks of 128, whose exponents pass between lanes (12 x 8192 tokens over 16-token
+// pages 41.8 us, 48.1 with two; blocks of 128 33.5 and 35.8); elsewhere plan_f32 (attention.hip) decides together with the splits.
 template <int N, int HG, int PL, bool PAGED, bool SHARE, bool THREE = HG == 1 && (PAGED || N == 128)>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(THREE ? 3 : 2, 4)))
 void decode_split_mfma_p4(DecodeArgs a, int dt) {
@@ -476,12 +474,8 @@ void decode_split_lds_p4_w8(DecodeArgs a, int dt) {
 // limbs and the three-limb bf16 query (the FP8 query limbs of the LDS pipeline carry 16 bits, too few for the
 // 1e-5 bar).
 template <int HG, bool PAGED, bool SHARE>
-hipError_t launch_reg(const DecodeArgs& a, int dt, int block, dim3 grid, hipStream_t s) {
+hipError_t launch_reg(const DecodeArgs& a, int dt, int block, bool three, dim3 grid, hipStream_t s) {
     if constexpr (HG == 1 && !PAGED) {
-        const unsigned workgroups = grid.x * grid.y * grid.z;
-        // (the last: one split, lengths that differ; 96 ragged sequences of up to 1024 tokens 26.7 us, 28.5 with two)
-        const bool three = a.direct == kvbfp::kPaired || (a.max_len <= 256 * (int64_t)a.n_splits && workgroups > 512 && workgroups <= 768) ||
-                           (a.seq_len && a.n_splits == 1 && a.max_len <= 1280 && workgroups > 640 && workgroups <= 768);
         if (three && block != 128) {
             if (block == 16) decode_split_mfma_p4<16, 1, 3, false, SHARE, true><<<grid, 256, 0, s>>>(a, dt);
             else if (block == 32) decode_split_mfma_p4<32, 1, 3, false, SHARE, true><<<grid, 256, 0, s>>>(a, dt);
@@ -519,9 +513,9 @@ hipError_t launch_lds_w8(const DecodeArgs& a, int dt, int block, dim3 grid, hipS
 }
 
 template <int HG, bool PAGED>
-hipError_t launch_n(const DecodeArgs& a, int dt, int block, int waves, dim3 grid, hipStream_t s) {
+hipError_t launch_n(const DecodeArgs& a, int dt, int block, int waves, bool three, dim3 grid, hipStream_t s) {
     if (waves == 8) return launch_lds_w8<HG, PAGED>(a, dt, block, grid, s);
-    if (dt == KVBFP_F32) return a.share_above ? launch_reg<HG, PAGED, true>(a, dt, block, grid, s) : launch_reg<HG, PAGED, false>(a, dt, block, grid, s);
+    if (dt == KVBFP_F32) return a.share_above ? launch_reg<HG, PAGED, true>(a, dt, block, three, grid, s) : launch_reg<HG, PAGED, false>(a, dt, block, three, grid, s);
     return a.share_above ? launch_lds<HG, PAGED, true>(a, dt, block, grid, s) : launch_lds<HG, PAGED, false>(a, dt, block, grid, s);
 }
 
@@ -529,11 +523,11 @@ hipError_t launch_n(const DecodeArgs& a, int dt, int block, int waves, dim3 grid
 
 namespace kvbfp {
 
-hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, int waves, hipStream_t s) {
+hipError_t launch_decode_split_mfma(const DecodeArgs& a, int dtype, int block, int batch, int waves, bool three, hipStream_t s) {
     if (waves == 8 && (dtype == KVBFP_F32 || a.share_above)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)a.n_splits, (unsigned)a.H_kv, (unsigned)batch);
-    if (a.block_table) return a.g_cnt <= 4 ? launch_n<1, true>(a, dtype, block, waves, grid, s) : launch_n<2, true>(a, dtype, block, waves, grid, s);
-    return a.g_cnt <= 4 ? launch_n<1, false>(a, dtype, block, waves, grid, s) : launch_n<2, false>(a, dtype, block, waves, grid, s);
+    if (a.block_table) return a.g_cnt <= 4 ? launch_n<1, true>(a, dtype, block, waves, three, grid, s) : launch_n<2, true>(a, dtype, block, waves, three, grid, s);
+    return a.g_cnt <= 4 ? launch_n<1, false>(a, dtype, block, waves, three, grid, s) : launch_n<2, false>(a, dtype, block, waves, three, grid, s);
 }
 
 }  // namespace kvbfp
