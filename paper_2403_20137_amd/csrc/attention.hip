@@ -699,16 +699,18 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // Short sequences, 16-bit I/O: one workgroup of eight wavefronts a sequence and kv-head instead of splits and a combine pass, as
     // long as the tiles of 512 tokens that it takes one after the other cost less than that launch.  With many units the splits
     // are busy for longer, so the line moves up with them; beyond 256 units the workgroups would not be spread evenly over the
-    // compute units.  8 kv-heads, one call in a graph, splits -> one workgroup: 4 bits, 1 x 900 tokens 10.4 -> 9.7 us, 8 x 512 9.5 -> 7.3,
-    // 8 x 1024 10.0 -> 9.5 (8 x 2048 12.0 -> 13.0), 16 x 1536 14.0 -> 11.3, 24 x 2048 16.6 -> 13.6, ragged 14.8 -> 13.7 (24 x 3072 16.6 ->
-    // 16.9); 5 to 8 heads, 8 x 768 12.6 -> 12.2 (8 x 1024 12.7 -> 13.7), 16 x 1024 15.2 -> 13.8, 24 x 1536 ragged 18.6 -> 16.1; 8 bits, 8 x
-    // 512 10.0 -> 8.8 (8 x 1024 11.2 -> 12.9), 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5 (20 x 1536 14.6 -> 15.3); 8 bits and 5 to 8
-    // heads 8 x 512 13.5 -> 13.1 (8 x 768 13.9 -> 14.7).
+    // compute units.  8 kv-heads, one call in a graph, splits -> one workgroup: 4 bits, 8 x 512 9.5 -> 7.3, 16 x 1536 14.0 -> 11.3, 24 x 2048
+    // 16.6 -> 13.6, ragged 14.8 -> 13.7 (24 x 3072 16.6 -> 16.9); 5 to 8 heads, 16 x 1024 15.2 -> 13.8, 24 x 1536 ragged 18.6 -> 16.1; 8 bits,
+    // 8 x 512 10.0 -> 8.8, 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5.  With few units a tile for every wavefront always pays, and of
+    // a second round one that costs little: 4 bits up to 768 tokens (8 x 768 10.2 -> 8.6; 5 to 8 heads 12.7 -> 12.1, over pages 13.3 -> 14.4), not 8
+    // bits (32 units 600 tokens 10.5 -> 10.9, 17 x 786 ragged over pages 15.2 -> 16.9).  From there to 1024 tokens it is slower in a graph (1 x 900
+    // 10.5 -> 10.9, 32 units 926 9.8 -> 10.6), but a call takes longer on the host than either and so one launch is faster (11.7 -> 10.9, 11.3 ->
+    // 10.9): not over pages or with a query cast, where the passes take as long as the host (32 units 793 tokens over pages 12.4 -> 12.6).
     int waves = 4;
     if (fast && !wide && dtype != KVBFP_F32 && sp.n_splits > 1) {
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
         const bool p4 = L->mant_bits == 4, one_group = a.G <= 4;
-        const int64_t few_units = p4 && one_group ? 1024 : p4 || one_group ? 768 : 512;
+        const int64_t few_units = !p4 || (paging && !one_group) ? 512 : one_group && !paging && !q_mant_bits ? 1024 : 768;
         if (units <= 256 && max_len <= std::max(few_units, (p4 ? one_group ? 12 : 10 : 7) * units)) {
             sp.n_splits = 1;
             waves = 8;

@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 D = 128
 
 
-# the longest sequence decides: 257 tokens and up (fewer are one split of four wavefronts), 512 are one tile of the workgroup, the last
-# lengths are the longest that take it with these few units (the next token takes splits)
+# the longest sequence decides: 257 tokens and up (fewer are one split of four wavefronts), 512 are one tile of the workgroup; the last
+# lengths are on either side of the lines for these few units (test_where_the_lines_lie)
 @pytest.mark.parametrize("p,n,G,longest", [(4, 32, 4, 1024), (4, 16, 1, 1025), (4, 128, 8, 768), (4, 64, 5, 769), (8, 16, 2, 768), (8, 32, 4, 769), (8, 64, 8, 512), (8, 128, 7, 513)])
 def test_current_token_at_the_edges_of_the_tiles(p, n, G, longest):
     dtype = torch.float16 if n == 64 else torch.bfloat16
@@ -64,3 +64,26 @@ def test_many_units_take_it_for_longer_sequences(p, n, G, S):
     k, v, q, pk, pv = make_small(torch.bfloat16, B=4, S=S, Hkv=32, G=G, seed=430)
     got, want = run_both(k, v, q, n, p, [S, 513, 1, S - 64], 0.1, pk, pv)
     assert_attention_close(got, want, torch.bfloat16, "p=%d n=%d G=%d S=%d" % (p, n, G, S))
+
+
+@pytest.mark.parametrize("p,G,page,qbits,longest", [(4, 4, 0, 0, 1024), (4, 4, 0, 8, 768), (4, 4, 64, 0, 768), (4, 8, 0, 0, 768), (4, 8, 16, 0, 512), (8, 1, 0, 0, 512), (8, 4, 0, 8, 512), (8, 2, 256, 0, 512), (8, 8, 0, 0, 512)])
+def test_where_the_lines_lie(p, G, page, qbits, longest):
+    # 8 units; one workgroup leaves no partial results in the workspace, splits do
+    for S in (longest, longest + 1):
+        q = torch.ones((1, 8 * G, D), dtype=torch.bfloat16, device="cuda")
+        kw = dict(q_mant_bits=qbits)
+        if page:
+            pages = -(-S // page)
+            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, pages, page), "cuda", fill=0)
+            table = dev_i32(np.arange(pages)[None])
+            ws = torch.zeros(kvbfp.decode_workspace_bytes_paged(cache.layout, pages, 1, 8 * G, S) + 256, dtype=torch.uint8, device="cuda")
+            kvbfp.decode_attention_paged(cache, table, q, S, 0.1, workspace=ws, **kw)
+        else:
+            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, 1, S), "cuda", fill=0)
+            ws = torch.zeros(kvbfp.decode_workspace_bytes(cache.layout, 8 * G, S) + 256, dtype=torch.uint8, device="cuda")
+            if qbits:
+                kvbfp.decode_attention_qbfp(cache, q, S, 0.1, qbits, workspace=ws)
+            else:
+                kvbfp.decode_attention(cache, q, S, 0.1, workspace=ws)
+        torch.cuda.synchronize()
+        assert bool(ws.any()) == (S > longest), S
