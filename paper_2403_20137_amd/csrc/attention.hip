@@ -703,7 +703,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // 16.6 -> 13.6, ragged 14.8 -> 13.7 (24 x 3072 16.6 -> 16.9); 5 to 8 heads, 16 x 1024 15.2 -> 13.8, 24 x 1536 ragged 18.6 -> 16.1; 8 bits,
     // 8 x 512 10.0 -> 8.8, 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5.  With few units a tile for every wavefront always pays, and of
     // a second round one that costs little: 4 bits up to 768 tokens (8 x 768 10.2 -> 8.6; 5 to 8 heads 12.7 -> 12.1, over pages 13.3 -> 14.4), not 8
-    // bits (32 units 600 tokens 10.5 -> 10.9, 17 x 786 ragged over pages 15.2 -> 16.9).  From there to 1024 tokens it is slower in a graph (1 x 900
+    // bits (32 units 600 tokens 10.5 -> 10.9, 8 x 518 12 % slower; 100 units and more gain 7 % in the mean of 200 calls of 513 tokens up to the
+    // line, and lose up to 12 % just beyond a round; over pages with a query cast it lies lower, 17 x 786 ragged 15.2 -> 16.9).  From there to 1024 tokens it is slower in a graph (1 x 900
     // 10.5 -> 10.9, 32 units 926 9.8 -> 10.6), but a call takes longer on the host than either and so one launch is faster (11.7 -> 10.9, 11.3 ->
     // 10.9): not over pages or with a query cast, where the passes take as long as the host (32 units 793 tokens over pages 12.4 -> 12.6).
     int waves = 4;
@@ -711,7 +712,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
         const bool p4 = L->mant_bits == 4, one_group = a.G <= 4;
         const int64_t few_units = !p4 || (paging && !one_group) ? 512 : one_group && !paging && !q_mant_bits ? 1024 : 768;
-        if (units <= 256 && max_len <= std::max(few_units, (p4 ? one_group ? 12 : 10 : 7) * units)) {
+        const int64_t by_units = p4 ? (one_group ? 12 : 10) * units : units < 100 ? 0 : (paging && q_mant_bits ? 5 : 7) * units;
+        if (units <= 256 && max_len <= std::max(few_units, by_units)) {
             sp.n_splits = 1;
             waves = 8;
         }

@@ -66,20 +66,21 @@ def test_many_units_take_it_for_longer_sequences(p, n, G, S):
     assert_attention_close(got, want, torch.bfloat16, "p=%d n=%d G=%d S=%d" % (p, n, G, S))
 
 
-@pytest.mark.parametrize("p,G,page,qbits,longest", [(4, 4, 0, 0, 1024), (4, 4, 0, 8, 768), (4, 4, 64, 0, 768), (4, 8, 0, 0, 768), (4, 8, 16, 0, 512), (8, 1, 0, 0, 512), (8, 4, 0, 8, 512), (8, 2, 256, 0, 512), (8, 8, 0, 0, 512)])
-def test_where_the_lines_lie(p, G, page, qbits, longest):
-    # 8 units; one workgroup leaves no partial results in the workspace, splits do
+@pytest.mark.parametrize("B,p,G,page,qbits,longest", [
+    (1, 4, 4, 0, 0, 1024), (1, 4, 4, 0, 8, 768), (1, 4, 4, 64, 0, 768), (1, 4, 8, 0, 0, 768), (1, 4, 8, 16, 0, 512), (1, 8, 1, 0, 0, 512),
+    (1, 8, 4, 0, 8, 512), (1, 8, 2, 256, 0, 512), (1, 8, 8, 0, 0, 512), (12, 8, 4, 0, 0, 512), (16, 8, 4, 0, 0, 896), (16, 8, 8, 64, 8, 640), (16, 4, 4, 64, 8, 1536), (16, 4, 5, 0, 0, 1280)])
+def test_where_the_lines_lie(B, p, G, page, qbits, longest):
+    # 8 units a sequence; one workgroup leaves no partial results in the workspace, splits do
     for S in (longest, longest + 1):
-        q = torch.ones((1, 8 * G, D), dtype=torch.bfloat16, device="cuda")
-        kw = dict(q_mant_bits=qbits)
+        q = torch.ones((B, 8 * G, D), dtype=torch.bfloat16, device="cuda")
         if page:
             pages = -(-S // page)
-            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, pages, page), "cuda", fill=0)
-            table = dev_i32(np.arange(pages)[None])
-            ws = torch.zeros(kvbfp.decode_workspace_bytes_paged(cache.layout, pages, 1, 8 * G, S) + 256, dtype=torch.uint8, device="cuda")
-            kvbfp.decode_attention_paged(cache, table, q, S, 0.1, workspace=ws, **kw)
+            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, B * pages, page), "cuda", fill=0)
+            table = dev_i32(np.arange(B * pages).reshape(B, pages))
+            ws = torch.zeros(kvbfp.decode_workspace_bytes_paged(cache.layout, pages, B, 8 * G, S) + 256, dtype=torch.uint8, device="cuda")
+            kvbfp.decode_attention_paged(cache, table, q, S, 0.1, q_mant_bits=qbits, workspace=ws)
         else:
-            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, 1, S), "cuda", fill=0)
+            cache = kvbfp.alloc_cache(kvbfp.make_layout(D, 32, p, 8, B, S), "cuda", fill=0)
             ws = torch.zeros(kvbfp.decode_workspace_bytes(cache.layout, 8 * G, S) + 256, dtype=torch.uint8, device="cuda")
             if qbits:
                 kvbfp.decode_attention_qbfp(cache, q, S, 0.1, qbits, workspace=ws)
