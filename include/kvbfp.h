@@ -284,7 +284,7 @@ int kvbfp_permute_rope(const float* theta, kvbfp_rope_pairs pairs, int32_t n_hea
  * As kvbfp_decode_attention, except that the key of token t of a sequence enters the score as
  *     k_rot[j] = k'[j] cos(t Theta'[j]) + s'[j] k'[i'[j]] sin(t Theta'[j])      (k' = the cached row)
  * with the token index t = its position in the cache and the angle t * Theta'[j] taken exactly (the
- * kernels start their sine/cosine phasors in double precision).  q is used as given: the caller rotates the
+ * kernels start their sine/cosine phasors in double precision; angles of up to 2^50 in magnitude).  q is used as given: the caller rotates the
  * query at its own token index, in whatever order it keeps it (perm_k gathers it as usual).
  *   rope_theta, rope_sign : DEVICE float [n_kv_heads][head_dim];  rope_partner : DEVICE int32, same shape:
  *       what kvbfp_permute_rope returns for perm_k (identity permutation if the rows were never

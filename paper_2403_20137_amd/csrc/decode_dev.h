@@ -93,17 +93,17 @@ __device__ __forceinline__ void bfp_round_queries(float* q_s, uint32_t* amax_s, 
 }
 
 // (cs, sn) of a remainder after n multiples of pi / 2 -> of the whole angle
-template <class T>
-__device__ __forceinline__ void add_quarters(double n, T cs, T sn, T& c, T& s) {
+__device__ __forceinline__ void add_quarters(double n, double cs, double sn, double& c, double& s) {
     const int quarter = (int)fma(-4.0, rint(n * 0.25), n) & 3;       // n modulo 4
     const bool swap = quarter & 1;
-    const T ca = swap ? sn : cs, sa = swap ? cs : sn;
+    const double ca = swap ? sn : cs, sa = swap ? cs : sn;
     c = (quarter == 1 || quarter == 2) ? -ca : ca;
     s = quarter >= 2 ? -sa : sa;
 }
 // Cosine and sine of t * th in double precision: the product of a token index below 2^29 with a 24-bit number is exact, what
 // is left of it after multiples of pi / 2 (in two parts) is within pi / 4, and there the Taylor series up to r^15 and r^16 are off by
-// less than 2^-54.  Some 45 instructions, without the branches of the library's sincos.
+// less than 2^-54.  Some 45 instructions, without the branches of the library's sincos.  Angles of up to 2^50: beyond, the multiple is
+// rounded.
 __device__ __forceinline__ void phasor(double t, double th, double& c, double& s) {
     const double x = t * th;
     const double n = rint(x * 0.63661977236758134308);
@@ -132,22 +132,6 @@ __device__ __forceinline__ void turn(double& c, double& s, double dc, double ds)
     const double n = fma(c, dc, -(s * ds));
     s = fma(s, dc, c * ds);
     c = n;
-}
-
-// The same in fp32, for t * th of up to some thousands: the remainder is rounded once, the series end with r^9 and r^10 (3e-9).
-__device__ __forceinline__ void phasor(float t, float th, float& c, float& s) {
-    const double x = (double)t * (double)th;
-    const double n = rint(x * 0.63661977236758134308);
-    const float r = (float)fma(-n, 1.57079632679489655800, x);
-    const float z = r * r;
-    float a = fmaf(z, 1.f / 362880.f, -1.f / 5040.f);
-    a = fmaf(z, a, 1.f / 120.f);
-    a = fmaf(z, a, -1.f / 6.f);
-    float b = fmaf(z, -1.f / 3628800.f, 1.f / 40320.f);
-    b = fmaf(z, b, -1.f / 720.f);
-    b = fmaf(z, b, 1.f / 24.f);
-    b = fmaf(z, b, -0.5f);
-    add_quarters(n, fmaf(z, b, 1.f), fmaf(r * z, a, r), c, s);
 }
 
 }  // namespace dev

@@ -60,8 +60,8 @@ def test_rotation_is_not_a_no_op_and_rows_need_not_be_reordered(dtype):
 
 
 def test_token_indices_beyond_100k_keep_fp32_accuracy():
-    # angles up to 1.3e5 radians at the highest frequency (theta = 1): the sequence is long enough for
-    # many splits, the kernel's tile phasors are stepped across all of them, and fp32 I/O holds the 1e-5 bar
+    # angles up to 1.3e5 radians at the highest frequency (theta = 1): 512 splits start all along the sequence (two of them step
+    # their phasors to a second tile, the others have one), and fp32 I/O holds the 1e-5 bar
     S = 131072 + 300
     k, v, q, pk, pv = make_small(torch.float32, B=1, S=S, Hkv=1, G=2, seed=140)
     got, want = run_both(k, v, q, 32, 4, [S], 128 ** -0.5, pk, pv, 1)
@@ -114,6 +114,15 @@ def test_profile_variant_returns_the_same_result_and_two_durations():
     (got, split_ms, combine_ms), want = run_both(k, v, q, 16, 4, [600, 1], 0.09, pk, pv, 0, profile=True)
     assert_attention_close(got, want, torch.bfloat16)
     assert split_ms > 0 and combine_ms > 0
+
+
+@pytest.mark.parametrize("dtype,p,n", [(torch.float16, 4, 32), (torch.bfloat16, 4, 16), (torch.float32, 4, 64), (torch.float16, 8, 32)])
+def test_angles_up_to_the_limit(dtype, p, n):
+    # frequencies of 2^43 to 2^44 radians a token over 60 tokens: pi / 2 in one part (53 bits) is 2^-53 of 2^49, several hundredths, off
+    theta = (2.0 ** np.random.default_rng(3).uniform(43, 44, D // 2)).astype(np.float32)
+    k, v, q, pk, pv = make_small(dtype, B=1, S=60, Hkv=2, G=3, seed=155)
+    got, want = run_both(k, v, q, n, p, [60], 0.05, pk, pv, 1, theta=theta)
+    assert_attention_close(got, want, dtype, "p=%d n=%d" % (p, n))
 
 
 # ---- the pass in fp32 (8-bit mantissas, fp32 I/O, exponent planes of any alignment)
