@@ -19,8 +19,8 @@
 //   * A code is a binary16 integer, exactly, and the product with the table entry one v_fma_mix; the power of two of a block
 //     multiplies the sum of 16 products (the integer-mantissa products plus one exponent addition per block of Sec. II-B).
 // Values, softmax and the merge of the four wavefronts are those of the register-staged plain pass: probabilities are three
-// bf16 limbs (24 bits), and a tile with an exponent byte that the values' conversion to bf16 does not hold exactly takes fp32
-// multiply-adds for its values.
+// bf16 limbs (24 bits), and a tile with an exponent byte that the values' conversion to bf16 does not hold exactly, or with a
+// weight that the limbs do not hold, takes fp32 multiply-adds for its values.
 // Bound by instruction issue: per wavefront and 64 tokens, 8 bits, some 1230 vector and 320 matrix instructions, which share the issue
 // slots (67 % of them used; without half of the small matrix instructions a call took 8 us less, without the values 8, with the table's
 // entries in registers nothing).  Calls with 8 kv-heads, 4 heads, one token a thread and all products on the vector ALUs before -> now:
@@ -111,9 +111,10 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
     // What lane (b, h) = 4 b + h takes for the operand registers r = 4 rh + x, channels 16 r + b: [q | q2][rh][lane][x]
     __shared__ __align__(16) float q_op_s[2][2][64][4];
     __shared__ float top_s[NH];
-    // Per wavefront: the phasor of its tile's t0, [cos | sin][rh][b][x]; then the probabilities of the tile, [limb][head][token]
+    // Per wavefront: the phasor of its tile's t0, [cos | sin][rh][b][x]; then the probabilities of the tile,
+    // [limb][head][token] (or as fp32 numbers, [head][token])
     constexpr int kWaveBytes = PL * NH * kSuper * 2;
-    static_assert(kWaveBytes >= 2 * 2 * 16 * 4 * 4, "the phasor fits");
+    static_assert(kWaveBytes >= 2 * 2 * 16 * 4 * 4 && kWaveBytes >= NH * kSuper * 4, "the phasor fits, and fp32 probabilities do");
     __shared__ __align__(16) unsigned char wave_s[kWaves][kWaveBytes];
     __shared__ __align__(16) uint32_t ve_s[kWaves][kExpWords][kSuper];           // exponent bytes of the tile's value rows
     __shared__ float ml_s[kWaves][NH][2];
@@ -455,26 +456,43 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
         transpose_rows(s);                                       // now lane (j, kg): head kg, tokens 16u + j
 
         // ---------------- online softmax
-        float alpha;
+        bool light;                                              // the tile's probabilities are fp32 numbers (the same for a wavefront)
         {
             const float tmax = row_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
             const float m_new = fmaxf(m_run, tmax);
             const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            alpha = exp2_raw(m_run - m_ref);
+            const float alpha = exp2f(m_run - m_ref);            // (keeps subnormal numbers)
             const float m_p = m_ref - (float)kShift;             // probabilities carry 2^kShift
             float psum = 0.f;
             fence();                                             // (the phasor has been read)
+            // Below 2^-110 the third limb loses bits to bf16's smallest number, 2^-133, and below 2^-126 exp2_raw has none: a tile with
+            // such a weight that fp32 still holds keeps them in fp32, which holds 24 bits down to 2^-126 and something down to 2^-149, and
+            // takes fp32 multiply-adds for its values.  (A light token counts where its values are larger by as much.)
+            constexpr float kLow = (float)kShift - 150.5f, kHigh = -109.5f;
+            const float m_mid = m_p + 0.5f * (kLow + kHigh);
+            const float off = fminf(fminf(fabsf(s[0] - m_mid), fabsf(s[1] - m_mid)), fminf(fabsf(s[2] - m_mid), fabsf(s[3] - m_mid)));
+            const bool low = off < 0.5f * (kHigh - kLow);
+            light = __builtin_amdgcn_ballot_w64(low) != 0;
+            if (light) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float pw = exp2_raw(s[u] - m_p);
-                float rest = pw;
-#pragma unroll
-                for (int l = 0; l < PL; ++l) {
-                    const __bf16 limb = (__bf16)rest;
-                    rest -= (float)limb;
-                    p_s[(l * NH + kg) * kSuper + 16 * u + j] = __builtin_bit_cast(unsigned short, limb);
+                for (int u = 0; u < 4; ++u) {
+                    const float pw = exp2f(s[u] - m_ref);
+                    ((float*)p_s)[kg * kSuper + 16 * u + j] = pw;
+                    psum = fmaf(pw, (float)(1 << kShift), psum);
                 }
-                psum += pw - rest;                               // what the limbs hold
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float pw = exp2_raw(s[u] - m_p);
+                    float rest = pw;
+#pragma unroll
+                    for (int l = 0; l < PL; ++l) {
+                        const __bf16 limb = (__bf16)rest;
+                        rest -= (float)limb;
+                        p_s[(l * NH + kg) * kSuper + 16 * u + j] = __builtin_bit_cast(unsigned short, limb);
+                    }
+                    psum += pw - rest;                           // what the limbs hold
+                }
             }
             l_run = l_run * alpha + psum;
             m_run = m_new;
@@ -496,7 +514,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
         fence();
 
         // ---------------- values of the same 64 tokens
-        if (__builtin_amdgcn_ballot_w64(out != 0) == 0) {
+        if (!light && __builtin_amdgcn_ballot_w64(out != 0) == 0) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const u32x4 ve = *(const u32x4*)&ve_s[wave][ve_word][16 * u + 4 * kg];
@@ -545,9 +563,13 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
 #pragma unroll 1
             for (int t = 0; t < count; ++t) {
                 float pw = 0.f;
+                if (light) {
+                    pw = ((const float*)p_s)[kg * kSuper + t];
+                } else {
 #pragma unroll
-                for (int l = 0; l < PL; ++l) pw += __uint_as_float((uint32_t)p_s[(l * NH + kg) * kSuper + t] << 16);
-                pw *= 1.0f / (float)(1 << kShift);
+                    for (int l = 0; l < PL; ++l) pw += __uint_as_float((uint32_t)p_s[(l * NH + kg) * kSuper + t] << 16);
+                    pw *= 1.0f / (float)(1 << kShift);
+                }
                 const uint32_t* const wp = (const uint32_t*)(v_mant + (size_t)(T0 + t) * kRowB + j * P);
                 const float scale = ldexpf(1.0f, (int)((ve_s[wave][ve_word][t] >> (8 * ve_byte)) & 0xFFu) - (125 + P));
 #pragma unroll

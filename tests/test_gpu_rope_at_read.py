@@ -222,3 +222,42 @@ def test_a_call_of_many_heads_over_short_sequences_costs_little_more_than_one_of
             got.append(a.elapsed_time(b))
         times[G] = min(got)
     assert times[16] < 2 * times[4], times
+
+
+def _unit(cache, q, b, h, G, n, p, length, scale, r, pk, pv):
+    """The oracle's output of one (sequence, kv-head) from the cache's bytes (compared with the oracle's own cast elsewhere)."""
+    planes = [x[b:b + 1, h:h + 1].cpu().numpy() for x in cache.planes()]
+    one = [None if x is None else np.ascontiguousarray(x[h:h + 1]) for x in (*r, pk, pv)]
+    return O.decode_attention_rope(*planes, D, n, p, synth.to_f32_numpy(q[b:b + 1, h * G:(h + 1) * G].cpu()), [length], scale, *one[:3], perm_k=one[3], perm_v=one[4])
+
+
+@pytest.mark.parametrize("p", [4, 8])
+@pytest.mark.parametrize("light", [112, 124, 131, 141])
+@pytest.mark.parametrize("tiles", [1, 3])
+def test_light_weights_beside_a_heavy_one_keep_their_bits(p, light, tiles):
+    # one token 2^light as heavy as every other one, whose values are 2^120 times as large; three tiles: 512 units have one split, the heavy token is
+    # in the second tile of a wavefront and what the first one left is scaled by 2^-light.  Frequencies are 0, the second head sees no heavy token.
+    B, Hkv, S, at, n, G = (1, 1, 200, 70, 32, 2) if tiles == 1 else (64, 8, 600, 256 + 70, 16, 2)
+    gen = torch.Generator(device="cuda").manual_seed(light)
+    k = torch.zeros(B, S, Hkv, D, device="cuda")
+    k[:, at, :, 0] = 1.0
+    v = torch.randn(B, S, Hkv, D, generator=gen, device="cuda") * 2.0 ** 100
+    v[:, at] *= 2.0 ** -120
+    q = torch.zeros(B, Hkv * G, D, device="cuda")
+    q[:, ::G, 0] = 1.0
+    scale = float(np.float32(light * np.log(2.0)))
+    cache = gpu_cache(k, v, n, p, S)
+    ident = np.tile(np.arange(D, dtype=np.int32), (Hkv, 1))
+    r = kvbfp.permute_rope(np.zeros(D // 2, np.float32), ident, 0)
+    got = kvbfp.decode_attention_rope(cache, q, S, scale, *(torch.from_numpy(x).cuda() for x in r))
+    torch.cuda.synchronize()
+    for b, h in {(0, 0), (B // 2, Hkv // 2), (B - 1, Hkv - 1)}:
+        want = _unit(cache, q, b, h, G, n, p, S, scale, r, None, None)[0]
+        top = float(v[b, :, h].abs().max())
+        # the bar of fp32, on the light part what rounding a score of `light` twice does to its power, and fp32's step below 2^-126: half of 2^-149 a token
+        # and for the scaling of a tile's sum
+        bar = [1e-5 + 2 * light * np.log(2.0) * 2.0 ** -23, 1e-5]
+        step = [2.0 ** -149 * top * S, 0.0]
+        for g in range(G):
+            err = np.linalg.norm(got[b, h * G + g].double().cpu().numpy() - want[g])
+            assert err <= bar[g] * np.linalg.norm(want[g]) + step[g], (b, h, g, err, np.linalg.norm(want[g]))
