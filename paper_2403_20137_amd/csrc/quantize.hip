@@ -205,11 +205,12 @@ __device__ __forceinline__ void store16_stream(void* p, uint32_t x, uint32_t y, 
 // fp32 rows pass through LDS in either case: a lane's eight numbers are 32 bytes, and as two stores each of which fills every
 // other 16 bytes of a line they leave the write path in halves (4 x 8000 tokens x 8 heads, 4 bits: 65.4 us with
 // the permutation and 51.0 without, now 32.2 and 27.8; 8 bits 61.1 and 44.6, now 31.6 and 29.6).  Now 16 lanes store 256 bytes at a time.
-template <int DT, int P, int LPB, bool PERM>
+// LINES: that way.  Few rows, which the write path keeps up with, are stored as they are (kFewRows).
+template <int DT, int P, int LPB, bool PERM, bool LINES = PERM>
 __global__ __launch_bounds__(256) void dequantize_rows_kernel(DequantArgs a) {
+    static_assert(LINES || !PERM, "a permutation is applied in LDS");
     constexpr int ESZ = DT == KVBFP_F32 ? 4 : 2;
-    constexpr bool kThroughLds = PERM || DT == KVBFP_F32;
-    __shared__ __align__(16) uint8_t stage[kThroughLds ? kDqRowsPerBlock * kD * ESZ : 16];
+    __shared__ __align__(16) uint8_t stage[LINES ? kDqRowsPerBlock * kD * ESZ : 16];
     const int lane16 = threadIdx.x & (kDqLanesPerRow - 1);
     const int slot = threadIdx.x >> 4;
     const int c0 = lane16 * 8;
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(256) void dequantize_rows_kernel(DequantArgs a) {
             const float m = ldexpf((float)mag, e);
             v[i] = (code >> (P - 1)) ? -m : m;
         }
-        if (kThroughLds) {
+        if (LINES) {
             uint8_t* lrow = stage + (k * kDqRowsPerStep + slot) * (kD * ESZ);
             if (PERM) {
 #pragma unroll
@@ -295,10 +296,15 @@ __global__ __launch_bounds__(256) void dequantize_rows_kernel(DequantArgs a) {
                 }
             }
         } else if (live[k]) {
-            uint32_t w[4];
+            if (DT == KVBFP_F32) {
+                store16_stream((float*)a.out + orow[k] + c0, __float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3]));
+                store16_stream((float*)a.out + orow[k] + c0 + 4, __float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7]));
+            } else {
+                uint32_t w[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = narrow16<DT>(v[2 * i]) | (narrow16<DT>(v[2 * i + 1]) << 16);
-            store16_stream((uint16_t*)a.out + orow[k] + c0, w[0], w[1], w[2], w[3]);
+                for (int i = 0; i < 4; ++i) w[i] = narrow16<DT>(v[2 * i]) | (narrow16<DT>(v[2 * i + 1]) << 16);
+                store16_stream((uint16_t*)a.out + orow[k] + c0, w[0], w[1], w[2], w[3]);
+            }
         }
     }
 }
@@ -326,19 +332,27 @@ hipError_t launch_quant(int dt, int p, int block, const QuantArgs& a, dim3 grid,
     }
 }
 
-template <int DT, int P, bool PERM>
+// fp32 in cache order, rows up to which they are stored without the way through LDS (stored as they are, as lines): 8 rows 1.69 and 1.95 us,
+// 800 2.41 to 2.51 and 2.60 to 2.63, 4000 2.79 to 2.88 and 2.91, 5600 2.87 to 2.95 and 2.94 to 2.96, 8000 3.08 to 3.17 and 3.10 to 3.12,
+// 12800 3.49 to 3.58 and 3.36.
+constexpr int64_t kFewRows = 6000;
+
+template <int DT, int P, bool PERM, bool LINES = PERM>
 hipError_t launch_dequant_lpb(int block, const DequantArgs& a, dim3 grid, hipStream_t s) {
     switch (block) {
-        case 16: dequantize_rows_kernel<DT, P, 2, PERM><<<grid, 256, 0, s>>>(a); break;
-        case 32: dequantize_rows_kernel<DT, P, 4, PERM><<<grid, 256, 0, s>>>(a); break;
-        case 64: dequantize_rows_kernel<DT, P, 8, PERM><<<grid, 256, 0, s>>>(a); break;
-        default: dequantize_rows_kernel<DT, P, 16, PERM><<<grid, 256, 0, s>>>(a); break;
+        case 16: dequantize_rows_kernel<DT, P, 2, PERM, LINES><<<grid, 256, 0, s>>>(a); break;
+        case 32: dequantize_rows_kernel<DT, P, 4, PERM, LINES><<<grid, 256, 0, s>>>(a); break;
+        case 64: dequantize_rows_kernel<DT, P, 8, PERM, LINES><<<grid, 256, 0, s>>>(a); break;
+        default: dequantize_rows_kernel<DT, P, 16, PERM, LINES><<<grid, 256, 0, s>>>(a); break;
     }
     return hipGetLastError();
 }
 template <int DT>
 hipError_t launch_dequant_p(int p, int block, const DequantArgs& a, dim3 grid, hipStream_t s) {
     if (a.perm) return p == 4 ? launch_dequant_lpb<DT, 4, true>(block, a, grid, s) : launch_dequant_lpb<DT, 8, true>(block, a, grid, s);
+    if constexpr (DT == KVBFP_F32) {
+        if (a.n_rows > kFewRows) return p == 4 ? launch_dequant_lpb<DT, 4, false, true>(block, a, grid, s) : launch_dequant_lpb<DT, 8, false, true>(block, a, grid, s);
+    }
     return p == 4 ? launch_dequant_lpb<DT, 4, false>(block, a, grid, s) : launch_dequant_lpb<DT, 8, false>(block, a, grid, s);
 }
 

@@ -183,9 +183,9 @@ def test_round_trip_through_both_kernels():
 
 
 @pytest.mark.parametrize("p,n", [(4, 16), (4, 128), (8, 32)])
-@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 33])
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 33, 1500, 1501])
 def test_dequantize_to_fp32_at_the_edges_of_a_workgroup(p, n, tokens):
-    # 4 rows per token and 64 to a workgroup: a single row group, one less and one more than a workgroup, a ragged third;
+    # 4 rows per token and 64 to a workgroup: a single row group, one less and one more than a workgroup, a ragged third; 6000 rows and more;
     # in cache order and through a permutation, bit for bit, and nothing behind the last row is written
     B, H, D = 2, 2, 128
     rng = np.random.default_rng(tokens)
