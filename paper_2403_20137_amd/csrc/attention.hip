@@ -555,32 +555,34 @@ struct DecodeExtras {
 
 // fp32 I/O, 4-bit mantissas, up to four heads, one region per sequence, blocks of up to 64: splits (at most the n that the workspace has room
 // for) of `units` (sequence, kv-head) pairs of `tiles` 256-token tiles; lengths: they may differ.  Two workgroups per compute unit with the
-// steady tiles of decode_mfma.hip, or (true) three of the form with a branch around the requests.  Two rounded down to one resident
-// round are faster nearly everywhere: 8 kv-heads, three -> two, all sequences full, 4 x 4352 tokens 18.2 -> 17.3 us, 4 x 9216 25.0 -> 21.1,
-// 8 x 4608 25.0 -> 20.4, 16 x 1536 19.8 -> 17.0, 20 x 16384 99 -> 79, lengths log-uniform 16 x 8192 25.7 -> 20.7.  But
-// - 171 to 192 units leave a quarter of the places empty as two and none as three: long sequences take three (24 x 16384, three and two:
-//   102 and 106, ragged 36.9 and 42.2, blocks of 16 96 and 108, 34.8 and 43.0; 24 x 8192, 32 tiles, 60.1 and 59.2, ragged 28.8 and 27.8).
-//   So do 5 and 6 tiles there with lengths, whose two-tile splits by the actual lengths (kPaired) a test holds: 24.2 and 20.4.
+// steady tiles of decode_mfma.hip, or (true) three of the form with a branch around the requests.  Of some 14000 calls of any shape, full and ragged,
+// two rounded down to one resident round are within 1 % of the better one up to 256 units, three 6 to 18 % behind: 8 kv-heads, three -> two,
+// 4 x 4352 tokens 18.2 -> 17.3 us, 4 x 9216 25.0 -> 21.1, 20 x 16384 99 -> 79, lengths log-uniform 16 x 8192 25.7 -> 20.7.  (Where three are
+// just enough for a tile each, they can be faster: 8 sequences log-uniform up to 35970, 2 kv-heads 19.6 and 25.2.)  But
+// - 171 to 192 units leave a quarter of the places empty as two and none as three: long sequences take three (two and three as multiples of
+//   the better one: 17 to 32 tiles 1.05 and 1.01, 33 to 48 1.05 and 1.00; lengths that differ, 9 to 12 1.03 and 1.02, 13 to 16 1.08 and 1.00, beyond
+//   1.05 to 1.13 and 1.00).  So do 5 and 6 tiles there with lengths, whose two-tile splits by the actual lengths (kPaired) a test holds: 24.2 and 20.4 us.
 // - 257 to 512 units would have a split each or two, which are more than fit: one while the longest place, which then is the longest sequence,
-//   is short (three, one, two splits: 48 x 1024 25.7, 21.3, 25.7, ragged 19.7, 17.3, 20.8; 64 x 2048 49.3, 35.4, 43.0, ragged 32.3, 28.7, 29.2), two
-//   beyond (33 x 4096 55.4, 55.8, 50.3, ragged 25.9, 35.1, 22.4; ragged 64 x 4096 40.4, 45.6, 36.5, 64 x 16384 83.8, 139, 70.9; ragged
-//   48 x 4096 30.8, 37.5, 32.1, full 60.2, 57.3, 53.2; 60 x 3072
-//   34.1, 35.5, 31.7, full 63.4, 46.6, 54.0).  Equal lengths of more than 384 units always take one (64 x 8192 143.7, 116.4, 120.5).
-// - More than 512 likewise, one up to 4096 tokens (ragged 65 x 3000 39.6, 32.0, 35.4, 65 x 4096 43.3, 39.5, 38.0, 88 x 4096 50.6, 51.4, 48.6, full
-//   108, 87, 97; ragged 65 x 8192 57.7, 68.4, 49.9).  Sequences of one tile that fit as three take three (65 x 128 11.8 and 14.1, 96 x 128 13.4
-//   and 14.9, ragged 96 x 256 15.0 and 16.8), and up to five where they are most and may differ (ragged 96 x 1024 26.8 and 28.6,
-//   88 x 768 22.2 and 23.4, 80 x 1024 26.5 and 22.0; full 96 x 1024 34.8 and 32.1).
+//   is short (three, one, two splits: 48 x 1024 25.7, 21.3, 25.7 us, ragged 19.7, 17.3, 20.8; 64 x 2048 49.3, 35.4, 43.0, ragged 32.3, 28.7,
+//   29.2), two beyond (33 x 4096 55.4, 55.8, 50.3; ragged 64 x 4096 40.4, 45.6, 36.5, 64 x 16384 83.8, 139, 70.9).  Equal lengths of more than 384 units
+//   always take one (64 x 8192 143.7, 116.4, 120.5).  With lengths, 301 to 384 units take their two as three workgroups per compute unit, which fit
+//   (7 to 24 tiles, two and three: log-uniform 1.07 to 1.11 and 1.00 to 1.04 times the better one, uniform 1.02 to 1.08 and 1.01 to 1.06, but all
+//   equal 1.00 to 1.03 and 1.04 to 1.12).
+// - More than 512 likewise, one up to 4096 tokens (ragged 65 x 3000 39.6, 32.0, 35.4, 65 x 4096 43.3, 39.5, 38.0; 65 x 8192 57.7, 68.4, 49.9).  Few tiles
+//   take three where these are fewer rounds (not from 769 to 1024 units): one tile 1.18 to 1.28 as two and 1.00 to 1.01 as three, two 1.03 to 1.14
+//   and 1.00 to 1.02, three 1.01 to 1.03 and 1.03 to 1.06 up to 640 units, 1.02 to 1.06 and 1.01 to 1.02 from there, four 1.02 and 1.03 up to
+//   1536 units, 1.03 to 1.04 and 1.02 beyond, five 1.00 to 1.02 and 1.03 to 1.18.
 static bool plan_f32(int64_t units, int64_t tiles, bool lengths, int32_t& n) {
     if (units > 512) {
         if (!lengths || tiles <= 16) n = 1;
-        return n == 1 && units <= 768 && (tiles == 1 || (lengths && units > 640 && tiles <= 5));
+        return n == 1 && (units <= 768 || units > 1024) && tiles <= (units <= 640 ? 2 : units <= 1536 ? 3 : 4);
     }
     if (units > 256) {
         n = std::min(n, (lengths ? tiles <= units / 42 : units > 384 || tiles <= 8) ? 1 : 2);
-        return false;
+        return n == 2 && lengths && units > 300 && units <= 384;
     }
     const int32_t fit2 = (int32_t)(512 / units), fit3 = std::min(n, (int32_t)(768 / units));
-    const bool three = units * fit2 <= 384 && (tiles > 32 || (lengths && tiles > 2 * fit2 && kvbfp::spans::paired_splits(fit3, tiles) != fit3));
+    const bool three = units * fit2 <= 384 && (tiles > (lengths ? 12 : 16) || (lengths && tiles > 2 * fit2 && kvbfp::spans::paired_splits(fit3, tiles) != fit3));
     n = three ? fit3 : std::min(n, fit2);
     return three;
 }

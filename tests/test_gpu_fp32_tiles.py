@@ -23,8 +23,7 @@ def test_edges_of_a_wavefronts_tiles(n, G, S):
 
 
 # 128 units: up to 4 tiles of 256 tokens have a workgroup each at two per compute unit, 5 to 7 are shared by 4 splits; 520, 640 and 704: one
-# split, three per compute unit for one tile and for up to 1280 tokens of 641 to 768 units with lengths on the device; 768 and 776: all that
-# fit as three, and one sequence more
+# split, three per compute unit up to 512 and 768 tokens; 768 and 776: all that fit as three, and one sequence more
 @pytest.mark.parametrize("n", [16, 32, 64, 128])
 @pytest.mark.parametrize("B,S,lengths", [(16, 1024, False), (16, 1025, True), (16, 1536, False), (16, 1537, True), (65, 256, True), (65, 1030, True),
                                          (80, 700, True), (88, 1280, True), (88, 1281, True), (96, 1200, True), (96, 600, False), (97, 600, True)])
@@ -66,7 +65,7 @@ def _planned(dtype, p, n, B, Hkv, G, S, lengths, length):
 # (8 kv-heads) between one and two splits, two and three workgroups per compute unit
 @pytest.mark.parametrize("B,S,lengths,want", [
     (4, 4352, True, 16), (4, 9216, True, 16), (16, 1536, True, 4),          # 17, 36 tiles of 32 units, 6 of 128: two per compute unit
-    (24, 1200, True, 3), (24, 8192, True, 2), (24, 8193, True, 4),          # 192 units: three where it pays
+    (24, 1200, True, 3), (24, 3072, True, 2), (24, 3073, True, 4), (24, 4096, False, 2), (24, 4097, False, 4),      # 192 units: three where it pays
     (33, 1536, True, 0), (33, 1537, True, 2), (33, 2048, False, 0), (33, 2100, False, 2),
     (64, 3072, True, 0), (64, 3073, True, 2), (64, 4096, False, 0),
     (65, 4096, True, 0), (65, 4097, True, 2), (65, 4097, False, 0)])
@@ -74,6 +73,6 @@ def test_splits_of_the_plan(B, S, lengths, want):
     assert _planned(torch.float32, 4, 32, B, 8, 1, S, lengths, S) == want
 
 
-@pytest.mark.parametrize("n,B,S,lengths", [(16, 24, 8193, True), (32, 33, 1536, True), (64, 33, 1537, True), (32, 64, 3073, True), (16, 48, 2100, False)])
+@pytest.mark.parametrize("n,B,S,lengths", [(16, 24, 3073, True), (32, 24, 4097, False), (16, 40, 2400, True), (32, 130, 200, True), (64, 200, 700, False), (32, 33, 1536, True), (64, 33, 1537, True), (32, 64, 3073, True), (16, 48, 2100, False)])
 def test_either_side_of_the_lines_of_the_plan(n, B, S, lengths):
     test_two_and_three_workgroups_per_compute_unit(n, B, S, lengths)

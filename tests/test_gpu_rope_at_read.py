@@ -261,3 +261,41 @@ def test_light_weights_beside_a_heavy_one_keep_their_bits(p, light, tiles):
         for g in range(G):
             err = np.linalg.norm(got[b, h * G + g].double().cpu().numpy() - want[g])
             assert err <= bar[g] * np.linalg.norm(want[g]) + step[g], (b, h, g, err, np.linalg.norm(want[g]))
+
+
+@pytest.mark.parametrize("dtype,p,n,G", [(torch.bfloat16, 8, 16, 4), (torch.float16, 8, 64, 1), (torch.bfloat16, 8, 128, 6), (torch.float32, 8, 32, 3), (torch.float32, 8, 16, 5),
+                                         (torch.float32, 4, 32, 4), (torch.float32, 4, 128, 2), (torch.float16, 4, 64, 33)])
+@pytest.mark.parametrize("B,S,ragged", [(16, 2700, False), (24, 2000, True)])
+def test_fp32_pass_over_several_tiles_of_a_wavefront(dtype, p, n, G, B, S, ragged):
+    # 128 or 192 units (times the groups of four heads): 4 splits or fewer, three tiles and more each, the last one ragged; the phasor steps, the keys
+    # requested ahead are used, the sums are scaled.  Lengths that differ: the workgroups are shared out.
+    Hkv = 8 if G <= 8 else 2
+    name = {torch.float32: "f32", torch.float16: "f16", torch.bfloat16: "bf16"}[dtype]
+    gains = synth.outlier_gains(11, 0, Hkv, D)
+    k, v = (synth.kv_rows(B, S, Hkv, D, name, gains, 11, 2 + t, "cuda") for t in (0, 1))
+    q = synth.queries(B, Hkv * G, D, name, 11, 4, "cuda")
+    pk = O.calibrate_perm(synth.to_f32_numpy(k[0, :64].cpu()))
+    lens = [S] * B
+    if ragged:
+        rng = np.random.default_rng(B + G)
+        lens = [int(x) for x in np.exp(rng.uniform(np.log(20), np.log(S), B))]
+        lens[3], lens[B - 1], lens[B // 2] = S, 0, 1025
+    cache = gpu_cache(k, v, n, p, S, perm_k=pk, perm_v=pk)
+    r = kvbfp.permute_rope(llama_theta(500000.0), pk, 1)
+    scale = float(np.float32(D ** -0.5))
+    got = kvbfp.decode_attention_rope(cache, q, S, scale, *(torch.from_numpy(x).cuda() for x in r), seq_len_dev=dev_i32(np.asarray(lens)) if ragged else None,
+                                      perm_k=dev_i32(pk), perm_v=dev_i32(pk))
+    torch.cuda.synchronize()
+    for b, h in [(0, 0), (1, Hkv - 1), (3, Hkv - 1), (B // 2, 1), (B - 1, 0)]:
+        want = _unit(cache, q, b, h, G, n, p, lens[b], scale, r, pk, pk)
+        assert_attention_close(got[b:b + 1, h * G:(h + 1) * G], want, dtype, "p=%d n=%d G=%d (%d, %d) of %d" % (p, n, G, b, h, lens[b]))
+
+
+@pytest.mark.parametrize("dtype,p,n", [(torch.float32, 4, 16), (torch.float32, 8, 128), (torch.bfloat16, 8, 32)])
+def test_heads_of_very_different_ranges_beside_each_other(dtype, p, n):
+    # above 2^60 (a softmax of one token), zero (the mean), ordinary and below 2^-60 in one group of four: all are normalised together
+    k, v, q, pk, pv = make_small(dtype, B=2, S=300, Hkv=2, G=5, seed=195)
+    q = (q.float().view(2, 2, 5, D) * torch.tensor([2.0 ** 70, 0.0, 1.0, 2.0 ** -70, 1.0]).view(1, 1, 5, 1)).to(dtype).view(2, 10, D)
+    got, want = run_both(k, v, q, n, p, [300, 67], 0.11, pk, pv, 1)
+    assert bool(torch.isfinite(got).all())
+    assert_attention_close(got, want, dtype, "p=%d n=%d" % (p, n))

@@ -150,7 +150,7 @@ def test_lengths_that_change_between_replays(B, Hkv, S):
 
 def test_a_workspace_without_room_for_the_table_is_enough():
     # the partial results alone, as before there was a table: nothing is shared out then
-    B, Hkv, G, S = 48, 8, 2, 2100                # 768 workgroups: a pass takes all the splits that there is room for
+    B, Hkv, G, S = 48, 8, 2, 2400                # ten tiles of 384 units: two splits, shared out (nine have one)
     lens = _lens(B, S, 4)
     k, v, q, _, _ = make_small(torch.float32, B=B, S=S, Hkv=Hkv, G=G, seed=670)
     cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
@@ -239,7 +239,8 @@ def test_a_query_that_is_not_a_number_stays_in_its_sequence(dtype, p, G, B, Hkv,
     assert bool((got[1].isnan() | (got[1] == 0)).all())
 
 
-@pytest.mark.parametrize("dt,p,B,rope", [("bf16", 4, 24, False), ("f32", 4, 24, False), ("bf16", 8, 16, False), ("f32", 8, 16, False), ("f16", 4, 16, True)])
+@pytest.mark.parametrize("dt,p,B,rope", [("bf16", 4, 24, False), ("f32", 4, 24, False), ("bf16", 8, 16, False), ("f32", 8, 16, False), ("f16", 4, 16, True),
+                                            ("bf16", 8, 16, True), ("f32", 4, 16, True), ("f32", 8, 16, True)])
 @pytest.mark.parametrize("given", [False, True])
 def test_five_tiles_where_four_splits_fit(dt, p, B, rope, given):
     """Three splits of two, two and one tile take their place: whole tiles, one token in the last, none in it, none at all."""
@@ -264,7 +265,8 @@ def test_five_tiles_where_four_splits_fit(dt, p, B, rope, given):
     assert_attention_close(got, want, torch_dt, "%s p=%d B=%d" % (dt, p, B))
 
 
-@pytest.mark.parametrize("dt,p,B,rope,five", [("f32", 4, 24, False, 3), ("bf16", 8, 16, False, 4), ("f32", 8, 16, False, 4), ("f16", 4, 16, True, 4)])
+@pytest.mark.parametrize("dt,p,B,rope,five", [("f32", 4, 24, False, 3), ("bf16", 8, 16, False, 4), ("f32", 8, 16, False, 4), ("f16", 4, 16, True, 4),
+                                                 ("bf16", 8, 16, True, 4), ("f32", 4, 16, True, 4)])
 def test_the_splits_follow_the_lengths_and_not_max_len(dt, p, B, rope, five):
     """Planned for five tiles, four splits fit.  Lengths of four tiles and fewer have a split for every tile; five tiles
     take three (two, two and one) with fp32 I/O and 4 bits, four elsewhere."""
