@@ -270,9 +270,10 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
     // for a tile's values where it needs the keys.  The scheduling barriers keep the requests behind the last use of their
     // registers.  Blocks of 16, 8 kv-heads, 4 heads, with the branch and three wavefronts per SIMD (168 registers and spills) -> now:
     // 4 x 8192 tokens 20.7 -> 18.4 us, 32 x 8192 76.8 -> 62.6, 20 ragged sequences of up to 16384 36.1 -> 30.7.
-    // Up to four heads: with two groups the second instantiation takes all 256 registers and spills up to 7, for no gain (4 x 8192 tokens, 8
-    // heads 23.6 us with it and 23.7, 1 x 32768 25.1 and 24.3, 8 x 16384 49.0 and 50.1, blocks of 128 8 x 8192 33.0 and 32.9).
-    constexpr bool kSteady = HG == 1 && !PAGED && !THREE;
+    // Two groups of heads: with blocks of 16, 64 and 128 the second instantiation takes all 256 registers and spills up to 7, for no gain (4 x
+    // 8192 tokens, 8 heads 23.6 us with it and 23.7, 1 x 32768 25.1 and 24.3, 8 x 16384 49.0 and 50.1, blocks of 128 8 x 8192 33.0 and 32.9); with
+    // blocks of 32 it takes 255 and spills none, 1 % less in the mean of 370 calls (11 x 24162 tokens 93.9 -> 90.4 us, 2 x 32866 27.3 -> 26.2).
+    constexpr bool kSteady = (HG == 1 || N == 32) && !PAGED && !THREE;
     auto tile = [&](const int T0, auto full_tag) {
         constexpr bool FULL = decltype(full_tag)::value;
         const int left = n_tok - T0;                 // cached tokens from T0 on (>= 1)
