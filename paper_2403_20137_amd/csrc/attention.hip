@@ -703,18 +703,19 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     // are busy for longer, so the line moves up with them; beyond 256 units the workgroups would not be spread evenly over the
     // compute units.  8 kv-heads, one call in a graph, splits -> one workgroup: 4 bits, 8 x 512 9.5 -> 7.3, 16 x 1536 14.0 -> 11.3, 24 x 2048
     // 16.6 -> 13.6, ragged 14.8 -> 13.7 (24 x 3072 16.6 -> 16.9); 5 to 8 heads, 16 x 1024 15.2 -> 13.8, 24 x 1536 ragged 18.6 -> 16.1; 8 bits,
-    // 8 x 512 10.0 -> 8.8, 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5.  With few units a tile for every wavefront always pays, and of
-    // a second round one that costs little: 4 bits up to 768 tokens (8 x 768 10.2 -> 8.6; 5 to 8 heads 12.7 -> 12.1, over pages 13.3 -> 14.4), not 8
-    // bits (32 units 600 tokens 10.5 -> 10.9, 8 x 518 12 % slower; 100 units and more gain 7 % in the mean of 200 calls of 513 tokens up to the
-    // line, and lose up to 12 % just beyond a round; over pages with a query cast it lies lower, 17 x 786 ragged 15.2 -> 16.9).  From there to 1024 tokens it is slower in a graph (1 x 900
-    // 10.5 -> 10.9, 32 units 926 9.8 -> 10.6), but a call takes longer on the host than either and so one launch is faster (11.7 -> 10.9, 11.3 ->
-    // 10.9): not over pages or with a query cast, where the passes take as long as the host (32 units 793 tokens over pages 12.4 -> 12.6).
+    // 8 x 512 10.0 -> 8.8, 16 x 1024 14.4 -> 13.1, 24 x 1536 ragged 17.3 -> 15.5.  With few units a tile for every wavefront always pays (0.80 to 0.93
+    // of the time), and of a second round one that costs little: 4 bits up to 768 tokens (up to 64 units 0.85 to 0.97; 5 to 8 heads 0.96 to
+    // 1.02), not 8 bits (0.95 to 1.07, 5 to 8 heads 1.11) unless the three tiles of 256 tokens are more workgroups than compute units (from 86 units
+    // on 0.83 to 0.95, 5 to 8 heads 0.93 to 1.03; four tiles up to 128 units 0.99 to 1.09, beyond them 0.82 to 0.91 and ragged 0.93 to 1.13).  4
+    // bits up to four heads from there to 1024 tokens: 0.92 to 1.06 in a graph, over pages up to 1.09, and 0.88 to 0.97 and up to 1.04 as single calls,
+    // of which the host makes one launch in less time (5 to 8 heads 1.02 to 1.13 either way).  One line whatever the
+    // query's cast and whether over pages, which are within 6 % of each other and return the bits of a region.
     int waves = 4;
     if (fast && !wide && dtype != KVBFP_F32 && sp.n_splits > 1) {
         const int64_t units = (int64_t)L->batch * L->n_kv_heads;
         const bool p4 = L->mant_bits == 4, one_group = a.G <= 4;
-        const int64_t few_units = !p4 || (paging && !one_group) ? 512 : one_group && !paging && !q_mant_bits ? 1024 : 768;
-        const int64_t by_units = p4 ? (one_group ? 12 : 10) * units : units < 100 ? 0 : (paging && q_mant_bits ? 5 : 7) * units;
+        const int64_t few_units = !p4 ? 512 : one_group ? 1024 : 768;
+        const int64_t by_units = p4 ? (one_group ? 12 : 10) * units : units < 86 ? 0 : units <= 128 ? 768 : 7 * units;
         if (units <= 256 && max_len <= std::max(few_units, by_units)) {
             sp.n_splits = 1;
             waves = 8;
