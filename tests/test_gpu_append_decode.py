@@ -41,8 +41,9 @@ def _oracle_units(cache, got, k, v, q, lens, n, p, G, S_max, pk, pv, scale, qbit
         assert_attention_close(out_unit, want, dtype, "append_decode_attention unit (%d,%d) n=%d p=%d" % (b, h, n, p))
 
 
-def _case(dtype, n, p, G, lens, S_max, use_perm, seed, qbits=0, Hkv=2, units=None):
+def _case(dtype, n, p, G, lens, S_max, use_perm, seed, qbits=0, Hkv=2, units=None, max_len=None):
     B = len(lens)
+    max_len = max(lens) if max_len is None else max_len
     S = max(max(lens), 1)
     gains = synth.outlier_gains(seed, 0, Hkv, D)
     k = synth.kv_rows(B, S, Hkv, D, DT[dtype], gains, seed, 2, "cuda")
@@ -72,10 +73,10 @@ def _case(dtype, n, p, G, lens, S_max, use_perm, seed, qbits=0, Hkv=2, units=Non
     scale = 0.1
     kvbfp.quantize_append(a, k_new.unsqueeze(1), v_new.unsqueeze(1), pos_dev=lens_t - 1, perm_k=pk, perm_v=pv)
     if qbits:
-        want = kvbfp.decode_attention_qbfp(a, q, max(lens), scale, qbits, seq_len_dev=lens_t, perm_k=pk, perm_v=pv)
+        want = kvbfp.decode_attention_qbfp(a, q, max_len, scale, qbits, seq_len_dev=lens_t, perm_k=pk, perm_v=pv)
     else:
-        want = kvbfp.decode_attention(a, q, max(lens), scale, seq_len_dev=lens_t, perm_k=pk, perm_v=pv)
-    got = kvbfp.append_decode_attention(f, k_new, v_new, q, max(lens), scale, seq_len_dev=lens_t, perm_k=pk, perm_v=pv,
+        want = kvbfp.decode_attention(a, q, max_len, scale, seq_len_dev=lens_t, perm_k=pk, perm_v=pv)
+    got = kvbfp.append_decode_attention(f, k_new, v_new, q, max_len, scale, seq_len_dev=lens_t, perm_k=pk, perm_v=pv,
                                         q_mant_bits=qbits)
     torch.cuda.synchronize()
     for name in ("k_mant", "k_exp", "v_mant", "v_exp"):
@@ -103,21 +104,21 @@ def test_cast_inside_the_split_pass_equals_two_calls(n, G, use_perm, qbits):
     # rows itself.  4 x 64 = 256 (batch, kv-head) units ask for 3 splits (2 with 12 heads per kv-head),
     # tiles are dealt round-robin; the current tokens fall into the last tile of a sequence of seven
     # full tiles (fourth wavefront), into tile 2 (third wavefront) and into tile 5 (first wavefront),
-    # and one sequence is empty.
-    _case(torch.bfloat16, n, 4, G, [1792, 700, 1300, 0], 1792, use_perm, seed=60 + n + G, qbits=qbits, Hkv=64,
-          units=[(0, 0), (0, 63), (1, 17), (2, 40), (3, 5)])
+    # and one sequence is empty.  (max_len is what the lengths may become: up to 12 x 256 tokens a sequence has one workgroup of eight.)
+    _case(torch.bfloat16, n, 4, G, [1792, 700, 1300, 0], 3200, use_perm, seed=60 + n + G, qbits=qbits, Hkv=64,
+          units=[(0, 0), (0, 63), (1, 17), (2, 40), (3, 5)], max_len=3200)
 
 
 @pytest.mark.parametrize("n,G,use_perm,qbits", [(16, 1, True, 0), (16, 8, False, 0), (32, 4, True, 8), (64, 2, True, 0), (128, 6, True, 0)])
 def test_cast_inside_the_split_pass_8_bit_mantissas(n, G, use_perm, qbits):
-    # the same with 8-bit mantissas (two workgroups per compute unit: 64 x 4 units ask for 2 splits)
-    _case(torch.bfloat16, n, 8, G, [1792, 700, 1300, 0], 1792, use_perm, seed=80 + n + G, qbits=qbits, Hkv=64,
-          units=[(0, 0), (0, 63), (1, 17), (2, 40), (3, 5)])
+    # the same with 8-bit mantissas (two workgroups per compute unit: 64 x 4 units ask for 2 splits, from 7 x 256 tokens on)
+    _case(torch.bfloat16, n, 8, G, [1792, 700, 1300, 0], 2000, use_perm, seed=80 + n + G, qbits=qbits, Hkv=64,
+          units=[(0, 0), (0, 63), (1, 17), (2, 40), (3, 5)], max_len=2000)
 
 
 def test_cast_inside_the_split_pass_fp16():
-    _case(torch.float16, 32, 4, 1, [1700, 1792, 1537, 1], 1792, True, seed=77, Hkv=64,
-          units=[(0, 3), (1, 63), (2, 31), (3, 0), (3, 62)])
+    _case(torch.float16, 32, 4, 1, [1700, 1792, 1537, 1], 3200, True, seed=77, Hkv=64,
+          units=[(0, 3), (1, 63), (2, 31), (3, 0), (3, 62)], max_len=3200)
 
 
 @pytest.mark.parametrize("dtype,n,p", [(torch.bfloat16, 16, 8), (torch.bfloat16, 64, 4), (torch.float32, 32, 4),

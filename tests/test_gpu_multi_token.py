@@ -28,7 +28,7 @@ DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
     ("f32", 8, 16, 3, 13),     # 39, fp32 I/O: general pass
 ])
 def test_each_query_token_matches_single_token_attention(dt, p, n, G, Tq):
-    B, Hkv, S = 3, 2, 830
+    B, Hkv, S, S_max = 3, 2, 830, 1100
     seed = 300 + 7 * Tq + G + p
     kg = synth.outlier_gains(seed, 0, Hkv, D)
     vg = synth.outlier_gains(seed, 1, Hkv, D)
@@ -39,21 +39,23 @@ def test_each_query_token_matches_single_token_attention(dt, p, n, G, Tq):
     pv = O.calibrate_perm(synth.to_f32_numpy(synth.kv_rows(1, 32, Hkv, D, dt, vg, seed, 6)[0]))
     # a full sequence ending mid-tile, one shorter than the number of query tokens, one crossing a 256-token boundary
     lens = [S, max(Tq - 2, 1), 257 + Tq // 2]
-    planes = oracle_cache(k, v, n, p, S, 0, pk, pv)
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S, perm_k=pk, perm_v=pv)
+    planes = oracle_cache(k, v, n, p, S_max, 0, pk, pv)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S_max, perm_k=pk, perm_v=pv)
     assert_planes_equal(cache, planes, "cache")
     scale = 0.09
-    got = kvbfp.decode_attention_multi(cache, q.cuda(), S, scale, seq_len_dev=dev_i32(np.asarray(lens)),
-                                       perm_k=dev_i32(pk), perm_v=dev_i32(pv))
+    # up to 8 virtual heads, 4 bits: one workgroup of eight wavefronts a sequence, and splits
+    one, got = (kvbfp.decode_attention_multi(cache, q.cuda(), max_len, scale, seq_len_dev=dev_i32(np.asarray(lens)),
+                                             perm_k=dev_i32(pk), perm_v=dev_i32(pv)) for max_len in (S, S_max))
     torch.cuda.synchronize()
     assert got.shape == q.shape
     for i in range(Tq):
         seen = [max(l - (Tq - 1 - i), 0) for l in lens]
         want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q[:, i]), seen, float(np.float32(scale)), pk, pv)
-        assert_attention_close(got[:, i], want, DT[dt], "query token %d of %d sees %s" % (i, Tq, seen))
+        for x in (one, got):
+            assert_attention_close(x[:, i], want, DT[dt], "query token %d of %d sees %s" % (i, Tq, seen))
         for b, l in enumerate(seen):
             if l == 0:
-                assert bool((got[b, i] == 0).all())
+                assert bool((got[b, i] == 0).all()) and bool((one[b, i] == 0).all())
 
 
 def test_one_query_token_is_the_plain_call():

@@ -21,26 +21,27 @@ FAMILIES = [(torch.bfloat16, 32, 4), (torch.bfloat16, 16, 4), (torch.float16, 32
 def _run(dtype, n, p, k_shift, v_shift, q_shift, compensate=True, G=4):
     """K, V, q drawn as usual, multiplied by 2^shift (exact), rounded to dtype; with `compensate` the softmax
     scale takes the inverse of the key and query shifts, so the logits stay where they were."""
-    B, S, Hkv = 2, 600, 2
+    B, S, Hkv, S_max = 2, 600, 2, 1100
     g = synth.outlier_gains(5, 0, Hkv, D)
     mk = lambda t, sh: (t * 2.0 ** sh).to(dtype)
     k = mk(synth.kv_rows(B, S, Hkv, D, "f32", g, 5, 2), k_shift)
     v = mk(synth.kv_rows(B, S, Hkv, D, "f32", g, 5, 3), v_shift)
     q = mk(synth.queries(B, Hkv * G, D, "f32", 5, 4), q_shift)
     assert bool(torch.isfinite(k).all() and torch.isfinite(v).all() and torch.isfinite(q).all())
-    planes = oracle_cache(k, v, n, p, S, 0)
-    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S)
+    planes = oracle_cache(k, v, n, p, S_max, 0)
+    cache = gpu_cache(k.cuda(), v.cuda(), n, p, S_max)
     assert_planes_equal(cache, planes, "cache at the end of the range")
     scale = float(np.float32(D ** -0.5) * np.float32(2.0 ** (-(k_shift + q_shift) if compensate else 0)))
     lens = [S, 259]
     want = O.decode_attention(*planes, D, n, p, synth.to_f32_numpy(q), lens, scale)
-    got = kvbfp.decode_attention(cache, q.cuda(), S, scale,
-                                 seq_len_dev=torch.tensor(lens, dtype=torch.int32, device="cuda"))
-    torch.cuda.synchronize()
-    assert bool(torch.isfinite(got).all())
     emin = [int(pl[pl > 0].min()) for pl in (planes[1], planes[3])]
-    assert_attention_close(got, want, dtype, "%s n=%d p=%d shifts k %d v %d q %d (smallest exponent bytes %s)" % (
-        DT_NAME[dtype], n, p, k_shift, v_shift, q_shift, emin))
+    for max_len in (S, S_max):        # one workgroup of eight wavefronts a sequence (4 bits, 16-bit I/O, up to 8 heads), splits
+        got = kvbfp.decode_attention(cache, q.cuda(), max_len, scale,
+                                     seq_len_dev=torch.tensor(lens, dtype=torch.int32, device="cuda"))
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(got).all())
+        assert_attention_close(got, want, dtype, "%s n=%d p=%d shifts k %d v %d q %d (smallest exponent bytes %s) max_len %d" % (
+            DT_NAME[dtype], n, p, k_shift, v_shift, q_shift, emin, max_len))
 
 
 @pytest.mark.parametrize("dtype,n,p", FAMILIES)
@@ -82,14 +83,18 @@ def test_many_heads_at_the_ends_of_the_range(dtype, n, p, which, shift, G):
     _run(dtype, n, p, shift if which == "k" else 0, shift if which == "v" else 0, shift if which == "q" else 0, G=G)
 
 
-@pytest.mark.parametrize("S", [1500, 1024, 700, 300])
-def test_sums_beyond_the_range_are_infinite_whatever_the_number_of_splits(S):
+@pytest.mark.parametrize("B,Hkv,S,splits", [(2, 2, 1500, 6), (3, 64, 2400, 4), (4, 64, 3100, 3), (6, 64, 700, 2), (2, 2, 1024, 0), (2, 2, 700, 0), (2, 2, 300, 0)])
+def test_sums_beyond_the_range_are_infinite_whatever_the_number_of_splits(B, Hkv, S, splits):
     # the value sums of a split leave fp32 before the division by the normaliser: an infinity, and no NaN from a
-    # split that is not there (6, 4, 3 and 2 splits here)
-    v = torch.full((2, S, 2, D), 2.0 ** 125, dtype=torch.bfloat16)
-    k = synth.kv_rows(2, S, 2, D, "bf16", synth.outlier_gains(5, 0, 2, D), 5, 2)
-    q = synth.queries(2, 8, D, "bf16", 5, 4)
-    cache = gpu_cache(k.cuda(), v.cuda(), 32, 4, S)
-    got = kvbfp.decode_attention(cache, q.cuda(), S, 1e-3)
+    # split that is not there (0: one workgroup, which writes the output itself)
+    v = torch.full((B, S, Hkv, D), 2.0 ** 125, dtype=torch.bfloat16, device="cuda")
+    k = synth.kv_rows(B, S, Hkv, D, "bf16", synth.outlier_gains(5, 0, Hkv, D), 5, 2, "cuda")
+    q = synth.queries(B, 4 * Hkv, D, "bf16", 5, 4)
+    cache = gpu_cache(k, v, 32, 4, S)
+    ws = torch.zeros(kvbfp.decode_workspace_bytes(cache.layout, 4 * Hkv, S), dtype=torch.uint8, device="cuda")
+    got = kvbfp.decode_attention(cache, q.cuda(), S, 1e-3, workspace=ws)
     torch.cuda.synchronize()
     assert bool(torch.isposinf(got).all())
+    heads = B * 4 * Hkv                              # rows of partial results: an infinity and no zero in each that was written
+    assert int((ws.view(torch.float32)[:heads * splits * D].view(-1, D)[:, 0] != 0).sum()) == heads * splits
+    assert bool(ws.any()) == (splits > 0)
