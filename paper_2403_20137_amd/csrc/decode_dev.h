@@ -5,6 +5,8 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 
 #include "kvbfp.h"
 
@@ -16,6 +18,12 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
+
+// f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): arrays it indexes stay in registers
+template <class F, int... I>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for(std::make_integer_sequence<int, N>{}, f); }
 
 constexpr int kD = 128;
 constexpr int kWaves = 4;
@@ -62,6 +70,56 @@ __device__ __forceinline__ bf16x8 join(bf16x2 a, bf16x2 b, bf16x2 c, bf16x2 d) {
     r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
     r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
     return r;
+}
+
+// scale operand of the conversions: only the exponent field is looked at, and it is the stored exponent byte
+__device__ __forceinline__ float scale_operand(uint32_t E) { return __uint_as_float(E << 23); }
+// 8 sign-magnitude nibbles -> FP8 bytes: the nibble s|mmm widened to the byte s0000mmm is the FP8-E4M3 subnormal (-1)^s m 2^-9
+__device__ __forceinline__ void spread4(uint32_t w, uint32_t& lo, uint32_t& hi) {
+    lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);          // even nibbles
+    hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);          // odd nibbles
+}
+// 4 sign-magnitude bytes s mmmm lll -> s000mmmm (worth eight times as much) and s0000lll, both valid FP8-E4M3 numbers (the subnormals
+// and the first binade share one spacing: s000xxxx reads as +-x 2^-9 for x = 0..15)
+__device__ __forceinline__ void spread8(uint32_t w, uint32_t& hi, uint32_t& lo) {
+    hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u);
+    lo = w & 0x87878787u;
+}
+// 8 nibbles -> 8 bf16 values in slot order [c0,c2,c4,c6,c1,c3,c5,c7]
+struct Unpacked4 { bf16x2 p[4]; };
+__device__ __forceinline__ Unpacked4 unpack8_p4(uint32_t w, float scale) {
+    uint32_t lo, hi;
+    spread4(w, lo, hi);
+    Unpacked4 u;
+    u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, false);      // (c0, c2)
+    u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, true);       // (c4, c6)
+    u.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, false);      // (c1, c3)
+    u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, true);       // (c5, c7)
+    return u;
+}
+// 4 bytes -> hi pieces (c0,c1), (c2,c3) and lo pieces (c0,c1), (c2,c3) as bf16 pairs; the hi piece takes 8 times the scale
+struct Pieces8 { bf16x2 h01, h23, l01, l23; };
+__device__ __forceinline__ Pieces8 unpack4_p8(uint32_t w, float s_hi, float s_lo) {
+    uint32_t hi, lo;
+    spread8(w, hi, lo);
+    Pieces8 r;
+    r.h01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, false);
+    r.h23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, true);
+    r.l01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, false);
+    r.l23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, true);
+    return r;
+}
+// channel offset inside a dword of MFMA slot x (4-bit mantissas)
+__device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 * (x - 4) + 1; }
+// Lane (j, row) of a wavefront, row = lane / 16, holds M[row][r] in v[r].  Afterwards v[r] holds M[r][row]:
+// first the 2 x 2 blocks are exchanged between the two halves of the wavefront, then single rows
+// between neighbouring 16-lane rows.
+__device__ __forceinline__ void transpose_rows(u32x4& v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
+    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+    v[0] = c[0]; v[1] = c[1]; v[2] = d[0]; v[3] = d[1];
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding

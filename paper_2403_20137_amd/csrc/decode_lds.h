@@ -20,35 +20,6 @@ namespace lds {
 using kvbfp::DecodeArgs;
 using namespace kvbfp::dev;
 
-// scale operand of the conversions: only the exponent field is looked at, and it is the stored exponent byte
-__device__ __forceinline__ float scale_operand(uint32_t E) { return __uint_as_float(E << 23); }
-// 8 sign-magnitude nibbles -> 8 bf16 values in slot order [c0,c2,c4,c6,c1,c3,c5,c7] (the nibble s|mmm widened to
-// the byte s0000mmm is the FP8-E4M3 subnormal (-1)^s m 2^-9)
-struct Unpacked4 { bf16x2 p[4]; };
-__device__ __forceinline__ Unpacked4 unpack8_p4(uint32_t w, float scale) {
-    const uint32_t lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);          // even nibbles as FP8 bytes
-    const uint32_t hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);          // odd nibbles
-    Unpacked4 u;
-    u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, false);      // (c0, c2)
-    u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, true);       // (c4, c6)
-    u.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, false);      // (c1, c3)
-    u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, true);       // (c5, c7)
-    return u;
-}
-// 8-bit mantissas: the byte s mmmm lll is split into s000mmmm and s0000lll, both valid FP8-E4M3 numbers (the
-// subnormals and the first binade share one spacing: s000xxxx reads as +-x 2^-9 for x = 0..15).  4 bytes ->
-// hi pieces (c0,c1), (c2,c3) and lo pieces (c0,c1), (c2,c3) as bf16 pairs; the hi piece takes 8 times the scale.
-struct Pieces8 { bf16x2 h01, h23, l01, l23; };
-__device__ __forceinline__ Pieces8 unpack4_p8(uint32_t w, float s_hi, float s_lo) {
-    const uint32_t hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u);
-    const uint32_t lo = w & 0x87878787u;
-    Pieces8 r;
-    r.h01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, false);
-    r.h23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, true);
-    r.l01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, false);
-    r.l23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, true);
-    return r;
-}
 typedef int v4i __attribute__((ext_vector_type(4)));
 // four sign-magnitude bytes -> four two's-complement bytes (a stored code is never "minus zero", so no carry
 // crosses a byte)
@@ -57,9 +28,6 @@ __device__ __forceinline__ int twos_complement4(uint32_t w) {
     const uint32_t ones = (sgn << 8) - sgn;             // 0xFF in every negative byte
     return (int)((mag ^ ones) + sgn);
 }
-// channel offset inside a dword of MFMA slot x
-__device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 * (x - 4) + 1; }
-
 // ------------------------------------------------------------------------------------------------
 // LDS-staged split pass (Sec. III run-time flow; every block size, 4- and 8-bit mantissas, fp16/bf16 I/O):
 // the packed rows travel global -> LDS by DMA (global_load_lds) instead of through registers, so every
@@ -89,12 +57,6 @@ __device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 
 // row/2 % 8, value rows in the same 4*(row%4) + row/4 order, read eight bytes at a time.
 #define KVBFP_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define KVBFP_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
-// Compile-time loop: f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N-1>{}).
-template <int... I, class F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
 // LDS byte address of a pointer into __shared__ memory.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
@@ -323,7 +285,7 @@ __device__ __forceinline__ void decode_split_lds_body(const DecodeArgs& a, const
     // into a list of kPreTiles tiles in LDS, slot = tile index % kPreTiles: all of it at kernel start, and one half of
     // it, for the tiles 32..63 ahead, whenever the loop enters the other half.  (One variant's 80 KB of LDS leave no
     // room for the list: it looks its pages up tile by tile.)
-    constexpr int kPreTiles = !PAGED || (P == 8 && HG == 2 && N == 16) ? 0 : 64;      // 4 KB of LDS per workgroup
+    constexpr int kPreTiles = !PAGED || (P == 8 && HG == 2 && N == 16) ? 0 : 64;      // 1 KB of LDS per wavefront
     __shared__ __align__(16) int32_t pt_lds[kPreTiles > 0 ? W * kPreTiles * 4 : 4];
     const int64_t tile_step = (int64_t)span.n * kWgTok;
     auto fetch_pages = [&](auto n_tag, const int first_tile) {    // tiles first_tile .. first_tile + n - 1, n = 32 or 64

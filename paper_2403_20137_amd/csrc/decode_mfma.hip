@@ -51,22 +51,6 @@ using namespace kvbfp::dev;
 // 2^-124, lose low-order bits, an absolute error under 2^-126).  E = 255 (a block maximum within a
 // factor 1.07 of the largest fp32 number) would read as an infinite scale and is not supported here.
 constexpr int kShift = 7;
-__device__ __forceinline__ float scale_operand(uint32_t E) { return __uint_as_float(E << 23); }
-
-// 8 sign-magnitude nibbles -> 8 bf16 values in slot order [c0,c2,c4,c6,c1,c3,c5,c7]
-struct Unpacked { bf16x2 p[4]; };
-__device__ __forceinline__ Unpacked unpack8(uint32_t w, float scale) {
-    const uint32_t lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);          // even nibbles as FP8 bytes
-    const uint32_t hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);          // odd nibbles
-    Unpacked u;
-    u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, false);      // (c0, c2)
-    u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, true);       // (c4, c6)
-    u.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, false);      // (c1, c3)
-    u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, true);       // (c5, c7)
-    return u;
-}
-// channel offset inside a dword of MFMA slot x
-__device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 * (x - 4) + 1; }
 
 // N = block size, HG = groups of four query heads per KV head (G <= 4*HG).
 // grid = (n_splits, H_kv, B), block = 256 (four wavefronts).
@@ -289,7 +273,7 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
             for (int hg = 0; hg < HG; ++hg) s_acc[hg][u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const Unpacked kk = unpack8(raw[d], d < 2 ? sc0 : sc1);
+                const Unpacked4 kk = unpack8_p4(raw[d], d < 2 ? sc0 : sc1);
                 const bf16x8 bk = join(kk.p[0], kk.p[1], kk.p[2], kk.p[3]);
 #pragma unroll
                 for (int hg = 0; hg < HG; ++hg)
@@ -353,11 +337,11 @@ void decode_split_mfma_p4(DecodeArgs a, int dt) {
         // ---------------- values of the same 64 tokens
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            Unpacked vv[4];
+            Unpacked4 vv[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const uint32_t E = N == 128 ? (uint32_t)__shfl((int)rows.ve[u][0], 20 * kg + i) : rows.ve[u][N == 128 ? 0 : i];
-                vv[i] = unpack8(rows.v[u][i], scale_operand(E));
+                vv[i] = unpack8_p4(rows.v[u][i], scale_operand(E));
             }
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) {

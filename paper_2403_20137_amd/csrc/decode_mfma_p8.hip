@@ -56,20 +56,6 @@ constexpr int kShift = 3;
 __device__ __forceinline__ float scale_lo(uint32_t E) { return __uint_as_float(E << 23); }
 __device__ __forceinline__ float scale_hi(uint32_t E) { return __uint_as_float((E + 3u) << 23); }
 
-// 4 sign-magnitude bytes -> hi pieces (c0,c1), (c2,c3) and lo pieces (c0,c1), (c2,c3) as bf16 pairs
-struct Pieces { bf16x2 h01, h23, l01, l23; };
-__device__ __forceinline__ Pieces unpack4(uint32_t w, float s_hi, float s_lo) {
-    const uint32_t sign = w & 0x80808080u;
-    const uint32_t hi = ((w >> 3) & 0x0F0F0F0Fu) | sign;
-    const uint32_t lo = w & 0x87878787u;
-    Pieces r;
-    r.h01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, false);
-    r.h23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, s_hi, true);
-    r.l01 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, false);
-    r.l23 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, s_lo, true);
-    return r;
-}
-
 // N = block size, HG = groups of four query heads per KV head (G <= 4*HG).
 // grid = (n_splits, H_kv, B), block = 256 (four wavefronts).
 // PL = bf16 limbs of a probability: 2 (16 bits, enough for 16-bit outputs) or 3 (24 bits, fp32 outputs).
@@ -295,7 +281,7 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
             for (int hg = 0; hg < HG; ++hg) s_acc[hg][u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int d = 0; d < 8; ++d) {
-                const Pieces kk = d < 4 ? unpack4(raw0[d & 3], sh0, sl0) : unpack4(raw1[d & 3], sh1, sl1);
+                const Pieces8 kk = d < 4 ? unpack4_p8(raw0[d & 3], sh0, sl0) : unpack4_p8(raw1[d & 3], sh1, sl1);
                 const bf16x8 bk = join(kk.h01, kk.h23, kk.l01, kk.l23);
 #pragma unroll
                 for (int hg = 0; hg < HG; ++hg)
@@ -357,14 +343,14 @@ void decode_split_mfma_p8(DecodeArgs a, int dt) {
         // ---------------- values of the same 64 tokens
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            Pieces va[4], vb[4];   // channels 8j..8j+3 and 8j+4..8j+7 of tokens 16u + 4kg + i
+            Pieces8 va[4], vb[4];   // channels 8j..8j+3 and 8j+4..8j+7 of tokens 16u + 4kg + i
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const u32x2 w = rows.v[u][i];
                 const uint32_t E = rows.ve[u][i];
                 const float sh = scale_hi(E), sl = scale_lo(E);
-                va[i] = unpack4(w[0], sh, sl);
-                vb[i] = unpack4(w[1], sh, sl);
+                va[i] = unpack4_p8(w[0], sh, sl);
+                vb[i] = unpack4_p8(w[1], sh, sl);
             }
 #pragma unroll
             for (int hg = 0; hg < HG; ++hg) {

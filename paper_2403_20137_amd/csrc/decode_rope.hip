@@ -58,29 +58,12 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // values: as in the plain pass, value * 2^-kShift in bf16 with the exponent byte as the scale operand
 constexpr int kShift = 7;
-__device__ __forceinline__ float scale_operand(uint32_t E) { return __uint_as_float(E << 23); }
 
-// 8 sign-magnitude nibbles -> 8 numbers in slot order [c0,c2,c4,c6,c1,c3,c5,c7]: the nibble s|mmm widened
-// to the byte s0000mmm is the FP8-E4M3 subnormal (-1)^s m 2^-9
-__device__ __forceinline__ void spread(uint32_t w, uint32_t& lo, uint32_t& hi) {
-    lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);          // even nibbles as FP8 bytes
-    hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);          // odd nibbles
-}
-struct UnpackedB { bf16x2 p[4]; };
-__device__ __forceinline__ UnpackedB unpack8_bf16(uint32_t w, float scale) {
-    uint32_t lo, hi;
-    spread(w, lo, hi);
-    UnpackedB u;
-    u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, false);
-    u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, true);
-    u.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, false);
-    u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, true);
-    return u;
-}
+// 8 sign-magnitude nibbles -> 8 binary16 numbers in slot order [c0,c2,c4,c6,c1,c3,c5,c7]
 struct UnpackedH { f16x2 p[4]; };
 __device__ __forceinline__ UnpackedH unpack8_f16(uint32_t w, float scale) {
     uint32_t lo, hi;
-    spread(w, lo, hi);
+    spread4(w, lo, hi);
     UnpackedH u;
     u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, false);
     u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(lo, scale, true);
@@ -88,7 +71,6 @@ __device__ __forceinline__ UnpackedH unpack8_f16(uint32_t w, float scale) {
     u.p[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(hi, scale, true);
     return u;
 }
-__device__ __forceinline__ int slot_channel(int x) { return (x < 4) ? 2 * x : 2 * (x - 4) + 1; }
 // position of channel c in "slot order": chunk, dword, slot inside the dword
 __device__ __forceinline__ int slot_index(int c) {
     const int i8 = c & 7;
@@ -99,24 +81,6 @@ __device__ __forceinline__ f16x8 join_h(f16x2 a, f16x2 b, f16x2 c, f16x2 d) {
     r[0] = a[0]; r[1] = a[1]; r[2] = b[0]; r[3] = b[1];
     r[4] = c[0]; r[5] = c[1]; r[6] = d[0]; r[7] = d[1];
     return r;
-}
-
-// Lane (j, row) of a wavefront, row = lane / 16, holds M[row][r] in v[r].  Afterwards v[r] holds M[r][row]:
-// first the 2 x 2 blocks are exchanged between the two halves of the wavefront, then single rows
-// between neighbouring 16-lane rows.
-__device__ __forceinline__ void transpose_rows(u32x4& v) {
-    const auto a = __builtin_amdgcn_permlane32_swap(v[0], v[2], false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(v[1], v[3], false, false);
-    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-    v[0] = c[0]; v[1] = c[1]; v[2] = d[0]; v[3] = d[1];
-}
-
-// f(std::integral_constant<int, 0>{}) ... f(std::integral_constant<int, 3>{})
-template <class F>
-__device__ __forceinline__ void static_for4(F&& f) {
-    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{});
-    f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
 constexpr int kHeadStride = kD + 4;     // fp32 words per head of the normalised queries: four heads hit different banks
@@ -416,7 +380,7 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
                 ze2[r] = odd ? x2 : hi2[r];
                 zo2[r] = odd ? hi2[r] : x2;
             }
-            static_for4([&](auto BLK) {
+            static_for<4>([&](auto BLK) {
                 constexpr int blk = decltype(BLK)::value;
                 constexpr int ctrl = blk | ((blk ^ 1) << 2) | (blk << 4) | ((blk ^ 1) << 6);
                 uint32_t p1[4], p2[4];
@@ -554,9 +518,9 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
         // ---------------- values of the same 64 tokens: lane (j, kg) takes dword j of rows 4kg .. 4kg+3
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            UnpackedB vv[4];
+            Unpacked4 vv[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) vv[i] = unpack8_bf16(dv.vw[4 * u + i], scale_operand(dv.vex[4 * u + i]));
+            for (int i = 0; i < 4; ++i) vv[i] = unpack8_p4(dv.vw[4 * u + i], scale_operand(dv.vex[4 * u + i]));
             uint2 pp = *(const uint2*)&p_s[wave][a_limb][a_head][16 * u + 4 * kg];
             uint32_t ar[4];
             ar[0] = __builtin_amdgcn_perm(pp.x, pp.x, sel_even);

@@ -47,39 +47,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// f(0) .. f(N - 1), the argument a constant of the type's
-template <class F, int... I>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) { static_for(std::make_integer_sequence<int, N>{}, f); }
-
-// 8 sign-magnitude nibbles -> FP8 bytes: the nibble s|mmm widened to the byte s0000mmm is the FP8-E4M3 subnormal (-1)^s m 2^-9
-__device__ __forceinline__ void spread4(uint32_t w, uint32_t& lo, uint32_t& hi) {
-    lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);          // even nibbles
-    hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);          // odd nibbles
-}
-// 4 sign-magnitude bytes s mmmm lll -> the FP8 numbers s000mmmm (worth eight times as much) and s0000lll
-__device__ __forceinline__ void spread8(uint32_t w, uint32_t& hi, uint32_t& lo) {
-    hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u);
-    lo = w & 0x87878787u;
-}
 // The values' conversions make pairs of channels of a dword, P = 4: (0,2), (4,6), (1,3), (5,7), P = 8: (0,1), (2,3); where channel x is
 template <int P>
 __device__ constexpr int pair_of(int x) { return P == 4 ? (x & 1) * 2 + (x >> 2) : x >> 1; }
 template <int P>
 __device__ constexpr int half_of(int x) { return P == 4 ? (x >> 1) & 1 : x & 1; }
-
-// Lane (j, row) of a wavefront, row = lane / 16, holds M[row][r] in v[r].  Afterwards v[r] holds M[r][row]:
-// first the 2 x 2 blocks are exchanged between the two halves of the wavefront, then single rows
-// between neighbouring 16-lane rows.
-__device__ __forceinline__ void transpose_rows(float (&v)[4]) {
-    auto u = [&](int i) { return __float_as_uint(v[i]); };
-    const auto a = __builtin_amdgcn_permlane32_swap(u(0), u(2), false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(u(1), u(3), false, false);
-    const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-    const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-    v[0] = __uint_as_float(c[0]); v[1] = __uint_as_float(c[1]); v[2] = __uint_as_float(d[0]); v[3] = __uint_as_float(d[1]);
-}
 
 // P = mantissa bits, N = block.  grid = (n_splits, ceil(G / 4) * H_kv, B), block = 256: a workgroup serves four heads of a kv-head (the last
 // ones maybe fewer), and all of a call are in one launch, since with few and short sequences a launch of four heads leaves most of the chip
@@ -443,7 +415,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x2, P == 4 ? 2 : 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x2, 2, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if constexpr (g % 4 == 0 && q > 0) finish(std::integral_constant<int, q - 1 < 0 ? 0 : q - 1>{});
@@ -453,7 +425,12 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
         }
 #pragma unroll
         for (int h = 0; h < NH; ++h) s[h] = lane < left ? s[h] : -INFINITY;
-        transpose_rows(s);                                       // now lane (j, kg): head kg, tokens 16u + j
+        {                                                        // now lane (j, kg): head kg, tokens 16u + j
+            u32x4 w = {__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])};
+            transpose_rows(w);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s[u] = __uint_as_float(w[u]);
+        }
 
         // ---------------- online softmax
         bool light;                                              // the tile's probabilities are fp32 numbers (the same for a wavefront)
@@ -546,7 +523,7 @@ void decode_split_rope_f32(DecodeArgs a, int dt) {
                 }
                 // a third limb takes a second round with that limb in the rows of limb 0 and zeros in the others
 #pragma unroll
-                for (int round = 0; round < (PL == 3 ? 2 : 1); ++round) {
+                for (int round = 0; round < 2; ++round) {
                     uint2 pp = *(const uint2*)&p_s[((round == 0 ? a_limb : PL - 1) * NH + a_head) * kSuper + 16 * u + 4 * kg];
                     if (round == 1 && a_limb == 1) pp = make_uint2(0u, 0u);
                     const bf16x8 ap = __builtin_bit_cast(bf16x8, u32x4{__builtin_amdgcn_perm(pp.x, pp.x, sel_even), __builtin_amdgcn_perm(pp.x, pp.x, sel_odd),

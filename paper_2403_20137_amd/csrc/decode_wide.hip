@@ -65,8 +65,8 @@ __device__ __forceinline__ uint32_t bits(bf16x2 v) { return __builtin_bit_cast(u
 // Eight 4-bit codes -> bf16 pairs (c0,c2), (c4,c6), (c1,c3), (c5,c7), scaled by 2^(E - 136) per unit (value * 2^-7):
 // the nibble s|mmm widened to the byte s0000mmm is the FP8-E4M3 subnormal (-1)^s m 2^-9.
 __device__ __forceinline__ void unpack8_p4(uint32_t w, float scale, uint32_t (&p)[4]) {
-    const uint32_t lo = ((w << 4) & 0x80808080u) | (w & 0x07070707u);
-    const uint32_t hi = (w & 0x80808080u) | ((w >> 4) & 0x07070707u);
+    uint32_t lo, hi;
+    spread4(w, lo, hi);
     p[0] = bits(__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, false));
     p[1] = bits(__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, scale, true));
     p[2] = bits(__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, scale, false));
@@ -78,7 +78,8 @@ __device__ __forceinline__ void unpack8_p4(uint32_t w, float scale, uint32_t (&p
 // `field`: the exponent byte at bit 23 (nothing else of the scale operand counts).
 __device__ __forceinline__ void unpack4_p8(uint32_t w, uint32_t field, float (&x)[4]) {
     const float s_lo = __uint_as_float(field), s_hi = __uint_as_float(field + (3u << 23));
-    const uint32_t hi = ((w >> 3) & 0x0F0F0F0Fu) | (w & 0x80808080u), lo = w & 0x87878787u;
+    uint32_t hi, lo;
+    spread8(w, hi, lo);
     const f32x2 h01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, s_hi, false), h23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, s_hi, true);
     const f32x2 l01 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, s_lo, false), l23 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, s_lo, true);
     x[0] = h01[0] + l01[0]; x[1] = h01[1] + l01[1];
@@ -102,12 +103,6 @@ struct ExpRange {
 __device__ __forceinline__ uint32_t raise_pair(uint32_t w, bool lo, bool hi) {
     return w + (lo && (w & 0x7FFFu) ? 8u << 7 : 0u) + (hi && (w & 0x7FFF0000u) ? 8u << 23 : 0u);
 }
-
-// f(0) .. f(N - 1), the argument a constant of the type's (arrays it indexes stay in registers)
-template <class F, int... I>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
-template <int N, class F>
-__device__ __forceinline__ void static_for(F&& f) { static_for(std::make_integer_sequence<int, N>{}, f); }
 
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32); }
 __device__ __forceinline__ float both_halves_max(float v) {
