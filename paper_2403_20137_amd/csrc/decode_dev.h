@@ -150,23 +150,28 @@ __device__ __forceinline__ void bfp_round_queries(float* q_s, uint32_t* amax_s, 
     lds_only_barrier();
 }
 
-// (cs, sn) of a remainder after n multiples of pi / 2 -> of the whole angle
-__device__ __forceinline__ void add_quarters(double n, double cs, double sn, double& c, double& s) {
-    const int quarter = (int)fma(-4.0, rint(n * 0.25), n) & 3;       // n modulo 4
+// x - n pi / 2 for the nearest whole n, and n modulo 4.  The sum with 1.5 * 2^52 rounds to whole numbers and has them in its lowest bits.
+__device__ __forceinline__ double pi_half_remainder(double x, int& quarter) {
+    const double whole = fma(x, 0.63661977236758134308, 6755399441055744.0);
+    const double n = whole - 6755399441055744.0;
+    quarter = (int)__double_as_longlong(whole) & 3;
+    return fma(-n, 6.12323399573676603587e-17, fma(-n, 1.57079632679489655800, x));
+}
+// (cs, sn) of the remainder -> of the whole angle
+template <class T>
+__device__ __forceinline__ void add_quarters(int quarter, T cs, T sn, T& c, T& s) {
     const bool swap = quarter & 1;
-    const double ca = swap ? sn : cs, sa = swap ? cs : sn;
+    const T ca = swap ? sn : cs, sa = swap ? cs : sn;
     c = (quarter == 1 || quarter == 2) ? -ca : ca;
     s = quarter >= 2 ? -sa : sa;
 }
 // Cosine and sine of t * th in double precision: the product of a token index below 2^29 with a 24-bit number is exact, what
 // is left of it after multiples of pi / 2 (in two parts) is within pi / 4, and there the Taylor series up to r^15 and r^16 are off by
-// less than 2^-54.  Some 45 instructions, without the branches of the library's sincos.  Angles of up to 2^50: beyond, the multiple is
+// less than 2^-54.  Some 40 instructions, without the branches of the library's sincos.  Angles of up to 2^50: beyond, the multiple is
 // rounded.
 __device__ __forceinline__ void phasor(double t, double th, double& c, double& s) {
-    const double x = t * th;
-    const double n = rint(x * 0.63661977236758134308);
-    double r = fma(-n, 1.57079632679489655800, x);
-    r = fma(-n, 6.12323399573676603587e-17, r);
+    int quarter;
+    const double r = pi_half_remainder(t * th, quarter);
     const double z = r * r;
     double a = fma(z, -1.0 / 1307674368000.0, 1.0 / 6227020800.0);
     a = fma(z, a, -1.0 / 39916800.0);
@@ -182,8 +187,22 @@ __device__ __forceinline__ void phasor(double t, double th, double& c, double& s
     b = fma(z, b, -1.0 / 720.0);
     b = fma(z, b, 1.0 / 24.0);
     b = fma(z, b, -0.5);
-    const double cs = fma(z, b, 1.0);
-    add_quarters(n, cs, sn, c, s);
+    add_quarters(quarter, fma(z, b, 1.0), sn, c, s);
+}
+// The same to fp32: the remainder as two fp32 numbers, the series up to r^9 and r^10 (3e-9).
+__device__ __forceinline__ void phasor(double t, double th, float& c, float& s) {
+    int quarter;
+    const double rd = pi_half_remainder(t * th, quarter);
+    const float r = (float)rd, rest = (float)(rd - (double)r), z = r * r;
+    float a = fmaf(z, 1.f / 362880.f, -1.f / 5040.f);
+    a = fmaf(z, a, 1.f / 120.f);
+    a = fmaf(z, a, -1.f / 6.f);
+    float b = fmaf(z, -1.f / 3628800.f, 1.f / 40320.f);
+    b = fmaf(z, b, -1.f / 720.f);
+    b = fmaf(z, b, 1.f / 24.f);
+    b = fmaf(z, b, -0.5f);
+    const float cs = 1.f + fmaf(-rest, r, z * b);
+    add_quarters(quarter, cs, r + fmaf(r * z, a, rest * cs), c, s);
 }
 // the phasor (c, s) turned by (dc, ds)
 __device__ __forceinline__ void turn(double& c, double& s, double dc, double ds) {

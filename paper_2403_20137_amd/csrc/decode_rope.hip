@@ -30,11 +30,12 @@
 // Values, softmax and the merge of the four wavefronts are those of the register-staged plain pass.
 // Bound by vector ALUs: some 920 instructions a wavefront and tile of 64 tokens, 256 of them the table products, 320 the
 // unpacking of keys and values, 130 the operand rebuild; 90 % of the issue slots once the set-up (5 to 6 us) is done.  8 x 16384
-// tokens x 8 kv-heads, 4 heads: 50.5 us a call, 64 x 300 tokens 16.8; 58 with 64-bit addresses per row, accumulation
+// tokens x 8 kv-heads, 4 heads: 48.0 us a call, 64 x 300 tokens 16.2; 58 (where this took 51) with 64-bit addresses per row, accumulation
 // registers that were copied to and fro (the compiler's choice without the two wavefronts per SIMD stated) and a sine and a cosine per
-// table entry.  The set-up's sines and cosines are formed in double precision (the library's single ones of a corrected angle took as long;
-// short fp32 series were 0.4 us faster, but 10 % further off in the root mean square): the table's entries are 2.3e-7 off at most, 3 to 3.6e-8 in
-// the root mean square over frequency bases from 100 to 10^6, before they are cut to 8 + 11 bits, 6.4e-7 after.
+// table entry.  The set-up's sines and cosines come from short series over the angle's remainder as two fp32 numbers: 64 x 300 tokens 16.6 us with
+// double precision or the library's single one.  Over 40 frequency bases from 50 to 2 * 10^6 the table's entries are 3.39e-8 off in the root
+// mean square and 2.1e-7 at most before they are cut to 8 + 11 bits, 1.507e-7 and 6.7e-7 after (the library's of a corrected angle: 3.42e-8,
+// 2.1e-7, 1.508e-7, 6.7e-7; a remainder in one fp32 number 3.61e-8 and 2.4e-7).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -225,10 +226,7 @@ void decode_split_rope_p4(DecodeArgs a, int dt) {
         for (int half = 0; half < 2; ++half) {                       // (four channels at a time: the code of four sine/cosine pairs is enough)
 #pragma unroll
             for (int x = 0; x < 4; ++x) {                            // slot 4 half + x
-                double c0, s0;
-                phasor((double)t, (double)theta_s[8 * group + 2 * x + half], c0, s0);
-                cs[x] = (float)c0;
-                sn[x] = (float)s0;
+                phasor((double)t, (double)theta_s[8 * group + 2 * x + half], cs[x], sn[x]);
             }
             u32x2* const at = (u32x2*)tab_raw + (size_t)(((group >> 2) * 4 * 4 + (group & 3)) * 4 * 16 + t) * 2 + half;
 #pragma unroll
