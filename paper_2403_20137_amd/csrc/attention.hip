@@ -587,6 +587,23 @@ static bool plan_f32(int64_t units, int64_t tiles, bool lengths, int32_t& n) {
     return three;
 }
 
+// Rotation at read in fp32, more than four heads, no lengths: splits (at most n) of `workgroups` (sequence, kv-head, four heads) of `tiles`
+// 256-token tiles, two resident per compute unit.  Those with the shortest of up to two rounds, a round being half a tile's time and the tiles of a
+// workgroup: of some 3300 calls none is slower than with a launch for every four heads, where one round at most (two where it would
+// be less than two splits) was up to 13 % slower (17 x 8 units x 8 heads of 700 tokens, 8 bits 40.2 us, now 33.2; 12 x 8 x 5 heads of
+// 9000 tokens 166 and 143).
+static int32_t plan_rope_groups(int64_t workgroups, int64_t tiles, int32_t n) {
+    int32_t best = 1;
+    int64_t best_time = INT64_MAX;
+    for (int32_t i = 1; i <= n; ++i) {
+        const int64_t rounds = (i * workgroups + 511) / 512, time = rounds * (1 + 2 * ((tiles + i - 1) / i));
+        if ((i > 1 && rounds > 2) || time >= best_time) continue;
+        best = i;
+        best_time = time;
+    }
+    return best;
+}
+
 static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t n_q_heads,
                        const void* q, kvbfp_dtype dtype, const int32_t* seq_len_dev,
                        int64_t max_len, float softmax_scale, const int32_t* perm_k,
@@ -679,7 +696,8 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
     if (wide) sp.n_splits = wp.n_splits;
     const int log2_tile = wide ? wp.log2_tile : 8;
     // rotation at read: 4-bit mantissas with 16-bit I/O go through binary16 operands, everything else through fp32 ones
-    // (8 sequences x 16384 tokens, 4 bits, bf16: 51.4 us, 64.9 in fp32)
+    // (8 sequences x 16384 tokens, 4 bits, bf16: 48 us, 65 in fp32).  More than 32 heads have fp32 products, as they always had; in one launch they
+    // also take less time over short sequences than a launch for every four heads would (64 heads, 1 x 1000 tokens 18.4 us).
     const bool rope_halves = rope && dtype != KVBFP_F32 && L->mant_bits == 4 && a.G <= 32 && aligned16(a.k_exp) && aligned16(a.v_exp);
     // One resident round: the workgroups that fit the compute units together (three each, two of the passes for 8-bit mantissas,
     // for more than four heads with fp32 I/O and for the rotation, whose workgroups hold a 64 KB table in LDS) and not a few more, which
@@ -695,6 +713,7 @@ static int decode_impl(const kvbfp_layout* L, const kvbfp_cache* cache, int32_t 
         const bool two = rope || L->mant_bits == 8 || (dtype == KVBFP_F32 && a.G > 4);
         const int64_t round = 256 * (two ? 2 : 3) / units;
         if (f32_steady) f32_three = plan_f32(units, (max_len + 255) / 256, seq_len_dev != nullptr, sp.n_splits);
+        else if (rope && !rope_halves && gg > 1 && !seq_len_dev) sp.n_splits = plan_rope_groups(units, (max_len + 255) / 256, sp.n_splits);
         else if (round >= 2 && sp.n_splits > round) sp.n_splits = (int32_t)round;
         else if (rope && round < 2) sp.n_splits = (int32_t)std::min<int64_t>(sp.n_splits, (512 + units - 1) / units);
     }

@@ -265,10 +265,11 @@ def test_light_weights_beside_a_heavy_one_keep_their_bits(p, light, tiles):
 
 @pytest.mark.parametrize("dtype,p,n,G", [(torch.bfloat16, 8, 16, 4), (torch.float16, 8, 64, 1), (torch.bfloat16, 8, 128, 6), (torch.float32, 8, 32, 3), (torch.float32, 8, 16, 5),
                                          (torch.float32, 4, 32, 4), (torch.float32, 4, 128, 2), (torch.float16, 4, 64, 33)])
-@pytest.mark.parametrize("B,S,ragged", [(16, 2700, False), (24, 2000, True)])
+@pytest.mark.parametrize("B,S,ragged", [(16, 2700, False), (17, 700, False), (24, 2000, True)])
 def test_fp32_pass_over_several_tiles_of_a_wavefront(dtype, p, n, G, B, S, ragged):
     # 128 or 192 units (times the groups of four heads): 4 splits or fewer, three tiles and more each, the last one ragged; the phasor steps, the keys
-    # requested ahead are used, the sums are scaled.  Lengths that differ: the workgroups are shared out.
+    # requested ahead are used, the sums are scaled.  17 x 8 units of two groups: three splits of a tile, in two rounds.  Lengths that differ: the
+    # workgroups are shared out.
     Hkv = 8 if G <= 8 else 2
     name = {torch.float32: "f32", torch.float16: "f16", torch.bfloat16: "bf16"}[dtype]
     gains = synth.outlier_gains(11, 0, Hkv, D)
