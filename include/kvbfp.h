@@ -297,9 +297,9 @@ int kvbfp_permute_rope(const float* theta, kvbfp_rope_pairs pairs, int32_t n_hea
  * matrix-core pass (the rotation is carried by the query operand per 64-token tile and by a table of
  * cos/sin per token offset; same bars as kvbfp_decode_attention, any exponent bytes 3..254, queries
  * and softmax_scale whose product stays finite in fp32); 8-bit mantissas and fp32 I/O take the same in fp32
- * products (8 sequences x 16384 tokens: 51 us; 8 bits 85).  Either way the rotation costs arithmetic per cached key element
- * that the plain path does not have: about 2.3x the time of kvbfp_decode_attention on the same cache
- * (a cache of already rotated keys, reordered at append time, needs none of it).
+ * products (8 sequences x 16384 tokens: 48 us; 8 bits 84).  Either way the rotation costs arithmetic per cached key element
+ * that the plain path does not have: 1.7 to 1.8 times the time of kvbfp_decode_attention on the same cache with 16-bit I/O, 1.4
+ * to 1.8 with fp32 (a cache of already rotated keys, reordered at append time, needs none of it).
  * Errors: INVALID_ARG, UNSUPPORTED, WORKSPACE, HIP. */
 int kvbfp_decode_attention_rope(const kvbfp_layout* layout, const kvbfp_cache* cache, int32_t n_q_heads,
                                 const void* q, kvbfp_dtype dtype, const int32_t* seq_len_dev,

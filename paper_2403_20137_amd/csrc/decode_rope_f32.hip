@@ -21,11 +21,12 @@
 // Values, softmax and the merge of the four wavefronts are those of the register-staged plain pass: probabilities are three
 // bf16 limbs (24 bits), and a tile with an exponent byte that the values' conversion to bf16 does not hold exactly, or with a
 // weight that the limbs do not hold, takes fp32 multiply-adds for its values.
-// Bound by instruction issue: per wavefront and 64 tokens, 8 bits, some 1230 vector and 320 matrix instructions, which share the issue
-// slots (67 % of them used; without half of the small matrix instructions a call took 8 us less, without the values 8, with the table's
-// entries in registers nothing).  Calls with 8 kv-heads, 4 heads, one token a thread and all products on the vector ALUs before -> now:
-// 8 bits, bf16, 8 x 16384 tokens 250 -> 85 us, fp32 7 x 59535 1307 -> 257, fp32 with 4 bits 4 x 8192 64 -> 26, 1 x 1000 tokens 24.6 -> 15.7.
-// Against 64 bits partial results are as far off as those were (fp32 outputs 3 to 8e-7 of their norm, both).
+// Bound by instruction issue: per wavefront and 64 tokens, 8 bits, some 1230 vector instructions of 4 cycles and 320 matrix instructions of
+// about 9, which hardly overlap and are two thirds of the time (without half of the small matrix instructions a call took 8 us less,
+// without the values 8, with the table's entries in registers nothing).  Calls with 8 kv-heads, 4 heads, one token a thread and all products
+// on the vector ALUs before -> now: 8 bits, bf16, 8 x 16384 tokens 241 -> 86 us, fp32 7 x 59535 1301 -> 253, fp32 with 4 bits 4 x 8192
+// 64 -> 25.9, 1 x 1000 tokens, 8 bits 23.5 -> 14.6.  Against 64 bits fp32 outputs are 0.93 (4 bits) and 0.85 times (8 bits) as far off as
+// those were, 2.6 and 2.4e-7 of their norm in the mean of 60 calls of any shape.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
